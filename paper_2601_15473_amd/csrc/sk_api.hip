@@ -108,6 +108,12 @@ LaunchHooks* launch_hooks() { return g_hooks; }
 
 namespace {
 
+// Room for slabs behind the recomputed Z of a factor gradient: a shape that fits the fixed scratch
+// of sk_linear_bwd_weight_noalloc without splits is not split past it, one that does not has no limit.
+size_t slab_room(size_t z_bytes) {
+  return z_bytes < SK_NOALLOC_SCRATCH_BYTES ? SK_NOALLOC_SCRATCH_BYTES - z_bytes : SIZE_MAX;
+}
+
 // Tile choice for the general GEMM (measured on MI355X).  The 256 x 256 tile with eight
 // waves has the best steady state (fewest LDS instructions per MFMA) but a long prologue,
 // so it pays from a contraction of 512 on when its tiles fill the chip; 128 x 128 runs two work-groups per CU, which overlaps one
@@ -130,16 +136,50 @@ int choose_tile(int64_t M, int64_t N, int64_t K, int splits) {
   return TILE_64x64;
 }
 
-// fp32 first contraction (one tile shape, 64 x 64): split over a long contraction when its
-// tiles leave most of the chip idle -- ranges at least 256 long, at most 8.
-int f32_first_splits(int64_t M, int64_t N, int64_t K) {
-  const int64_t tiles = ((M + F32_BM - 1) / F32_BM) * ((N + F32_BN - 1) / F32_BN);
-  int64_t sp = NUM_CUS / tiles;
-  if (sp > K / 256) sp = K / 256;
-  if (sp > 8) sp = 8;
-  if (sp < 2 || K < 1024) return 1;
-  const int64_t kps = ((K + sp - 1) / sp + F32_BK - 1) / F32_BK * F32_BK;
-  return (int)((K + kps - 1) / kps);
+// fp32 contraction [M, N] over K: tile and split of the contraction (fp32 slabs, summed by one
+// more launch), the pair with the least modelled time.  Measured rates of one CU: a lone 64 x 64
+// work-group 0.39 TFLOP/s, two or more 0.52; 128 x 128 tiles 0.50 and 0.53, at 2 us more before
+// the first and behind the last MFMA; 6 us for the launch that sums the slabs, which are written
+// and read at 4 TB/s.  [4096 x 3072] . [3072 x 128]: 64 x 64 unsplit 66 us, 2 ranges 38 + sum,
+// 4 ranges 34 + sum, 8 ranges 33 + longer sum; 128 x 128, 8 ranges, 36 + sum.  [8192 x 512] .
+// [512 x 4096]: 128 x 128 264 us, 64 x 64 276-292.
+struct F32Plan {
+  int tile, splits, k_per_split;
+  size_t slab_bytes;   // of the slabs (0 when not split)
+};
+F32Plan plan_f32(int64_t M, int64_t N, int64_t K, int forced_splits, size_t max_slabs = SIZE_MAX) {
+  static const int cand[] = {TILE_64x64, TILE_128x128};
+  const int forced = tune(SK_TUNE_TILE);
+  const bool force_tile = forced == TILE_64x64 || forced == TILE_128x128;
+  int64_t from = 1, most = K / 128 < 16 ? K / 128 : 16;   // ranges of at least 128
+  if (most < 1) most = 1;
+  if (forced_splits >= 0) from = most = forced_splits < 1 ? 1 : (forced_splits > most ? most : forced_splits);
+  F32Plan f{};
+  double best = -1.0;
+  for (int t : cand) {
+    if (force_tile && t != forced) continue;
+    int bm, bn;
+    tile_dims(t, bm, bn);
+    const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+    for (int64_t sp = from; sp <= most; ++sp) {
+      const int64_t kps = ((K + sp - 1) / sp + F32_BK - 1) / F32_BK * F32_BK;
+      const int64_t splits = (K + kps - 1) / kps;
+      if (splits > 1 && forced_splits < 0 && align_up((size_t)splits * M * N * 4) > max_slabs) continue;
+      const int64_t per_cu = (tiles * splits + NUM_CUS - 1) / NUM_CUS;
+      const double rate = t == TILE_64x64 ? (per_cu > 1 ? 0.52e12 : 0.39e12) : (per_cu > 1 ? 0.53e12 : 0.50e12);
+      double time = per_cu * (double)kps * 2.0 * bm * bn / rate + (t == TILE_64x64 ? 0.0 : 2.0e-6);
+      if (splits > 1) time += 6.0e-6 + splits * (double)M * N * 8.0 / 4.0e12;
+      if (best < 0.0 || time < best) {
+        best = time;
+        f.tile = t; f.splits = (int)splits; f.k_per_split = (int)kps;
+      }
+    }
+  }
+  f.slab_bytes = f.splits > 1 ? align_up((size_t)f.splits * M * N * 4) : 0;
+  return f;
+}
+F32Plan plan_f32_first(int64_t M, int64_t N, int64_t K, size_t max_slabs = SIZE_MAX) {
+  return plan_f32(M, N, K, tune(SK_TUNE_SSPLITS), max_slabs);
 }
 
 // A first contraction of the layer run as a general GEMM: bf16 [M, N] result (the narrow
@@ -208,8 +248,12 @@ struct WeightPlan {
   int z_tile;          // bf16: tile of the GEMM that recomputes Z^T
   int z_splits;        // split of that GEMM over `in` (fp32 slabs, summed into bf16 Z^T)
   int z_k_per_split;
+  // workspace: Z | then either the slabs of Z (dead once summed) or the slabs of dU and db
   size_t z_bytes, part_bytes, csum_bytes, zpart_bytes;
-  size_t total() const { return z_bytes + part_bytes + csum_bytes + zpart_bytes; }
+  size_t total() const {
+    const size_t du = part_bytes + csum_bytes;
+    return z_bytes + (du > zpart_bytes ? du : zpart_bytes);
+  }
 };
 
 // A contraction over the token axis with a small fp32 output [M, N] (a weight gradient):
@@ -217,7 +261,7 @@ struct WeightPlan {
 // so: as few splits as fill the chip, at least 256 tokens each, summed in a fixed
 // order (deterministic).
 struct TokenPlan {
-  int tile;            // bf16 tile configuration; -1 for fp32 (one tile shape)
+  int tile;
   bool big_tile;       // 256 x 256: no registers left for column sums in the kernel
   int splits, k_per_split;
 };
@@ -230,9 +274,9 @@ struct SplitChoice {
   double time;
   int64_t splits, kps;
 };
-static SplitChoice best_split(int64_t M, int64_t N, int64_t T, int bm, int bn, bool bf16) {
+static SplitChoice best_split(int64_t M, int64_t N, int64_t T, int bm, int bn) {
   const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-  const double wg_rate = !bf16 ? 0.3e12 : bm * bn >= 256 * 256 ? 5.0e12
+  const double wg_rate = bm * bn >= 256 * 256 ? 5.0e12
                          : bm * bn >= 128 * 128 ? 3.5e12 : bm * bn >= 128 * 64 ? 2.2e12 : 1.5e12;
   const double t_token = 2.0 * bm * bn / wg_rate;
   const double t_slab = (double)M * N * 8.0 / 4.0e12;
@@ -250,10 +294,18 @@ static SplitChoice best_split(int64_t M, int64_t N, int64_t T, int bm, int bn, b
   return c;
 }
 
-TokenPlan plan_tokens(int64_t M, int64_t N, int64_t T, sk_dtype dtype, bool tunable) {
+TokenPlan plan_tokens(int64_t M, int64_t N, int64_t T, sk_dtype dtype, bool tunable,
+                      size_t room = SIZE_MAX) {
   TokenPlan w{};
+  if (dtype != SK_BF16) {
+    const size_t sums = align_up((size_t)16 * N * 4);   // the column sums' slabs, at the most splits
+    const F32Plan f = plan_f32(M, N, T, tunable ? tune(SK_TUNE_WSPLITS) : -1,
+                               room == SIZE_MAX ? room : (room > sums ? room - sums : 0));
+    w.tile = f.tile; w.splits = f.splits; w.k_per_split = f.k_per_split;
+    return w;
+  }
   int bm, bn;
-  if (dtype == SK_BF16) {
+  {
     w.tile = M > 64 ? TILE_128x64 : TILE_64x64;
     if (((M + 255) / 256) * ((N + 255) / 256) >= NUM_CUS) {
       w.tile = TILE_256x256_W8;
@@ -262,17 +314,14 @@ TokenPlan plan_tokens(int64_t M, int64_t N, int64_t T, sk_dtype dtype, bool tuna
       // tile fills the chip with fewer token splits (few tokens: c1, c2), the square one
       // moves fewer bytes per flop (from half a chip of tiles on, or many tokens:
       // [65536 x 768 -> 3072], R = 128 measured 152 -> 132 us)
-      if (best_split(M, N, T, 128, 128, true).time < best_split(M, N, T, 128, 64, true).time)
+      if (best_split(M, N, T, 128, 128).time < best_split(M, N, T, 128, 64).time)
         w.tile = TILE_128x128;
     }
     if (const int t = tunable ? tune(SK_TUNE_WTILE) : -1; t >= 0 && t < TILE_COUNT) w.tile = t;  // forced
     w.big_tile = w.tile == TILE_256x256_W8 || w.tile == TILE_256x256;
     tile_dims(w.tile, bm, bn);
-  } else {
-    w.tile = -1;
-    bm = F32_BM; bn = F32_BN;
   }
-  const SplitChoice c = best_split(M, N, T, bm, bn, dtype == SK_BF16);
+  const SplitChoice c = best_split(M, N, T, bm, bn);
   int64_t splits = c.splits, kps = c.kps;
   int64_t max_splits = (T + 255) / 256;
   if (max_splits > 32) max_splits = 32;
@@ -289,14 +338,14 @@ TokenPlan plan_tokens(int64_t M, int64_t N, int64_t T, sk_dtype dtype, bool tuna
 // dU = Z^T . dY with Z recomputed: where its pieces live in the workspace.
 WeightPlan plan_weight(const Shape& s) {
   WeightPlan w{};
-  const TokenPlan t = plan_tokens(s.R, s.out, s.T, s.dtype, true);
+  w.ldz = s.dtype == SK_BF16 ? (s.T + 63) / 64 * 64 : s.R;
+  w.z_bytes = align_up((size_t)(s.dtype == SK_BF16 ? s.R * w.ldz * 2 : s.T * s.R * 4));
+  const TokenPlan t = plan_tokens(s.R, s.out, s.T, s.dtype, true, slab_room(w.z_bytes));
   w.tile = t.tile;
   w.own_colsum = t.big_tile;
   w.z_splits = 1;
   w.z_k_per_split = (int)s.in;
   if (s.dtype == SK_BF16) {
-    w.ldz = (s.T + 63) / 64 * 64;
-    w.z_bytes = align_up((size_t)s.R * w.ldz * 2);
     // Z^T [R, T] recomputed as a general GEMM over `in` (plan_first: split over a long
     // `in` when its tiles are few -- the paper's 8192-wide layers at R = 16: 64 tiles of
     // 64 x 64 walking 128 chunks each took 51 us, four ranges and the sum take 17)
@@ -306,11 +355,9 @@ WeightPlan plan_weight(const Shape& s) {
     w.z_k_per_split = f.k_per_split;
     w.zpart_bytes = w.z_splits > 1 ? align_up((size_t)w.z_splits * s.R * w.ldz * 4) : 0;
   } else {
-    w.ldz = s.R;
-    w.z_bytes = align_up((size_t)s.T * s.R * 4);
-    w.z_tile = -1;
-    w.z_splits = f32_first_splits(s.T, s.R, s.in);   // Z = x . S_cat, split like any first GEMM
-    w.zpart_bytes = w.z_splits > 1 ? align_up((size_t)w.z_splits * s.T * s.R * 4) : 0;
+    const F32Plan f = plan_f32_first(s.T, s.R, s.in, slab_room(w.z_bytes));   // Z = x . S_cat, split like any first GEMM
+    w.z_splits = f.splits;
+    w.zpart_bytes = f.slab_bytes;
   }
   const int64_t splits = t.splits, kps = t.k_per_split;
   w.splits = (int)splits;
@@ -472,8 +519,7 @@ size_t first_stage_bytes(const Shape& s, int64_t nc) {
   if (s.dtype == SK_BF16) {
     g_slabs = plan_first(s.T, nc, s.out).slab_bytes;
   } else {
-    const int sp = f32_first_splits(s.T, nc, s.out);
-    g_slabs = sp > 1 ? align_up((size_t)sp * s.T * nc * 4) : 0;
+    g_slabs = plan_f32_first(s.T, nc, s.out).slab_bytes;
   }
   return align_up((size_t)s.T * nc * s.esize) + (da_slabs > g_slabs ? da_slabs : g_slabs);
 }
@@ -533,10 +579,8 @@ size_t workspace_for(sk_op op, const Shape& s) {
       size_t need = mid;
       if (s.dtype == SK_BF16)   // two GEMMs with the first one split: slabs behind the intermediate
         need += plan_first(s.T, s.R, op == SK_OP_FWD ? s.in : s.out).slab_bytes;
-      else {
-        const int sp = f32_first_splits(s.T, s.R, op == SK_OP_FWD ? s.in : s.out);
-        if (sp > 1) need += align_up((size_t)sp * s.T * s.R * 4);
-      }
+      else
+        need += plan_f32_first(s.T, s.R, op == SK_OP_FWD ? s.in : s.out).slab_bytes;
       if (s.dtype == SK_BF16 && chain_supported(s.R)) {
         const size_t b = plan_sketch(s, op == SK_OP_FWD ? s.in : s.out).bytes;
         if (b > need) need = b;
@@ -566,22 +610,20 @@ size_t workspace_for(sk_op op, const Shape& s) {
 
 hipError_t gemm(const Shape& s, GemmKind kind, GemmArgs a, hipStream_t st) {
   if (s.dtype == SK_BF16) return launch_gemm_bf16(kind, choose_tile(a.M, a.N, a.K, 1), a, st);
-  return launch_gemm_f32(kind, a, st);
+  return launch_gemm_f32(kind, plan_f32(a.M, a.N, a.K, 1).tile, a, st);
 }
 
 // The first of the two GEMMs of a call: as it is, or (bf16, plan_first) split over its
 // contraction into fp32 slabs at `slabs` that are then summed into the bf16 result a.C.
 hipError_t first_gemm(const Shape& s, GemmKind kind, GemmKind kind_slabs, GemmArgs a, void* slabs,
-                      hipStream_t st) {
+                      hipStream_t st, size_t max_slabs = SIZE_MAX) {
   if (s.dtype != SK_BF16) {
-    const int splits = f32_first_splits(a.M, a.N, a.K);
-    if (splits == 1) return launch_gemm_f32(kind, a, st);
+    const F32Plan f = plan_f32_first(a.M, a.N, a.K, max_slabs);
+    if (f.splits == 1) return launch_gemm_f32(kind, f.tile, a, st);
     // fp32: the same kernel writes the slabs (one per range of the contraction); summed in order
     float* out = static_cast<float*>(a.C);
-    a.C = slabs; a.splits = splits;
-    a.k_per_split = (int)(((a.K + splits - 1) / splits + F32_BK - 1) / F32_BK * F32_BK);
-    a.splits = (a.K + a.k_per_split - 1) / a.k_per_split;
-    const hipError_t e = launch_gemm_f32(kind, a, st);
+    a.C = slabs; a.splits = f.splits; a.k_per_split = f.k_per_split;
+    const hipError_t e = launch_gemm_f32(kind, f.tile, a, st);
     if (e != hipSuccess) return e;
     ReduceArgs r{};
     r.part = static_cast<const float*>(slabs); r.out = out; r.n = (int64_t)a.M * a.N; r.scale = 1.0f;
@@ -827,7 +869,7 @@ sk_status sk_linear_bwd_weight(const void* x, const void* S_cat, const void* dY,
     GemmArgs z = dense_args(S_cat, s.R, x, in, Z, w.ldz, s.R, tokens, in, 1.0f, nullptr);
     z.n_store = (int)w.ldz;
     if (w.z_splits > 1) {
-      float* zpart = reinterpret_cast<float*>(ws + w.z_bytes + w.part_bytes + w.csum_bytes);
+      float* zpart = reinterpret_cast<float*>(ws + w.z_bytes);
       z.C = zpart; z.splits = w.z_splits; z.k_per_split = w.z_k_per_split;
       e = launch_gemm_bf16(GEMM_TT_F32, w.z_tile, z, hs);
       if (e == hipSuccess) e = launch_reduce_to_bf16(zpart, Z, (int64_t)s.R * w.ldz, w.z_splits, hs);
@@ -837,7 +879,7 @@ sk_status sk_linear_bwd_weight(const void* x, const void* S_cat, const void* dY,
     a.A = Z; a.lda = w.ldz;
   } else {
     e = first_gemm(s, GEMM_NN, GEMM_NN_F32, dense_args(x, in, S_cat, s.R, Z, s.R, tokens, s.R, in, 1.0f, nullptr),
-                   ws + w.z_bytes + w.part_bytes + w.csum_bytes, hs);
+                   ws + w.z_bytes, hs, slab_room(w.z_bytes));
     a.A = Z; a.lda = s.R;
   }
   if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd_weight (x.S)");
@@ -880,7 +922,7 @@ sk_status sk_linear_bwd_weight(const void* x, const void* S_cat, const void* dY,
       e = launch_gemm_bf16(GEMM_NN_F32, w.tile, a, hs);
   } else {
     e = s.dtype == SK_BF16 ? launch_gemm_bf16(GEMM_NN_F32_COLSUM, w.tile, a, hs)
-                           : launch_gemm_f32(GEMM_TN_F32, a, hs);
+                           : launch_gemm_f32(GEMM_TN_F32, w.tile, a, hs);
   }
   if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd_weight (Z^T.dY)");
   if (w.head_cols > 0) {
@@ -1096,7 +1138,7 @@ sk_status sk_linear_bwd_weight_first(const void* x, const void* U_cat, const voi
   if (t.splits == 1) { a.C = dA; a.scale = scale; }
   else { a.C = part; a.scale = 1.0f; }
   e = dtype == SK_BF16 ? launch_gemm_bf16(GEMM_TN_F32_PLAIN, t.tile, a, hs)
-                       : launch_gemm_f32(GEMM_TN_F32, a, hs);
+                       : launch_gemm_f32(GEMM_TN_F32, t.tile, a, hs);
   if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd_weight_first (x^T.G)");
   if (t.splits > 1) {
     ReduceArgs r{};

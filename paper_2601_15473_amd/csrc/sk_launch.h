@@ -153,9 +153,9 @@ inline void note_reduce(const ReduceArgs& r) {
 
 // bf16 operands, fp32 accumulation (MFMA).  `tiles_m/tiles_n` of `a` are filled in here.
 hipError_t launch_gemm_bf16(GemmKind kind, int tile, const GemmArgs& a, hipStream_t s);
-// fp32 operands and accumulation (MFMA), one tile shape.
-hipError_t launch_gemm_f32(GemmKind kind, const GemmArgs& a, hipStream_t s);
-constexpr int F32_BM = 64, F32_BN = 64, F32_BK = 16;
+// fp32 operands and accumulation (MFMA), on TILE_64x64 or TILE_128x128.
+hipError_t launch_gemm_f32(GemmKind kind, int tile, const GemmArgs& a, hipStream_t s);
+constexpr int F32_BK = 32;
 
 hipError_t launch_reduce_splits(const ReduceArgs& a, hipStream_t s);
 // out[i] = bf16(sum over s of part[s][i]), i < n (n a multiple of 4; slabs n elements apart,
