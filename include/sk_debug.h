@@ -22,8 +22,8 @@ extern "C" {
  * sk_linear_workspace_bytes follows the knobs, so size the workspace after setting them.
  */
 typedef enum {
-  SK_TUNE_TILE = 0,     /* tile of the general GEMMs (0..7: 256x256/4 waves, 128x128, 128x64, 64x128,
-                           64x64, 256x128, 128x256, 256x256/8 waves) */
+  SK_TUNE_TILE = 0,     /* tile of the general GEMMs (0..4: 256x256, 128x128, 128x64, 64x128, 64x64;
+                           5..7: 256x256) */
   SK_TUNE_WTILE = 1,    /* tile of the token contraction of sk_linear_bwd_weight (same numbering) */
   SK_TUNE_WSPLITS = 2,  /* number of token splits of that contraction */
   SK_TUNE_BM = 3,       /* rows of a token tile in the on-chip (chain) kernels: 64 or 128 */

@@ -30,6 +30,11 @@ std::atomic<int> g_plan{0};
 // Forced plan parameters (sk_set_tuning; negative = the planner chooses).
 std::atomic<int> g_tune[SK_TUNE_COUNT] = {{-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}};
 int tune(sk_tune_knob knob) { return g_tune[knob].load(std::memory_order_relaxed); }
+// The tile a knob forces (the values past the list stand for the 256 x 256 tile as well), or -1.
+int forced_tile(sk_tune_knob knob) {
+  const int t = tune(knob);
+  return t < 0 ? -1 : t < TILE_COUNT ? t : t <= 7 ? TILE_256x256 : -1;
+}
 
 // The calling thread's launch trace or kernel timer (include/sk_debug.h); null otherwise.
 struct Hooks : LaunchHooks {
@@ -121,15 +126,15 @@ size_t slab_room(size_t z_bytes) {
 // every CU a work-group without being mostly padding, the smallest when the problem
 // cannot fill the chip.
 int choose_tile(int64_t M, int64_t N, int64_t K, int splits) {
-  if (const int t = tune(SK_TUNE_TILE); t >= 0 && t < TILE_COUNT) return t;  // forced (tests, sweeps)
+  if (const int t = forced_tile(SK_TUNE_TILE); t >= 0) return t;  // forced (tests, sweeps)
   const int64_t m_cap = (M + 63) / 64 * 64, n_cap = (N + 63) / 64 * 64;
-  static const int order[] = {TILE_256x256_W8, TILE_128x128, TILE_128x64, TILE_64x128, TILE_64x64};
+  static const int order[] = {TILE_256x256, TILE_128x128, TILE_128x64, TILE_64x128, TILE_64x64};
   for (int i = 0; i < (int)(sizeof(order) / sizeof(order[0])); ++i) {
     const int t = order[i];
     int bm, bn;
     tile_dims(t, bm, bn);
     if (bm > m_cap || bn > n_cap) continue;
-    if (t == TILE_256x256_W8 && K / splits < 512) continue;
+    if (t == TILE_256x256 && K / splits < 512) continue;
     const int64_t wgs = ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
     if (wgs >= NUM_CUS) return t;
   }
@@ -282,10 +287,11 @@ static SplitChoice best_split(int64_t M, int64_t N, int64_t T, int bm, int bn) {
   const double t_slab = (double)M * N * 8.0 / 4.0e12;
   int64_t max_splits = (T + 255) / 256;   // at least 256 tokens each
   if (max_splits > 32) max_splits = 32;
-  SplitChoice c{-1.0, 1, (T + 63) / 64 * 64};
+  const int64_t unit = bm * bn >= 256 * 256 ? 128 : 64;   // of a range: what the tile's kernel takes
+  SplitChoice c{-1.0, 1, (T + unit - 1) / unit * unit};
   for (int64_t sp = 1; sp <= max_splits; ++sp) {
     int64_t k = (T + sp - 1) / sp;
-    k = (k + 63) / 64 * 64;
+    k = (k + unit - 1) / unit * unit;
     const int64_t sp_eff = (T + k - 1) / k;
     const int64_t rounds = (tiles * sp_eff + NUM_CUS - 1) / NUM_CUS;
     const double t = rounds * k * t_token + (sp_eff > 1 ? sp_eff * t_slab + 2.0e-6 : 0.0);
@@ -308,7 +314,7 @@ TokenPlan plan_tokens(int64_t M, int64_t N, int64_t T, sk_dtype dtype, bool tuna
   {
     w.tile = M > 64 ? TILE_128x64 : TILE_64x64;
     if (((M + 255) / 256) * ((N + 255) / 256) >= NUM_CUS) {
-      w.tile = TILE_256x256_W8;
+      w.tile = TILE_256x256;
     } else if (M > 64) {
       // 128 x 64 or 128 x 128, whichever the model has finishing first: the narrower
       // tile fills the chip with fewer token splits (few tokens: c1, c2), the square one
@@ -317,8 +323,8 @@ TokenPlan plan_tokens(int64_t M, int64_t N, int64_t T, sk_dtype dtype, bool tuna
       if (best_split(M, N, T, 128, 128).time < best_split(M, N, T, 128, 64).time)
         w.tile = TILE_128x128;
     }
-    if (const int t = tunable ? tune(SK_TUNE_WTILE) : -1; t >= 0 && t < TILE_COUNT) w.tile = t;  // forced
-    w.big_tile = w.tile == TILE_256x256_W8 || w.tile == TILE_256x256;
+    if (const int t = tunable ? forced_tile(SK_TUNE_WTILE) : -1; t >= 0) w.tile = t;  // forced
+    w.big_tile = w.tile == TILE_256x256;
     tile_dims(w.tile, bm, bn);
   }
   const SplitChoice c = best_split(M, N, T, bm, bn);
@@ -327,7 +333,8 @@ TokenPlan plan_tokens(int64_t M, int64_t N, int64_t T, sk_dtype dtype, bool tuna
   if (max_splits > 32) max_splits = 32;
   if (const int f = tunable ? tune(SK_TUNE_WSPLITS) : -1; f >= 0) {  // forced (clamped to 1..max)
     splits = f < 1 ? 1 : (f > max_splits ? max_splits : f);
-    kps = ((T + splits - 1) / splits + 63) / 64 * 64;
+    const int64_t unit = w.big_tile ? 128 : 64;
+    kps = ((T + splits - 1) / splits + unit - 1) / unit * unit;
     splits = (T + kps - 1) / kps;
   }
   w.splits = (int)splits;
@@ -392,7 +399,7 @@ WeightPlan plan_weight(const Shape& s) {
       if (sp > (s.T + 1023) / 1024) sp = (s.T + 1023) / 1024;
       if (sp > 8) sp = 8;
       if (sp >= 2) {
-        int64_t k2 = ((s.T + sp - 1) / sp + 63) / 64 * 64;
+        int64_t k2 = ((s.T + sp - 1) / sp + 127) / 128 * 128;
         w.head_cols = (int)(head_tn * 256);
         w.splits = (int)((s.T + k2 - 1) / k2);
         w.k_per_split = (int)k2;
@@ -897,7 +904,9 @@ sk_status sk_linear_bwd_weight(const void* x, const void* S_cat, const void* dY,
   if (s.dtype == SK_BF16 && w.own_colsum) {
     // the bias gradient from its own kernel -- or, with the uneven split, inside the launch of
     // the second, shorter round, whose GEMM leaves CUs free
-    const bool ride = dbias && w.head_cols > 0 && w.tile == TILE_256x256_W8;
+    GemmArgs tail = a;
+    tail.N = (int)out - w.head_cols;
+    const bool ride = dbias && w.head_cols > 0 && gemm256_supported(GEMM_NN_F32, tail);
     if (dbias && !ride) {
       e = launch_colsum_bf16(dY, w.colsum_splits == 1 ? dbias : cpart, (int)tokens, (int)out,
                              w.colsum_splits, w.colsum_rows, hs);
@@ -916,7 +925,7 @@ sk_status sk_linear_bwd_weight(const void* x, const void* S_cat, const void* dY,
     }
     a.colsum = nullptr;   // (the big tiles have no column-sum epilogue: that is what the kernel above is for)
     if (ride)
-      e = launch_gemm_f32slabs_with_colsum(w.tile, a, dY, w.colsum_splits == 1 ? dbias : cpart, (int)tokens,
+      e = launch_gemm256_with_colsum(a, dY, w.colsum_splits == 1 ? dbias : cpart, (int)tokens,
                                            (int)out, w.colsum_splits, w.colsum_rows, hs);
     else
       e = launch_gemm_bf16(GEMM_NN_F32, w.tile, a, hs);
@@ -1072,7 +1081,7 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
   // beside Z^T.dY the expansion of dX runs on 128 x 128 tiles even where it would take the
   // eight-wave tile on its own: that one leaves no room on a CU to share (measured at
   // BERT-large: 125 us shared against 133 us one after the other)
-  if (dx_tile == TILE_256x256_W8) dx_tile = TILE_128x128;
+  if (dx_tile == TILE_256x256) dx_tile = TILE_128x128;
   if (bf16_auto && in_plan == PLAN_TWO_GEMM && plan_first(tokens, s.R, out).splits == 1 &&
       dual_gemm_supported(GEMM_NT, g_tile, GEMM_TT, z_tile) &&
       dual_gemm_supported(du_kind, w.tile, GEMM_NT, dx_tile)) {

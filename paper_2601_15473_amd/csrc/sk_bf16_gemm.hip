@@ -3,15 +3,13 @@
 //
 //   C[M, N] = scale * (A . B) (+ bias[n]),   or raw fp32 split-K partial slabs.
 //
-// One work-group of WAVES_M x WAVES_N waves (2 x 2, or 2 x 4 for the eight-wave
-// 256 x 256 tile) owns a BM x BN tile; each wave a (BM/WAVES_M) x (BN/WAVES_N)
-// sub-tile of 32x32 MFMA blocks.  Operands go global -> registers -> LDS (double
+// (The 256 x 256 tile is a kernel of its own: sk_bf16_gemm256.hip.)  One work-group of 2 x 2
+// waves owns a BM x BN tile; each wave a (BM/2) x (BN/2) sub-tile of 32x32 MFMA blocks.
+// Operands go global -> registers -> LDS (double
 // buffered, one barrier per 64-wide k chunk) and are read from LDS directly in the
 // MFMA fragment layout; operands whose contiguous dimension is not k are read with
 // the LDS transpose read.  Results leave straight from registers: fp32 as 16-byte
-// pieces, bf16 after a half-wave exchange that gives each lane eight consecutive
-// columns (no LDS re-layout).  Eight-wave launches with more tiles than CUs run as a
-// crew of one work-group per CU that walks the tiles.
+// pieces, bf16 in whole lines through a wave-private strip of LDS.
 #include "sk_bf16_tile.h"
 #include "sk_launch.h"
 
@@ -21,61 +19,37 @@ namespace sk {
 // (the work of one work-group, given the group's index in the launch and LDS of at
 // least LDS_BYTES).  The body is a device function so that one launch can carry the
 // work-groups of two independent GEMMs (dual_gemm_kernel below).
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, typename OutT,
-          bool COLSUM, int PF>
+template <int BM, int BN, bool A_KC, bool B_KC, typename OutT, bool COLSUM>
 struct GemmTile {
-  static constexpr int NTH = 64 * WAVES_M * WAVES_N;
+  static constexpr int NTH = 256, WAVES_N = 2;
   typedef OpTile<BM, A_KC, BK, NTH> TA;
   typedef OpTile<BN, B_KC, BK, NTH> TB;
-  static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
+  static constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
   static constexpr int STAGE = TA::ELEMS + TB::ELEMS;
   static constexpr int LDS_BYTES = 2 * STAGE * 2;
   // bf16 results leave through a wave-private strip of LDS (32 rows of the wave's sub-tile at
   // a time, see the epilogue), carved out of a main buffer that is idle by then.
   static constexpr int WAVE_STRIP = 32 * WN * 2;
   static_assert((NTH / 64) * WAVE_STRIP <= STAGE * 2, "the waves' strips fit one main buffer");
-  // stride > 0: the work-group goes on to tiles block + stride, block + 2 stride, ... below
-  // `total` (large tiles only), fetching the next tile's first chunk behind the last
-  // MFMAs of the current one.
-  static __device__ __forceinline__ void run(const GemmArgs& p, int block, unsigned char* smem,
-                                             int stride = 0, int total = 0);
+  static __device__ __forceinline__ void run(const GemmArgs& p, int block, unsigned char* smem);
 };
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, typename OutT,
-          bool COLSUM, int PF>
+template <int BM, int BN, bool A_KC, bool B_KC, typename OutT, bool COLSUM>
 __device__ __forceinline__ void
-GemmTile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, OutT, COLSUM, PF>::run(const GemmArgs& p, int block,
-                                                                      unsigned char* const smem,
-                                                                      const int stride, const int total) {
+GemmTile<BM, BN, A_KC, B_KC, OutT, COLSUM>::run(const GemmArgs& p, int block, unsigned char* const smem) {
   bf16* const lds = reinterpret_cast<bf16*>(smem);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
 
   const int tiles = p.tiles_m * p.tiles_n;
-  // where work-group index `blk` of the launch works
-  struct Where {
-    int split, tile_m, m0, n0, k_begin, k_end;
-  };
-  auto locate = [&](int blk) {
-    Where w;
-    const int id = xcd_remap(blk, tiles * p.splits);
-    w.split = id / tiles;
-    int tile_n;
-    tile_coords(id - w.split * tiles, p.tiles_m, p.tiles_n, w.tile_m, tile_n);
-    w.m0 = w.tile_m * BM;
-    w.n0 = tile_n * BN;
-    w.k_begin = w.split * p.k_per_split;
-    w.k_end = (w.k_begin + p.k_per_split < p.K) ? w.k_begin + p.k_per_split : p.K;
-    return w;
-  };
-  Where here = locate(block);
-  int chunk = 0;  // chunks done by this work-group: its parity picks the LDS buffer
-  for (bool first_tile = true;; first_tile = false) {
-  const bool has_next = PF == 1 && stride > 0 && block + stride < total;
-  const Where next = has_next ? locate(block + stride) : here;
-  const int split = here.split, tile_m = here.tile_m, m0 = here.m0, n0 = here.n0;
-  const int k_begin = here.k_begin, k_end = here.k_end;
+  const int id = xcd_remap(block, tiles * p.splits);
+  const int split = id / tiles;
+  int tile_m, tile_n;
+  tile_coords(id - split * tiles, p.tiles_m, p.tiles_n, tile_m, tile_n);
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int k_begin = split * p.k_per_split;
+  const int k_end = (k_begin + p.k_per_split < p.K) ? k_begin + p.k_per_split : p.K;
   const int nk = (k_end - k_begin + BK - 1) / BK;
 
   const bf16* __restrict__ A = static_cast<const bf16*>(p.A);
@@ -126,14 +100,12 @@ GemmTile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, OutT, COLSUM, PF>::run(const Gemm
       }
     }
   };
-  // Work per chunk and thread: NMMA MFMAs per k step, NDSR fragment reads per k step,
-  // NVM global loads and as many LDS stores per chunk.  Each k step is one scheduling
+  // Work per chunk and thread: NMMA MFMAs and NDSR fragment reads per k step.  Each k step is one scheduling
   // phase in which the other instructions are spread evenly between the MFMAs
   // (sched_phase), so they issue in the shadow of the matrix pipe instead of in a
   // burst that stalls it (the texture path takes 16 cycles per 16-byte-per-lane load).
   constexpr int NDSR = (A_KC ? TM : 2 * TM) + (B_KC ? TN : 2 * TN);
   constexpr int NMMA = TM * TN;
-  constexpr int NVM = TA::PIECES + TB::PIECES;
 
   // This lane's bias values (four columns per 8-column group of each 32-column block),
   // fetched before the main loop so the epilogue does not wait for them; through a
@@ -153,56 +125,8 @@ GemmTile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, OutT, COLSUM, PF>::run(const Gemm
       }
   }
 
-  // Iteration shape (PF == 1): the global loads of chunk kc + 1 are issued during k
-  // step 0 of chunk kc and stored to the other LDS buffer during k step 3.
-  // Chunks past the end of the k range load as zeros: no branch around any load.
-  if (PF == 1) {
-    uint4 ra[TA::PIECES], rb[TB::PIECES];
-    if (first_tile) {
-      TA::load(ra, A, p.lda, m0, p.M, k_begin, k_end, p.K, tid);
-      TB::load(rb, B, p.ldb, n0, p.N, k_begin, k_end, p.K, tid);
-      TA::store(lds, ra, tid);
-      TB::store(lds + TA::ELEMS, rb, tid);
-      __syncthreads();
-    }
-    for (int kc = 0; kc < nk; ++kc, ++chunk) {
-      const bf16* As = lds + (chunk & 1) * STAGE;
-      bf16* An = lds + ((chunk + 1) & 1) * STAGE;
-      // the chunk fetched during this one: the next of this tile, or, behind the last
-      // one, the first of the work-group's next tile
-      const bool into_next = has_next && kc + 1 == nk;
-      const int lm0 = into_next ? next.m0 : m0, ln0 = into_next ? next.n0 : n0;
-      const int k0 = into_next ? next.k_begin : k_begin + (kc + 1) * BK;
-      const int lk_end = into_next ? next.k_end : k_end;
-      read(As, 0, fa0, fb0);
-      __builtin_amdgcn_sched_barrier(0);
-      // k step 0: MFMAs + fragment reads of step 1 + all loads of the next chunk (issued
-      // as early as possible: they are stored to LDS three k steps later)
-      read(As, 1, fa1, fb1);
-      TA::load(ra, A, p.lda, lm0, p.M, k0, lk_end, p.K, tid);
-      TB::load(rb, B, p.ldb, ln0, p.N, k0, lk_end, p.K, tid);
-      mma(fa0, fb0);
-      sched_phase<NMMA, NDSR, NVM, 0>();
-      // k step 1
-      read(As, 2, fa0, fb0);
-      mma(fa1, fb1);
-      sched_phase<NMMA, NDSR, 0, 0>();
-      // k step 2
-      read(As, 3, fa1, fb1);
-      mma(fa0, fb0);
-      sched_phase<NMMA, NDSR, 0, 0>();
-      // k step 3: MFMAs + LDS stores of the next chunk.  (Stores and barrier one step
-      // earlier, with the next chunk's first fragments read behind this step's MFMAs as
-      // the small tiles do below, cost the eight-wave tile 5 %: its loads then have
-      // two k steps to land instead of three, and the extra live fragments spill.)
-      mma(fa1, fb1);
-      TA::store(An, ra, tid);
-      TB::store(An + TA::ELEMS, rb, tid);
-      sched_phase<NMMA, 0, 0, NVM>();
-      __syncthreads();
-    }
-  } else {
-    // Small tiles: an iteration is too short to cover a load's latency, so two
+  {
+    // An iteration is too short to cover a load's latency, so two
     // register sets keep the loads of chunk kc + 2 in flight while chunk kc + 1,
     // loaded one iteration earlier, is stored.  (Four and six sets were measured on the
     // shapes of this layer and were no faster.)
@@ -289,12 +213,10 @@ GemmTile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, OutT, COLSUM, PF>::run(const Gemm
     constexpr int PPRW = WN / 8;        // 16-byte pieces per row of the wave's sub-tile
     constexpr int RPI = 64 / PPRW;      // rows one store instruction covers
     constexpr int ROW_BYTES = WN * 2;
-    // The strips live in the main buffer that is idle now.  Large tiles: the one the last
-    // chunk was multiplied out of (everybody passed the barrier behind it; the other buffer
-    // may already hold the first chunk of the work-group's next tile).  Small tiles: their
-    // last k step still read fragments after the loop's last barrier, so one more comes first.
-    if constexpr (PF != 1) __syncthreads();
-    unsigned char* const strip = smem + (PF == 1 ? ((chunk + 1) & 1) * STAGE * 2 : 0) + wave * WAVE_STRIP;
+    // The strips live in the main buffer.  The last k step still read fragments after the
+    // loop's last barrier, so one more comes first.
+    __syncthreads();
+    unsigned char* const strip = smem + wave * WAVE_STRIP;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int row_w = lane & 31;
@@ -352,31 +274,11 @@ GemmTile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, OutT, COLSUM, PF>::run(const Gemm
         }
     }
   }
-
-  if (!has_next) break;
-  // (the next tile's first chunk will store into the buffer the strips were in)
-  if constexpr (sizeof(OutT) == 2) __syncthreads();
-  block += stride;
-  here = next;
-  }  // tiles of this work-group
 }
 
-// The large tiles as a fixed crew of work-groups, one per CU, each walking the tiles
-// index, index + crew, ...: the first chunk of a work-group's next tile is fetched behind
-// the last MFMAs of its current one instead of in a new work-group's prologue.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, typename OutT,
-          bool COLSUM, int PF>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_crew_kernel(const GemmArgs p,
-                                                                                 const int total) {
-  typedef GemmTile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, OutT, COLSUM, PF> G;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[G::LDS_BYTES];
-  G::run(p, blockIdx.x, smem, gridDim.x, total);
-}
-
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, typename OutT,
-          bool COLSUM, int PF>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(const GemmArgs p) {
-  typedef GemmTile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, OutT, COLSUM, PF> G;
+template <int BM, int BN, bool A_KC, bool B_KC, typename OutT, bool COLSUM>
+__global__ __launch_bounds__(256) void gemm_bf16_kernel(const GemmArgs p) {
+  typedef GemmTile<BM, BN, A_KC, B_KC, OutT, COLSUM> G;
   __shared__ __attribute__((aligned(16))) unsigned char smem[G::LDS_BYTES];
   G::run(p, blockIdx.x, smem);
 }
@@ -442,46 +344,32 @@ __global__ __launch_bounds__(256) void reduce_to_bf16_kernel(const float* __rest
 template <typename OutT>
 static std::string out_label() { return sizeof(OutT) == 2 ? "bf16" : "float"; }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, typename OutT, bool COLSUM>
+template <int BM, int BN, bool A_KC, bool B_KC, typename OutT, bool COLSUM>
 static hipError_t launch_cfg(GemmArgs a, hipStream_t s) {
   a.tiles_m = (a.M + BM - 1) / BM;
   a.tiles_n = (a.N + BN - 1) / BN;
   const long long grid = (long long)a.tiles_m * a.tiles_n * a.splits;
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
   note_gemm(a, A_KC, B_KC, 2, sizeof(OutT), sizeof(OutT) == 4);
-  // big per-wave tiles have no registers to spare for a second set of loads in flight
-  constexpr int PF = (BM * BN / (WAVES_M * WAVES_N) >= 128 * 64) ? 1 : 2;
-  const auto params = {lbl(BM), lbl(BN), lbl(WAVES_M), lbl(WAVES_N), lbl(A_KC), lbl(B_KC), out_label<OutT>(),
-                       lbl(COLSUM), lbl(PF)};
-  if constexpr (PF == 1 && !COLSUM && WAVES_M * WAVES_N == 8) if (grid > NUM_CUS && grid < 0x7fffffffLL - NUM_CUS) {
-    // more tiles than CUs: one work-group per CU (the tile's LDS admits no second) walks them
-    static const std::string name = kernel_label("gemm_bf16_crew_kernel", params);
-    return launch_kernel(name.c_str(), gemm_work(a, 2, sizeof(OutT), sizeof(OutT) == 4), gemm_bf16_crew_kernel<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, OutT, COLSUM, PF>,
-                         dim3((unsigned)NUM_CUS), dim3(64 * WAVES_M * WAVES_N), s, a, (int)grid);
-  }
-  static const std::string name = kernel_label("gemm_bf16_kernel", params);
-  return launch_kernel(name.c_str(), gemm_work(a, 2, sizeof(OutT), sizeof(OutT) == 4), gemm_bf16_kernel<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, OutT, COLSUM, PF>,
-                       dim3((unsigned)grid), dim3(64 * WAVES_M * WAVES_N), s, a);
+  static const std::string name = kernel_label("gemm_bf16_kernel", {lbl(BM), lbl(BN), lbl(A_KC), lbl(B_KC), out_label<OutT>(), lbl(COLSUM)});
+  return launch_kernel(name.c_str(), gemm_work(a, 2, sizeof(OutT), sizeof(OutT) == 4), gemm_bf16_kernel<BM, BN, A_KC, B_KC, OutT, COLSUM>,
+                       dim3((unsigned)grid), dim3(256), s, a);
 }
 
 template <bool A_KC, bool B_KC, typename OutT, bool COLSUM>
 static hipError_t launch_tiles(int tile, const GemmArgs& a, hipStream_t s) {
-  // the 256 x 256 tiles have no registers left for the column sums
-  if (COLSUM && (tile == TILE_256x256 || tile == TILE_256x256_W8)) return hipErrorInvalidValue;
   switch (tile) {
-    case TILE_256x256: return launch_cfg<256, 256, 2, 2, A_KC, B_KC, OutT, false>(a, s);
-    case TILE_128x128: return launch_cfg<128, 128, 2, 2, A_KC, B_KC, OutT, COLSUM>(a, s);
-    case TILE_128x64: return launch_cfg<128, 64, 2, 2, A_KC, B_KC, OutT, COLSUM>(a, s);
-    case TILE_64x128: return launch_cfg<64, 128, 2, 2, A_KC, B_KC, OutT, COLSUM>(a, s);
-    case TILE_64x64: return launch_cfg<64, 64, 2, 2, A_KC, B_KC, OutT, COLSUM>(a, s);
-    case TILE_256x128: return launch_cfg<256, 128, 2, 2, A_KC, B_KC, OutT, COLSUM>(a, s);
-    case TILE_128x256: return launch_cfg<128, 256, 2, 2, A_KC, B_KC, OutT, COLSUM>(a, s);
-    case TILE_256x256_W8: return launch_cfg<256, 256, 2, 4, A_KC, B_KC, OutT, false>(a, s);
+    case TILE_256x256:   // (what that kernel cannot take)
+    case TILE_128x128: return launch_cfg<128, 128, A_KC, B_KC, OutT, COLSUM>(a, s);
+    case TILE_128x64: return launch_cfg<128, 64, A_KC, B_KC, OutT, COLSUM>(a, s);
+    case TILE_64x128: return launch_cfg<64, 128, A_KC, B_KC, OutT, COLSUM>(a, s);
+    case TILE_64x64: return launch_cfg<64, 64, A_KC, B_KC, OutT, COLSUM>(a, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 hipError_t launch_gemm_bf16(GemmKind kind, int tile, const GemmArgs& a, hipStream_t s) {
+  if (tile == TILE_256x256 && gemm256_supported(kind, a)) return launch_gemm256_bf16(kind, a, s);
   switch (kind) {
     case GEMM_NN: return launch_tiles<true, false, bf16, false>(tile, a, s);
     case GEMM_NT: return launch_tiles<true, true, bf16, false>(tile, a, s);
@@ -493,76 +381,6 @@ hipError_t launch_gemm_bf16(GemmKind kind, int tile, const GemmArgs& a, hipStrea
     case GEMM_NT_F32: return launch_tiles<true, true, float, false>(tile, a, s);
     case GEMM_TT_F32: return launch_tiles<false, true, float, false>(tile, a, s);
     default: return hipErrorInvalidValue;
-  }
-}
-
-// Column sums of a dense row-major bf16 matrix [rows, cols] in fp32, the row range cut
-// into `splits` runs of rows_per_split (out[s][c] = sum of rows of run s; fixed order).
-// One work-group owns 512 columns of one run: a wave reads one whole 1 KB row segment
-// per instruction (lane = 8 columns), the four waves stride over the rows, and their
-// four partial sums meet in LDS and are added in wave order.
-constexpr int COLSUM_COLS = 512;
-// The work of one work-group of NW waves at grid position (bx, by); `part` is NW rows of
-// COLSUM_COLS + 8 floats of LDS.
-template <int NW>
-__device__ __forceinline__ void colsum_body(const unsigned short* __restrict__ in, float* __restrict__ out,
-                                            int rows, int cols, int rows_per_split, int bx, int by,
-                                            float* part) {
-  constexpr int PLD = COLSUM_COLS + 8;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c = bx * COLSUM_COLS + lane * 8;
-  const int r_begin = by * rows_per_split;
-  const int r_end = (r_begin + rows_per_split < rows) ? r_begin + rows_per_split : rows;
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (c < cols) {
-#pragma unroll 8
-    for (int r = r_begin + wave; r < r_end; r += NW) {
-      const uint4 v = *reinterpret_cast<const uint4*>(in + (int64_t)r * cols + c);
-      const unsigned w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc[2 * e] += __builtin_bit_cast(float, w[e] << 16);
-        acc[2 * e + 1] += __builtin_bit_cast(float, w[e] & 0xffff0000u);
-      }
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) part[wave * PLD + lane * 8 + e] = acc[e];
-  __syncthreads();
-  for (int i = tid; i < COLSUM_COLS; i += 64 * NW) {
-    const int gc = bx * COLSUM_COLS + i;
-    if (gc < cols) {
-      float s = part[i];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) s += part[w * PLD + i];   // in wave order
-      out[(int64_t)by * cols + gc] = s;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void colsum_bf16_kernel(const unsigned short* __restrict__ in,
-                                                          float* __restrict__ out, int rows,
-                                                          int cols, int rows_per_split) {
-  __shared__ float part[4 * (COLSUM_COLS + 8)];
-  colsum_body<4>(in, out, rows, cols, rows_per_split, blockIdx.x, blockIdx.y, part);
-}
-
-// An eight-wave GEMM launch that does not fill the chip, with the column sums riding
-// along: work-groups past the GEMM's own run the column-sum body (eight waves each) on
-// the CUs the GEMM leaves free -- one streams from HBM while the other multiplies.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, typename OutT, int PF>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_with_colsum_kernel(
-    const GemmArgs p, const int gemm_groups, const ColsumArgs c) {
-  typedef GemmTile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, OutT, false, PF> G;
-  static_assert(G::NTH == 512, "the column-sum body here runs eight waves");
-  static_assert(G::LDS_BYTES >= 8 * (COLSUM_COLS + 8) * 4, "LDS of the GEMM tile covers the partial sums");
-  __shared__ __attribute__((aligned(16))) unsigned char smem[G::LDS_BYTES];
-  if ((int)blockIdx.x < gemm_groups) {
-    G::run(p, blockIdx.x, smem);
-  } else {
-    const int w = blockIdx.x - gemm_groups;
-    colsum_body<8>(static_cast<const unsigned short*>(c.in), c.out, c.rows, c.cols, c.rows_per_split,
-                   w % c.col_groups, w / c.col_groups, reinterpret_cast<float*>(smem));
   }
 }
 
@@ -619,15 +437,15 @@ hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKi
     work.flops += wb.flops;
     work.bytes += wb.bytes;
   }
-  typedef GemmTile<64, 128, 2, 2, true, true, float, false, 2> NTF_64x128;
-  typedef GemmTile<64, 64, 2, 2, true, true, float, false, 2> NTF_64x64;
-  typedef GemmTile<64, 64, 2, 2, false, true, bf16, false, 2> TT_64x64;
-  typedef GemmTile<128, 128, 2, 2, true, true, bf16, false, 2> NT_128x128;
-  typedef GemmTile<128, 128, 2, 2, false, true, bf16, false, 2> TT_128x128;
-  typedef GemmTile<128, 64, 2, 2, true, false, float, true, 2> NNFC_128x64;
-  typedef GemmTile<128, 128, 2, 2, true, false, float, true, 2> NNFC_128x128;
-  typedef GemmTile<64, 64, 2, 2, true, true, bf16, false, 2> NT_64x64;
-  typedef GemmTile<128, 64, 2, 2, true, true, bf16, false, 2> NT_128x64;
+  typedef GemmTile<64, 128, true, true, float, false> NTF_64x128;
+  typedef GemmTile<64, 64, true, true, float, false> NTF_64x64;
+  typedef GemmTile<64, 64, false, true, bf16, false> TT_64x64;
+  typedef GemmTile<128, 128, true, true, bf16, false> NT_128x128;
+  typedef GemmTile<128, 128, false, true, bf16, false> TT_128x128;
+  typedef GemmTile<128, 64, true, false, float, true> NNFC_128x64;
+  typedef GemmTile<128, 128, true, false, float, true> NNFC_128x128;
+  typedef GemmTile<64, 64, true, true, bf16, false> NT_64x64;
+  typedef GemmTile<128, 64, true, true, bf16, false> NT_128x64;
   const char* name = "dual_gemm_kernel";
   switch (pair) {
     case 0: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x128, TT_64x64>, grid, block, s, a, b, (int)ga);
@@ -639,37 +457,6 @@ hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKi
     case 6: return launch_kernel(name, work, dual_gemm_kernel<NNFC_128x64, NT_128x64>, grid, block, s, a, b, (int)ga);
     default: return hipErrorInvalidValue;
   }
-}
-
-hipError_t launch_gemm_f32slabs_with_colsum(int tile, GemmArgs a, const void* in, float* out, int rows,
-                                            int cols, int splits, int rows_per_split, hipStream_t s) {
-  if (tile != TILE_256x256_W8) return hipErrorInvalidValue;
-  a.tiles_m = (a.M + 255) / 256;
-  a.tiles_n = (a.N + 255) / 256;
-  ColsumArgs c;
-  c.in = in; c.out = out; c.rows = rows; c.cols = cols; c.rows_per_split = rows_per_split;
-  c.col_groups = (cols + COLSUM_COLS - 1) / COLSUM_COLS;
-  const long long gg = (long long)a.tiles_m * a.tiles_n * a.splits;
-  const long long grid = gg + (long long)c.col_groups * splits;
-  if (gg <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  note_gemm(a, true, false, 2, 4, true);
-  note_matrix(in, rows, cols, cols, 2, false);
-  note_matrix(out, splits, cols, cols, 4, true);
-  Work work = gemm_work(a, 2, 4, true);
-  work.bytes += (double)rows * cols * 2 + (double)splits * cols * 4;
-  return launch_kernel("gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float, 1>", work,
-                       gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float, 1>,
-                       dim3((unsigned)grid), dim3(512), s, a, (int)gg, c);
-}
-
-hipError_t launch_colsum_bf16(const void* in, float* out, int rows, int cols, int splits,
-                              int rows_per_split, hipStream_t s) {
-  const dim3 grid((unsigned)((cols + COLSUM_COLS - 1) / COLSUM_COLS), (unsigned)splits);
-  note_matrix(in, rows, cols, cols, 2, false);
-  note_matrix(out, splits, cols, cols, 4, true);
-  return launch_kernel("colsum_bf16_kernel", Work{0.0, (double)rows * cols * 2 + (double)splits * cols * 4},
-                       colsum_bf16_kernel, grid, dim3(256), s,
-                       static_cast<const unsigned short*>(in), out, rows, cols, rows_per_split);
 }
 
 __global__ __launch_bounds__(256) void reduce_splits_2d_kernel(const float* __restrict__ part,

@@ -100,15 +100,11 @@ enum TileCfg : int {
   TILE_128x64 = 2,
   TILE_64x128 = 3,
   TILE_64x64 = 4,
-  TILE_256x128 = 5,
-  TILE_128x256 = 6,
-  TILE_256x256_W8 = 7,   // 256 x 256 with eight waves (2 x 4), two per SIMD
-  TILE_COUNT = 8,
+  TILE_COUNT = 5,
 };
 
 inline void tile_dims(int tile, int& bm, int& bn) {
-  static const int dims[TILE_COUNT][2] = {{256, 256}, {128, 128}, {128, 64}, {64, 128},
-                                          {64, 64},   {256, 128}, {128, 256}, {256, 256}};
+  static const int dims[TILE_COUNT][2] = {{256, 256}, {128, 128}, {128, 64}, {64, 128}, {64, 64}};
   bm = dims[tile][0];
   bn = dims[tile][1];
 }
@@ -153,6 +149,11 @@ inline void note_reduce(const ReduceArgs& r) {
 
 // bf16 operands, fp32 accumulation (MFMA).  `tiles_m/tiles_n` of `a` are filled in here.
 hipError_t launch_gemm_bf16(GemmKind kind, int tile, const GemmArgs& a, hipStream_t s);
+// The 256 x 256 tile of the above, for what gemm256_supported says it can take (launch_gemm_bf16 asks,
+// and runs the rest on 128 x 128 tiles): no column sums, k ranges but the last multiples of 128 and at
+// least 256 long, a range's rows of an operand that is not k-contiguous within 2 GB.
+bool gemm256_supported(GemmKind kind, const GemmArgs& a);
+hipError_t launch_gemm256_bf16(GemmKind kind, const GemmArgs& a, hipStream_t s);
 // fp32 operands and accumulation (MFMA), on TILE_64x64 or TILE_128x128.
 hipError_t launch_gemm_f32(GemmKind kind, int tile, const GemmArgs& a, hipStream_t s);
 constexpr int F32_BK = 32;
@@ -175,10 +176,10 @@ hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKi
 // `cols` sums per run of rows_per_split rows (splits runs)
 hipError_t launch_colsum_bf16(const void* in, float* out, int rows, int cols, int splits,
                               int rows_per_split, hipStream_t s);
-// The split-K GEMM_NN_F32 `a` on the eight-wave 256 x 256 tile with the column sums above
-// computed in the same launch, on the CUs the GEMM's work-groups leave free.
-hipError_t launch_gemm_f32slabs_with_colsum(int tile, GemmArgs a, const void* in, float* out, int rows,
-                                            int cols, int splits, int rows_per_split, hipStream_t s);
+// The split-K GEMM_NN_F32 `a` on the 256 x 256 tile with the column sums above computed in the
+// same launch, on the CUs the GEMM's work-groups leave free.
+hipError_t launch_gemm256_with_colsum(GemmArgs a, const void* in, float* out, int rows, int cols, int splits,
+                                      int rows_per_split, hipStream_t s);
 
 // Second contraction of the layer with the R-wide intermediate of a 64-token tile
 // resident on chip (bf16, R <= 512), optionally with the first contraction fused in:
