@@ -119,22 +119,30 @@ size_t slab_room(size_t z_bytes) {
   return z_bytes < SK_NOALLOC_SCRATCH_BYTES ? SK_NOALLOC_SCRATCH_BYTES - z_bytes : SIZE_MAX;
 }
 
-// Tile choice for the general GEMM (measured on MI355X).  The 256 x 256 tile with eight
-// waves has the best steady state (fewest LDS instructions per MFMA) but a long prologue,
-// so it pays from a contraction of 512 on when its tiles fill the chip; 128 x 128 runs two work-groups per CU, which overlaps one
-// tile's stores with the other's MFMAs.  Otherwise: the largest tile that still gives
-// every CU a work-group without being mostly padding, the smallest when the problem
-// cannot fill the chip.
+// Tile choice for the general GEMM (measured on MI355X).  256 x 256 where its rounds of 256
+// work-groups are modelled to end before 128 x 128's (two work-groups per CU): a round takes
+// 6 us + 0.0215 us per k against 4.2 + 0.0165 for 512 of the smaller tiles, so 192 of the big
+// tiles already win (K = 320: 18.6 against 18.7 us; K = 2048: 49 against 60), 128 do not (K = 512: 19.5
+// against 16.3), and one more than a round has no use for them.  Otherwise the largest tile that
+// still gives every CU a work-group without being mostly padding, the smallest when the
+// problem cannot fill the chip.
 int choose_tile(int64_t M, int64_t N, int64_t K, int splits) {
   if (const int t = forced_tile(SK_TUNE_TILE); t >= 0) return t;  // forced (tests, sweeps)
   const int64_t m_cap = (M + 63) / 64 * 64, n_cap = (N + 63) / 64 * 64;
-  static const int order[] = {TILE_256x256, TILE_128x128, TILE_128x64, TILE_64x128, TILE_64x64};
+  if (K / splits > 128 && m_cap >= 256 && n_cap >= 256) {
+    const int64_t big = ((M + 255) / 256) * ((N + 255) / 256) * splits;
+    const int64_t small = ((M + 127) / 128) * ((N + 127) / 128) * splits;
+    const double rounds = (double)((big + NUM_CUS - 1) / NUM_CUS);
+    const double halves = (double)((small + NUM_CUS - 1) / NUM_CUS);   // half rounds: one work-group per CU
+    const double k = (double)K / splits;
+    if (6.0 + rounds * (6.0 + 0.0215 * k) < 5.0 + (halves < 2 ? 2 : halves) / 2 * (4.2 + 0.0165 * k)) return TILE_256x256;
+  }
+  static const int order[] = {TILE_128x128, TILE_128x64, TILE_64x128, TILE_64x64};
   for (int i = 0; i < (int)(sizeof(order) / sizeof(order[0])); ++i) {
     const int t = order[i];
     int bm, bn;
     tile_dims(t, bm, bn);
     if (bm > m_cap || bn > n_cap) continue;
-    if (t == TILE_256x256 && K / splits < 512) continue;
     const int64_t wgs = ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
     if (wgs >= NUM_CUS) return t;
   }
