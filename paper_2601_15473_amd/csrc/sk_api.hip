@@ -206,9 +206,34 @@ F32Plan plan_f32_first(int64_t M, int64_t N, int64_t K, size_t max_slabs = SIZE_
 struct FirstPlan {
   int tile, splits, k_per_split;
   size_t slab_bytes;   // fp32 slabs (0 when not split)
+  bool few;            // the few-rows kernel
 };
-FirstPlan plan_first(int64_t M, int64_t N, int64_t K) {
+
+// Splits of a GEMM_NN or GEMM_NT [M, N] over K on the few-rows kernel, 0 where the tiles are the better
+// choice.  Up to 64 rows it wins everywhere (one kernel each, us, against the tiles: [8 x 2048] .
+// [2048 x 11008] 12 : 15, [64 x 1024] . [1024 x 512] 4.5 : 8); above, every 64 rows stream B again,
+// and it wins while that is less than a round of short work-groups ([131 x 768] . [768 x 128] 4 : 7,
+// [128 x 384] . [384 x 8192] level, [512 x 512] . [512 x 4096] 11 : 8).  Its columns lie a row of B apart,
+// which for a power-of-two row is one L2 channel an XCD: past K = 3072 a first contraction gives each
+// XCD a k range instead ([8 x 4096] . [4096 x 2048] 17.5 us in one range, 6.6 + 4 for the sum in eight).
+int few_rows_splits(int64_t M, int64_t N, int64_t K, bool first) {
+  if (M > 256 || tune(SK_TUNE_TILE) >= 0) return 0;
+  const int64_t tiles = (M + 63) / 64 * ((N + 63) / 64);
+  int splits = first && K > 3072 ? 8 : 1;
+  while (splits > 1 && M <= 64 && tiles * splits > NUM_CUS) splits /= 2;
+  if (M > 64 && (tiles > 160 || tiles * splits > NUM_CUS || tiles * K / 64 / splits > 1024)) return 0;
+  return splits;
+}
+
+FirstPlan plan_first(int64_t M, int64_t N, int64_t K, bool rows) {
   FirstPlan f{};
+  if (const int sp = rows ? few_rows_splits(M, N, K, true) : 0; sp > 0) {
+    f.few = true;
+    f.splits = sp;
+    f.k_per_split = (int)(((K + sp - 1) / sp + 63) / 64 * 64);
+    f.slab_bytes = sp > 1 ? align_up((size_t)sp * M * N * 4) : 0;
+    return f;
+  }
   f.tile = choose_tile(M, N, K, 1);
   f.splits = 1;
   f.k_per_split = (int)((K + 63) / 64 * 64);
@@ -364,7 +389,7 @@ WeightPlan plan_weight(const Shape& s) {
     // Z^T [R, T] recomputed as a general GEMM over `in` (plan_first: split over a long
     // `in` when its tiles are few -- the paper's 8192-wide layers at R = 16: 64 tiles of
     // 64 x 64 walking 128 chunks each took 51 us, four ranges and the sum take 17)
-    const FirstPlan f = plan_first(s.R, s.T, s.in);
+    const FirstPlan f = plan_first(s.R, s.T, s.in, false);
     w.z_tile = f.tile;
     w.z_splits = f.splits;
     w.z_k_per_split = f.k_per_split;
@@ -461,7 +486,7 @@ ChainShape chain_shape(int64_t T, int64_t N, int R, bool share_cu) {
   return c;
 }
 
-Plan pick_plan(const Shape& s, sk_op op) {
+Plan pick_plan(const Shape& s, sk_op op, bool workspace) {
   const int forced = g_plan.load(std::memory_order_relaxed);
   const bool chain_ok = s.dtype == SK_BF16 && chain_supported(s.R);
   const bool fused_ok = chain_ok && s.R <= CHAIN_FUSED_MAX_R;
@@ -479,9 +504,14 @@ Plan pick_plan(const Shape& s, sk_op op) {
   // gradient, 3072 long, from two slices down, i.e. from 6144 tokens on, where it
   // measured level at two slices and 16-20 % ahead at one).  Beyond that the first
   // contraction is split over its length instead and the expansion sums the slabs.
+  const int64_t k1 = op == SK_OP_FWD ? s.in : s.out;
+  const int64_t n2 = op == SK_OP_FWD ? s.out : s.in;
+  // Few tokens: two launches of the few-rows kernel beat even the single fused one ([8 x 768] -> 768,
+  // R = 32: 6.6 us against 8.1; [131 x 768] -> 3072, R = 128: 8.4 against 11.8 split), which stays for
+  // callers without a workspace.
+  if (s.dtype == SK_BF16 && workspace && few_rows_splits(s.T, s.R, k1, true) > 0 && few_rows_splits(s.T, n2, s.R, false) > 0)
+    return PLAN_TWO_GEMM;
   if (chain_ok && s.R <= 128) {
-    const int64_t k1 = op == SK_OP_FWD ? s.in : s.out;
-    const int64_t n2 = op == SK_OP_FWD ? s.out : s.in;
     return k1 * chain_shape(s.T, n2, s.R, false).slices <= 6144 ? PLAN_FUSED : PLAN_SPLIT_EXPAND;
   }
   return PLAN_TWO_GEMM;
@@ -532,7 +562,7 @@ size_t first_stage_bytes(const Shape& s, int64_t nc) {
   // region of the dA slabs
   size_t g_slabs;
   if (s.dtype == SK_BF16) {
-    g_slabs = plan_first(s.T, nc, s.out).slab_bytes;
+    g_slabs = plan_first(s.T, nc, s.out, true).slab_bytes;
   } else {
     g_slabs = plan_f32_first(s.T, nc, s.out).slab_bytes;
   }
@@ -593,7 +623,7 @@ size_t workspace_for(sk_op op, const Shape& s) {
       // the maximum over the plans, so one buffer serves whichever is selected
       size_t need = mid;
       if (s.dtype == SK_BF16)   // two GEMMs with the first one split: slabs behind the intermediate
-        need += plan_first(s.T, s.R, op == SK_OP_FWD ? s.in : s.out).slab_bytes;
+        need += plan_first(s.T, s.R, op == SK_OP_FWD ? s.in : s.out, true).slab_bytes;
       else
         need += plan_f32_first(s.T, s.R, op == SK_OP_FWD ? s.in : s.out).slab_bytes;
       if (s.dtype == SK_BF16 && chain_supported(s.R)) {
@@ -624,6 +654,7 @@ size_t workspace_for(sk_op op, const Shape& s) {
 }
 
 hipError_t gemm(const Shape& s, GemmKind kind, GemmArgs a, hipStream_t st) {
+  if (s.dtype == SK_BF16 && few_rows_splits(a.M, a.N, a.K, false) > 0) return launch_gemm_few_rows_bf16(kind, a, st);
   if (s.dtype == SK_BF16) return launch_gemm_bf16(kind, choose_tile(a.M, a.N, a.K, 1), a, st);
   return launch_gemm_f32(kind, plan_f32(a.M, a.N, a.K, 1).tile, a, st);
 }
@@ -645,11 +676,11 @@ hipError_t first_gemm(const Shape& s, GemmKind kind, GemmKind kind_slabs, GemmAr
     r.splits = a.splits; r.splits2 = 1; r.scale2 = 1.0f;
     return launch_reduce_splits(r, st);
   }
-  const FirstPlan f = plan_first(a.M, a.N, a.K);
-  if (f.splits == 1) return launch_gemm_bf16(kind, f.tile, a, st);
+  const FirstPlan f = plan_first(a.M, a.N, a.K, true);
+  if (f.splits == 1) return f.few ? launch_gemm_few_rows_bf16(kind, a, st) : launch_gemm_bf16(kind, f.tile, a, st);
   void* out = a.C;
   a.C = slabs; a.splits = f.splits; a.k_per_split = f.k_per_split;
-  const hipError_t e = launch_gemm_bf16(kind_slabs, f.tile, a, st);
+  const hipError_t e = f.few ? launch_gemm_few_rows_bf16(kind, a, st) : launch_gemm_bf16(kind_slabs, f.tile, a, st);
   if (e != hipSuccess) return e;
   return launch_reduce_to_bf16(static_cast<const float*>(slabs), out, (int64_t)a.M * a.N, f.splits, st);
 }
@@ -777,7 +808,7 @@ sk_status sk_linear_fwd(const void* x, const void* S_cat, const void* U_cat, con
   const float scale = 1.0f / (float)l;
   g_hip_error.clear();
 
-  const Plan plan = pick_plan(s, SK_OP_FWD);
+  const Plan plan = pick_plan(s, SK_OP_FWD, workspace && workspace_bytes >= workspace_for(SK_OP_FWD, s));
   if (plan != PLAN_FUSED && (!workspace || workspace_bytes < workspace_for(SK_OP_FWD, s)))
     return SK_ERR_WORKSPACE;
   if (plan == PLAN_FUSED || plan == PLAN_SPLIT_EXPAND) {
@@ -823,7 +854,7 @@ sk_status sk_linear_bwd_input(const void* dY, const void* S_cat, const void* U_c
   const float scale = 1.0f / (float)l;
   g_hip_error.clear();
 
-  const Plan plan = pick_plan(s, SK_OP_BWD_INPUT);
+  const Plan plan = pick_plan(s, SK_OP_BWD_INPUT, workspace && workspace_bytes >= workspace_for(SK_OP_BWD_INPUT, s));
   if (plan != PLAN_FUSED && (!workspace || workspace_bytes < workspace_for(SK_OP_BWD_INPUT, s)))
     return SK_ERR_WORKSPACE;
   if (plan == PLAN_FUSED || plan == PLAN_SPLIT_EXPAND) {
@@ -1037,7 +1068,7 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
   // (not when Z^T is recomputed in split form: that is four launches of its own)
   const bool bf16_auto = s.dtype == SK_BF16 && g_plan.load(std::memory_order_relaxed) == PLAN_AUTO &&
                          !w.own_colsum && w.z_splits == 1;
-  const Plan in_plan = pick_plan(s, SK_OP_BWD_INPUT);
+  const Plan in_plan = pick_plan(s, SK_OP_BWD_INPUT, true);
   const int z_tile = bf16_auto ? choose_tile(s.R, tokens, in, 1) : -1;
   const GemmKind du_kind = GEMM_NN_F32_COLSUM;
 
@@ -1090,7 +1121,8 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
   // eight-wave tile on its own: that one leaves no room on a CU to share (measured at
   // BERT-large: 125 us shared against 133 us one after the other)
   if (dx_tile == TILE_256x256) dx_tile = TILE_128x128;
-  if (bf16_auto && in_plan == PLAN_TWO_GEMM && plan_first(tokens, s.R, out).splits == 1 &&
+  const FirstPlan first = plan_first(tokens, s.R, out, true);
+  if (bf16_auto && in_plan == PLAN_TWO_GEMM && first.splits == 1 && !first.few &&
       dual_gemm_supported(GEMM_NT, g_tile, GEMM_TT, z_tile) &&
       dual_gemm_supported(du_kind, w.tile, GEMM_NT, dx_tile)) {
     g_hip_error.clear();

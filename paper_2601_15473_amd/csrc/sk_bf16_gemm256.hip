@@ -28,79 +28,14 @@
 // U [2048 x 11008] 710 -> 580, [16384 x 11008] . U^T 705 -> 557-590, [16384 x 2048] . S^T 250 -> 212,
 // S^T . x^T 255 -> 207, [8192 x 512] . [512 x 4096] 49 -> 39.  Long launches run into the power limit
 // (1.6 GHz instead of 2.1), which is why the last ones gain least.
-#include "sk_bf16_tile.h"
+#include "sk_bf16_lds.h"
 #include "sk_launch.h"
 
 namespace sk {
 
-namespace {
-
-// One operand's chunk in LDS, 256 rows (m or n) by 64 k: four 8 KB panels of 64 rows, a panel
-// [64 rows][64 k] for a k-contiguous operand, else [64 k][64 m or n] (read through the LDS transpose
-// read).  Either way a panel is 64 lines of 128 bytes, one load instruction of a wave fills eight
-// lines, and the 16-byte pieces of a line are XOR-swizzled by line so that no read conflicts: the
-// swizzle is in which piece of its line a lane asks for.
-template <bool KC>
-struct Panels {
-  static __device__ __forceinline__ int swizzle(int line) { return KC ? (line >> 1) & 7 : ((line >> 1) & 1) << 2; }
-  // Byte offset from the chunk's origin of what `lane` loads as line 8 `line8` + lane / 8 of panel 0
-  static __device__ __forceinline__ unsigned load_offset(int line8, int lane, unsigned ld_bytes) {
-    const int line = line8 * 8 + (lane >> 3);
-    return (unsigned)line * ld_bytes + (unsigned)((lane & 7) ^ swizzle(line)) * 16u;
-  }
-  // ... of its first k in the chunk (k-contiguous operands)
-  static __device__ __forceinline__ int load_k(int line8, int lane) { return ((lane & 7) ^ swizzle(line8 * 8 + (lane >> 3))) * 8; }
-  // LDS address a lane reads block 0, k step 0 of 128 rows `half` at; frag: any block and k step
-  static __device__ __forceinline__ unsigned read_address(int half, int lane) {
-    if (KC) {
-      const int line = lane & 31;
-      return half * 16384 + line * 128 + (((lane >> 5) ^ swizzle(line)) << 4);
-    } else {   // (see read_frag: lane j of 16 addresses k row j / 4, columns 4 (j % 4) .. + 3)
-      const int k = (lane >> 5) * 8 + ((lane & 15) >> 2), col = ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
-      return half * 16384 + k * 128 + (((col >> 3) ^ swizzle(k)) << 4) + (col & 4) * 2;
-    }
-  }
-  static __device__ __forceinline__ bf16x8 frag(unsigned address, int block, int ks) {
-    if constexpr (KC) {
-      typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
-      return *(lds_bf16x8*)(uintptr_t)((address ^ (ks << 5)) + block * 4096);
-    } else {
-      const unsigned p = (address ^ ((block & 1) << 6)) + (block >> 1) * 8192 + ks * 2048;
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(p));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(p + 512));
-      typedef short s16x8 __attribute__((ext_vector_type(8)));
-      const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      return __builtin_bit_cast(bf16x8, both);
-    }
-  }
-};
-
-// Resource descriptor of what is left of an array of `total` elements from element `origin` on.
-__device__ __forceinline__ u32x4 descriptor(const void* base, int64_t origin, int64_t total, int esize) {
-  int64_t bytes = (total - origin) * esize;
-  if (bytes < 0) bytes = 0;
-  if (bytes > 0x7fffffff) bytes = 0x7fffffff;
-  const uint64_t at = (uint64_t)base + origin * esize;
-  return u32x4{(unsigned)at, (unsigned)(at >> 32), (unsigned)bytes, 0x00020000u};
-}
-
-// Each lane's 16 bytes at voff + soff of the array (zeros past its end) to LDS byte lds + 16 lane.
-__device__ __forceinline__ void load_to_lds(unsigned lds, unsigned voff, u32x4 array, unsigned soff) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(array), "s"(soff));
-}
-
-// The lane number computed afresh, for what is not to be kept in registers through the main loop.
-__device__ __forceinline__ int lane_again() {
-  int zero = 0;
-  asm volatile("" : "+v"(zero));
-  return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
-}
-
 constexpr int CHUNK = 65536;                      // bytes of a chunk in LDS: A's 32 KB, then B's
 constexpr int STRIPS = 2 * CHUNK;                 // then 8 KB per wave for its results (and bias values)
 constexpr int GEMM256_LDS = STRIPS + 4 * 8192;    // all of a CU's LDS
-
-}  // namespace
 
 // The work of one work-group: tiles block, block + stride, ... below `total`.  `smem` must be the
 // kernel's only LDS (it then starts at LDS address 0), and the kernel's first argument a GemmArgs.

@@ -154,6 +154,8 @@ hipError_t launch_gemm_bf16(GemmKind kind, int tile, const GemmArgs& a, hipStrea
 // least 256 long, a range's rows of an operand that is not k-contiguous within 2 GB.
 bool gemm256_supported(GemmKind kind, const GemmArgs& a);
 hipError_t launch_gemm256_bf16(GemmKind kind, const GemmArgs& a, hipStream_t s);
+// GEMM_NN and GEMM_NT for few rows of A: one launch that streams B once per 64 rows.
+hipError_t launch_gemm_few_rows_bf16(GemmKind kind, const GemmArgs& a, hipStream_t s);
 // fp32 operands and accumulation (MFMA), on TILE_64x64 or TILE_128x128.
 hipError_t launch_gemm_f32(GemmKind kind, int tile, const GemmArgs& a, hipStream_t s);
 constexpr int F32_BK = 32;
