@@ -59,8 +59,10 @@ __device__ __forceinline__ u32x4 descriptor(const void* base, int64_t origin, in
 }
 
 // Each lane's 16 bytes at voff + soff of the array (zeros past its end) to LDS byte lds + 16 lane.
+// (One wait state between the write of M0 and the load that reads it; in inline assembly the
+// compiler does not insert it.)
 __device__ __forceinline__ void load_to_lds(unsigned lds, unsigned voff, u32x4 array, unsigned soff) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(array), "s"(soff));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(array), "s"(soff));
 }
 
 // The lane number computed afresh, for what is not to be kept in registers through the main loop.
