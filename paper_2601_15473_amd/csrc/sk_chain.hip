@@ -13,8 +13,8 @@
 // fragment is read from LDS by exactly one wave and used for all 32-row blocks.
 // Two kernels share that plan:
 //   chain_small_kernel (R <= 128, the one the automatic plans use): B2 arrives one whole
-//     [R x 128] tile at a time, double buffered across tile boundaries, and output rows
-//     leave straight from registers as 16-byte pieces (no LDS re-layout);
+//     [R x 128] tile at a time, double buffered across tile boundaries, and output tiles
+//     leave one step later through LDS, in whole rows;
 //   chain_kernel (R <= 512, forced plans only): B2 streams in 64-row chunks and the output
 //     tile is re-laid out through LDS into whole rows.
 #include "sk_bf16_tile.h"
@@ -264,7 +264,8 @@ __global__ __launch_bounds__(256) void chain_kernel(const ChainArgs p) {
 //     A 64-lane LDS instruction costs the CU about 9 cycles, a transposing read
 //     twice that per fragment, so the waves split the tile's columns 1 x 4: every
 //     wave holds all rows of Zt in registers and each B2 fragment is read from LDS
-//     exactly once.  Output rows leave straight from registers.
+//     exactly once.  A finished tile is turned over in LDS and leaves one step later, a
+//     store instruction writing four whole 256-byte rows.
 //   - In both stages each k step is one scheduling phase: fragment reads of the next
 //     step, the step's MFMAs, a share of the global loads of the chunk / tile two
 //     ahead and of the LDS stores of the next one.  A wave that issues its loads in
@@ -279,7 +280,9 @@ struct SmallLds {
   typedef OpTile<RT, B1_KC> TB1;
   static constexpr int Z_LD = RT + 8;
   static constexpr int Z_BYTES = MB * Z_LD * 2;
-  static constexpr int HEAD_BYTES = Z_BYTES;
+  // two finished output tiles, over Zt (which is in registers by then)
+  static constexpr int OUT_BYTES = MB * CS_BN * 2;
+  static constexpr int HEAD_BYTES = Z_BYTES > 2 * OUT_BYTES ? Z_BYTES : 2 * OUT_BYTES;
   static constexpr int S2_BYTES = 2 * TB2::ELEMS * 2;
   static constexpr int S1_BYTES = FUSED ? 2 * (TA::ELEMS + TB1::ELEMS) * 2 : 0;
   static constexpr int BYTES = HEAD_BYTES + (S1_BYTES > S2_BYTES ? S1_BYTES : S2_BYTES);
@@ -554,16 +557,42 @@ __global__ __launch_bounds__(256) void chain_small_kernel(const ChainArgs p) {
   TB2::store(Bbuf, rb0, tid);
   __syncthreads();
 
-  bf16* __restrict__ C = static_cast<bf16*>(p.C);
   const float scale = p.scale;
+
+  // Finished tiles leave through LDS, in whole rows: wave w stores rows MB / 4 * w .. of what all
+  // waves have put into the tile's buffer by the barrier that ends its step.  (Straight
+  // from registers a store instruction wrote 32-byte segments of 32 rows: 8192 wide, 4096
+  // tokens, R = 16, where the stores are what bounds it, forward expansion 22.1 -> 18.1 us, 3.7
+  // TB/s, input gradient 19.8 -> 17.1; level where the first contraction dominates.)  The 16-byte
+  // pieces of a row are XOR-swizzled by row, so neither side conflicts; rows past M and columns
+  // past N fall outside the window.
+  const GWindow out_w = make_window(p.C, (int64_t)m0 * p.ldc, (int64_t)p.M * p.ldc, 2);
+  constexpr int ROWS_OUT = MB / 16;   // store instructions per wave and tile
+  auto tile_read = [&](const unsigned char* buf, uint4 (&v)[ROWS_OUT]) {
+#pragma unroll
+    for (int u = 0; u < ROWS_OUT; ++u) {
+      const int row = wave * (MB / 4) + u * 4 + (lane >> 4);
+      v[u] = *reinterpret_cast<const uint4*>(buf + row * 256 + (((lane & 15) ^ (row & 15)) * 16));
+    }
+  };
+  auto tile_store = [&](int jt, const uint4 (&v)[ROWS_OUT]) {
+    const int gn = (t_begin + jt) * CS_BN + (lane & 15) * 8;
+    const unsigned row = (unsigned)(wave * (MB / 4) + (lane >> 4));
+    const unsigned at = jt >= 0 && jt < my_tiles && gn < p.N ? (row * (unsigned)p.ldc + (unsigned)gn) * 2u : OOB_OFFSET;
+#pragma unroll
+    for (int u = 0; u < ROWS_OUT; ++u) window_store16(out_w, at + (unsigned)(u * 8) * (unsigned)p.ldc, v[u]);
+  };
 
   // One [MB x 128] output tile (wave w owns columns 32 w .. 32 w + 31 of it) from the B2
   // tile in `Bs`.  Between its MFMAs go the loads of the tile two ahead (into rl), the
   // next tile's bias (into bvn) and the LDS stores of the next tile (from rs, loaded one
   // step ago, into Bn): issued in one burst, the loads hold every wave at the memory
   // pipe's queue while LDS and MFMA sit idle.
+  // The tile before it leaves from `done`; its own result goes to `out`.
   auto step = [&](int jt, const bf16* Bs, bf16* Bn, const uint2 (&bv)[4], uint2 (&bvn)[4],
-                  uint4 (&rl)[TB2::PIECES], uint4 (&rs)[TB2::PIECES]) {
+                  uint4 (&rl)[TB2::PIECES], uint4 (&rs)[TB2::PIECES], const unsigned char* done, unsigned char* out) {
+    uint4 leaving[ROWS_OUT];
+    tile_read(done, leaving);
     f32x16 acc[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -587,15 +616,13 @@ __global__ __launch_bounds__(256) void chain_small_kernel(const ChainArgs p) {
       fb = fbn;
     });
     sched_stage2<KS, B2_KC ? 1 : 2, MT>();
-    // Result rows leave straight from registers.  A lane holds, per 8-column group q, the
-    // four columns 8 q + 4 (l / 32) .. +3 of its row; exchanging the upper half-wave's part
-    // of an even group with the lower half-wave's part of the odd group next to it
-    // (v_permlane32_swap) leaves every lane with eight consecutive columns -- 16 bytes --
-    // so no trip through LDS, and no barrier, is needed to form whole pieces.
-    const int n0 = (t_begin + jt) * CS_BN + wave * 32;
-    const int n_lim = jt < my_tiles ? p.N : 0;
+    tile_store(jt - 1, leaving);
+    // A lane holds, per 8-column group q, the four columns 8 q + 4 (l / 32) .. +3 of its row;
+    // exchanging the upper half-wave's part of an even group with the lower half-wave's part
+    // of the odd group next to it (v_permlane32_swap) leaves every lane with eight
+    // consecutive columns: 16 bytes, piece 4 w + 2 pr + l / 32 of the tile's row.
     auto rows_out = [&](const f32x16& acc, int row0) {
-      const int gm = m0 + row0 + (lane & 31);
+      const int row = row0 + (lane & 31);
 #pragma unroll
       for (int pr = 0; pr < 2; ++pr) {
         uint2 w[2];
@@ -610,9 +637,8 @@ __global__ __launch_bounds__(256) void chain_small_kernel(const ChainArgs p) {
         typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
         const u32x2 s0 = __builtin_amdgcn_permlane32_swap(w[0].x, w[1].x, false, false);
         const u32x2 s1 = __builtin_amdgcn_permlane32_swap(w[0].y, w[1].y, false, false);
-        const int gn = n0 + 16 * pr + 8 * (lane >> 5);
-        if (gm < p.M && gn < n_lim)
-          *reinterpret_cast<uint4*>(C + (int64_t)gm * p.ldc + gn) = make_uint4(s0.x, s1.x, s0.y, s1.y);
+        const int piece = wave * 4 + pr * 2 + (lane >> 5);
+        *reinterpret_cast<uint4*>(out + row * 256 + ((piece ^ (row & 15)) * 16)) = make_uint4(s0.x, s1.x, s0.y, s1.y);
       }
     };
 #pragma unroll
@@ -620,12 +646,18 @@ __global__ __launch_bounds__(256) void chain_small_kernel(const ChainArgs p) {
     __syncthreads();
   };
 
-  for (int jt = 0; jt < my_tiles; jt += 2) {
+  unsigned char* const out0 = smem;
+  unsigned char* const out1 = smem + L::OUT_BYTES;
+  int jt = 0;
+  for (; jt < my_tiles; jt += 2) {
     // tile jt sits in buffer 0; set 1 holds tile jt + 1
-    step(jt, Bbuf, Bbuf + TB2::ELEMS, bv0, bv1, rb0, rb1);
+    step(jt, Bbuf, Bbuf + TB2::ELEMS, bv0, bv1, rb0, rb1, out1, out0);
     // (computes on zeros and stores nothing past the run)
-    step(jt + 1, Bbuf + TB2::ELEMS, Bbuf, bv1, bv0, rb1, rb0);
+    step(jt + 1, Bbuf + TB2::ELEMS, Bbuf, bv1, bv0, rb1, rb0, out0, out1);
   }
+  uint4 leaving[ROWS_OUT];
+  tile_read(out1, leaving);
+  tile_store(jt - 1, leaving);
 }
 
 bool chain_supported(int R) { return R >= 16 && R <= 512; }
