@@ -15,6 +15,7 @@ There is no CPU path: tensors that are not on a GPU raise.
 from __future__ import annotations
 
 import collections
+import contextlib
 import math
 
 import torch
@@ -24,6 +25,7 @@ from . import libsk as sk
 _DTYPES = {torch.float32: sk.SK_F32, torch.bfloat16: sk.SK_BF16}
 _workspaces: "collections.OrderedDict" = collections.OrderedDict()
 _MAX_WORKSPACES = 8
+_HERE = contextlib.nullcontext()
 
 
 def _workspace(device: torch.device, stream: int, nbytes: int) -> torch.Tensor:
@@ -56,6 +58,30 @@ def _check(x: torch.Tensor, name: str, dtype: torch.dtype):
         raise TypeError(f"SKLinear: {name} has dtype {x.dtype}, the layer's is {dtype}")
 
 
+def _rows(x: torch.Tensor, width: int) -> torch.Tensor:
+    """x as dense rows of ``width``; x itself where it is that already (a view and a copy that do
+    nothing cost a small layer more than its kernels' arguments)."""
+    if x.dim() == 2 and x.is_contiguous():
+        return x
+    return x.reshape(-1, width).contiguous()
+
+
+def _on(device: torch.device):
+    """The context that makes ``device`` current: none where it is."""
+    return _HERE if torch.cuda.current_device() == device.index else torch.cuda.device(device)
+
+
+def _stream(device: torch.device) -> int:
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
+def _in_type(grads32: torch.Tensor, dtype: torch.dtype, *shapes):
+    """The fp32 gradients that lie one behind the other in ``grads32`` (from its start; it may hold
+    more), in the layer's type: one conversion for all of them instead of one launch each."""
+    sizes = [math.prod(s) for s in shapes]
+    return [t.view(s) for t, s in zip(grads32[:sum(sizes)].to(dtype).split(sizes), shapes)]
+
+
 class SKLinearFunction(torch.autograd.Function):
     """y = sklinear(x, S_cat, U_cat, bias); S_cat [in, l*k] gets no gradient (fixed sketch)."""
 
@@ -70,14 +96,14 @@ class SKLinearFunction(torch.autograd.Function):
             raise ValueError("SKLinear: shapes do not match (x [..., in], S_cat [in, l*k], U_cat [l*k, out])")
         for t, n in ((x, "x"), (S_cat, "S_cat"), (U_cat, "U_cat")) + (((bias, "bias"),) if bias is not None else ()):
             _check(t, n, dtype)
-        x2 = x.reshape(-1, d_in).contiguous()
+        x2 = _rows(x, d_in)
         S_cat, U_cat = S_cat.contiguous(), U_cat.contiguous()
         bias_c = bias.contiguous() if bias is not None else None
         tokens = x2.shape[0]
         y = torch.empty((tokens, d_out), dtype=dtype, device=x.device)
         args = (tokens, d_in, d_out, l, k, _DTYPES[dtype])
-        with torch.cuda.device(x.device):
-            stream = torch.cuda.current_stream().cuda_stream
+        with _on(x.device):
+            stream = _stream(x.device)
             need = sk.sk_linear_workspace_bytes(sk.SK_OP_FWD, *args)
             if need == 2 ** 64 - 1:
                 raise sk.SkError(sk.SK_ERR_UNSUPPORTED)
@@ -87,27 +113,31 @@ class SKLinearFunction(torch.autograd.Function):
         ctx.args = args
         ctx.x_shape = x.shape
         ctx.has_bias = bias is not None
-        return y.reshape(*x.shape[:-1], d_out)
+        return y if x.dim() == 2 else y.reshape(*x.shape[:-1], d_out)
 
     @staticmethod
     def backward(ctx, dY):
         x2, S_cat, U_cat = ctx.saved_tensors
         tokens, d_in, d_out, l, k, dt = ctx.args
         dtype = S_cat.dtype
-        dY2 = dY.reshape(-1, d_out).to(dtype).contiguous()
+        dY2 = _rows(dY if dY.dtype == dtype else dY.to(dtype), d_out)
         need_dx, _, need_du, need_db = ctx.needs_input_grad[:4]
         dX = dU = db = None
-        with torch.cuda.device(dY.device):
-            stream = torch.cuda.current_stream().cuda_stream
+        with _on(dY.device):
+            stream = _stream(dY.device)
             want_w = need_du or (need_db and ctx.has_bias)
-            need = max(sk.sk_linear_workspace_bytes(op, *ctx.args)
-                       for op in (sk.SK_OP_BWD_INPUT, sk.SK_OP_BWD_WEIGHT, sk.SK_OP_BWD))
-            ws = _workspace(dY.device, stream, need)
+            # (never less than that of either gradient by itself)
+            ws = _workspace(dY.device, stream, sk.sk_linear_workspace_bytes(sk.SK_OP_BWD, *ctx.args))
             if need_dx:
                 dX = torch.empty((tokens, d_in), dtype=dtype, device=dY.device)
             if want_w:
-                dU32 = torch.empty((l * k, d_out), dtype=torch.float32, device=dY.device)
-                db32 = torch.empty((d_out,), dtype=torch.float32, device=dY.device) if ctx.has_bias else None
+                R = l * k
+                if dtype == torch.float32:
+                    dU32 = torch.empty((R, d_out), dtype=dtype, device=dY.device)
+                    db32 = torch.empty((d_out,), dtype=dtype, device=dY.device) if ctx.has_bias else None
+                else:
+                    g32 = torch.empty((R + ctx.has_bias) * d_out, dtype=torch.float32, device=dY.device)
+                    dU32, db32 = g32, g32[R * d_out:] if ctx.has_bias else None
             if need_dx and want_w:      # both gradients from one call (its kernels share launches)
                 sk.check(sk.sk_linear_bwd(x2, dY2, S_cat, U_cat, dX, dU32, db32, *ctx.args,
                                           ws, ws.numel(), stream))
@@ -115,11 +145,14 @@ class SKLinearFunction(torch.autograd.Function):
                 sk.check(sk.sk_linear_bwd_input(dY2, S_cat, U_cat, dX, *ctx.args, ws, ws.numel(), stream))
             elif want_w:
                 sk.check(sk.sk_linear_bwd_weight(x2, S_cat, dY2, dU32, db32, *ctx.args, ws, ws.numel(), stream))
-            if need_dx:
+            if need_dx and dX.shape != ctx.x_shape:
                 dX = dX.reshape(ctx.x_shape)
             if want_w:
-                dU = dU32.to(dtype) if need_du else None
-                db = db32.to(dtype) if (need_db and ctx.has_bias) else None
+                if dtype != torch.float32:
+                    dU32, db32 = _in_type(g32, dtype, (R, d_out), (d_out,)) if ctx.has_bias else \
+                        (*_in_type(g32, dtype, (R, d_out)), None)
+                dU = dU32 if need_du else None
+                db = db32 if need_db else None
         return dX, None, dU, db, None, None
 
 
@@ -216,13 +249,13 @@ class SKLinearTwoSidedFunction(torch.autograd.Function):
         else:
             A_cat = torch.cat([S1_cat, U2_cat], dim=1).contiguous()
             B_cat = torch.cat([U1_cat, S2T_cat], dim=0).contiguous()
-        x2 = x.reshape(-1, d_in).contiguous()
+        x2 = _rows(x, d_in)
         bias_c = bias.contiguous() if bias is not None else None
         tokens = x2.shape[0]
         y = torch.empty((tokens, d_out), dtype=dtype, device=x.device)
         args = (tokens, d_in, d_out, 2 * l, k, _DTYPES[dtype])
-        with torch.cuda.device(x.device):
-            stream = torch.cuda.current_stream().cuda_stream
+        with _on(x.device):
+            stream = _stream(x.device)
             need = sk.sk_linear_workspace_bytes(sk.SK_OP_FWD, *args)
             if need == 2 ** 64 - 1:
                 raise sk.SkError(sk.SK_ERR_UNSUPPORTED)
@@ -230,30 +263,40 @@ class SKLinearTwoSidedFunction(torch.autograd.Function):
             sk.check(sk.sk_linear_fwd(x2, A_cat, B_cat, bias_c, y, *args, ws, ws.numel(), stream))
         ctx.save_for_backward(x2, A_cat, B_cat)
         ctx.args, ctx.x_shape, ctx.has_bias, ctx.half = args, x.shape, bias is not None, half
-        return y.reshape(*x.shape[:-1], d_out)
+        return y if x.dim() == 2 else y.reshape(*x.shape[:-1], d_out)
 
     @staticmethod
     def backward(ctx, dY):
         x2, A_cat, B_cat = ctx.saved_tensors
         tokens, d_in, d_out, l2, k, dt = ctx.args
         dtype, half = A_cat.dtype, ctx.half
-        dY2 = dY.reshape(-1, d_out).to(dtype).contiguous()
+        dY2 = _rows(dY if dY.dtype == dtype else dY.to(dtype), d_out)
         dev = dY.device
-        with torch.cuda.device(dev):
-            stream = torch.cuda.current_stream().cuda_stream
+        with _on(dev):
+            stream = _stream(dev)
             need = max(sk.sk_linear_workspace_bytes(op, *ctx.args)
                        for op in (sk.SK_OP_BWD, sk.SK_OP_BWD_WEIGHT_FIRST))
             ws = _workspace(dev, stream, need)
             dX = torch.empty((tokens, d_in), dtype=dtype, device=dev)
-            dB = torch.empty((2 * half, d_out), dtype=torch.float32, device=dev)
-            db = torch.empty((d_out,), dtype=torch.float32, device=dev) if ctx.has_bias else None
-            dA = torch.empty((d_in, half), dtype=torch.float32, device=dev)
+            if dtype == torch.float32:
+                db = torch.empty((d_out,), dtype=dtype, device=dev) if ctx.has_bias else None
+                dA = torch.empty((d_in, half), dtype=dtype, device=dev)
+                dB = torch.empty((2 * half, d_out), dtype=dtype, device=dev)
+            else:
+                # dB last: its rows from `half` on belong to S2^T, gradients of fixed numbers that are
+                # dropped, and what lies before them is converted in one go
+                n_db = d_out if ctx.has_bias else 0
+                g32 = torch.empty(n_db + d_in * half + 2 * half * d_out, dtype=torch.float32, device=dev)
+                db, dA, dB = g32 if ctx.has_bias else None, g32[n_db:], g32[n_db + d_in * half:]
             sk.check(sk.sk_linear_bwd(x2, dY2, A_cat, B_cat, dX, dB, db, *ctx.args, ws, ws.numel(), stream))
             sk.check(sk.sk_linear_bwd_weight_first(x2, B_cat, dY2, dA, tokens, d_in, d_out, l2, k,
                                                    half, half, dt, ws, ws.numel(), stream))
-        # the rows of dB below `half` belong to S2^T: gradients of fixed numbers, dropped
-        return (dX.reshape(ctx.x_shape), None, dB[:half].to(dtype), dA.to(dtype), None,
-                db.to(dtype) if db is not None else None, None, None, None)
+            if dtype == torch.float32:
+                dB = dB[:half]
+            else:
+                db, dA, dB = _in_type(g32, dtype, (n_db,), (d_in, half), (half, d_out))
+        return (dX if dX.shape == ctx.x_shape else dX.reshape(ctx.x_shape), None, dB, dA, None,
+                db if ctx.has_bias else None, None, None, None)
 
 
 class SKLinearTwoSided(torch.nn.Module):
