@@ -77,9 +77,10 @@ def _stream(device: torch.device) -> int:
 
 def _in_type(grads32: torch.Tensor, dtype: torch.dtype, *shapes):
     """The fp32 gradients that lie one behind the other in ``grads32`` (from its start; it may hold
-    more), in the layer's type: one conversion for all of them instead of one launch each."""
+    more), in the layer's type: one conversion for all of them instead of one launch each.  Detached,
+    because a view made without a graph may not be changed in place by something that has one."""
     sizes = [math.prod(s) for s in shapes]
-    return [t.view(s) for t, s in zip(grads32[:sum(sizes)].to(dtype).split(sizes), shapes)]
+    return [t.view(s).detach() for t, s in zip(grads32[:sum(sizes)].to(dtype).split(sizes), shapes)]
 
 
 class SKLinearFunction(torch.autograd.Function):

@@ -27,6 +27,17 @@ def test_no_cpu_path():
         sknn.sklinear(x, S, U, None, 1, 16)
 
 
+def test_converted_gradients_can_be_changed_in_place():
+    """As plain tensors can: also by a factor that is itself being differentiated."""
+    from paper_2601_15473_amd import nn as sknn
+    with torch.no_grad():   # as a backward pass runs
+        dU, db = sknn._in_type(torch.arange(20.0), torch.bfloat16, (3, 4), (4,))
+    w = torch.full((3, 4), 2.0, dtype=torch.bfloat16, requires_grad=True)
+    assert dU.mul_(w).requires_grad and not db.requires_grad
+    assert torch.equal(dU.detach(), 2 * torch.arange(12.0).view(3, 4).bfloat16())
+    assert torch.equal(db, torch.arange(12.0, 16.0).bfloat16())
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,tol", [(torch.bfloat16, 2e-2), (torch.float32, 1e-4)], ids=["bf16", "f32"])
 @pytest.mark.parametrize("shape", [(5, 40, 96), (333, 96)], ids=["batched", "flat"])
