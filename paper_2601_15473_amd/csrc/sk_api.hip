@@ -1118,8 +1118,10 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
   const int g_tile = bf16_auto ? choose_tile(tokens, s.R, out, 1) : -1;
   int dx_tile = bf16_auto ? choose_tile(tokens, in, s.R, 1) : -1;
   // beside Z^T.dY the expansion of dX runs on 128 x 128 tiles even where it would take the
-  // eight-wave tile on its own: that one leaves no room on a CU to share (measured at
-  // BERT-large: 125 us shared against 133 us one after the other)
+  // 256 x 256 tile on its own: that one takes all of a CU's LDS and leaves no room to share.  Shared
+  // against one after the other, us per backward call: [8192 x 3072 -> 4096], R = 768, 218 : 235;
+  // [16384 x 1024 -> 4096], R = 144, 103 : 112; [16384 x 4096 -> 4096], R = 512, level; the
+  // best the separate launches did was 2 % ahead ([8192 x 4096 -> 8192], R = 1024, 478 : 468)
   if (dx_tile == TILE_256x256) dx_tile = TILE_128x128;
   const FirstPlan first = plan_first(tokens, s.R, out, true);
   if (bf16_auto && in_plan == PLAN_TWO_GEMM && first.splits == 1 && !first.few &&
