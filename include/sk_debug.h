@@ -56,6 +56,9 @@ typedef struct {
 } sk_trace_access;
 
 void sk_trace_begin(void);
+/* Work-groups of kernel launch `launch` of the open trace, and its name as a profiler prints it in `name`
+ * (at most max - 1 characters; may be NULL); -1 if there is no such launch. */
+int32_t sk_trace_kernel(int32_t launch, char* name, int32_t max);
 /* Ends the trace; copies up to `max` records to `out` (may be NULL when max is 0) and
  * returns how many were recorded in all.  `launches`, if not NULL, receives the number of
  * kernel launches the traced calls would have made. */

@@ -40,7 +40,7 @@ int forced_tile(sk_tune_knob knob) {
 struct Hooks : LaunchHooks {
   bool trace = false;
   std::vector<sk_trace_access> accesses;
-  int launches = 0;
+  std::vector<std::string> launches;      // trace mode: the kernels, and their work-groups in `groups`
   // profile mode
   std::vector<hipEvent_t> events;       // 2 per kernel: before, after
   std::vector<std::string> names;
@@ -55,10 +55,13 @@ struct Hooks : LaunchHooks {
     a.address = (uint64_t)reinterpret_cast<uintptr_t>(p);
     a.bytes = bytes;
     a.write = write ? 1 : 0;
-    a.launch = launches;
+    a.launch = (int)launches.size();
     accesses.push_back(a);
   }
-  void launch_recorded() override { ++launches; }
+  void launch_recorded(const char* name, unsigned g) override {
+    launches.push_back(name);
+    groups.push_back(g);
+  }
   void before(const char* name, unsigned g, double flops, double bytes, hipStream_t s) override {
     recording = (int)names.size() < max_kernels;
     if (!recording) return;
@@ -333,7 +336,10 @@ static SplitChoice best_split(int64_t M, int64_t N, int64_t T, int bm, int bn) {
   return c;
 }
 
-TokenPlan plan_tokens(int64_t M, int64_t N, int64_t T, sk_dtype dtype, bool tunable,
+// `lda`: stride of the first operand's rows where it is k-contiguous (bf16 Z^T, a row of which is all
+// tokens long), 0 where it is not.  Its rows of a tile have to lie within a window: past 4.2 million
+// tokens 256 rows do not, past 8.4 million 128.
+TokenPlan plan_tokens(int64_t M, int64_t N, int64_t T, sk_dtype dtype, bool tunable, int64_t lda,
                       size_t room = SIZE_MAX) {
   TokenPlan w{};
   if (dtype != SK_BF16) {
@@ -344,11 +350,15 @@ TokenPlan plan_tokens(int64_t M, int64_t N, int64_t T, sk_dtype dtype, bool tuna
     return w;
   }
   int bm, bn;
+  auto in_window = [&](int tile) {
+    tile_dims(tile, bm, bn);
+    return lda == 0 || within_window(bm, lda, bm == 256 ? T + 512 : 64, 2);
+  };
   {
-    w.tile = M > 64 ? TILE_128x64 : TILE_64x64;
-    if (((M + 255) / 256) * ((N + 255) / 256) >= NUM_CUS) {
+    w.tile = M <= 64 ? TILE_64x64 : in_window(TILE_128x64) ? TILE_128x64 : TILE_64x128;
+    if (((M + 255) / 256) * ((N + 255) / 256) >= NUM_CUS && in_window(TILE_256x256)) {
       w.tile = TILE_256x256;
-    } else if (M > 64) {
+    } else if (w.tile == TILE_128x64) {
       // 128 x 64 or 128 x 128, whichever the model has finishing first: the narrower
       // tile fills the chip with fewer token splits (few tokens: c1, c2), the square one
       // moves fewer bytes per flop (from half a chip of tiles on, or many tokens:
@@ -356,7 +366,7 @@ TokenPlan plan_tokens(int64_t M, int64_t N, int64_t T, sk_dtype dtype, bool tuna
       if (best_split(M, N, T, 128, 128).time < best_split(M, N, T, 128, 64).time)
         w.tile = TILE_128x128;
     }
-    if (const int t = tunable ? forced_tile(SK_TUNE_WTILE) : -1; t >= 0) w.tile = t;  // forced
+    if (const int t = tunable ? forced_tile(SK_TUNE_WTILE) : -1; t >= 0 && in_window(t)) w.tile = t;  // forced
     w.big_tile = w.tile == TILE_256x256;
     tile_dims(w.tile, bm, bn);
   }
@@ -380,7 +390,7 @@ WeightPlan plan_weight(const Shape& s) {
   WeightPlan w{};
   w.ldz = s.dtype == SK_BF16 ? (s.T + 63) / 64 * 64 : s.R;
   w.z_bytes = align_up((size_t)(s.dtype == SK_BF16 ? s.R * w.ldz * 2 : s.T * s.R * 4));
-  const TokenPlan t = plan_tokens(s.R, s.out, s.T, s.dtype, true, slab_room(w.z_bytes));
+  const TokenPlan t = plan_tokens(s.R, s.out, s.T, s.dtype, true, w.ldz, slab_room(w.z_bytes));
   w.tile = t.tile;
   w.own_colsum = t.big_tile;
   w.z_splits = 1;
@@ -556,7 +566,7 @@ SketchPlan plan_sketch(const Shape& s, int64_t K) {
 // Workspace of the first-stage gradient for nc columns: G = dY . U_sub^T [T, nc] in the
 // storage type, then the token-split slabs of dA [in, nc].
 size_t first_stage_bytes(const Shape& s, int64_t nc) {
-  const TokenPlan t = plan_tokens(s.in, nc, s.T, s.dtype, false);
+  const TokenPlan t = plan_tokens(s.in, nc, s.T, s.dtype, false, 0);
   const size_t da_slabs = t.splits > 1 ? align_up((size_t)t.splits * s.in * nc * 4) : 0;
   // slabs of G when its GEMM is split over `out`: dead once summed, so they share the
   // region of the dA slabs
@@ -735,10 +745,19 @@ int64_t sk_trace_end(sk_trace_access* out, int64_t max, int32_t* launches) {
   if (g_hooks == nullptr || !g_hooks->trace) return 0;
   const int64_t n = (int64_t)g_hooks->accesses.size();
   for (int64_t i = 0; i < n && i < max && out != nullptr; ++i) out[i] = g_hooks->accesses[i];
-  if (launches != nullptr) *launches = g_hooks->launches;
+  if (launches != nullptr) *launches = (int32_t)g_hooks->launches.size();
   delete g_hooks;
   g_hooks = nullptr;
   return n;
+}
+
+int32_t sk_trace_kernel(int32_t launch, char* name, int32_t max) {
+  if (g_hooks == nullptr || !g_hooks->trace || launch < 0 || launch >= (int32_t)g_hooks->launches.size()) return -1;
+  if (name != nullptr && max > 0) {
+    strncpy(name, g_hooks->launches[launch].c_str(), max - 1);
+    name[max - 1] = 0;
+  }
+  return (int32_t)g_hooks->groups[launch];
 }
 
 int32_t sk_profile_begin(int32_t max_kernels) {
@@ -1178,7 +1197,7 @@ sk_status sk_linear_bwd_weight_first(const void* x, const void* U_cat, const voi
   if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd_weight_first (dY.U^T)");
 
   // dA = scale * x^T . G, the token axis split in order
-  const TokenPlan t = plan_tokens(in, nc, tokens, dtype, false);
+  const TokenPlan t = plan_tokens(in, nc, tokens, dtype, false, 0);
   GemmArgs a{};
   a.A = x; a.lda = in;
   a.B = G; a.ldb = nc;

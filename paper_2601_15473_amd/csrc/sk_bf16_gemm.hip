@@ -349,7 +349,8 @@ static hipError_t launch_cfg(GemmArgs a, hipStream_t s) {
   a.tiles_m = (a.M + BM - 1) / BM;
   a.tiles_n = (a.N + BN - 1) / BN;
   const long long grid = (long long)a.tiles_m * a.tiles_n * a.splits;
-  if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (grid <= 0 || grid > 0x7fffffffLL || (A_KC && !within_window(BM, a.lda, BK, 2)) || (B_KC && !within_window(BN, a.ldb, BK, 2)))
+    return hipErrorInvalidValue;
   note_gemm(a, A_KC, B_KC, 2, sizeof(OutT), sizeof(OutT) == 4);
   static const std::string name = kernel_label("gemm_bf16_kernel", {lbl(BM), lbl(BN), lbl(A_KC), lbl(B_KC), out_label<OutT>(), lbl(COLSUM)});
   return launch_kernel(name.c_str(), gemm_work(a, 2, sizeof(OutT), sizeof(OutT) == 4), gemm_bf16_kernel<BM, BN, A_KC, B_KC, OutT, COLSUM>,

@@ -238,7 +238,6 @@ __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const i
     const float scale = q->scale;
     if constexpr (sizeof(OutT) == 2) {
       unsigned char* const strip = smem + STRIPS + wave * 8192;
-      const GWindow out = make_window(q->C, (int64_t)here.m0 * q->ldc, (int64_t)q->M * q->ldc, 2);
       const unsigned ldc = (unsigned)q->ldc * 2u;
       uint2 bias[4][4];
 #pragma unroll
@@ -247,11 +246,13 @@ __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const i
         for (int e = 0; e < 4; ++e)
           bias[j][e] = *reinterpret_cast<const uint2*>(strip + (j * 32 + e * 8 + (el >> 5) * 4) * 2);
       const int gn = here.n0 + wn * 128 + (el & 15) * 8;
-      const unsigned at = gn < q->n_store ? (unsigned)(wm * 128 + (el >> 4)) * ldc + (unsigned)gn * 2u : OOB_OFFSET;
+      const unsigned at = gn < q->n_store ? (unsigned)(el >> 4) * ldc + (unsigned)gn * 2u : OOB_OFFSET;
       unsigned char* const wr = strip + (el & 31) * 256;
       const unsigned char* const rd = strip + (el >> 4) * 256;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
+        // a window for every 32 rows: Z^T's are all tokens long, and 256 of them pass 2 GB
+        const GWindow out = make_window(q->C, (int64_t)(here.m0 + wm * 128 + i * 32) * q->ldc, (int64_t)q->M * q->ldc, 2);
         // (the accumulators stay in their own registers until their block is due: copied out ahead
         // they crowd out what the next tile's main loop needs)
 #pragma unroll
@@ -284,7 +285,7 @@ __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const i
           v[u] = *reinterpret_cast<const uint4*>(rd + u * 1024 + (((el & 15) ^ ((u * 4 + (el >> 4)) & 15)) * 16));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) window_store16(out, at + (unsigned)(i * 32 + u * 4) * ldc, v[u]);
+        for (int u = 0; u < 8; ++u) window_store16(out, at + (unsigned)(u * 4) * ldc, v[u]);
       }
     } else {
       const GWindow out = make_window(q->C, ((int64_t)here.split * q->M + here.m0) * q->ldc, (int64_t)(here.split + 1) * q->M * q->ldc, 4);
@@ -390,7 +391,10 @@ bool gemm256_supported(GemmKind kind, const GemmArgs& a) {
   if (a.splits > 1 && (a.k_per_split % 128 != 0 || a.k_per_split < 256)) return false;
   // byte offsets from a tile's origin are 32-bit: rows of an operand that is not k-contiguous
   const int64_t range = (int64_t)(a.splits > 1 ? a.k_per_split : a.K) + 512;
-  return (a_kc || range * a.lda * 2 < 0x7fffffffLL) && (b_kc || range * a.ldb * 2 < 0x7fffffffLL);
+  if (!(a_kc ? within_window(256, a.lda, range, 2) : range * a.lda * 2 < 0x7fffffffLL)) return false;
+  if (!(b_kc ? within_window(256, a.ldb, range, 2) : range * a.ldb * 2 < 0x7fffffffLL)) return false;
+  // ... and rows of the result: a window's 32 in bf16, all 256 in fp32
+  return within_window(f32 ? 256 : 32, a.ldc, a.n_store > 0 ? a.n_store : a.N, f32 ? 4 : 2);
 }
 
 template <bool A_KC, bool B_KC, typename OutT>

@@ -18,7 +18,7 @@ struct LaunchHooks {
   // trace mode: returns true when launches are to be recorded instead of made
   virtual bool tracing() const = 0;
   virtual void access(const void* p, uint64_t bytes, bool write) = 0;   // of the launch that follows
-  virtual void launch_recorded() = 0;
+  virtual void launch_recorded(const char* name, unsigned groups) = 0;
   // profile mode: events around the launch
   virtual void before(const char* name, unsigned groups, double flops, double bytes, hipStream_t s) = 0;
   virtual void after(hipStream_t s) = 0;
@@ -50,7 +50,7 @@ inline hipError_t launch_kernel(const char* name, Work work, void (*kernel)(KArg
                                 hipStream_t s, typename std::common_type<KArgs>::type... args) {
   LaunchHooks* h = launch_hooks();
   if (h != nullptr && h->tracing()) {
-    h->launch_recorded();
+    h->launch_recorded(name, grid.x * grid.y * grid.z);
     return hipSuccess;
   }
   if (h != nullptr) h->before(name, grid.x * grid.y * grid.z, work.flops, work.bytes, s);
@@ -147,11 +147,18 @@ inline void note_reduce(const ReduceArgs& r) {
   }
 }
 
+// Byte offsets from a tile's origin are 32-bit and end at 2 GB (what lies past a window is pointed
+// further): whether `rows` rows, `ld` elements apart and `cols` of the last one long, stay below.
+inline bool within_window(int64_t rows, int64_t ld, int64_t cols, int esize) {
+  return ((rows - 1) * ld + cols) * esize <= 0x7fffffffLL;
+}
+
 // bf16 operands, fp32 accumulation (MFMA).  `tiles_m/tiles_n` of `a` are filled in here.
 hipError_t launch_gemm_bf16(GemmKind kind, int tile, const GemmArgs& a, hipStream_t s);
 // The 256 x 256 tile of the above, for what gemm256_supported says it can take (launch_gemm_bf16 asks,
 // and runs the rest on 128 x 128 tiles): no column sums, k ranges but the last multiples of 128 and at
-// least 256 long, a range's rows of an operand that is not k-contiguous within 2 GB.
+// least 256 long, a range's rows of an operand that is not k-contiguous within 2 GB, and so 256 rows
+// of one that is.
 bool gemm256_supported(GemmKind kind, const GemmArgs& a);
 hipError_t launch_gemm256_bf16(GemmKind kind, const GemmArgs& a, hipStream_t s);
 // GEMM_NN and GEMM_NT for few rows of A: one launch that streams B once per 64 rows.

@@ -85,12 +85,14 @@ _lib.sk_trace_begin.restype = None
 _lib.sk_trace_begin.argtypes = []
 _lib.sk_trace_end.restype = ctypes.c_int64
 _lib.sk_trace_end.argtypes = [ctypes.POINTER(TraceAccess), ctypes.c_int64, ctypes.POINTER(ctypes.c_int32)]
+_lib.sk_trace_kernel.restype = ctypes.c_int32
+_lib.sk_trace_kernel.argtypes = [ctypes.c_int32, ctypes.c_char_p, ctypes.c_int32]
 _lib.sk_profile_begin.restype = ctypes.c_int32
 _lib.sk_profile_begin.argtypes = [ctypes.c_int32]
 _lib.sk_profile_end.restype = ctypes.c_int32
 _lib.sk_profile_end.argtypes = [ctypes.POINTER(KernelTime), ctypes.c_int32]
 
-DEBUG_EXPORTS = ("sk_set_tuning", "sk_trace_begin", "sk_trace_end", "sk_profile_begin", "sk_profile_end")
+DEBUG_EXPORTS = ("sk_set_tuning", "sk_trace_begin", "sk_trace_end", "sk_trace_kernel", "sk_profile_begin", "sk_profile_end")
 
 EXPORTS = ("sk_linear_fwd", "sk_linear_bwd_input", "sk_linear_bwd_weight", "sk_linear_bwd",
            "sk_linear_bwd_weight_first", "sk_linear_bwd_weight_noalloc",
@@ -196,6 +198,14 @@ def sk_trace_end():
     if n > len(_trace_buf):
         raise RuntimeError(f"launch trace holds {n} records, buffer {len(_trace_buf)}")
     return [(a.address, a.bytes, a.write, a.launch) for a in _trace_buf[:n]], launches.value
+
+
+def sk_trace_kernels():
+    """-> list of (kernel name, work-groups), one per launch of the open trace."""
+    got, name = [], ctypes.create_string_buffer(120)
+    while (groups := _lib.sk_trace_kernel(len(got), name, len(name))) >= 0:
+        got.append((name.value.decode(), groups))
+    return got
 
 
 def sk_profile_begin(max_kernels):
