@@ -39,8 +39,9 @@ constexpr int GEMM256_LDS = STRIPS + 4 * 8192;    // all of a CU's LDS
 
 // The work of one work-group: tiles block, block + stride, ... below `total`.  `smem` must be the
 // kernel's only LDS (it then starts at LDS address 0), and the kernel's first argument a GemmArgs.
-// k ranges but the last are multiples of 128, at least 256 long; n_store is set.
-template <bool A_KC, bool B_KC, typename OutT>
+// k ranges but the last are multiples of 128, at least 256 long; n_store is set.  FAR: for operands
+// that are not k-contiguous and span more than 2 GB of a tile's k range.
+template <bool A_KC, bool B_KC, typename OutT, bool FAR>
 __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const int block, const int stride, const int total) {
   typedef Panels<A_KC> PA;
   typedef Panels<B_KC> PB;
@@ -104,6 +105,24 @@ __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const i
   auto load_b = [&](int i, int h, unsigned chunk) {
     load_to_lds(chunk + 32768u + lds_of(i, h), B_KC ? (lane_k < b_left ? vb : OOB_OFFSET) : vb, b_src,
                 b_off + (h ? panel_b : 0u) + (i & 1 ? ldb * 32u : 0u) + (i & 2 ? 2 * panel_b : 0u));
+  };
+
+  // Offsets are 32-bit: far operands take their origin along whenever a chunk starts 1 GB behind
+  // it (64 rows are 128 MB at most).  (For all operands the two compares a chunk cost 0.3 %.)
+  auto move_on = [](u32x4& src, unsigned& off, const void* base, int64_t total) {
+    const uint64_t at = ((uint64_t)src.y << 32 | src.x) + off;
+    src = descriptor((const void*)at, 0, ((int64_t)((uint64_t)base - at) >> 1) + total, 2);
+    off = 0;
+  };
+  auto move_a = [&]() {
+    if (!FAR || A_KC || a_off < (1u << 30)) return;
+    const ArgPtr q = args();
+    move_on(a_src, a_off, q->A, (int64_t)(q->K - 1) * q->lda + q->M);
+  };
+  auto move_b = [&]() {
+    if (!FAR || B_KC || b_off < (1u << 30)) return;
+    const ArgPtr q = args();
+    move_on(b_src, b_off, q->B, (int64_t)(q->K - 1) * q->ldb + q->N);
   };
 
   bf16x8 fa[2][2][4], fb[2][4][4];   // fragments [set][block][k step]
@@ -195,9 +214,11 @@ __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const i
           if (FIRST != 1) {
             b_off += step_b; b_left -= 64;
             if (kc + 3 == nk) { b_src = next.b; b_off = 0; b_left = next.k_len; }
+            move_b();
           }
         } else {
           a_off += step_a; a_left -= 64;
+          move_a();
         }
         // This phase's reads done, and the loads two phases back and older: what the next phase
         // reads.  Behind an epilogue 32 (bf16) or 64 (fp32) stores and the bias load lie in between:
@@ -311,11 +332,11 @@ __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const i
 }
 
 // One work-group per CU (the tile takes all of its LDS) walks the tiles index, index + grid, ...
-template <int BM, int BN, int CHUNKS, int STEPS, bool A_KC, bool B_KC, typename OutT>
+template <int BM, int BN, int CHUNKS, int STEPS, bool A_KC, bool B_KC, typename OutT, bool FAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_crew_kernel(const GemmArgs, const int total) {
   static_assert(BM == 256 && BN == 256 && CHUNKS == 2 && STEPS == 4, "256 x 256, two chunks of four k steps in LDS");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[GEMM256_LDS];
-  gemm256_tiles<A_KC, B_KC, OutT>(smem, blockIdx.x, gridDim.x, total);
+  gemm256_tiles<A_KC, B_KC, OutT, FAR>(smem, blockIdx.x, gridDim.x, total);
 }
 
 // ---- column sums ----
@@ -369,13 +390,13 @@ __global__ __launch_bounds__(256) void colsum_bf16_kernel(const unsigned short* 
 // A launch of the GEMM that does not fill the chip, with the column sums riding along:
 // work-groups past the GEMM's own run the column-sum body on the CUs the GEMM leaves free --
 // one streams from HBM while the other multiplies.
-template <int BM, int BN, int CHUNKS, int STEPS, bool A_KC, bool B_KC, typename OutT>
+template <int BM, int BN, int CHUNKS, int STEPS, bool A_KC, bool B_KC, typename OutT, bool FAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_with_colsum_kernel(
     const GemmArgs, const int gemm_groups, const ColsumArgs c) {
   static_assert(BM == 256 && BN == 256 && CHUNKS == 2 && STEPS == 4, "256 x 256, two chunks of four k steps in LDS");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[GEMM256_LDS];
   if ((int)blockIdx.x < gemm_groups) {
-    gemm256_tiles<A_KC, B_KC, OutT>(smem, blockIdx.x, gemm_groups, gemm_groups);
+    gemm256_tiles<A_KC, B_KC, OutT, FAR>(smem, blockIdx.x, gemm_groups, gemm_groups);
   } else {
     const int w = blockIdx.x - gemm_groups;
     colsum_body(static_cast<const unsigned short*>(c.in), c.out, c.rows, c.cols, c.rows_per_split,
@@ -389,16 +410,23 @@ bool gemm256_supported(GemmKind kind, const GemmArgs& a) {
   if (kind == GEMM_NN_F32_COLSUM || kind == GEMM_TN_F32) return false;   // no registers for the sums
   // ranges but the last: whole pairs of chunks (their zero chunks would be the next range's rows)
   if (a.splits > 1 && (a.k_per_split % 128 != 0 || a.k_per_split < 256)) return false;
-  // byte offsets from a tile's origin are 32-bit: rows of an operand that is not k-contiguous
+  // byte offsets from a tile's origin are 32-bit: 256 rows of a k-contiguous operand, over the whole
+  // k range, a few chunks of the other kind (far_operands)
   const int64_t range = (int64_t)(a.splits > 1 ? a.k_per_split : a.K) + 512;
-  if (!(a_kc ? within_window(256, a.lda, range, 2) : range * a.lda * 2 < 0x7fffffffLL)) return false;
-  if (!(b_kc ? within_window(256, a.ldb, range, 2) : range * a.ldb * 2 < 0x7fffffffLL)) return false;
+  if (!(a_kc ? within_window(256, a.lda, range, 2) : a.lda <= 1 << 20)) return false;
+  if (!(b_kc ? within_window(256, a.ldb, range, 2) : a.ldb <= 1 << 20)) return false;
   // ... and rows of the result: a window's 32 in bf16, all 256 in fp32
   return within_window(f32 ? 256 : 32, a.ldc, a.n_store > 0 ? a.n_store : a.N, f32 ? 4 : 2);
 }
 
-template <bool A_KC, bool B_KC, typename OutT>
-static hipError_t launch_crew(GemmArgs a, hipStream_t s) {
+// Whether an operand that is not k-contiguous spans more of a tile's k range than offsets reach.
+static bool far_operands(bool a_kc, bool b_kc, const GemmArgs& a) {
+  const int64_t range = (int64_t)(a.splits > 1 ? a.k_per_split : a.K) + 512;
+  return (!a_kc && range * a.lda * 2 > 0x7fffffffLL) || (!b_kc && range * a.ldb * 2 > 0x7fffffffLL);
+}
+
+template <bool A_KC, bool B_KC, typename OutT, bool FAR>
+static hipError_t launch_crew_as(GemmArgs a, hipStream_t s) {
   a.tiles_m = (a.M + 255) / 256;
   a.tiles_n = (a.N + 255) / 256;
   if (a.n_store <= 0) a.n_store = a.N;
@@ -406,9 +434,16 @@ static hipError_t launch_crew(GemmArgs a, hipStream_t s) {
   if (total <= 0 || total > 0x7fffffffLL - NUM_CUS) return hipErrorInvalidValue;
   constexpr bool F32 = sizeof(OutT) == 4;
   note_gemm(a, A_KC, B_KC, 2, sizeof(OutT), F32);
-  static const std::string name = kernel_label("gemm_bf16_crew_kernel", {lbl(256), lbl(256), lbl(2), lbl(4), lbl(A_KC), lbl(B_KC), F32 ? "float" : "bf16"});
-  return launch_kernel(name.c_str(), gemm_work(a, 2, sizeof(OutT), F32), gemm_bf16_crew_kernel<256, 256, 2, 4, A_KC, B_KC, OutT>,
+  static const std::string name = kernel_label("gemm_bf16_crew_kernel", {lbl(256), lbl(256), lbl(2), lbl(4), lbl(A_KC), lbl(B_KC), F32 ? "float" : "bf16", lbl(FAR)});
+  return launch_kernel(name.c_str(), gemm_work(a, 2, sizeof(OutT), F32), gemm_bf16_crew_kernel<256, 256, 2, 4, A_KC, B_KC, OutT, FAR>,
                        dim3((unsigned)(total < NUM_CUS ? total : NUM_CUS)), dim3(256), s, a, (int)total);
+}
+
+template <bool A_KC, bool B_KC, typename OutT>
+static hipError_t launch_crew(const GemmArgs& a, hipStream_t s) {
+  if constexpr (!A_KC || !B_KC)
+    if (far_operands(A_KC, B_KC, a)) return launch_crew_as<A_KC, B_KC, OutT, true>(a, s);
+  return launch_crew_as<A_KC, B_KC, OutT, false>(a, s);
 }
 
 hipError_t launch_gemm256_bf16(GemmKind kind, const GemmArgs& a, hipStream_t s) {
@@ -442,9 +477,13 @@ hipError_t launch_gemm256_with_colsum(GemmArgs a, const void* in, float* out, in
   note_matrix(out, splits, cols, cols, 4, true);
   Work work = gemm_work(a, 2, 4, true);
   work.bytes += (double)rows * cols * 2 + (double)splits * cols * 4;
-  return launch_kernel("gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float>", work,
-                       gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float>,
-                       dim3((unsigned)grid), dim3(256), s, a, (int)gg, c);
+  return far_operands(true, false, a)
+             ? launch_kernel("gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float, true>", work,
+                             gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float, true>,
+                             dim3((unsigned)grid), dim3(256), s, a, (int)gg, c)
+             : launch_kernel("gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float, false>", work,
+                             gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float, false>,
+                             dim3((unsigned)grid), dim3(256), s, a, (int)gg, c);
 }
 
 hipError_t launch_colsum_bf16(const void* in, float* out, int rows, int cols, int splits,

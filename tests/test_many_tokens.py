@@ -66,3 +66,73 @@ def test_factor_gradient_over_millions_of_tokens(blocks, d_in, R, kernel):
     assert rel_err(to_f64(dU), blocks * O.grad_factors(v["x"], v["S"], v["dY"]).reshape(R, 16)) <= TOL["bf16"]
     assert rel_err(to_f64(db), blocks * O.grad_bias(v["dY"])) <= TOL["bf16"]
     assert any(n.startswith(kernel) for n in names), names
+
+
+@pytest.mark.parametrize("tokens,out,R", [(98304, 11008, 2048), (131072, 8192, 2048), (300000, 4096, 4096)])
+def test_operands_past_two_gib_keep_their_tile(tokens, out, R):
+    assert tokens * out * 2 >= 2 ** 31
+    args = (tokens, 256, out, 1, R, sk.SK_BF16)
+    sk.sk_trace_begin()
+    st = sk.sk_linear_bwd_weight(BASE, 2 * BASE, 3 * BASE, 4 * BASE, 5 * BASE, *args, 6 * BASE,
+                                 sk.sk_linear_workspace_bytes(sk.SK_OP_BWD_WEIGHT, *args))
+    names = [n for n, _ in sk.sk_trace_kernels()]
+    sk.sk_trace_end()
+    assert st == sk.SK_OK and not any(n.startswith("gemm_bf16_kernel") for n in names), names
+
+
+@pytest.mark.gpu
+def test_factor_gradient_of_operands_past_two_gib():
+    """Z^T . dY with more than 2 GB of dY under one column of tiles: a round of whole-token tiles and the
+    split rest.  Blocks of an odd length, repeated; bound as above (98376 tokens)."""
+    from skgpu import TOL, rel_err, to_dev, to_f64
+    blocks, d_out, R = 24, 11008, 2048
+    w = W.Workload("past_two_gib", 4099, 16, d_out, 1, R, "bf16", seed=6)
+    t = W.generate(w)
+    v = {n: a.astype(np.float64) for n, a in t.value.items()}
+    x, dY = (to_dev(t.stored[n], "bf16").repeat(blocks, 1) for n in ("x", "dY"))
+    assert dY.numel() * 2 > 2 ** 31
+    S = to_dev(t.S_cat(), "bf16")
+    args = (x.shape[0], 16, d_out, 1, R, sk.SK_BF16)
+    nbytes = sk.sk_linear_workspace_bytes(sk.SK_OP_BWD_WEIGHT, *args)
+    ws = torch.full((nbytes,), 0xff, dtype=torch.uint8, device="cuda")
+    dU = torch.empty((R, d_out), dtype=torch.float32, device="cuda")
+    db = torch.empty((d_out,), dtype=torch.float32, device="cuda")
+    print(f"case T={x.shape[0]} out={d_out} R={R}", flush=True)
+    sk.sk_profile_begin(16)
+    sk.check(sk.sk_linear_bwd_weight(x, S, dY, dU, db, *args, ws, nbytes, torch.cuda.current_stream().cuda_stream))
+    names = [r[0] for r in sk.sk_profile_end(16)]
+    torch.cuda.synchronize()
+    assert rel_err(to_f64(dU), blocks * O.grad_factors(v["x"], v["S"], v["dY"]).reshape(R, d_out)) <= TOL["bf16"]
+    assert rel_err(to_f64(db), blocks * O.grad_bias(v["dY"])) <= TOL["bf16"]
+    assert names[1] == "gemm_bf16_crew_kernel<256, 256, 2, 4, true, false, float, true>", names
+    assert names[2].startswith("gemm_bf16_with_colsum_kernel"), names
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tokens,blocks,d_in,nc", [(4099, 65, 4096, 4096), (300, 1, 4112, 3856), (1, 1, 4096, 4096), (63, 1, 8192, 2048)],
+                         ids=lambda v: str(v))
+def test_first_stage_gradient_on_big_tiles(tokens, blocks, d_in, nc):
+    """x^T . G on 256 x 256 tiles, neither operand k-contiguous: what lies past the contraction comes from
+    the ends of both arrays.  The first case has more than 2 GB of either.  Bound: G rounded to 8 bits errs
+    by 2^-9 / sqrt(6) of its size in the root mean square, the largest of 2^24 such errors by 5.5 times that,
+    4.4e-3, against rows whose size varies by a fifth where 256 products make up G: 6e-3."""
+    from skgpu import TOL, rel_err, to_dev, to_f64
+    w = W.Workload("first_stage_big", tokens, d_in, 256, 1, nc, "bf16", seed=7)
+    t = W.generate(w)
+    v = {n: a.astype(np.float64) for n, a in t.value.items()}
+    x, dY = (to_dev(t.stored[n], "bf16").repeat(blocks, 1) for n in ("x", "dY"))
+    U = to_dev(t.U_cat(), "bf16")
+    args = (x.shape[0], d_in, 256, 1, nc)
+    nbytes = sk.sk_linear_workspace_bytes(sk.SK_OP_BWD_WEIGHT_FIRST, *args, sk.SK_BF16)
+    ws = torch.full((nbytes,), 0xff, dtype=torch.uint8, device="cuda")
+    dA = torch.full((d_in, nc), float("nan"), dtype=torch.float32, device="cuda")
+    print(f"case T={x.shape[0]} in={d_in} columns={nc}", flush=True)
+    sk.sk_profile_begin(16)
+    sk.check(sk.sk_linear_bwd_weight_first(x, U, dY, dA, *args, 0, nc, sk.SK_BF16, ws, nbytes,
+                                           torch.cuda.current_stream().cuda_stream))
+    names = [r[0] for r in sk.sk_profile_end(16)]
+    torch.cuda.synchronize()
+    G = v["dY"] @ v["U"].reshape(nc, 256).T
+    assert rel_err(to_f64(dA), blocks * (v["x"].T @ G)) <= TOL["bf16"]
+    far = "true" if blocks > 1 else "false"
+    assert f"gemm_bf16_crew_kernel<256, 256, 2, 4, false, false, float, {far}>" in names, names
