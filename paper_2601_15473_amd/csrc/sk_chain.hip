@@ -273,6 +273,11 @@ __global__ __launch_bounds__(256) void chain_kernel(const ChainArgs p) {
 // ---------------------------------------------------------------------------
 constexpr int CS_BN = 128;
 
+// Finished output tiles kept in LDS: two, and one where that lets two work-groups share a CU, at one
+// more barrier a step ([40000 x 384] -> 384, R = 32, forward 22.4 -> 17.4 us; 65536 tokens, 768 wide 39.7 ->
+// 32.8; 3072 wide, runs of 24 tiles, 103 -> 108).
+constexpr int chain_outs(int mb, int rt) { return mb == 128 && rt == 64 ? 1 : 2; }
+
 template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC>
 struct SmallLds {
   typedef OpTile<CS_BN, B2_KC, RT> TB2;
@@ -280,12 +285,13 @@ struct SmallLds {
   typedef OpTile<RT, B1_KC> TB1;
   static constexpr int Z_LD = RT + 8;
   static constexpr int Z_BYTES = MB * Z_LD * 2;
-  // two finished output tiles, over Zt (which is in registers by then)
+  // finished output tiles, over Zt (which is in registers by then), then the B2 tiles
+  static constexpr int OUTS = chain_outs(MB, RT);
   static constexpr int OUT_BYTES = MB * CS_BN * 2;
-  static constexpr int HEAD_BYTES = Z_BYTES > 2 * OUT_BYTES ? Z_BYTES : 2 * OUT_BYTES;
+  static constexpr int HEAD_BYTES = Z_BYTES > OUTS * OUT_BYTES ? Z_BYTES : OUTS * OUT_BYTES;
   static constexpr int S2_BYTES = 2 * TB2::ELEMS * 2;
-  static constexpr int S1_BYTES = FUSED ? 2 * (TA::ELEMS + TB1::ELEMS) * 2 : 0;
-  static constexpr int BYTES = HEAD_BYTES + (S1_BYTES > S2_BYTES ? S1_BYTES : S2_BYTES);
+  static constexpr int S1_BYTES = FUSED ? 2 * (TA::ELEMS + TB1::ELEMS) * 2 : 0;   // (behind Zt)
+  static constexpr int BYTES = Z_BYTES + S1_BYTES > HEAD_BYTES + S2_BYTES ? Z_BYTES + S1_BYTES : HEAD_BYTES + S2_BYTES;
 };
 
 // Scheduling of one stage-2 tile of the narrow kernel: per k step the fragment reads of
@@ -305,7 +311,7 @@ __device__ __forceinline__ void sched_stage2() {
 }
 
 template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC>
-__global__ __launch_bounds__(256) void chain_small_kernel(const ChainArgs p) {
+__global__ __launch_bounds__(256, chain_outs(MB, RT) == 1 ? 2 : 1) void chain_small_kernel(const ChainArgs p) {
   static_assert(MB == 64 || MB == 128, "token tiles are 64 or 128 rows");
   typedef SmallLds<MB, RT, B2_KC, FUSED, B1_KC> L;
   typedef typename L::TB2 TB2;
@@ -317,8 +323,7 @@ __global__ __launch_bounds__(256) void chain_small_kernel(const ChainArgs p) {
   constexpr int TM1 = WM1 / 32, TN1 = WN1 / 32;
   __shared__ __attribute__((aligned(16))) unsigned char smem[L::BYTES];
   bf16* const Zs = reinterpret_cast<bf16*>(smem);
-  unsigned char* const work = smem + L::HEAD_BYTES;
-  bf16* const Bbuf = reinterpret_cast<bf16*>(work);
+  bf16* const Bbuf = reinterpret_cast<bf16*>(smem + L::HEAD_BYTES);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;  // stage-1 wave grid
@@ -385,7 +390,7 @@ __global__ __launch_bounds__(256) void chain_small_kernel(const ChainArgs p) {
     typedef typename L::TA TA;
     typedef typename L::TB1 TB1;
     constexpr int STAGE = TA::ELEMS + TB1::ELEMS;
-    bf16* const s1 = reinterpret_cast<bf16*>(work);
+    bf16* const s1 = reinterpret_cast<bf16*>(smem + L::Z_BYTES);
     const bf16* __restrict__ A = static_cast<const bf16*>(p.A);
     const bf16* __restrict__ B1 = static_cast<const bf16*>(p.B1);
     f32x16 acc1[TM1][TN1];
@@ -641,23 +646,24 @@ __global__ __launch_bounds__(256) void chain_small_kernel(const ChainArgs p) {
         *reinterpret_cast<uint4*>(out + row * 256 + ((piece ^ (row & 15)) * 16)) = make_uint4(s0.x, s1.x, s0.y, s1.y);
       }
     };
+    if (L::OUTS == 1) __syncthreads();   // (everybody has read the tile before it)
 #pragma unroll
     for (int i = 0; i < MT; ++i) rows_out(acc[i], i * 32);
     __syncthreads();
   };
 
   unsigned char* const out0 = smem;
-  unsigned char* const out1 = smem + L::OUT_BYTES;
-  int jt = 0;
-  for (; jt < my_tiles; jt += 2) {
+  unsigned char* const out1 = smem + (L::OUTS - 1) * L::OUT_BYTES;
+  for (int jt = 0; jt < my_tiles; jt += 2) {
     // tile jt sits in buffer 0; set 1 holds tile jt + 1
     step(jt, Bbuf, Bbuf + TB2::ELEMS, bv0, bv1, rb0, rb1, out1, out0);
-    // (computes on zeros and stores nothing past the run)
-    step(jt + 1, Bbuf + TB2::ELEMS, Bbuf, bv1, bv0, rb1, rb0, out0, out1);
+    // (behind an odd last tile a step on zeros, 2000 cycles, would hold up its stores: [2048 x 768] -> 768,
+    // R = 128, forward 11.4 us with it, 10.8 without)
+    if (jt + 1 < my_tiles) step(jt + 1, Bbuf + TB2::ELEMS, Bbuf, bv1, bv0, rb1, rb0, out0, out1);
   }
   uint4 leaving[ROWS_OUT];
-  tile_read(out1, leaving);
-  tile_store(jt - 1, leaving);
+  tile_read(my_tiles & 1 ? out0 : out1, leaving);
+  tile_store(my_tiles - 1, leaving);
 }
 
 bool chain_supported(int R) { return R >= 16 && R <= 512; }
