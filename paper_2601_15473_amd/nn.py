@@ -77,10 +77,16 @@ def _stream(device: torch.device) -> int:
 
 def _in_type(grads32: torch.Tensor, dtype: torch.dtype, *shapes):
     """The fp32 gradients that lie one behind the other in ``grads32`` (from its start; it may hold
-    more), in the layer's type: one conversion for all of them instead of one launch each.  Detached,
-    because a view made without a graph may not be changed in place by something that has one."""
+    more), in the layer's type: one launch for all of them.  Each is a tensor of its own, since the
+    caller's program may change, keep or save any of them by itself."""
     sizes = [math.prod(s) for s in shapes]
-    return [t.view(s).detach() for t, s in zip(grads32[:sum(sizes)].to(dtype).split(sizes), shapes)]
+    rest = grads32.numel() - sum(sizes)
+    parts = [t.view(s) for t, s in zip(grads32.split(sizes + [rest] if rest else sizes), shapes)]
+    if len(parts) == 1:
+        return [parts[0].to(dtype)]
+    out = [torch.empty(s, dtype=dtype, device=grads32.device) for s in shapes]
+    torch._foreach_copy_(out, parts)
+    return out
 
 
 class SKLinearFunction(torch.autograd.Function):
@@ -138,7 +144,7 @@ class SKLinearFunction(torch.autograd.Function):
                     db32 = torch.empty((d_out,), dtype=dtype, device=dY.device) if ctx.has_bias else None
                 else:
                     g32 = torch.empty((R + ctx.has_bias) * d_out, dtype=torch.float32, device=dY.device)
-                    dU32, db32 = g32, g32[R * d_out:] if ctx.has_bias else None
+                    dU32, db32 = g32, g32.data_ptr() + R * d_out * 4 if ctx.has_bias else None
             if need_dx and want_w:      # both gradients from one call (its kernels share launches)
                 sk.check(sk.sk_linear_bwd(x2, dY2, S_cat, U_cat, dX, dU32, db32, *ctx.args,
                                           ws, ws.numel(), stream))
@@ -149,11 +155,15 @@ class SKLinearFunction(torch.autograd.Function):
             if need_dx and dX.shape != ctx.x_shape:
                 dX = dX.reshape(ctx.x_shape)
             if want_w:
-                if dtype != torch.float32:
-                    dU32, db32 = _in_type(g32, dtype, (R, d_out), (d_out,)) if ctx.has_bias else \
-                        (*_in_type(g32, dtype, (R, d_out)), None)
-                dU = dU32 if need_du else None
-                db = db32 if need_db else None
+                need_db = need_db and ctx.has_bias
+                if dtype == torch.float32:
+                    dU, db = dU32 if need_du else None, db32 if need_db else None
+                elif need_du and need_db:
+                    dU, db = _in_type(g32, dtype, (R, d_out), (d_out,))
+                elif need_du:
+                    dU, = _in_type(g32, dtype, (R, d_out))
+                else:
+                    db, = _in_type(g32[R * d_out:], dtype, (d_out,))
         return dX, None, dU, db, None, None
 
 
@@ -288,16 +298,19 @@ class SKLinearTwoSidedFunction(torch.autograd.Function):
                 # dropped, and what lies before them is converted in one go
                 n_db = d_out if ctx.has_bias else 0
                 g32 = torch.empty(n_db + d_in * half + 2 * half * d_out, dtype=torch.float32, device=dev)
-                db, dA, dB = g32 if ctx.has_bias else None, g32[n_db:], g32[n_db + d_in * half:]
+                db, dA = g32 if ctx.has_bias else None, g32.data_ptr() + n_db * 4
+                dB = dA + d_in * half * 4
             sk.check(sk.sk_linear_bwd(x2, dY2, A_cat, B_cat, dX, dB, db, *ctx.args, ws, ws.numel(), stream))
             sk.check(sk.sk_linear_bwd_weight_first(x2, B_cat, dY2, dA, tokens, d_in, d_out, l2, k,
                                                    half, half, dt, ws, ws.numel(), stream))
             if dtype == torch.float32:
                 dB = dB[:half]
+            elif ctx.has_bias:
+                db, dA, dB = _in_type(g32, dtype, (d_out,), (d_in, half), (half, d_out))
             else:
-                db, dA, dB = _in_type(g32, dtype, (n_db,), (d_in, half), (half, d_out))
+                dA, dB = _in_type(g32, dtype, (d_in, half), (half, d_out))
         return (dX if dX.shape == ctx.x_shape else dX.reshape(ctx.x_shape), None, dB, dA, None,
-                db if ctx.has_bias else None, None, None, None)
+                db, None, None, None)
 
 
 class SKLinearTwoSided(torch.nn.Module):

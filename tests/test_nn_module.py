@@ -38,6 +38,40 @@ def test_converted_gradients_can_be_changed_in_place():
     assert torch.equal(db, torch.arange(12.0, 16.0).bfloat16())
 
 
+def test_converted_gradients_are_tensors_of_their_own():
+    """Neither a graph that holds one nor its storage knows of the others."""
+    from paper_2601_15473_amd import nn as sknn
+    with torch.no_grad():
+        dU, db = sknn._in_type(torch.arange(20.0), torch.bfloat16, (3, 4), (4,))
+        alone, = sknn._in_type(torch.arange(20.0)[12:], torch.bfloat16, (4,))
+    w = torch.ones((3, 4), dtype=torch.bfloat16, requires_grad=True)
+    loss = (dU * w).sum()
+    db.mul_(0.5)
+    loss.backward()
+    assert torch.equal(w.grad, torch.arange(12.0).view(3, 4).bfloat16())
+    assert [t.untyped_storage().nbytes() for t in (dU, db, alone)] == [24, 8, 8]
+    assert torch.equal(alone, torch.arange(12.0, 16.0).bfloat16())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("two_sided", [False, True])
+def test_gradients_of_a_bf16_layer_do_not_share(two_sided):
+    from paper_2601_15473_amd.nn import SKLinear, SKLinearTwoSided
+    layer = (SKLinearTwoSided if two_sided else SKLinear)(64, 96, 1, 16, dtype=torch.bfloat16, seed=3)
+    x = torch.randn(40, 64, device="cuda").bfloat16()
+    layer(x).float().square().sum().backward()
+    grads = [p.grad for p in layer.parameters()]
+    assert len({g.untyped_storage().data_ptr() for g in grads}) == len(grads)
+    assert all(g.untyped_storage().nbytes() == 2 * g.numel() for g in grads)
+    if not two_sided:   # bias alone trained: nothing but its gradient stays
+        want = layer.bias.grad.clone()
+        layer.zero_grad(set_to_none=True)
+        layer.U_cat.requires_grad_(False)
+        layer(x).float().square().sum().backward()
+        assert layer.U_cat.grad is None and torch.equal(layer.bias.grad, want)
+        assert layer.bias.grad.untyped_storage().nbytes() == 2 * want.numel()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,tol", [(torch.bfloat16, 2e-2), (torch.float32, 1e-4)], ids=["bf16", "f32"])
 @pytest.mark.parametrize("shape", [(5, 40, 96), (333, 96)], ids=["batched", "flat"])
