@@ -62,7 +62,8 @@ typedef enum {
   SK_OP_FWD = 0,
   SK_OP_BWD_INPUT = 1,
   SK_OP_BWD_WEIGHT = 2,
-  SK_OP_BWD_WEIGHT_FIRST = 3, /* sized so that it serves any column range */
+  SK_OP_BWD_WEIGHT_FIRST = 3, /* sized so that it serves any column range (asked with a smaller l or k: any
+                                 range of that many columns) */
   SK_OP_BWD = 4               /* sk_linear_bwd: both gradients in one call */
 } sk_op;
 

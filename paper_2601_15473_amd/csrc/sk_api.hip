@@ -167,30 +167,37 @@ F32Plan plan_f32(int64_t M, int64_t N, int64_t K, int forced_splits, size_t max_
   static const int cand[] = {TILE_64x64, TILE_128x128};
   const int forced = tune(SK_TUNE_TILE);
   const bool force_tile = forced == TILE_64x64 || forced == TILE_128x128;
-  int64_t from = 1, most = K / 128 < 16 ? K / 128 : 16;   // ranges of at least 128
+  const unsigned k = (unsigned)K;
+  unsigned from = 1, most = k / 128 < 16 ? k / 128 : 16;   // ranges of at least 128
   if (most < 1) most = 1;
-  if (forced_splits >= 0) from = most = forced_splits < 1 ? 1 : (forced_splits > most ? most : forced_splits);
-  F32Plan f{};
-  double best = -1.0;
-  for (int t : cand) {
-    if (force_tile && t != forced) continue;
+  if (forced_splits >= 0) from = most = forced_splits < 1 ? 1 : (forced_splits > (int)most ? most : forced_splits);
+  struct Best {
+    int64_t tiles;
+    double time;
+    unsigned splits, kps;
+  } b[2];
+  for (int c = 0; c < 2; ++c) {
     int bm, bn;
-    tile_dims(t, bm, bn);
-    const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-    for (int64_t sp = from; sp <= most; ++sp) {
-      const int64_t kps = ((K + sp - 1) / sp + F32_BK - 1) / F32_BK * F32_BK;
-      const int64_t splits = (K + kps - 1) / kps;
-      if (splits > 1 && forced_splits < 0 && align_up((size_t)splits * M * N * 4) > max_slabs) continue;
-      const int64_t per_cu = (tiles * splits + NUM_CUS - 1) / NUM_CUS;
-      const double rate = t == TILE_64x64 ? (per_cu > 1 ? 0.52e12 : 0.39e12) : (per_cu > 1 ? 0.53e12 : 0.50e12);
-      double time = per_cu * (double)kps * 2.0 * bm * bn / rate + (t == TILE_64x64 ? 0.0 : 2.0e-6);
-      if (splits > 1) time += 6.0e-6 + splits * (double)M * N * 8.0 / 4.0e12;
-      if (best < 0.0 || time < best) {
-        best = time;
-        f.tile = t; f.splits = (int)splits; f.k_per_split = (int)kps;
-      }
+    tile_dims(cand[c], bm, bn);
+    b[c] = Best{((M + bm - 1) / bm) * ((N + bn - 1) / bn), -1.0, 0, 0};
+  }
+  // (a call asks for several plans, a workspace query for up to two per 16 columns: the ranges are
+  // worked out once for both tiles)
+  for (unsigned sp = from; sp <= most; ++sp) {
+    const unsigned kps = ((k + sp - 1) / sp + F32_BK - 1) / F32_BK * F32_BK;
+    const unsigned splits = (k + kps - 1) / kps;
+    if (splits > 1 && forced_splits < 0 && align_up((size_t)splits * M * N * 4) > max_slabs) continue;
+    const double sum = splits > 1 ? 6.0e-6 + splits * (double)M * N * 8.0 / 4.0e12 : 0.0;
+    for (int c = 0; c < 2; ++c) {
+      const int64_t per_cu = (b[c].tiles * splits + NUM_CUS - 1) / NUM_CUS;
+      const double time = (c == 0 ? per_cu * (double)kps * (2.0 * 64 * 64) / (per_cu > 1 ? 0.52e12 : 0.39e12)
+                                  : per_cu * (double)kps * (2.0 * 128 * 128) / (per_cu > 1 ? 0.53e12 : 0.50e12) + 2.0e-6) + sum;
+      if (b[c].time < 0.0 || time < b[c].time) { b[c].time = time; b[c].splits = splits; b[c].kps = kps; }
     }
   }
+  const int c = force_tile ? (forced == cand[1]) : b[1].time < b[0].time;
+  F32Plan f{};
+  f.tile = cand[c]; f.splits = (int)b[c].splits; f.k_per_split = (int)b[c].kps;
   f.slab_bytes = f.splits > 1 ? align_up((size_t)f.splits * M * N * 4) : 0;
   return f;
 }

@@ -285,8 +285,9 @@ class SKLinearTwoSidedFunction(torch.autograd.Function):
         dev = dY.device
         with _on(dev):
             stream = _stream(dev)
-            need = max(sk.sk_linear_workspace_bytes(op, *ctx.args)
-                       for op in (sk.SK_OP_BWD, sk.SK_OP_BWD_WEIGHT_FIRST))
+            # (the query plans every range a sketch of the given width has: `half` columns are asked for)
+            need = max(sk.sk_linear_workspace_bytes(sk.SK_OP_BWD, *ctx.args),
+                       sk.sk_linear_workspace_bytes(sk.SK_OP_BWD_WEIGHT_FIRST, tokens, d_in, d_out, l2 // 2, k, dt))
             ws = _workspace(dev, stream, need)
             dX = torch.empty((tokens, d_in), dtype=dtype, device=dev)
             if dtype == torch.float32:

@@ -200,6 +200,22 @@ def test_one_pass_backward_stays_inside_the_buffers():
             sk.sk_set_plan(0)
 
 
+@pytest.mark.parametrize("dtype", [sk.SK_BF16, sk.SK_F32])
+@pytest.mark.parametrize("shape", [(1, 16, 16, 1, 16), (4096, 768, 3072, 1, 64), (4096, 4096, 4096, 2, 128), (70001, 48, 8192, 3, 16),
+                                   (333, 8192, 80, 1, 1024)], ids=lambda s: "T%d_%dx%d_l%dk%d" % s)
+def test_first_stage_query_for_fewer_columns_serves_any_range_of_them(shape, dtype):
+    """As the two-sided layer asks: for its learned half of twice as many terms."""
+    T, d_in, d_out, l, k = shape
+    need = sk.sk_linear_workspace_bytes(sk.SK_OP_BWD_WEIGHT_FIRST, *shape, dtype)
+    P = SPACING
+    for c0 in (0, l * k):
+        sk.sk_trace_begin()
+        st = sk.sk_linear_bwd_weight_first(P, 2 * P, 3 * P, 4 * P, T, d_in, d_out, 2 * l, k, c0, l * k, dtype, 5 * P, need)
+        trace, _ = sk.sk_trace_end()
+        assert st == sk.SK_OK
+        assert all(a + n <= 5 * P + need for a, n, _, _ in trace if a >= 5 * P)
+
+
 def test_trace_mode_launches_nothing_and_ends_cleanly():
     sk.sk_trace_begin()
     st = sk.sk_linear_fwd(0x1000, 0x2000, 0x3000, None, 0x4000, 64, 64, 64, 1, 16, sk.SK_BF16, None, 0)
