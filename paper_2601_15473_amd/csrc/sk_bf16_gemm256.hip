@@ -173,7 +173,7 @@ __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const i
       // the wave's 128 bias values (zeros without a bias) wait for the epilogue in its strip
       const ArgPtr q = args();
       const u32x4 bias = descriptor(q->bias, here.n0 + wn * 128, q->bias != nullptr ? q->N : 0, 2);
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(STRIPS + wave * 8192), "v"(lane_again() * 4), "s"(bias));
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(STRIPS + wave * 8192), "v"(lane_again() * 4), "s"(bias) : "m0");
     }
     f32x16 acc[4][4];
 #pragma unroll

@@ -7,6 +7,10 @@
 #pragma once
 #include "sk_bf16_tile.h"
 
+// (the compiler remarks that M0, which the loads below name as overwritten, is a register it never
+// allocates; naming it keeps its own writes of M0 apart from their uses)
+#pragma clang diagnostic ignored "-Winline-asm"
+
 namespace sk {
 
 // A panel of an operand in LDS, 8 KB: [64 rows (m or n)][64 k] for a k-contiguous operand, else
@@ -62,7 +66,7 @@ __device__ __forceinline__ u32x4 descriptor(const void* base, int64_t origin, in
 // (One wait state between the write of M0 and the load that reads it; in inline assembly the
 // compiler does not insert it.)
 __device__ __forceinline__ void load_to_lds(unsigned lds, unsigned voff, u32x4 array, unsigned soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(array), "s"(soff));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(array), "s"(soff) : "m0");
 }
 
 // The lane number computed afresh, for what is not to be kept in registers through the main loop.

@@ -142,3 +142,16 @@ def test_noalloc_entry_rejects_before_any_hip_call():
     hdr = open(os.path.join(ROOT, "include", "sk.h")).read()
     assert re.search(r"#define SK_NOALLOC_SCRATCH_BYTES \(32u << 20\)", hdr)
     assert sk.SK_NOALLOC_SCRATCH_BYTES == 32 << 20
+
+
+def test_assembly_names_what_it_overwrites():
+    """Inline assembly that writes M0 says so, or the compiler may keep something of its own there."""
+    src = os.path.join(ROOT, "paper_2601_15473_amd", "csrc")
+    found = 0
+    for f in sorted(os.listdir(src)):
+        if f.endswith((".h", ".hip")):
+            for stmt in re.findall(r"asm volatile\((.*?)\);", open(os.path.join(src, f)).read(), flags=re.S):
+                if "s_mov_b32 m0" in stmt:
+                    found += 1
+                    assert re.search(r':\s*("[^"]*",\s*)*"m0"(,\s*"[^"]*")*\s*$', stmt), (f, stmt)
+    assert found >= 2
