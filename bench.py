@@ -5,7 +5,8 @@
 
 One step = forward (sk_linear_fwd) + input, factor and bias gradients
 (sk_linear_bwd, both gradients in one call) over one batch of synthetic input
-that is already resident in HBM.  Prints ONE JSON line.  The same step through
+that is already resident in HBM.  Prints ONE JSON line (--details FILE keeps everything
+behind it).  The same step through
 the three separate entry points is timed beside it (`three_call_step`), and
 every entry point by itself (`per_call`).
 
@@ -376,6 +377,30 @@ def cpu_baseline(w, tensors, seconds, two_sided):
                       f"(forward + both gradients, fp64 numpy/OpenBLAS, {el:.1f} s)"}
 
 
+CONFIG_LINE = ("tokens", "in", "out", "l", "k", "dtype", "ms_per_step", "tokens_per_s", "tflops", "bound", "step_frac",
+               "step_frac_of_measured", "three_call_ms_per_step", "max_rel_err_vs_oracle", "ok")
+
+
+def summary(out):
+    """What the printed line holds of the results: a line of a few thousand characters that whoever
+    reads the end of the output gets whole.  Configurations by their step, kernels by name and time,
+    numbers below the top level to five digits; --details keeps the rest."""
+    def short(v):
+        if isinstance(v, dict):
+            return {n: short(x) for n, x in v.items()}
+        if isinstance(v, (list, tuple)):
+            return [short(x) for x in v]
+        return float("%.5g" % v) if isinstance(v, float) else v
+    line = {n: v if isinstance(v, float) else short(v) for n, v in out.items()}
+    line["kernels"] = {"%s x%d" % (k["kernel"], k["groups"]): float("%.4g" % k["ms_per_step"]) for k in out["kernels"][:8]}
+    if "configs" in out:
+        line["configs"] = {name: {n: short(c[n]) for n in CONFIG_LINE if n in c} for name, c in out["configs"].items()}
+        for name, c in out["configs"].items():
+            if "dense_context" in c:
+                line["configs"][name]["over_dense_time"] = short(c["dense_context"].get("sketched_over_dense_time"))
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -387,6 +412,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-dense-context", action="store_true")
     ap.add_argument("--no-measured-peak", action="store_true")
+    ap.add_argument("--details", metavar="FILE", help="write every configuration's calls and kernels there as well")
     ap.add_argument("--cpu-seconds", type=float, default=12.0)
     ap.add_argument("--tokens", type=int, default=0, help="override the headline workload's token count")
     ap.add_argument("--three-calls", action="store_true",
@@ -520,7 +546,10 @@ def main():
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(w, tensors, args.cpu_seconds, args.two_sided)
 
-    print(json.dumps(out))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(summary(out)))
 
 
 if __name__ == "__main__":
