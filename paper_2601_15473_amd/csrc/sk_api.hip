@@ -124,11 +124,11 @@ size_t slab_room(size_t z_bytes) {
 
 // Tile choice for the general GEMM (measured on MI355X).  256 x 256 where its rounds of 256
 // work-groups are modelled to end before 128 x 128's (two work-groups per CU): a round takes
-// 6 us + 0.0215 us per k against 4.2 + 0.0165 for 512 of the smaller tiles, so 192 of the big
-// tiles already win (K = 320: 18.6 against 18.7 us; K = 2048: 49 against 60), 128 do not (K = 512: 19.5
-// against 16.3), and one more than a round has no use for them.  Otherwise the largest tile that
-// still gives every CU a work-group without being mostly padding, the smallest when the
-// problem cannot fill the chip.
+// 6 us + 0.0215 us per k against 4.2 + 0.0165 for 512 of the smaller tiles, on top of 6 and 5 us a
+// launch (fitted), so 192 of the big tiles already win (measured, K = 320: 18.6 against 18.7 us; K = 2048:
+// 49 against 60), 128 do not (K = 512: 19.5 against 16.3), and one more than a round has no use for
+// them.  Otherwise the largest tile that still gives every CU a work-group without being mostly
+// padding, the smallest when the problem cannot fill the chip.
 int choose_tile(int64_t M, int64_t N, int64_t K, int splits) {
   if (const int t = forced_tile(SK_TUNE_TILE); t >= 0) return t;  // forced (tests, sweeps)
   const int64_t m_cap = (M + 63) / 64 * 64, n_cap = (N + 63) / 64 * 64;

@@ -6,8 +6,9 @@
 // that: wave w takes the 64-wide k chunks w, w + 4, ... through a ring of its own in LDS, filled
 // by direct loads that only the wave itself waits for -- no barrier until the four partial sums
 // meet (in wave order) at the end, and up to 150 KB per CU in flight, which is what the
-// trip to HBM times a CU's share of its bandwidth asks for.  Nothing is split over work-groups,
-// so there are no slabs and no launch that sums them.
+// trip to HBM times a CU's share of its bandwidth asks for.  A long first contraction (past K = 3072, the
+// planner's few_rows_splits) is cut into two to eight ranges, each on XCDs of its own, that leave fp32
+// slabs for another launch to sum; everything else is one launch without slabs.
 #include "sk_bf16_lds.h"
 #include "sk_launch.h"
 

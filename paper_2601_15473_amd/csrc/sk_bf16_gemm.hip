@@ -360,7 +360,6 @@ static hipError_t launch_cfg(GemmArgs a, hipStream_t s) {
 template <bool A_KC, bool B_KC, typename OutT, bool COLSUM>
 static hipError_t launch_tiles(int tile, const GemmArgs& a, hipStream_t s) {
   switch (tile) {
-    case TILE_256x256:   // (what that kernel cannot take)
     case TILE_128x128: return launch_cfg<128, 128, A_KC, B_KC, OutT, COLSUM>(a, s);
     case TILE_128x64: return launch_cfg<128, 64, A_KC, B_KC, OutT, COLSUM>(a, s);
     case TILE_64x128: return launch_cfg<64, 128, A_KC, B_KC, OutT, COLSUM>(a, s);
@@ -370,7 +369,7 @@ static hipError_t launch_tiles(int tile, const GemmArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_gemm_bf16(GemmKind kind, int tile, const GemmArgs& a, hipStream_t s) {
-  if (tile == TILE_256x256 && gemm256_supported(kind, a)) return launch_gemm256_bf16(kind, a, s);
+  if (tile == TILE_256x256) return launch_gemm256_bf16(kind, a, s);
   switch (kind) {
     case GEMM_NN: return launch_tiles<true, false, bf16, false>(tile, a, s);
     case GEMM_NT: return launch_tiles<true, true, bf16, false>(tile, a, s);

@@ -332,11 +332,16 @@ __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const i
 }
 
 // One work-group per CU (the tile takes all of its LDS) walks the tiles index, index + grid, ...
-template <int BM, int BN, int CHUNKS, int STEPS, bool A_KC, bool B_KC, typename OutT, bool FAR>
+template <int BM, int BN, int CHUNKS, int STEPS, bool A_KC, bool B_KC, typename OutT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_crew_kernel(const GemmArgs, const int total) {
   static_assert(BM == 256 && BN == 256 && CHUNKS == 2 && STEPS == 4, "256 x 256, two chunks of four k steps in LDS");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[GEMM256_LDS];
-  gemm256_tiles<A_KC, B_KC, OutT, FAR>(smem, blockIdx.x, gridDim.x, total);
+  gemm256_tiles<A_KC, B_KC, OutT, false>(smem, blockIdx.x, gridDim.x, total);
+}
+template <bool A_KC, bool B_KC, typename OutT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_far_kernel(const GemmArgs, const int total) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[GEMM256_LDS];
+  gemm256_tiles<A_KC, B_KC, OutT, true>(smem, blockIdx.x, gridDim.x, total);
 }
 
 // ---- column sums ----
@@ -390,10 +395,8 @@ __global__ __launch_bounds__(256) void colsum_bf16_kernel(const unsigned short* 
 // A launch of the GEMM that does not fill the chip, with the column sums riding along:
 // work-groups past the GEMM's own run the column-sum body on the CUs the GEMM leaves free --
 // one streams from HBM while the other multiplies.
-template <int BM, int BN, int CHUNKS, int STEPS, bool A_KC, bool B_KC, typename OutT, bool FAR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_with_colsum_kernel(
-    const GemmArgs, const int gemm_groups, const ColsumArgs c) {
-  static_assert(BM == 256 && BN == 256 && CHUNKS == 2 && STEPS == 4, "256 x 256, two chunks of four k steps in LDS");
+template <bool A_KC, bool B_KC, typename OutT, bool FAR>
+__device__ __forceinline__ void gemm256_with_colsum(const int gemm_groups, const ColsumArgs& c) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[GEMM256_LDS];
   if ((int)blockIdx.x < gemm_groups) {
     gemm256_tiles<A_KC, B_KC, OutT, FAR>(smem, blockIdx.x, gemm_groups, gemm_groups);
@@ -403,11 +406,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 w % c.col_groups, w / c.col_groups, reinterpret_cast<float*>(smem));
   }
 }
+template <int BM, int BN, int CHUNKS, int STEPS, bool A_KC, bool B_KC, typename OutT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_with_colsum_kernel(
+    const GemmArgs, const int gemm_groups, const ColsumArgs c) {
+  static_assert(BM == 256 && BN == 256 && CHUNKS == 2 && STEPS == 4, "256 x 256, two chunks of four k steps in LDS");
+  gemm256_with_colsum<A_KC, B_KC, OutT, false>(gemm_groups, c);
+}
+template <bool A_KC, bool B_KC, typename OutT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_far_with_colsum_kernel(
+    const GemmArgs, const int gemm_groups, const ColsumArgs c) {
+  gemm256_with_colsum<A_KC, B_KC, OutT, true>(gemm_groups, c);
+}
 
 bool gemm256_supported(GemmKind kind, const GemmArgs& a) {
   bool a_kc, b_kc, f32;
   gemm_kind_traits(kind, a_kc, b_kc, f32);
   if (kind == GEMM_NN_F32_COLSUM || kind == GEMM_TN_F32) return false;   // no registers for the sums
+  if (kind == GEMM_NT_F32 || kind == GEMM_TT_F32) return false;          // (no plan splits these on this tile)
   // ranges but the last: whole pairs of chunks (their zero chunks would be the next range's rows)
   if (a.splits > 1 && (a.k_per_split % 128 != 0 || a.k_per_split < 256)) return false;
   // byte offsets from a tile's origin are 32-bit: 256 rows of a k-contiguous operand, over the whole
@@ -425,8 +440,8 @@ static bool far_operands(bool a_kc, bool b_kc, const GemmArgs& a) {
   return (!a_kc && range * a.lda * 2 > 0x7fffffffLL) || (!b_kc && range * a.ldb * 2 > 0x7fffffffLL);
 }
 
-template <bool A_KC, bool B_KC, typename OutT, bool FAR>
-static hipError_t launch_crew_as(GemmArgs a, hipStream_t s) {
+template <bool A_KC, bool B_KC, typename OutT>
+static hipError_t launch_crew(GemmArgs a, hipStream_t s) {
   a.tiles_m = (a.M + 255) / 256;
   a.tiles_n = (a.N + 255) / 256;
   if (a.n_store <= 0) a.n_store = a.N;
@@ -434,16 +449,16 @@ static hipError_t launch_crew_as(GemmArgs a, hipStream_t s) {
   if (total <= 0 || total > 0x7fffffffLL - NUM_CUS) return hipErrorInvalidValue;
   constexpr bool F32 = sizeof(OutT) == 4;
   note_gemm(a, A_KC, B_KC, 2, sizeof(OutT), F32);
-  static const std::string name = kernel_label("gemm_bf16_crew_kernel", {lbl(256), lbl(256), lbl(2), lbl(4), lbl(A_KC), lbl(B_KC), F32 ? "float" : "bf16", lbl(FAR)});
-  return launch_kernel(name.c_str(), gemm_work(a, 2, sizeof(OutT), F32), gemm_bf16_crew_kernel<256, 256, 2, 4, A_KC, B_KC, OutT, FAR>,
-                       dim3((unsigned)(total < NUM_CUS ? total : NUM_CUS)), dim3(256), s, a, (int)total);
-}
-
-template <bool A_KC, bool B_KC, typename OutT>
-static hipError_t launch_crew(const GemmArgs& a, hipStream_t s) {
-  if constexpr (!A_KC || !B_KC)
-    if (far_operands(A_KC, B_KC, a)) return launch_crew_as<A_KC, B_KC, OutT, true>(a, s);
-  return launch_crew_as<A_KC, B_KC, OutT, false>(a, s);
+  const dim3 grid((unsigned)(total < NUM_CUS ? total : NUM_CUS));
+  const Work work = gemm_work(a, 2, sizeof(OutT), F32);
+  if constexpr (!A_KC || !B_KC) {
+    if (far_operands(A_KC, B_KC, a)) {
+      static const std::string far = kernel_label("gemm_bf16_far_kernel", {lbl(A_KC), lbl(B_KC), F32 ? "float" : "bf16"});
+      return launch_kernel(far.c_str(), work, gemm_bf16_far_kernel<A_KC, B_KC, OutT>, grid, dim3(256), s, a, (int)total);
+    }
+  }
+  static const std::string name = kernel_label("gemm_bf16_crew_kernel", {lbl(256), lbl(256), lbl(2), lbl(4), lbl(A_KC), lbl(B_KC), F32 ? "float" : "bf16"});
+  return launch_kernel(name.c_str(), work, gemm_bf16_crew_kernel<256, 256, 2, 4, A_KC, B_KC, OutT>, grid, dim3(256), s, a, (int)total);
 }
 
 hipError_t launch_gemm256_bf16(GemmKind kind, const GemmArgs& a, hipStream_t s) {
@@ -453,8 +468,6 @@ hipError_t launch_gemm256_bf16(GemmKind kind, const GemmArgs& a, hipStream_t s) 
     case GEMM_NT: return launch_crew<true, true, bf16>(a, s);
     case GEMM_TT: return launch_crew<false, true, bf16>(a, s);
     case GEMM_NN_F32: return launch_crew<true, false, float>(a, s);
-    case GEMM_NT_F32: return launch_crew<true, true, float>(a, s);
-    case GEMM_TT_F32: return launch_crew<false, true, float>(a, s);
     case GEMM_TN_F32_PLAIN: return launch_crew<false, false, float>(a, s);
     default: return hipErrorInvalidValue;
   }
@@ -478,11 +491,10 @@ hipError_t launch_gemm256_with_colsum(GemmArgs a, const void* in, float* out, in
   Work work = gemm_work(a, 2, 4, true);
   work.bytes += (double)rows * cols * 2 + (double)splits * cols * 4;
   return far_operands(true, false, a)
-             ? launch_kernel("gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float, true>", work,
-                             gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float, true>,
-                             dim3((unsigned)grid), dim3(256), s, a, (int)gg, c)
-             : launch_kernel("gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float, false>", work,
-                             gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float, false>,
+             ? launch_kernel("gemm_bf16_far_with_colsum_kernel<true, false, float>", work,
+                             gemm_bf16_far_with_colsum_kernel<true, false, float>, dim3((unsigned)grid), dim3(256), s, a, (int)gg, c)
+             : launch_kernel("gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float>", work,
+                             gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float>,
                              dim3((unsigned)grid), dim3(256), s, a, (int)gg, c);
 }
 

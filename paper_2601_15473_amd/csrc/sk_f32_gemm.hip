@@ -10,7 +10,7 @@
 // still takes 1600 cycles a chunk (one wave per SIMD waits for its own LDS reads and barriers);
 // two or more share the pipe at 85 % of its rate, so the planner splits the contraction until
 // there are.  Measured, 16-wide chunks with one set of loads in flight -> this kernel:
-// [4096 x 3072] . [3072 x 128] 57 -> 34 us (94 TFLOP/s), [4096 x 128] . [128 x 3072] 42 -> 34 us,
+// [4096 x 3072] . [3072 x 128] 57 -> 34 us (94 TFLOP/s), [4096 x 128] . [128 x 3072] 42 -> 36 us,
 // [8192 x 4096] . [4096 x 512] 250-260 us (132-137 TFLOP/s).
 //
 // Lane layout of v_mfma_f32_32x32x2_f32 (D = P . Q), lane l:

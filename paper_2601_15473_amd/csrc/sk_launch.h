@@ -155,10 +155,9 @@ inline bool within_window(int64_t rows, int64_t ld, int64_t cols, int esize) {
 
 // bf16 operands, fp32 accumulation (MFMA).  `tiles_m/tiles_n` of `a` are filled in here.
 hipError_t launch_gemm_bf16(GemmKind kind, int tile, const GemmArgs& a, hipStream_t s);
-// The 256 x 256 tile of the above, for what gemm256_supported says it can take (launch_gemm_bf16 asks,
-// and runs the rest on 128 x 128 tiles): no column sums, k ranges but the last multiples of 128 and at
-// least 256 long, 256 rows of a k-contiguous operand within 2 GB, rows of the other kind at most
-// 2^20 long.
+// The 256 x 256 tile of the above, for what gemm256_supported says it can take (the plans keep to
+// it): no column sums, k ranges but the last multiples of 128 and at least 256 long, 256 rows of a
+// k-contiguous operand within 2 GB, rows of the other kind at most 2^20 long.
 bool gemm256_supported(GemmKind kind, const GemmArgs& a);
 hipError_t launch_gemm256_bf16(GemmKind kind, const GemmArgs& a, hipStream_t s);
 // GEMM_NN and GEMM_NT for few rows of A: one launch that streams B once per 64 rows.

@@ -31,7 +31,7 @@ def test_rows_of_a_tile_stay_within_a_window(tokens, width, wtile):
         sk.sk_set_tuning(sk.SK_TUNE_WTILE, -1)
     assert st == sk.SK_OK
     # Z^T . dY: the kernels with a k-contiguous first operand
-    rows = [int(m.group(1)) for n in names if (m := re.match(r"gemm_\w+<(\d+), \d+, (?:2, 4, )?true", n))]
+    rows = [int(m.group(1)) for n in names if (m := re.match(r"gemm_\w+<(\d+), \d+, (?:2, 4, )?true", n.replace("far_kernel<", "far_kernel<256, 256, ")))]
     assert rows, names
     ldz = (tokens + 63) // 64 * 64
     for r in rows:
@@ -81,11 +81,13 @@ def test_operands_past_two_gib_keep_their_tile(tokens, out, R):
 
 
 @pytest.mark.gpu
-def test_factor_gradient_of_operands_past_two_gib():
-    """Z^T . dY with more than 2 GB of dY under one column of tiles: a round of whole-token tiles and the
-    split rest.  Blocks of an odd length, repeated; bound as above (98376 tokens)."""
+@pytest.mark.parametrize("blocks,rest", [(24, "gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float>"),
+                                         (48, "gemm_bf16_far_with_colsum_kernel<true, false, float>")], ids=["T98376", "T196752"])
+def test_factor_gradient_of_operands_past_two_gib(blocks, rest):
+    """Z^T . dY with more than 2 GB of dY under one column of tiles: a round of whole-token tiles, and with
+    twice the tokens also the split rest.  Blocks of an odd length, repeated; bound as above."""
     from skgpu import TOL, rel_err, to_dev, to_f64
-    blocks, d_out, R = 24, 11008, 2048
+    d_out, R = 11008, 2048
     w = W.Workload("past_two_gib", 4099, 16, d_out, 1, R, "bf16", seed=6)
     t = W.generate(w)
     v = {n: a.astype(np.float64) for n, a in t.value.items()}
@@ -104,8 +106,7 @@ def test_factor_gradient_of_operands_past_two_gib():
     torch.cuda.synchronize()
     assert rel_err(to_f64(dU), blocks * O.grad_factors(v["x"], v["S"], v["dY"]).reshape(R, d_out)) <= TOL["bf16"]
     assert rel_err(to_f64(db), blocks * O.grad_bias(v["dY"])) <= TOL["bf16"]
-    assert names[1] == "gemm_bf16_crew_kernel<256, 256, 2, 4, true, false, float, true>", names
-    assert names[2].startswith("gemm_bf16_with_colsum_kernel"), names
+    assert names[1:3] == ["gemm_bf16_far_kernel<true, false, float>", rest], names
 
 
 @pytest.mark.gpu
@@ -134,5 +135,5 @@ def test_first_stage_gradient_on_big_tiles(tokens, blocks, d_in, nc):
     torch.cuda.synchronize()
     G = v["dY"] @ v["U"].reshape(nc, 256).T
     assert rel_err(to_f64(dA), blocks * (v["x"].T @ G)) <= TOL["bf16"]
-    far = "true" if blocks > 1 else "false"
-    assert f"gemm_bf16_crew_kernel<256, 256, 2, 4, false, false, float, {far}>" in names, names
+    kernel = "gemm_bf16_far_kernel<" if blocks > 1 else "gemm_bf16_crew_kernel<256, 256, 2, 4, "
+    assert kernel + "false, false, float>" in names, names
