@@ -40,7 +40,8 @@ constexpr int GEMM256_LDS = STRIPS + 4 * 8192;    // all of a CU's LDS
 // The work of one work-group: tiles block, block + stride, ... below `total`.  `smem` must be the
 // kernel's only LDS (it then starts at LDS address 0), and the kernel's first argument a GemmArgs.
 // k ranges but the last are multiples of 128, at least 256 long; n_store is set.  FAR: for operands
-// that are not k-contiguous and span more than 2 GB of a tile's k range.
+// that are not k-contiguous and span more than 2 GB over a tile's k range, and bf16 results that do
+// over its rows.
 template <bool A_KC, bool B_KC, typename OutT, bool FAR>
 __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const int block, const int stride, const int total) {
   typedef Panels<A_KC> PA;
@@ -259,6 +260,8 @@ __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const i
     const float scale = q->scale;
     if constexpr (sizeof(OutT) == 2) {
       unsigned char* const strip = smem + STRIPS + wave * 8192;
+      // (far results, Z^T over millions of tokens: a window for every 32 rows, 256 of which pass 2 GB)
+      const GWindow all = make_window(q->C, (int64_t)here.m0 * q->ldc, (int64_t)q->M * q->ldc, 2);
       const unsigned ldc = (unsigned)q->ldc * 2u;
       uint2 bias[4][4];
 #pragma unroll
@@ -267,13 +270,13 @@ __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const i
         for (int e = 0; e < 4; ++e)
           bias[j][e] = *reinterpret_cast<const uint2*>(strip + (j * 32 + e * 8 + (el >> 5) * 4) * 2);
       const int gn = here.n0 + wn * 128 + (el & 15) * 8;
-      const unsigned at = gn < q->n_store ? (unsigned)(el >> 4) * ldc + (unsigned)gn * 2u : OOB_OFFSET;
+      const unsigned at = gn < q->n_store ? (unsigned)((FAR ? 0 : wm * 128) + (el >> 4)) * ldc + (unsigned)gn * 2u : OOB_OFFSET;
       unsigned char* const wr = strip + (el & 31) * 256;
       const unsigned char* const rd = strip + (el >> 4) * 256;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        // a window for every 32 rows: Z^T's are all tokens long, and 256 of them pass 2 GB
-        const GWindow out = make_window(q->C, (int64_t)(here.m0 + wm * 128 + i * 32) * q->ldc, (int64_t)q->M * q->ldc, 2);
+        GWindow out = all;
+        if constexpr (FAR) out = make_window(q->C, (int64_t)(here.m0 + wm * 128 + i * 32) * q->ldc, (int64_t)q->M * q->ldc, 2);
         // (the accumulators stay in their own registers until their block is due: copied out ahead
         // they crowd out what the next tile's main loop needs)
 #pragma unroll
@@ -306,7 +309,7 @@ __device__ __forceinline__ void gemm256_tiles(unsigned char* const smem, const i
           v[u] = *reinterpret_cast<const uint4*>(rd + u * 1024 + (((el & 15) ^ ((u * 4 + (el >> 4)) & 15)) * 16));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) window_store16(out, at + (unsigned)(u * 4) * ldc, v[u]);
+        for (int u = 0; u < 8; ++u) window_store16(out, at + (unsigned)((FAR ? 0 : i * 32) + u * 4) * ldc, v[u]);
       }
     } else {
       const GWindow out = make_window(q->C, ((int64_t)here.split * q->M + here.m0) * q->ldc, (int64_t)(here.split + 1) * q->M * q->ldc, 4);
@@ -426,18 +429,20 @@ bool gemm256_supported(GemmKind kind, const GemmArgs& a) {
   // ranges but the last: whole pairs of chunks (their zero chunks would be the next range's rows)
   if (a.splits > 1 && (a.k_per_split % 128 != 0 || a.k_per_split < 256)) return false;
   // byte offsets from a tile's origin are 32-bit: 256 rows of a k-contiguous operand, over the whole
-  // k range, a few chunks of the other kind (far_operands)
+  // k range, a few chunks of the other kind (is_far)
   const int64_t range = (int64_t)(a.splits > 1 ? a.k_per_split : a.K) + 512;
   if (!(a_kc ? within_window(256, a.lda, range, 2) : a.lda <= 1 << 20)) return false;
   if (!(b_kc ? within_window(256, a.ldb, range, 2) : a.ldb <= 1 << 20)) return false;
-  // ... and rows of the result: a window's 32 in bf16, all 256 in fp32
-  return within_window(f32 ? 256 : 32, a.ldc, a.n_store > 0 ? a.n_store : a.N, f32 ? 4 : 2);
+  // ... and rows of the result: all 256, or 32 where there is a variant for far ones
+  return within_window(f32 || (a_kc && b_kc) ? 256 : 32, a.ldc, a.n_store > 0 ? a.n_store : a.N, f32 ? 4 : 2);
 }
 
-// Whether an operand that is not k-contiguous spans more of a tile's k range than offsets reach.
-static bool far_operands(bool a_kc, bool b_kc, const GemmArgs& a) {
+// Whether an operand that is not k-contiguous spans more over a tile's k range than offsets reach, or the
+// result over its rows.
+static bool is_far(bool a_kc, bool b_kc, const GemmArgs& a, int osize) {
   const int64_t range = (int64_t)(a.splits > 1 ? a.k_per_split : a.K) + 512;
-  return (!a_kc && range * a.lda * 2 > 0x7fffffffLL) || (!b_kc && range * a.ldb * 2 > 0x7fffffffLL);
+  return (!a_kc && range * a.lda * 2 > 0x7fffffffLL) || (!b_kc && range * a.ldb * 2 > 0x7fffffffLL) ||
+         !within_window(256, a.ldc, a.n_store > 0 ? a.n_store : a.N, osize);
 }
 
 template <bool A_KC, bool B_KC, typename OutT>
@@ -452,7 +457,7 @@ static hipError_t launch_crew(GemmArgs a, hipStream_t s) {
   const dim3 grid((unsigned)(total < NUM_CUS ? total : NUM_CUS));
   const Work work = gemm_work(a, 2, sizeof(OutT), F32);
   if constexpr (!A_KC || !B_KC) {
-    if (far_operands(A_KC, B_KC, a)) {
+    if (is_far(A_KC, B_KC, a, sizeof(OutT))) {
       static const std::string far = kernel_label("gemm_bf16_far_kernel", {lbl(A_KC), lbl(B_KC), F32 ? "float" : "bf16"});
       return launch_kernel(far.c_str(), work, gemm_bf16_far_kernel<A_KC, B_KC, OutT>, grid, dim3(256), s, a, (int)total);
     }
@@ -490,7 +495,7 @@ hipError_t launch_gemm256_with_colsum(GemmArgs a, const void* in, float* out, in
   note_matrix(out, splits, cols, cols, 4, true);
   Work work = gemm_work(a, 2, 4, true);
   work.bytes += (double)rows * cols * 2 + (double)splits * cols * 4;
-  return far_operands(true, false, a)
+  return is_far(true, false, a, 4)
              ? launch_kernel("gemm_bf16_far_with_colsum_kernel<true, false, float>", work,
                              gemm_bf16_far_with_colsum_kernel<true, false, float>, dim3((unsigned)grid), dim3(256), s, a, (int)gg, c)
              : launch_kernel("gemm_bf16_with_colsum_kernel<256, 256, 2, 4, true, false, float>", work,

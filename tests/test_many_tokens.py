@@ -40,7 +40,7 @@ def test_rows_of_a_tile_stay_within_a_window(tokens, width, wtile):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("blocks,d_in,R,kernel", [
-    (1025, 144, 256, "gemm_bf16_crew_kernel<256, 256, 2, 4, false, true, bf16"),   # Z^T on 256 x 256 tiles
+    (1025, 144, 256, "gemm_bf16_far_kernel<false, true, bf16>"),   # Z^T on 256 x 256 tiles
     (2065, 16, 128, "gemm_bf16_kernel<64, 128, true, false, float, true>"),        # Z^T . dY past 8.4 million
 ], ids=["T4198400_R256", "T8458240_R128"])
 def test_factor_gradient_over_millions_of_tokens(blocks, d_in, R, kernel):
