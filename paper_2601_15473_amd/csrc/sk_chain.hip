@@ -278,7 +278,7 @@ constexpr int CS_BN = 128;
 // 32.8; 3072 wide, runs of 24 tiles, 103 -> 108).
 constexpr int chain_outs(int mb, int rt) { return mb == 128 && rt == 64 ? 1 : 2; }
 
-template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC>
+template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC, bool SHORT>
 struct SmallLds {
   typedef OpTile<CS_BN, B2_KC, RT> TB2;
   typedef OpTile<MB, true> TA;
@@ -286,7 +286,7 @@ struct SmallLds {
   static constexpr int Z_LD = RT + 8;
   static constexpr int Z_BYTES = MB * Z_LD * 2;
   // finished output tiles, over Zt (which is in registers by then), then the B2 tiles
-  static constexpr int OUTS = chain_outs(MB, RT);
+  static constexpr int OUTS = SHORT ? 0 : chain_outs(MB, RT);
   static constexpr int OUT_BYTES = MB * CS_BN * 2;
   static constexpr int HEAD_BYTES = Z_BYTES > OUTS * OUT_BYTES ? Z_BYTES : OUTS * OUT_BYTES;
   static constexpr int S2_BYTES = 2 * TB2::ELEMS * 2;
@@ -310,10 +310,11 @@ __device__ __forceinline__ void sched_stage2() {
   }
 }
 
-template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC>
-__global__ __launch_bounds__(256, chain_outs(MB, RT) == 1 ? 2 : 1) void chain_small_kernel(const ChainArgs p) {
+// SHORT: for runs of few output tiles, which leave straight from registers as they are finished.
+template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC, bool SHORT>
+__device__ __forceinline__ void chain_small(const ChainArgs& p) {
   static_assert(MB == 64 || MB == 128, "token tiles are 64 or 128 rows");
-  typedef SmallLds<MB, RT, B2_KC, FUSED, B1_KC> L;
+  typedef SmallLds<MB, RT, B2_KC, FUSED, B1_KC, SHORT> L;
   typedef typename L::TB2 TB2;
   constexpr int KS = RT / 16;
   constexpr int MT = MB / 32;   // 32-row blocks of the token tile (stage 2: all of them in every wave)
@@ -597,7 +598,7 @@ __global__ __launch_bounds__(256, chain_outs(MB, RT) == 1 ? 2 : 1) void chain_sm
   auto step = [&](int jt, const bf16* Bs, bf16* Bn, const uint2 (&bv)[4], uint2 (&bvn)[4],
                   uint4 (&rl)[TB2::PIECES], uint4 (&rs)[TB2::PIECES], const unsigned char* done, unsigned char* out) {
     uint4 leaving[ROWS_OUT];
-    tile_read(done, leaving);
+    if constexpr (!SHORT) tile_read(done, leaving);
     f32x16 acc[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -621,7 +622,7 @@ __global__ __launch_bounds__(256, chain_outs(MB, RT) == 1 ? 2 : 1) void chain_sm
       fb = fbn;
     });
     sched_stage2<KS, B2_KC ? 1 : 2, MT>();
-    tile_store(jt - 1, leaving);
+    if constexpr (!SHORT) tile_store(jt - 1, leaving);
     // A lane holds, per 8-column group q, the four columns 8 q + 4 (l / 32) .. +3 of its row;
     // exchanging the upper half-wave's part of an even group with the lower half-wave's part
     // of the odd group next to it (v_permlane32_swap) leaves every lane with eight
@@ -643,7 +644,13 @@ __global__ __launch_bounds__(256, chain_outs(MB, RT) == 1 ? 2 : 1) void chain_sm
         const u32x2 s0 = __builtin_amdgcn_permlane32_swap(w[0].x, w[1].x, false, false);
         const u32x2 s1 = __builtin_amdgcn_permlane32_swap(w[0].y, w[1].y, false, false);
         const int piece = wave * 4 + pr * 2 + (lane >> 5);
-        *reinterpret_cast<uint4*>(out + row * 256 + ((piece ^ (row & 15)) * 16)) = make_uint4(s0.x, s1.x, s0.y, s1.y);
+        const uint4 v = make_uint4(s0.x, s1.x, s0.y, s1.y);
+        if constexpr (SHORT) {
+          const int gn = (t_begin + jt) * CS_BN + piece * 8;
+          window_store16(out_w, gn < p.N ? ((unsigned)row * (unsigned)p.ldc + (unsigned)gn) * 2u : OOB_OFFSET, v);
+        } else {
+          *reinterpret_cast<uint4*>(out + row * 256 + ((piece ^ (row & 15)) * 16)) = v;
+        }
       }
     };
     if (L::OUTS == 1) __syncthreads();   // (everybody has read the tile before it)
@@ -653,7 +660,7 @@ __global__ __launch_bounds__(256, chain_outs(MB, RT) == 1 ? 2 : 1) void chain_sm
   };
 
   unsigned char* const out0 = smem;
-  unsigned char* const out1 = smem + (L::OUTS - 1) * L::OUT_BYTES;
+  unsigned char* const out1 = smem + (L::OUTS == 2 ? L::OUT_BYTES : 0);
   for (int jt = 0; jt < my_tiles; jt += 2) {
     // tile jt sits in buffer 0; set 1 holds tile jt + 1
     step(jt, Bbuf, Bbuf + TB2::ELEMS, bv0, bv1, rb0, rb1, out1, out0);
@@ -661,9 +668,19 @@ __global__ __launch_bounds__(256, chain_outs(MB, RT) == 1 ? 2 : 1) void chain_sm
     // R = 128, forward 11.4 us with it, 10.8 without)
     if (jt + 1 < my_tiles) step(jt + 1, Bbuf + TB2::ELEMS, Bbuf, bv1, bv0, rb1, rb0, out0, out1);
   }
-  uint4 leaving[ROWS_OUT];
-  tile_read(my_tiles & 1 ? out0 : out1, leaving);
-  tile_store(my_tiles - 1, leaving);
+  if constexpr (!SHORT) {
+    uint4 leaving[ROWS_OUT];
+    tile_read(my_tiles & 1 ? out0 : out1, leaving);
+    tile_store(my_tiles - 1, leaving);
+  }
+}
+template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC>
+__global__ __launch_bounds__(256, chain_outs(MB, RT) == 1 ? 2 : 1) void chain_small_kernel(const ChainArgs p) {
+  chain_small<MB, RT, B2_KC, FUSED, B1_KC, false>(p);
+}
+template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC>
+__global__ __launch_bounds__(256) void chain_short_kernel(const ChainArgs p) {
+  chain_small<MB, RT, B2_KC, FUSED, B1_KC, true>(p);
 }
 
 bool chain_supported(int R) { return R >= 16 && R <= 512; }
@@ -695,6 +712,20 @@ template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC>
 static hipError_t launch_small_mb(const ChainArgs& a, hipStream_t s) {
   const long long grid = (long long)a.tiles_m * a.n_slices;
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  // Runs of up to three tiles (two of 128 rows) are over before whole rows pay for the trip through LDS, the
+  // barrier behind the last tile and the room for them, us, through LDS : straight: [9007 x 144] -> 208, R = 112,
+  // runs of 2, 8.2 : 7.8; [84448 x 64] -> 176, R = 48, runs of 2 of 128 rows, 17.1 : 15.7; [2048 x 768] -> 768,
+  // R = 128, runs of 1, 10.9 : 10.8; [40000 x 384] -> 384, R = 32, runs of 3 of 128 rows, 17.6 : 18.2; [4096 x 1024] ->
+  // 2048, R = 64, runs of 4, 13.9 : 14.2; [30000 x 768] -> 768, R = 64, runs of 6, 19.3 : 20.6.
+  // A lone token tile has next to nothing to store beside the weights it reads ([1 x 528] -> 131072, R = 128,
+  // runs of 4, 13.5 : 12.4).
+  const int run = ((a.N + CS_BN - 1) / CS_BN + a.n_slices - 1) / a.n_slices;
+  if (run <= (MB == 64 ? 3 : 2) || a.tiles_m == 1) {
+    static const std::string brief =
+        kernel_label("chain_short_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC)});
+    return launch_kernel(brief.c_str(), chain_work(a, FUSED), chain_short_kernel<MB, RT, B2_KC, FUSED, B1_KC>, dim3((unsigned)grid),
+                         dim3(256), s, a);
+  }
   static const std::string name =
       kernel_label("chain_small_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC)});
   return launch_kernel(name.c_str(), chain_work(a, FUSED), chain_small_kernel<MB, RT, B2_KC, FUSED, B1_KC>, dim3((unsigned)grid),
