@@ -223,7 +223,9 @@ struct FirstPlan {
 // choice.  Up to 64 rows it wins everywhere (one kernel each, us, against the tiles: [8 x 2048] .
 // [2048 x 11008] 12 : 15, [64 x 1024] . [1024 x 512] 4.5 : 8); above, every 64 rows stream B again,
 // and it wins while that is less than a round of short work-groups ([131 x 768] . [768 x 128] 4 : 7,
-// [128 x 384] . [384 x 8192] level, [512 x 512] . [512 x 4096] 11 : 8).  Its columns lie a row of B apart,
+// [128 x 384] . [384 x 8192] level, [512 x 512] . [512 x 4096] 11 : 8).  An expansion wide enough for more
+// rounds pays each round's start (a work-group takes a CU's LDS): calls with 528 in and 32768 out, R = 16,
+// 8.6 : 8.9 at 32 tokens, 8.4 : 7.7 at 8, 131072 out 10.8 : 22.0 and 9.8 : 17.2.  Its columns lie a row of B apart,
 // which for a power-of-two row is one L2 channel an XCD: past K = 3072 a first contraction gives each
 // XCD a k range instead ([8 x 4096] . [4096 x 2048] 17.5 us in one range, 6.6 + 4 for the sum in eight).
 int few_rows_splits(int64_t M, int64_t N, int64_t K, bool first) {
@@ -232,6 +234,7 @@ int few_rows_splits(int64_t M, int64_t N, int64_t K, bool first) {
   int splits = first && K > 3072 ? 8 : 1;
   while (splits > 1 && M <= 64 && tiles * splits > NUM_CUS) splits /= 2;
   if (M > 64 && (tiles > 160 || tiles * splits > NUM_CUS || tiles * K / 64 / splits > 1024)) return 0;
+  if (!first && tiles > (M > 16 ? 1 : 2) * NUM_CUS) return 0;
   return splits;
 }
 
@@ -523,11 +526,22 @@ Plan pick_plan(const Shape& s, sk_op op, bool workspace) {
   // contraction is split over its length instead and the expansion sums the slabs.
   const int64_t k1 = op == SK_OP_FWD ? s.in : s.out;
   const int64_t n2 = op == SK_OP_FWD ? s.out : s.in;
-  // Few tokens: two launches of the few-rows kernel beat even the single fused one ([8 x 768] -> 768,
-  // R = 32: 6.6 us against 8.1; [131 x 768] -> 3072, R = 128: 8.4 against 11.8 split), which stays for
-  // callers without a workspace.
-  if (s.dtype == SK_BF16 && workspace && few_rows_splits(s.T, s.R, k1, true) > 0 && few_rows_splits(s.T, n2, s.R, false) > 0)
-    return PLAN_TWO_GEMM;
+  // Few tokens: two launches of the few-rows kernel beat the single fused one past a short first
+  // contraction ([8 x 768] -> 768, R = 32: 6.6 us against 8.1; [131 x 768] -> 3072, R = 128: 8.4 against
+  // 11.8 split), which stays for callers without a workspace.  A walk of the fused kernel takes two chunks
+  // at a time, 0.65 us (forward) or 0.55 each up to R = 64, 0.85 or 0.7 above, on top of 4.1 to 5 us; the two
+  // launches take 6.2 to 7 us whatever they do.  1 to 256 tokens, 64 to 8192 wide, fused : few rows: K = 128
+  // 4.7-5.7 : 6.2-7.8, K = 384, R = 32, 5.9-6.2 : 6.2-7.1, K = 512 the forward of 1 to 16 tokens 6.6-6.9 : 6.2
+  // and the rest 6.2-7.3 : 6.7-8.3, K = 640 level but for the gradient past 32 tokens, 6.8-7.9 : 7.1-8.7; R = 128, K = 256 6.2-7.5 : 6.9-8.1, K = 384 7.0-8.5 : 6.9-8.5.
+  if (s.dtype == SK_BF16 && workspace && few_rows_splits(s.T, s.R, k1, true) > 0 && few_rows_splits(s.T, n2, s.R, false) > 0) {
+    const int64_t walk = (k1 + 127) / 128;
+    const bool brief = s.R > 64 ? walk <= 2 : walk <= 3 + (op != SK_OP_FWD) + (s.T > 32);
+    if (s.R <= 128 && brief) return PLAN_FUSED;
+    // Past 32 tokens a narrow sketch's first launch, one work-group per 64 rows, takes 1.9 us per 1000 of
+    // the contraction: beyond 1792 the split sketch is ahead (42 tokens, 672 out, R = 16: K = 1536 9.2 split :
+    // 8.8, 2048 9.2 : 9.6, 2944 9.8 : 11.3, 4096 10.5 : 11.4), where the chain plans would take it.
+    if (s.R > 64 || s.T <= 32 || k1 <= 1792 || k1 * chain_shape(s.T, n2, s.R, false).slices <= 6144) return PLAN_TWO_GEMM;
+  }
   if (chain_ok && s.R <= 128) {
     return k1 * chain_shape(s.T, n2, s.R, false).slices <= 6144 ? PLAN_FUSED : PLAN_SPLIT_EXPAND;
   }

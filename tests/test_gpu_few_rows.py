@@ -31,7 +31,7 @@ def test_few_rows(sk, shape, fwd_ranges, bwd_ranges):  # noqa: F811
     # bound: the repository's bf16 bar (the intermediate and the result rounded to 8 bits once each)
     T, d_in, d_out, l, k = shape
     w = W.Workload("few_rows", T, d_in, d_out, l, k, "bf16", seed=90 + T)
-    sk.sk_set_plan(0)
+    sk.sk_set_plan(2)   # (by itself the planner fuses the shortest of these)
     dev = DeviceLayer(W.generate(w), sk)
     for call, ranges, second in (("fwd", fwd_ranges, d_out), ("bwd_input", bwd_ranges, d_in)):
         tiles = [(T + 63) // 64 * ((n + 63) // 64) for n in (l * k, second)]
@@ -45,6 +45,7 @@ def test_few_rows(sk, shape, fwd_ranges, bwd_ranges):  # noqa: F811
     assert len([n for n in names if "few_rows" in n]) == 4, names
     check_all(sk, w, 0, single_call=True)
     check_all(sk, w, 0, with_bias=False)
+    check_all(sk, w, 2)
     # bit for bit from run to run
     y, dX = dev.y.clone(), dev.dX.clone()
     for t in (dev.y, dev.dX, dev.ws):

@@ -24,7 +24,22 @@ def _kernels(call, *shape):
     return names
 
 
+FEW = ["few_rows", "few_rows"]
+RANGES = ["few_rows", "reduce_to_bf16", "few_rows"]
+
+
 @pytest.mark.parametrize("call,shape,want", [
+    # few tokens, short first contraction (tokens, in, out, R): one fused launch
+    ("fwd", (8, 128, 768, 32), ["chain_short"]), ("fwd", (32, 384, 768, 64), ["chain_short"]), ("fwd", (32, 400, 768, 64), FEW),
+    ("fwd", (64, 512, 768, 64), ["chain_short"]), ("fwd", (64, 528, 768, 64), FEW), ("fwd", (8, 256, 768, 128), ["chain_short"]),
+    ("fwd", (8, 272, 768, 128), FEW), ("bwd_input", (8, 768, 512, 32), ["chain_short"]), ("bwd_input", (8, 768, 528, 32), FEW),
+    ("bwd_input", (64, 768, 640, 32), ["chain_short"]), ("bwd_input", (64, 768, 656, 32), FEW),
+    # ... past 32 tokens a narrow sketch of a long input is split
+    ("fwd", (32, 2944, 672, 16), FEW), ("fwd", (33, 1792, 672, 64), FEW), ("fwd", (33, 1808, 672, 64), ["kernel", "chain_short"]),
+    ("fwd", (33, 1808, 672, 80), FEW), ("fwd", (200, 4096, 672, 16), ["kernel", "chain_short"]), ("fwd", (33, 4096, 64, 16), RANGES),
+    # ... and an expansion of more than a round of work-groups is not theirs
+    ("fwd", (16, 1024, 32768, 16), FEW), ("fwd", (17, 1024, 32768, 16), ["kernel", "chain_short"]),
+    ("fwd", (64, 1024, 16384, 256), FEW), ("fwd", (64, 1024, 16400, 256), ["few_rows", "kernel"]),
     # runs of output tiles
     ("fwd", (2048, 768, 768, 128), ["chain_short"]), ("fwd", (4096, 768, 3072, 128), ["chain_small"]),
     ("fwd", (16384, 384, 384, 128), ["chain_short"]), ("fwd", (16384, 384, 512, 128), ["chain_small"]),
