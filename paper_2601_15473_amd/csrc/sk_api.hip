@@ -129,16 +129,21 @@ size_t slab_room(size_t z_bytes) {
 // 49 against 60), 128 do not (K = 512: 19.5 against 16.3), and one more than a round has no use for
 // them.  Otherwise the largest tile that still gives every CU a work-group without being mostly
 // padding, the smallest when the problem cannot fill the chip.
+double big_tiles_us(int64_t M, int64_t N, double k, int splits) {
+  const int64_t big = ((M + 255) / 256) * ((N + 255) / 256) * splits;
+  return 6.0 + (double)((big + NUM_CUS - 1) / NUM_CUS) * (6.0 + 0.0215 * k);
+}
+int64_t small_tiles(int64_t M, int64_t N) { return ((M + 127) / 128) * ((N + 127) / 128); }
+double small_tiles_us(int64_t tiles, double k) {
+  const double halves = (double)((tiles + NUM_CUS - 1) / NUM_CUS);   // half rounds: one work-group per CU
+  return 5.0 + (halves < 2 ? 2 : halves) / 2 * (4.2 + 0.0165 * k);
+}
 int choose_tile(int64_t M, int64_t N, int64_t K, int splits) {
   if (const int t = forced_tile(SK_TUNE_TILE); t >= 0) return t;  // forced (tests, sweeps)
   const int64_t m_cap = (M + 63) / 64 * 64, n_cap = (N + 63) / 64 * 64;
   if (K / splits > 128 && m_cap >= 256 && n_cap >= 256) {
-    const int64_t big = ((M + 255) / 256) * ((N + 255) / 256) * splits;
-    const int64_t small = ((M + 127) / 128) * ((N + 127) / 128) * splits;
-    const double rounds = (double)((big + NUM_CUS - 1) / NUM_CUS);
-    const double halves = (double)((small + NUM_CUS - 1) / NUM_CUS);   // half rounds: one work-group per CU
     const double k = (double)K / splits;
-    if (6.0 + rounds * (6.0 + 0.0215 * k) < 5.0 + (halves < 2 ? 2 : halves) / 2 * (4.2 + 0.0165 * k)) return TILE_256x256;
+    if (big_tiles_us(M, N, k, splits) < small_tiles_us(small_tiles(M, N) * splits, k)) return TILE_256x256;
   }
   static const int order[] = {TILE_128x128, TILE_128x64, TILE_64x128, TILE_64x64};
   for (int i = 0; i < (int)(sizeof(order) / sizeof(order[0])); ++i) {
@@ -1109,7 +1114,7 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
   const bool bf16_auto = s.dtype == SK_BF16 && g_plan.load(std::memory_order_relaxed) == PLAN_AUTO &&
                          !w.own_colsum && w.z_splits == 1;
   const Plan in_plan = pick_plan(s, SK_OP_BWD_INPUT, true);
-  const int z_tile = bf16_auto ? choose_tile(s.R, tokens, in, 1) : -1;
+  int z_tile = bf16_auto ? choose_tile(s.R, tokens, in, 1) : -1;
   const GemmKind du_kind = GEMM_NN_F32_COLSUM;
 
   void* Z = ws_w;
@@ -1155,7 +1160,20 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
   }
 
   // --- wide sketch (two GEMMs per gradient): dY.U^T beside Z^T | Z^T.dY beside G.S^T | sums ---
-  const int g_tile = bf16_auto ? choose_tile(tokens, s.R, out, 1) : -1;
+  int g_tile = bf16_auto ? choose_tile(tokens, s.R, out, 1) : -1;
+  // Nor do the first two share a launch on that tile: where it is faster by itself they go beside each
+  // other on 128 x 128 tiles unless the two launches are modelled 3 us ahead, which sorts all of 20 shapes
+  // measured ([12288 x 768 -> 768], R = 768, 89 us shared : 103; [33222 x 208 -> 48], R = 544, 71 : 82;
+  // [12288 x 4096 -> 1024], R = 1024, 306 : 266; [32768 x 1024 -> 1024], R = 512, 187 : 171, R = 384, 147 : 150).
+  auto square = [](int t) { return t == TILE_256x256 || t == TILE_128x128; };
+  if (square(g_tile) && square(z_tile) && g_tile + z_tile != 2 * TILE_128x128) {
+    auto alone = [&](int t, int64_t M, int64_t N, double k) {
+      return t == TILE_256x256 ? big_tiles_us(M, N, k, 1) : small_tiles_us(small_tiles(M, N), k);
+    };
+    const double apart = alone(g_tile, tokens, s.R, (double)out) + alone(z_tile, s.R, tokens, (double)in);
+    if (apart + 3.0 > small_tiles_us(2 * small_tiles(tokens, s.R), 0.5 * (double)(in + out)))
+      g_tile = z_tile = TILE_128x128;
+  }
   int dx_tile = bf16_auto ? choose_tile(tokens, in, s.R, 1) : -1;
   // beside Z^T.dY the expansion of dX runs on 128 x 128 tiles even where it would take the
   // 256 x 256 tile on its own: that one takes all of a CU's LDS and leaves no room to share.  Shared

@@ -44,6 +44,10 @@ RANGES = ["few_rows", "reduce_to_bf16", "few_rows"]
     ("fwd", (2048, 768, 768, 128), ["chain_short"]), ("fwd", (4096, 768, 3072, 128), ["chain_small"]),
     ("fwd", (16384, 384, 384, 128), ["chain_short"]), ("fwd", (16384, 384, 512, 128), ["chain_small"]),
     ("fwd", (40000, 384, 256, 32), ["chain_short"]), ("fwd", (40000, 384, 384, 32), ["chain_small"]),
+    # wide sketches: the first two contractions beside each other, or alone on 256 x 256 tiles
+    ("bwd", (12288, 768, 768, 768), ["dual_gemm", "dual_gemm", "reduce_splits"]),
+    ("bwd", (33222, 208, 48, 544), ["dual_gemm", "dual_gemm", "reduce_splits"]),
+    ("bwd", (12288, 4096, 1024, 1024), ["crew", "crew", "crew", "kernel", "reduce_splits"]),
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v if isinstance(v, str) else "")
 def test_kernels_on_either_side(call, shape, want):
     got = _kernels(call, *shape)
