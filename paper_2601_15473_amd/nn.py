@@ -75,18 +75,21 @@ def _stream(device: torch.device) -> int:
     return torch._C._cuda_getCurrentRawStream(device.index)
 
 
-def _in_type(grads32: torch.Tensor, dtype: torch.dtype, *shapes):
-    """The fp32 gradients that lie one behind the other in ``grads32`` (from its start; it may hold
-    more), in the layer's type: one launch for all of them.  Each is a tensor of its own, since the
+def _in_type(grads32, dtype: torch.dtype, *shapes):
+    """fp32 gradients (None: not wanted) in the layer's type, in one launch; with ``shapes``, one tensor
+    that holds them one behind the other from its start.  Each result is a tensor of its own, since the
     caller's program may change, keep or save any of them by itself."""
-    sizes = [math.prod(s) for s in shapes]
-    rest = grads32.numel() - sum(sizes)
-    parts = [t.view(s) for t, s in zip(grads32.split(sizes + [rest] if rest else sizes), shapes)]
-    if len(parts) == 1:
-        return [parts[0].to(dtype)]
-    out = [torch.empty(s, dtype=dtype, device=grads32.device) for s in shapes]
-    torch._foreach_copy_(out, parts)
-    return out
+    if shapes:
+        sizes = [math.prod(s) for s in shapes]
+        grads32 = [t.view(s) for t, s in zip(grads32[:sum(sizes)].split(sizes), shapes)]
+    wanted = [g for g in grads32 if g is not None]
+    if len(wanted) > 1:
+        out = [torch.empty(g.shape, dtype=dtype, device=g.device) for g in wanted]
+        torch._foreach_copy_(out, wanted)
+    else:
+        out = [g.to(dtype) for g in wanted]
+    out.reverse()
+    return [None if g is None else out.pop() for g in grads32]
 
 
 class SKLinearFunction(torch.autograd.Function):
@@ -138,32 +141,21 @@ class SKLinearFunction(torch.autograd.Function):
             if need_dx:
                 dX = torch.empty((tokens, d_in), dtype=dtype, device=dY.device)
             if want_w:
-                R = l * k
-                if dtype == torch.float32:
-                    dU32 = torch.empty((R, d_out), dtype=dtype, device=dY.device)
-                    db32 = torch.empty((d_out,), dtype=dtype, device=dY.device) if ctx.has_bias else None
-                else:
-                    g32 = torch.empty((R + ctx.has_bias) * d_out, dtype=torch.float32, device=dY.device)
-                    dU32, db32 = g32, g32.data_ptr() + R * d_out * 4 if ctx.has_bias else None
+                dU = torch.empty((l * k, d_out), dtype=torch.float32, device=dY.device)
+                db = torch.empty((d_out,), dtype=torch.float32, device=dY.device) if ctx.has_bias else None
             if need_dx and want_w:      # both gradients from one call (its kernels share launches)
-                sk.check(sk.sk_linear_bwd(x2, dY2, S_cat, U_cat, dX, dU32, db32, *ctx.args,
+                sk.check(sk.sk_linear_bwd(x2, dY2, S_cat, U_cat, dX, dU, db, *ctx.args,
                                           ws, ws.numel(), stream))
             elif need_dx:
                 sk.check(sk.sk_linear_bwd_input(dY2, S_cat, U_cat, dX, *ctx.args, ws, ws.numel(), stream))
             elif want_w:
-                sk.check(sk.sk_linear_bwd_weight(x2, S_cat, dY2, dU32, db32, *ctx.args, ws, ws.numel(), stream))
+                sk.check(sk.sk_linear_bwd_weight(x2, S_cat, dY2, dU, db, *ctx.args, ws, ws.numel(), stream))
             if need_dx and dX.shape != ctx.x_shape:
                 dX = dX.reshape(ctx.x_shape)
             if want_w:
-                need_db = need_db and ctx.has_bias
-                if dtype == torch.float32:
-                    dU, db = dU32 if need_du else None, db32 if need_db else None
-                elif need_du and need_db:
-                    dU, db = _in_type(g32, dtype, (R, d_out), (d_out,))
-                elif need_du:
-                    dU, = _in_type(g32, dtype, (R, d_out))
-                else:
-                    db, = _in_type(g32[R * d_out:], dtype, (d_out,))
+                dU, db = dU if need_du else None, db if need_db else None
+                if dtype != torch.float32:
+                    dU, db = _in_type((dU, db), dtype)
         return dX, None, dU, db, None, None
 
 
@@ -290,26 +282,15 @@ class SKLinearTwoSidedFunction(torch.autograd.Function):
                        sk.sk_linear_workspace_bytes(sk.SK_OP_BWD_WEIGHT_FIRST, tokens, d_in, d_out, l2 // 2, k, dt))
             ws = _workspace(dev, stream, need)
             dX = torch.empty((tokens, d_in), dtype=dtype, device=dev)
-            if dtype == torch.float32:
-                db = torch.empty((d_out,), dtype=dtype, device=dev) if ctx.has_bias else None
-                dA = torch.empty((d_in, half), dtype=dtype, device=dev)
-                dB = torch.empty((2 * half, d_out), dtype=dtype, device=dev)
-            else:
-                # dB last: its rows from `half` on belong to S2^T, gradients of fixed numbers that are
-                # dropped, and what lies before them is converted in one go
-                n_db = d_out if ctx.has_bias else 0
-                g32 = torch.empty(n_db + d_in * half + 2 * half * d_out, dtype=torch.float32, device=dev)
-                db, dA = g32 if ctx.has_bias else None, g32.data_ptr() + n_db * 4
-                dB = dA + d_in * half * 4
+            db = torch.empty((d_out,), dtype=torch.float32, device=dev) if ctx.has_bias else None
+            dA = torch.empty((d_in, half), dtype=torch.float32, device=dev)
+            dB = torch.empty((2 * half, d_out), dtype=torch.float32, device=dev)
             sk.check(sk.sk_linear_bwd(x2, dY2, A_cat, B_cat, dX, dB, db, *ctx.args, ws, ws.numel(), stream))
             sk.check(sk.sk_linear_bwd_weight_first(x2, B_cat, dY2, dA, tokens, d_in, d_out, l2, k,
                                                    half, half, dt, ws, ws.numel(), stream))
-            if dtype == torch.float32:
-                dB = dB[:half]
-            elif ctx.has_bias:
-                db, dA, dB = _in_type(g32, dtype, (d_out,), (d_in, half), (half, d_out))
-            else:
-                dA, dB = _in_type(g32, dtype, (d_in, half), (half, d_out))
+            dB = dB[:half]   # (the rest belongs to S2^T: gradients of fixed numbers, dropped)
+            if dtype != torch.float32:
+                db, dA, dB = _in_type((db, dA, dB), dtype)
         return (dX if dX.shape == ctx.x_shape else dX.reshape(ctx.x_shape), None, dB, dA, None,
                 db, None, None, None)
 
