@@ -304,11 +304,19 @@ struct WeightPlan {
   int z_tile;          // bf16: tile of the GEMM that recomputes Z^T
   int z_splits;        // split of that GEMM over `in` (fp32 slabs, summed into bf16 Z^T)
   int z_k_per_split;
-  // workspace: Z | then either the slabs of Z (dead once summed) or the slabs of dU and db
+  // workspace: Z | slabs of dU | of db | of Z, while that fits the fixed scratch of
+  // sk_linear_bwd_weight_noalloc; past it the slabs of Z, dead once summed, share the room of the
+  // others.  Z^T . dY writing into lines that the sum before it has just read takes up to 2 us longer:
+  // [2275 x 4800 -> 1040], R = 272, 35.3 us shared, 33.5 apart; [4096 x 8192 -> 1024], R = 128, 34.0, 32.2.
+  // With more than 32 MiB in all (the L2s' 8 x 4 MiB) thirteen shapes measured the same either way.
   size_t z_bytes, part_bytes, csum_bytes, zpart_bytes;
+  size_t zpart_at() const {
+    const size_t behind = z_bytes + part_bytes + csum_bytes;
+    return behind + zpart_bytes <= SK_NOALLOC_SCRATCH_BYTES ? behind : z_bytes;
+  }
   size_t total() const {
-    const size_t du = part_bytes + csum_bytes;
-    return z_bytes + (du > zpart_bytes ? du : zpart_bytes);
+    const size_t du_end = z_bytes + part_bytes + csum_bytes, z_end = zpart_at() + zpart_bytes;
+    return du_end > z_end ? du_end : z_end;
   }
 };
 
@@ -960,7 +968,7 @@ sk_status sk_linear_bwd_weight(const void* x, const void* S_cat, const void* dY,
     GemmArgs z = dense_args(S_cat, s.R, x, in, Z, w.ldz, s.R, tokens, in, 1.0f, nullptr);
     z.n_store = (int)w.ldz;
     if (w.z_splits > 1) {
-      float* zpart = reinterpret_cast<float*>(ws + w.z_bytes);
+      float* zpart = reinterpret_cast<float*>(ws + w.zpart_at());
       z.C = zpart; z.splits = w.z_splits; z.k_per_split = w.z_k_per_split;
       e = launch_gemm_bf16(GEMM_TT_F32, w.z_tile, z, hs);
       if (e == hipSuccess) e = launch_reduce_to_bf16(zpart, Z, (int64_t)s.R * w.ldz, w.z_splits, hs);
@@ -970,7 +978,7 @@ sk_status sk_linear_bwd_weight(const void* x, const void* S_cat, const void* dY,
     a.A = Z; a.lda = w.ldz;
   } else {
     e = first_gemm(s, GEMM_NN, GEMM_NN_F32, dense_args(x, in, S_cat, s.R, Z, s.R, tokens, s.R, in, 1.0f, nullptr),
-                   ws + w.z_bytes, hs, slab_room(w.z_bytes));
+                   ws + w.zpart_at(), hs, slab_room(w.z_bytes));
     a.A = Z; a.lda = s.R;
   }
   if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd_weight (x.S)");

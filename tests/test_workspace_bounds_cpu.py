@@ -216,6 +216,34 @@ def test_first_stage_query_for_fewer_columns_serves_any_range_of_them(shape, dty
         assert all(a + n <= 5 * P + need for a, n, _, _ in trace if a >= 5 * P)
 
 
+@pytest.mark.parametrize("shape", [
+    (2275, 4800, 1040, 1, 272, sk.SK_BF16), (4096, 8192, 1024, 2, 64, sk.SK_BF16), (1000, 4096, 768, 1, 64, sk.SK_F32),
+    (4096, 3072, 768, 2, 64, sk.SK_F32), (8626, 3856, 8976, 1, 208, sk.SK_BF16), (7928, 9424, 96, 1, 336, sk.SK_BF16),
+    (12630, 2688, 11152, 1, 80, sk.SK_F32)], ids=lambda s: "T%d_%dx%d_l%dk%d_%d" % s)
+def test_factor_gradient_slabs_lie_apart_while_they_fit_the_fixed_scratch(shape):
+    """The slabs of a split Z and those of dU and db: each in room of its own up to 32 MiB in all (a
+    kernel that writes lines another has just read is slower), in shared room past that -- and never
+    apart where that alone would take a shape out of the fixed scratch."""
+    B = Buffers(*shape, 16).base
+    need = sk.sk_linear_workspace_bytes(sk.SK_OP_BWD_WEIGHT, *shape)
+    sk.sk_trace_begin()
+    try:
+        st = sk.sk_linear_bwd_weight(B["x"], B["S"], B["dY"], B["dU"], B["db"], *shape, B["ws"], need)
+    finally:
+        trace, launches = sk.sk_trace_end()
+    assert st == sk.SK_OK and launches == 4, (st, launches)   # slabs of Z, their sum, slabs of dU and db, their sum
+    e = 2 if shape[-1] == sk.SK_BF16 else 4
+    spans = [{(a, a + n) for a, n, w, i in trace if w and a >= B["ws"] and i == k} for k in range(3)]
+    (z_slabs,), (z,), du_slabs = spans
+    assert z[0] == B["ws"] and z[1] - z[0] >= shape[0] * shape[3] * shape[4] * e
+    up = lambda n: (n + 255) // 256 * 256
+    apart = sum(up(b - a) for a, b in (z, z_slabs, *du_slabs))
+    overlap = any(a < z_slabs[1] and z_slabs[0] < b for a, b in du_slabs)
+    assert overlap == (apart > 32 << 20), (z, z_slabs, du_slabs)
+    if not overlap:
+        assert need <= 32 << 20
+
+
 def test_trace_mode_launches_nothing_and_ends_cleanly():
     sk.sk_trace_begin()
     st = sk.sk_linear_fwd(0x1000, 0x2000, 0x3000, None, 0x4000, 64, 64, 64, 1, 16, sk.SK_BF16, None, 0)
