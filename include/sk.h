@@ -145,6 +145,8 @@ sk_status sk_linear_bwd_weight_noalloc(const void* x, const void* S_cat, const v
  *     order -- two launches, dY read once.  dU_cat and dbias then differ from the
  *     separate call's in the order of their fp32 partial sums (they remain
  *     bit-reproducible from run to run).
+ *   - fp32: dY . U_cat^T shares a launch with x . S_cat, and the expansion of dX one with the
+ *     factor gradient.
  *   - Other shapes run the two gradients one after the other.
  *   x [tokens, in], dY [tokens, out], S_cat [in, R], U_cat [R, out],
  *   dX [tokens, in] (output), dU_cat [R, out] fp32 (output), dbias [out] fp32 (output) or NULL.

@@ -742,6 +742,61 @@ GemmArgs dense_args(const void* A, int64_t lda, const void* B, int64_t ldb, void
   return a;
 }
 
+
+// Two fp32 products of the backward pass in one launch where both take the same tile, else in two.
+hipError_t gemm_pair_f32(GemmKind kind_a, int tile_a, const GemmArgs& a, GemmKind kind_b, int tile_b, const GemmArgs& b, hipStream_t st) {
+  if (tile_a == tile_b) return launch_dual_gemm_f32(kind_a, a, kind_b, b, tile_a, st);
+  const hipError_t e = launch_gemm_f32(kind_a, tile_a, a, st);
+  return e != hipSuccess ? e : launch_gemm_f32(kind_b, tile_b, b, st);
+}
+
+// sk_linear_bwd in fp32 (workspaces laid out as those of the two separate calls).
+sk_status bwd_f32(const Shape& s, const void* x, const void* dY, const void* S_cat, const void* U_cat, void* dX, float* dU_cat,
+                  float* dbias, unsigned char* ws_in, unsigned char* ws_w, hipStream_t hs) {
+  g_hip_error.clear();
+  const float scale = 1.0f / (float)s.l;
+  const WeightPlan w = plan_weight(s);
+  const F32Plan gp = plan_f32_first(s.T, s.R, s.out), zp = plan_f32_first(s.T, s.R, s.in, slab_room(w.z_bytes));
+  float* const G = reinterpret_cast<float*>(ws_in);
+  float* const g_slabs = reinterpret_cast<float*>(ws_in + align_up((size_t)s.T * s.R * 4));
+  float* const Z = reinterpret_cast<float*>(ws_w);
+  float* const z_slabs = reinterpret_cast<float*>(ws_w + w.zpart_at());
+  float* const part = reinterpret_cast<float*>(ws_w + w.z_bytes);
+  float* const cpart = reinterpret_cast<float*>(ws_w + w.z_bytes + w.part_bytes);
+
+  GemmArgs g = dense_args(dY, s.out, U_cat, s.out, gp.splits > 1 ? g_slabs : G, s.R, s.T, s.R, s.out, 1.0f, nullptr);
+  g.splits = gp.splits; g.k_per_split = gp.k_per_split;
+  GemmArgs z = dense_args(x, s.in, S_cat, s.R, zp.splits > 1 ? z_slabs : Z, s.R, s.T, s.R, s.in, 1.0f, nullptr);
+  z.splits = zp.splits; z.k_per_split = zp.k_per_split;
+  hipError_t e = gemm_pair_f32(GEMM_NT, gp.tile, g, GEMM_NN, zp.tile, z, hs);
+  if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (dY.U^T beside x.S)");
+  if (gp.splits > 1 || zp.splits > 1) {
+    const int64_t n = s.T * s.R;
+    ReduceArgs r{};
+    r.part = g_slabs; r.out = G; r.n = gp.splits > 1 ? n : 0; r.splits = gp.splits; r.scale = 1.0f;
+    r.part2 = z_slabs; r.out2 = Z; r.n2 = zp.splits > 1 ? n : 0; r.splits2 = zp.splits; r.scale2 = 1.0f;
+    e = launch_reduce_splits(r, hs);
+    if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (sums of G and Z)");
+  }
+  GemmArgs du{};
+  du.A = Z; du.lda = s.R; du.B = dY; du.ldb = s.out; du.ldc = s.out;
+  du.M = s.R; du.N = (int)s.out; du.K = (int)s.T;
+  du.splits = w.splits; du.k_per_split = w.k_per_split;
+  if (w.splits == 1) { du.C = dU_cat; du.colsum = dbias; du.scale = scale; }
+  else { du.C = part; du.colsum = dbias ? cpart : nullptr; du.scale = 1.0f; }
+  const GemmArgs dx = dense_args(G, s.R, S_cat, s.R, dX, s.in, s.T, s.in, s.R, scale, nullptr);
+  e = gemm_pair_f32(GEMM_TN_F32, w.tile, du, GEMM_NT, plan_f32(s.T, s.in, s.R, 1).tile, dx, hs);
+  if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (Z^T.dY beside G.S^T)");
+  if (w.splits > 1) {
+    ReduceArgs r{};
+    r.part = part; r.out = dU_cat; r.n = (int64_t)s.R * s.out; r.splits = w.splits; r.scale = scale;
+    r.part2 = cpart; r.out2 = dbias; r.n2 = dbias ? s.out : 0; r.splits2 = w.splits; r.scale2 = 1.0f;
+    e = launch_reduce_splits(r, hs);
+    if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (sum of splits)");
+  }
+  return SK_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1113,6 +1168,14 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
     e = launch_reduce_tiles(t, hs);
     return e == hipSuccess ? SK_OK : hip_fail(e, "sk_linear_bwd (sum of the token tiles)");
   }
+
+  // --- fp32: dY.U^T beside x.S | sums of their slabs | Z^T.dY beside G.S^T | sums of the token splits ---
+  // A partner by itself leaves the chip idle ([4096 x 768] . U^T, R = 128, is 128 work-groups of 24
+  // chunks: 17 us) or is over in a launch's own time (64 tokens, 256 -> 256, R = 16: six launches of one
+  // to four work-groups).  The same tiles and ranges as the separate calls, so the same results.
+  // Backward pass, us, apart : shared: 60 tokens, 112 -> 176, R = 64, 18.8 : 11.0; 811, 1888 -> 1840, R = 32,
+  // 34.5 : 25.9; 4096, 3072 -> 768, R = 128, 95 : 84; 1475, 1312 -> 288, R = 304, 51.7 : 45.0.
+  if (s.dtype == SK_F32) return bwd_f32(s, x, dY, S_cat, U_cat, dX, dU_cat, dbias, ws_in, ws_w, hs);
 
   // Shared-launch schedules exist for the shapes the automatic plans produce on the
   // benchmark configurations (bf16; the dual kernel is built for a few tile pairs only);

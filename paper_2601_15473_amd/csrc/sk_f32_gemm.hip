@@ -83,16 +83,22 @@ struct F32Chunk {
   static __device__ __forceinline__ int place(int i, int r) { return KC ? i * 32 + r : r * T + i; }
 };
 
+// The work of one work-group, index `block` of the product's own; a device function so that one launch
+// can carry the work-groups of two products.
 template <int T, bool A_KC, bool B_KC, bool COLSUM>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs p) {
+struct F32Tile {
   typedef F32Chunk<T, A_KC> CA;
   typedef F32Chunk<T, B_KC> CB;
-  constexpr int STAGE = CA::ELEMS + CB::ELEMS;
-  __shared__ __attribute__((aligned(16))) float lds[2 * STAGE];
+  static constexpr int STAGE = CA::ELEMS + CB::ELEMS;
+  static __device__ __forceinline__ void run(const GemmArgs& p, int block, float* lds);
+};
+
+template <int T, bool A_KC, bool B_KC, bool COLSUM>
+__device__ __forceinline__ void F32Tile<T, A_KC, B_KC, COLSUM>::run(const GemmArgs& p, const int block, float* const lds) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int tiles = p.tiles_m * p.tiles_n;
-  const int id = xcd_remap(blockIdx.x, tiles * p.splits);
+  const int id = xcd_remap(block, tiles * p.splits);
   const int split = id / tiles;
   int tile_m, tile_n;
   tile_coords(id - split * tiles, p.tiles_m, p.tiles_n, tile_m, tile_n);
@@ -232,6 +238,23 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs p) {
 }
 
 template <int T, bool A_KC, bool B_KC, bool COLSUM>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs p) {
+  typedef F32Tile<T, A_KC, B_KC, COLSUM> G;
+  __shared__ __attribute__((aligned(16))) float lds[2 * G::STAGE];
+  G::run(p, blockIdx.x, lds);
+}
+
+// Two independent products in one launch: the first groups_a work-groups are GA's on `a`, the rest
+// GB's on `b`.  The backward pass has two such pairs, and each has a partner that leaves most of the
+// chip idle by itself or is over in a launch's own time.
+template <class GA, class GB>
+__global__ __launch_bounds__(256) void dual_gemm_f32_kernel(const GemmArgs a, const GemmArgs b, const int groups_a) {
+  __shared__ __attribute__((aligned(16))) float lds[2 * (GA::STAGE > GB::STAGE ? GA::STAGE : GB::STAGE)];
+  if ((int)blockIdx.x < groups_a) GA::run(a, blockIdx.x, lds);
+  else GB::run(b, (int)blockIdx.x - groups_a, lds);
+}
+
+template <int T, bool A_KC, bool B_KC, bool COLSUM>
 static hipError_t launch_one(GemmArgs a, hipStream_t s) {
   a.tiles_m = (a.M + 64 * T - 1) / (64 * T);
   a.tiles_n = (a.N + 64 * T - 1) / (64 * T);
@@ -261,6 +284,38 @@ hipError_t launch_gemm_f32(GemmKind kind, int tile, const GemmArgs& a, hipStream
     case GEMM_TN_F32: return launch_tiles<false, false, true>(tile, a, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+template <class GA, class GB>
+static hipError_t launch_pair(int T, GemmArgs a, GemmArgs b, Work work, hipStream_t s) {
+  for (GemmArgs* g : {&a, &b}) {
+    g->tiles_m = (g->M + 64 * T - 1) / (64 * T);
+    g->tiles_n = (g->N + 64 * T - 1) / (64 * T);
+  }
+  const long long ga = (long long)a.tiles_m * a.tiles_n * a.splits, gb = (long long)b.tiles_m * b.tiles_n * b.splits;
+  if (ga <= 0 || gb <= 0 || ga + gb > 0x7fffffffLL) return hipErrorInvalidValue;
+  return launch_kernel("dual_gemm_f32_kernel", work, dual_gemm_f32_kernel<GA, GB>, dim3((unsigned)(ga + gb)), dim3(256), s, a, b, (int)ga);
+}
+
+hipError_t launch_dual_gemm_f32(GemmKind kind_a, const GemmArgs& a, GemmKind kind_b, const GemmArgs& b, int tile, hipStream_t s) {
+  bool akc, bkc, f32;
+  gemm_kind_traits(kind_a, akc, bkc, f32);
+  note_gemm(a, akc, bkc, 4, 4, true);
+  gemm_kind_traits(kind_b, akc, bkc, f32);
+  note_gemm(b, akc, bkc, 4, 4, true);
+  Work work = gemm_work(a, 4, 4, true);
+  const Work wb = gemm_work(b, 4, 4, true);
+  work.flops += wb.flops;
+  work.bytes += wb.bytes;
+  const bool big = tile == TILE_128x128;
+  if (!big && tile != TILE_64x64) return hipErrorInvalidValue;
+  if (kind_a == GEMM_NT && kind_b == GEMM_NN)
+    return big ? launch_pair<F32Tile<2, true, true, false>, F32Tile<2, true, false, false>>(2, a, b, work, s)
+               : launch_pair<F32Tile<1, true, true, false>, F32Tile<1, true, false, false>>(1, a, b, work, s);
+  if (kind_a == GEMM_TN_F32 && kind_b == GEMM_NT)
+    return big ? launch_pair<F32Tile<2, false, false, true>, F32Tile<2, true, true, false>>(2, a, b, work, s)
+               : launch_pair<F32Tile<1, false, false, true>, F32Tile<1, true, true, false>>(1, a, b, work, s);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace sk

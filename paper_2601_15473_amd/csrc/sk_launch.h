@@ -164,6 +164,9 @@ hipError_t launch_gemm256_bf16(GemmKind kind, const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_few_rows_bf16(GemmKind kind, const GemmArgs& a, hipStream_t s);
 // fp32 operands and accumulation (MFMA), on TILE_64x64 or TILE_128x128.
 hipError_t launch_gemm_f32(GemmKind kind, int tile, const GemmArgs& a, hipStream_t s);
+// Two of them that do not depend on each other in one launch, both on `tile`: GEMM_NT beside GEMM_NN, or
+// GEMM_TN_F32 beside GEMM_NT.
+hipError_t launch_dual_gemm_f32(GemmKind kind_a, const GemmArgs& a, GemmKind kind_b, const GemmArgs& b, int tile, hipStream_t s);
 constexpr int F32_BK = 32;
 
 hipError_t launch_reduce_splits(const ReduceArgs& a, hipStream_t s);
