@@ -185,6 +185,12 @@ sk_status sk_linear_bwd_weight_first(const void* x, const void* U_cat, const voi
                                      void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * to[i][j] = bf16(from[i][j]) for j < n[i], i < count (1 to 3 arrays, 16-byte aligned), in one launch: the
+ * fp32 gradients of a bf16 layer in the layer's own type.
+ */
+sk_status sk_round_gradients(const float* const* from, void* const* to, const int64_t* n, int32_t count, void* stream);
+
+/*
  * Bytes of workspace that `op` needs for these sizes (0 when it needs none).
  * Returns (size_t)-1 for arguments the compute call would reject.
  */

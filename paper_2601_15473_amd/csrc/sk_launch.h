@@ -177,6 +177,14 @@ hipError_t launch_reduce_to_bf16(const float* part, void* out, int64_t n, int sp
 // slabs rows * cols elements apart, summed in index order): a column range of a wider matrix
 hipError_t launch_reduce_splits_2d(const float* part, float* out, int rows, int cols, int64_t ld_out,
                                    int splits, float scale, hipStream_t s);
+// to[i][j] = bf16(from[i][j]), j < n[i], of up to three arrays (n 0 for none)
+struct RoundArgs {
+  static constexpr int MAX = 3;
+  const float* from[MAX];
+  unsigned short* to[MAX];
+  int64_t n[MAX];
+};
+hipError_t launch_round_gradients(const RoundArgs& a, hipStream_t s);
 // Two GEMMs that do not depend on each other in one launch (see dual_gemm_kernel); built
 // for a few (kind, tile) pairs only -- ask dual_gemm_supported first.  `a` should be the
 // longer-running one.

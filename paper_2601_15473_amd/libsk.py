@@ -55,6 +55,8 @@ _lib.sk_linear_bwd.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp] + _tail
 _lib.sk_linear_bwd_weight_first.restype = ctypes.c_int
 _lib.sk_linear_bwd_weight_first.argtypes = [_vp, _vp, _vp, _vp, _i64, _i64, _i64, _i32, _i32, _i64, _i64,
                                             ctypes.c_int, _vp, _sz, _vp]
+_lib.sk_round_gradients.restype = ctypes.c_int
+_lib.sk_round_gradients.argtypes = [ctypes.POINTER(_vp), ctypes.POINTER(_vp), ctypes.POINTER(_i64), _i32, _vp]
 _lib.sk_linear_workspace_bytes.restype = _sz
 _lib.sk_linear_workspace_bytes.argtypes = [ctypes.c_int, _i64, _i64, _i64, _i32, _i32, ctypes.c_int]
 _lib.sk_status_string.restype = ctypes.c_char_p
@@ -96,7 +98,7 @@ DEBUG_EXPORTS = ("sk_set_tuning", "sk_trace_begin", "sk_trace_end", "sk_trace_ke
 
 EXPORTS = ("sk_linear_fwd", "sk_linear_bwd_input", "sk_linear_bwd_weight", "sk_linear_bwd",
            "sk_linear_bwd_weight_first", "sk_linear_bwd_weight_noalloc",
-           "sk_linear_workspace_bytes", "sk_status_string", "sk_last_hip_error", "sk_set_plan")
+           "sk_round_gradients", "sk_linear_workspace_bytes", "sk_status_string", "sk_last_hip_error", "sk_set_plan")
 
 
 class SkError(RuntimeError):
@@ -161,6 +163,12 @@ def sk_linear_bwd_weight_first(x, U_cat, dY, dA, tokens, d_in, d_out, l, k, col_
     return _lib.sk_linear_bwd_weight_first(_ptr(x), _ptr(U_cat), _ptr(dY), _ptr(dA),
                                            tokens, d_in, d_out, l, k, col_begin, col_count, dtype,
                                            _ptr(workspace), workspace_bytes, _stream(stream))
+
+
+def sk_round_gradients(sources, targets, counts, stream=None):
+    n = len(sources)
+    return _lib.sk_round_gradients((_vp * n)(*map(_ptr, sources)), (_vp * n)(*map(_ptr, targets)), (_i64 * n)(*counts),
+                                   n, _stream(stream))
 
 
 def sk_linear_workspace_bytes(op, tokens, d_in, d_out, l, k, dtype):

@@ -3,7 +3,8 @@ out_features, num_terms, low_rank)`` as a drop-in for ``torch.nn.Linear`` (the
 paper's "Tool Usage" section: the layer averages ``num_terms`` sketched products
 whose sketches have rank ``low_rank``), with autograd support.
 
-Everything that computes runs in libsk's HIP kernels: ``forward`` calls
+Everything that computes runs in libsk's HIP kernels; between them and autograd stands a native module
+(csrc/sk_torch.cpp), with the functions below for the calls that it leaves to Python.  ``forward`` calls
 ``sk_linear_fwd``; ``backward`` calls ``sk_linear_bwd`` (both gradients in one
 call) or, when only one of them is wanted, ``sk_linear_bwd_input`` or
 ``sk_linear_bwd_weight``; the factor gradient recomputes x.S rather than keeping
@@ -21,6 +22,12 @@ import math
 import torch
 
 from . import libsk as sk
+
+try:
+    from .lib import _sktorch as _native
+except ImportError as e:
+    raise ImportError("the PyTorch layers' native functions are missing or do not load: build them with "
+                      f"`python -m paper_2601_15473_amd.build` ({e})") from e
 
 _DTYPES = {torch.float32: sk.SK_F32, torch.bfloat16: sk.SK_BF16}
 _workspaces: "collections.OrderedDict" = collections.OrderedDict()
@@ -48,6 +55,7 @@ def _workspace(device: torch.device, stream: int, nbytes: int) -> torch.Tensor:
 def release_workspaces() -> None:
     """Give the layers' scratch buffers back to the allocator (they are re-created on demand)."""
     _workspaces.clear()
+    _native.release_workspaces()
 
 
 def _check(x: torch.Tensor, name: str, dtype: torch.dtype):
@@ -160,8 +168,24 @@ class SKLinearFunction(torch.autograd.Function):
 
 
 def sklinear(x, S_cat, U_cat, bias, num_terms: int, low_rank: int):
-    """Functional form; see SKLinearFunction."""
+    """Functional form; see SKLinearFunction.  The native function computes the same for plain tensors
+    outside of compilation, tracing and torch's modes and transforms, and takes nothing else."""
+    if not torch.compiler.is_compiling():
+        y = _native.linear(x, S_cat, U_cat, bias, num_terms, low_rank)
+        if y is not None:
+            return y
     return SKLinearFunction.apply(x, S_cat, U_cat, bias, num_terms, low_rank)
+
+
+def _held(module, name):
+    """The module's tensor of that name: from its own tables where it is there (an attribute of a module is
+    looked up in three of them, 0.6 us), else as any attribute, for example under a parametrization."""
+    t = module._parameters.get(name)
+    if t is None:
+        t = module._buffers.get(name)
+        if t is None:
+            t = getattr(module, name)
+    return t
 
 
 class SKLinear(torch.nn.Module):
@@ -216,7 +240,7 @@ class SKLinear(torch.nn.Module):
         return m
 
     def forward(self, x: torch.Tensor) -> torch.Tensor:
-        return SKLinearFunction.apply(x, self.S_cat, self.U_cat, self.bias, self.num_terms, self.low_rank)
+        return sklinear(x, _held(self, "S_cat"), _held(self, "U_cat"), _held(self, "bias"), self.num_terms, self.low_rank)
 
     def extra_repr(self) -> str:
         return (f"in_features={self.in_features}, out_features={self.out_features}, "
@@ -335,7 +359,7 @@ class SKLinearTwoSided(torch.nn.Module):
         written since the cached copies were made -- tensors count their in-place writes, which
         is how optimizers update parameters.  Stale copies are replaced, never overwritten: a
         backward pass that is still to come holds the ones its forward pass used."""
-        parts = (self.S1_cat, self.U2_cat, self.U1_cat, self.S2T_cat)
+        parts = tuple(_held(self, n) for n in ("S1_cat", "U2_cat", "U1_cat", "S2T_cat"))
         key = tuple((t.data_ptr(), t._version, t.dtype) for t in parts)
         if self._stage_key != key:
             with torch.no_grad():
@@ -345,8 +369,13 @@ class SKLinearTwoSided(torch.nn.Module):
         return self._stage
 
     def forward(self, x: torch.Tensor) -> torch.Tensor:
-        return SKLinearTwoSidedFunction.apply(x, self.S1_cat, self.U1_cat, self.U2_cat, self.S2T_cat,
-                                              self.bias, self.num_terms, self.low_rank, self._stage_matrices())
+        stage = self._stage_matrices()
+        args = (x, *(_held(self, n) for n in ("S1_cat", "U1_cat", "U2_cat", "S2T_cat", "bias")))
+        if not torch.compiler.is_compiling():
+            y = _native.linear_two_sided(*args, *stage, self.num_terms, self.low_rank)
+            if y is not None:
+                return y
+        return SKLinearTwoSidedFunction.apply(*args, self.num_terms, self.low_rank, stage)
 
     def extra_repr(self) -> str:
         return (f"in_features={self.in_features}, out_features={self.out_features}, "

@@ -1,0 +1,161 @@
+"""The layers' native functions against the Python ones: the same results and gradients bit for bit over the forms
+an input comes in, the same refusals, and the calls they leave to Python."""
+import threading
+
+import pytest
+import torch
+
+from paper_2601_15473_amd import nn as sknn
+
+
+def _layer(two_sided, dtype, bias=True):
+    cls = sknn.SKLinearTwoSided if two_sided else sknn.SKLinear
+    return cls(96, 80, 2, 16, bias=bias, dtype=dtype, seed=7)
+
+
+def _python(layer, x):
+    """The layer's forward pass through the Python functions."""
+    if isinstance(layer, sknn.SKLinear):
+        return sknn.SKLinearFunction.apply(x, layer.S_cat, layer.U_cat, layer.bias, layer.num_terms, layer.low_rank)
+    return sknn.SKLinearTwoSidedFunction.apply(x, layer.S1_cat, layer.U1_cat, layer.U2_cat, layer.S2T_cat, layer.bias,
+                                               layer.num_terms, layer.low_rank, layer._stage_matrices())
+
+
+FORMS = {
+    "rows": lambda x: x, "batched": lambda x: x.view(5, 26, 96), "one row": lambda x: x[3],
+    "strided": lambda x: x.t().contiguous().t(), "columns": lambda x: torch.cat([x, x], 1)[:, 96:],
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("two_sided", [False, True])
+def test_same_as_the_python_functions(two_sided, dtype, form):
+    layer = _layer(two_sided, dtype, bias=form != "batched")
+    base = torch.randn(130, 96, generator=torch.Generator().manual_seed(2)).to(dtype).cuda()
+    got = []
+    for run in (layer, lambda x: _python(layer, x)):
+        x = base.clone().requires_grad_()
+        y = run(FORMS[form](x))
+        dY = torch.arange(y.numel(), device="cuda").remainder_(7).view(y.shape).to(dtype)
+        layer.zero_grad(set_to_none=True)
+        y.backward(dY)
+        got.append((y.detach(), x.grad, *(p.grad for p in layer.parameters())))
+        if len(got) == 1:
+            assert "SKLinear" not in y.grad_fn.name(), y.grad_fn.name()   # (the Python functions' nodes bear their names)
+    for a, b in zip(*got):
+        assert a.shape == b.shape and a.dtype == b.dtype and torch.equal(a, b)
+
+
+@pytest.mark.gpu
+def test_only_the_wanted_gradients():
+    layer = _layer(False, torch.bfloat16)
+    x = torch.randn(40, 96, device="cuda").bfloat16()
+    layer(x).float().square().sum().backward()
+    want = [p.grad.clone() for p in layer.parameters()]
+    layer.zero_grad(set_to_none=True)
+    layer.U_cat.requires_grad_(False)
+    layer(x).float().square().sum().backward()
+    assert layer.U_cat.grad is None and torch.equal(layer.bias.grad, want[1])
+    x.requires_grad_()
+    y = layer(x)
+    dx, = torch.autograd.grad(y.float().sum(), x)
+    assert dx.shape == x.shape and x.grad is None
+    with torch.no_grad():
+        assert not layer(x).requires_grad
+
+
+@pytest.mark.gpu
+def test_hooks_transforms_and_tangents():
+    layer = _layer(False, torch.float32)
+    x = torch.randn(24, 96, device="cuda", requires_grad=True)
+    packed = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: packed.append(t) or t.cpu(), lambda t: t.cuda()):
+        y = layer(x)
+    y.sum().backward()
+    assert len(packed) == 3 and x.grad is not None
+    z = layer(x.detach()).clone()
+    # (as with the Python functions: neither has a vmap rule, a forward-mode or a second derivative)
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(layer)(x.detach().view(2, 12, 96))
+    with torch.autograd.forward_ad.dual_level(), pytest.raises(Exception):
+        layer(torch.autograd.forward_ad.make_dual(x.detach(), torch.ones_like(x)))
+    assert torch.equal(layer(x.detach()), z)
+    y = layer(x)
+    with torch.no_grad():
+        layer.U_cat.add_(1.0)   # saved for the backward pass
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        y.sum().backward()
+
+    class Tagged(torch.Tensor):
+        pass
+
+    assert sknn._native.linear(x.detach().as_subclass(Tagged), layer.S_cat, layer.U_cat, layer.bias, 2, 16) is None
+    assert layer(x.detach().as_subclass(Tagged)).shape == (24, 80)
+
+
+@pytest.mark.gpu
+def test_refusals():
+    layer = _layer(False, torch.bfloat16)
+    with pytest.raises(TypeError, match="dtype"):
+        layer(torch.zeros(4, 96, device="cuda"))
+    with pytest.raises(RuntimeError, match="GPU only"):
+        layer(torch.zeros(4, 96).bfloat16())
+    with pytest.raises(ValueError, match="shapes"):
+        layer(torch.zeros(4, 95, device="cuda").bfloat16())
+    with pytest.raises(RuntimeError):
+        layer(torch.zeros(0, 96, device="cuda").bfloat16())
+    odd = torch.zeros(4 * 96 + 1, device="cuda").bfloat16()[1:].view(4, 96)
+    with pytest.raises(RuntimeError, match="misaligned"):
+        layer(odd)
+
+
+@pytest.mark.gpu
+def test_threads_and_streams():
+    """Each thread on a stream of its own, and all on one: results as alone."""
+    layer = _layer(False, torch.bfloat16)
+    xs = [torch.randn(300 + 64 * i, 96, device="cuda").bfloat16() for i in range(4)]
+    want = [layer(x).detach() for x in xs]
+    torch.cuda.synchronize()
+    shared = torch.cuda.Stream()
+    for streams in ([torch.cuda.Stream() for _ in xs], [shared] * len(xs)):
+        got = [None] * len(xs)
+
+        def work(i):
+            with torch.cuda.stream(streams[i]):
+                for _ in range(20):
+                    y = layer(xs[i].detach().requires_grad_())
+                    y.backward(torch.ones_like(y))
+                got[i] = y.detach()
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(len(xs))]
+        [t.start() for t in threads]
+        [t.join() for t in threads]
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+    sknn.release_workspaces()
+    assert torch.equal(layer(xs[0]), want[0])
+
+
+def test_calls_left_to_python_are_not_taken():
+    t = torch.zeros(4, 32)
+    assert sknn._native.linear(t, t, t, None, 1, 16) is None                  # not on a GPU
+    assert sknn._native.linear(t, None, t, None, 1, 16) is None
+    assert sknn._native.linear(t, t, t, None, 1.0, 16) is None
+    assert sknn._native.linear_two_sided(t, t, t, t, t, None, t, t, 1, 16) is None
+    sknn.release_workspaces()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("counts", [(16,), (1, 1023), (4096, 3, 1040)])
+def test_round_gradients(counts):
+    from paper_2601_15473_amd import libsk as sk
+    src = [torch.randn(n, device="cuda") for n in counts]
+    src[0][0] = float("inf")
+    dst = [torch.full((n + 8,), 7.0, device="cuda").bfloat16() for n in counts]
+    sk.check(sk.sk_round_gradients(src, dst, counts))
+    torch.cuda.synchronize()
+    for s, d, n in zip(src, dst, counts):
+        assert torch.equal(d[:n], s.bfloat16()) and torch.equal(d[n:], torch.full((8,), 7.0, device="cuda").bfloat16())
+    assert sk.sk_round_gradients([], [], []) == sk.SK_ERR_INVALID_ARG
+    assert sk.sk_round_gradients(src[:1], [dst[0].data_ptr() + 4], (1,)) == sk.SK_ERR_INVALID_ARG
