@@ -5,12 +5,12 @@
 //
 // (The 256 x 256 tile is a kernel of its own: sk_bf16_gemm256.hip.)  One work-group of 2 x 2
 // waves owns a BM x BN tile; each wave a (BM/2) x (BN/2) sub-tile of 32x32 MFMA blocks.
-// Operands go global -> registers -> LDS (double
-// buffered, one barrier per 64-wide k chunk) and are read from LDS directly in the
+// Operands go global -> registers -> LDS (double buffered, one barrier per 64-wide k chunk), or
+// straight into a ring of chunks in LDS (sk_bf16_ring.h), and are read from LDS directly in the
 // MFMA fragment layout; operands whose contiguous dimension is not k are read with
 // the LDS transpose read.  Results leave straight from registers: fp32 as 16-byte
 // pieces, bf16 in whole lines through a wave-private strip of LDS.
-#include "sk_bf16_tile.h"
+#include "sk_bf16_ring.h"
 #include "sk_launch.h"
 
 namespace sk {
@@ -276,12 +276,20 @@ GemmTile<BM, BN, A_KC, B_KC, OutT, COLSUM>::run(const GemmArgs& p, int block, un
   }
 }
 
-template <int BM, int BN, bool A_KC, bool B_KC, typename OutT, bool COLSUM>
+// RING: the tile on a ring of chunks, for launches of one round.
+template <int BM, int BN, bool A_KC, bool B_KC, typename OutT, bool COLSUM, bool RING = false>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(const GemmArgs p) {
-  typedef GemmTile<BM, BN, A_KC, B_KC, OutT, COLSUM> G;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[G::LDS_BYTES];
+  typedef typename std::conditional<RING, RingTile<BM, BN, A_KC, B_KC, OutT, COLSUM>, GemmTile<BM, BN, A_KC, B_KC, OutT, COLSUM>>::type G;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[G::LDS_BYTES];
   G::run(p, blockIdx.x, smem);
 }
+
+// Whether a tile has a ring, for the launches of one round on which it is ahead.  Past a round two or more staged
+// work-groups on a CU hide each other's waits as well, and a ring takes their room ([11752 x 3344] . [3344 x 2032] and the like on
+// 128 x 128 rings in place of 256 x 256 tiles or staged ones: 4 to 10 % behind).  It is behind for bf16 results of 128 x 64
+// ([4001 x 384] . [384 x 768] 9.8 : 8.5 us) and for 64 x 128 (dY . U^T of [4096 x 3072], R = 128, in four ranges 12.3 : 12.0).
+template <int BM, int BN, typename OutT>
+constexpr bool has_ring() { return BM == BN || (BM == 128 && sizeof(OutT) == 4); }
 
 // Two independent GEMMs in one launch: the first `groups_a` work-groups run GA on `a`, the
 // rest run GB on `b`.  For small problems a kernel's fixed cost (launch, first trip to
@@ -290,9 +298,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const GemmArgs p) {
 template <class GA, class GB>
 __global__ __launch_bounds__(256) void dual_gemm_kernel(const GemmArgs a, const GemmArgs b,
                                                         const int groups_a) {
-  static_assert(GA::NTH == 256 && GB::NTH == 256, "both halves run 256 threads per work-group");
   constexpr int BYTES = GA::LDS_BYTES > GB::LDS_BYTES ? GA::LDS_BYTES : GB::LDS_BYTES;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[BYTES];
   if ((int)blockIdx.x < groups_a) GA::run(a, blockIdx.x, smem);
   else GB::run(b, (int)blockIdx.x - groups_a, smem);
 }
@@ -369,13 +376,19 @@ template <int BM, int BN, bool A_KC, bool B_KC, typename OutT, bool COLSUM>
 static hipError_t launch_cfg(GemmArgs a, hipStream_t s) {
   a.tiles_m = (a.M + BM - 1) / BM;
   a.tiles_n = (a.N + BN - 1) / BN;
-  const long long grid = (long long)a.tiles_m * a.tiles_n * a.splits;
-  if (grid <= 0 || grid > 0x7fffffffLL || (A_KC && !within_window(BM, a.lda, BK, 2)) || (B_KC && !within_window(BN, a.ldb, BK, 2)))
+  const long long total = (long long)a.tiles_m * a.tiles_n * a.splits;
+  if (total <= 0 || total > 0x7fffffffLL || (A_KC && !within_window(BM, a.lda, BK, 2)) || (B_KC && !within_window(BN, a.ldb, BK, 2)))
     return hipErrorInvalidValue;
   note_gemm(a, A_KC, B_KC, 2, sizeof(OutT), sizeof(OutT) == 4);
   static const std::string name = kernel_label("gemm_bf16_kernel", {lbl(BM), lbl(BN), lbl(A_KC), lbl(B_KC), out_label<OutT>(), lbl(COLSUM)});
-  return launch_kernel(name.c_str(), gemm_work(a, 2, sizeof(OutT), sizeof(OutT) == 4), gemm_bf16_kernel<BM, BN, A_KC, B_KC, OutT, COLSUM>,
-                       dim3((unsigned)grid), dim3(256), s, a);
+  const Work work = gemm_work(a, 2, sizeof(OutT), sizeof(OutT) == 4);
+  if constexpr (has_ring<BM, BN, OutT>()) {
+    if (total <= NUM_CUS * RingTile<BM, BN, A_KC, B_KC, OutT, COLSUM>::PER_CU) {
+      static const std::string ring = kernel_label("gemm_bf16_kernel", {lbl(BM), lbl(BN), lbl(A_KC), lbl(B_KC), out_label<OutT>(), lbl(COLSUM), lbl(true)});
+      return launch_kernel(ring.c_str(), work, gemm_bf16_kernel<BM, BN, A_KC, B_KC, OutT, COLSUM, true>, dim3((unsigned)total), dim3(256), s, a);
+    }
+  }
+  return launch_kernel(name.c_str(), work, gemm_bf16_kernel<BM, BN, A_KC, B_KC, OutT, COLSUM>, dim3((unsigned)total), dim3(256), s, a);
 }
 
 template <bool A_KC, bool B_KC, typename OutT, bool COLSUM>
@@ -458,6 +471,7 @@ hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKi
     work.flops += wb.flops;
     work.bytes += wb.bytes;
   }
+  const char* name = "dual_gemm_kernel";
   typedef GemmTile<64, 128, true, true, float, false> NTF_64x128;
   typedef GemmTile<64, 64, true, true, float, false> NTF_64x64;
   typedef GemmTile<64, 64, false, true, bf16, false> TT_64x64;
@@ -467,7 +481,16 @@ hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKi
   typedef GemmTile<128, 128, true, false, float, true> NNFC_128x128;
   typedef GemmTile<64, 64, true, true, bf16, false> NT_64x64;
   typedef GemmTile<128, 64, true, true, bf16, false> NT_128x64;
-  const char* name = "dual_gemm_kernel";
+  // 64 x 64 tiles in one round, two work-groups to a CU: on the ring, as a product by itself (backward pass of 568 tokens,
+  // 1216 -> 352, R = 48, 22.1 -> 17.8 us; 1024, 1024 -> 1024, R = 64, 21.0 -> 18.5; 1500, 768 -> 768, R = 192, 28.8 -> 25.5; on a
+  // ring of their own the 128 x 64 tiles of the other pairs are level with the staged ones)
+  typedef RingTile<64, 64, true, true, float, false> RING_NTF_64x64;
+  typedef RingTile<64, 64, false, true, bf16, false> RING_TT_64x64;
+  typedef RingTile<64, 64, true, true, bf16, false> RING_NT_64x64;
+  if (ga + gb <= NUM_CUS * RING_NT_64x64::PER_CU) {
+    if (pair == 1) return launch_kernel(name, work, dual_gemm_kernel<RING_NTF_64x64, RING_TT_64x64>, grid, block, s, a, b, (int)ga);
+    if (pair == 5) return launch_kernel(name, work, dual_gemm_kernel<RING_NT_64x64, RING_TT_64x64>, grid, block, s, a, b, (int)ga);
+  }
   switch (pair) {
     case 0: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x128, TT_64x64>, grid, block, s, a, b, (int)ga);
     case 1: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x64, TT_64x64>, grid, block, s, a, b, (int)ga);

@@ -69,6 +69,12 @@ __device__ __forceinline__ void load_to_lds(unsigned lds, unsigned voff, u32x4 a
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(array), "s"(soff) : "m0");
 }
 
+// A descriptor that is the same in all lanes, in scalar registers (some the compiler would compute in vector ones).
+__device__ __forceinline__ u32x4 scalar(u32x4 d) {
+  return u32x4{(unsigned)__builtin_amdgcn_readfirstlane((int)d.x), (unsigned)__builtin_amdgcn_readfirstlane((int)d.y),
+               (unsigned)__builtin_amdgcn_readfirstlane((int)d.z), (unsigned)__builtin_amdgcn_readfirstlane((int)d.w)};
+}
+
 // The lane number computed afresh, for what is not to be kept in registers through the main loop.
 __device__ __forceinline__ int lane_again() {
   int zero = 0;
