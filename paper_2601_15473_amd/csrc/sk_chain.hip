@@ -17,7 +17,7 @@
 //     leave one step later through LDS, in whole rows;
 //   chain_kernel (R <= 512, forced plans only): B2 streams in 64-row chunks and the output
 //     tile is re-laid out through LDS into whole rows.
-#include "sk_bf16_tile.h"
+#include "sk_bf16_lds.h"
 #include "sk_launch.h"
 
 namespace sk {
@@ -674,13 +674,286 @@ __device__ __forceinline__ void chain_small(const ChainArgs& p) {
     tile_store(my_tiles - 1, leaving);
   }
 }
-template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC>
-__global__ __launch_bounds__(256, chain_outs(MB, RT) == 1 ? 2 : 1) void chain_small_kernel(const ChainArgs p) {
-  chain_small<MB, RT, B2_KC, FUSED, B1_KC, false>(p);
+// The same chain with both stages fused, for token tiles of 64 rows: every operand goes straight into LDS.
+//   - stage 1 runs on a ring of four 64-wide chunks of x and B1 (as sk_bf16_ring.h: two phases of two k steps a chunk,
+//     one barrier, the loads up to four chunks ahead);
+//   - stage 2 on a ring of whole [R x 128] tiles of B2, each with its bias: a phase multiplies half of a tile's
+//     k steps and reads the other half, or the first half of the next tile; a finished tile is turned over in LDS and
+//     leaves in the second phase of the next step (runs of few tiles: straight from registers).
+// What it waits for: loads through registers, two chunks or tiles ahead, left a work-group alone on its CU 1110 cycles
+// a chunk (256 of MFMAs) and 2090 a tile (512).  Forward, us, before : now: 4096 tokens, 768 -> 3072, R = 128
+// 18.4 : 16.2; 768 -> 768, R = 128 11.8 : 9.7, R = 32 9.5 : 8.1; 1119, 944 -> 496, R = 32 9.2 : 7.0.
+template <int RT, bool KC, bool SHORT>
+struct ChainRing {
+  static constexpr int KS = RT / 16, KH = KS / 2;
+  static constexpr int S1 = 4, SLOT1 = (64 + RT) * 128, L1A = 2, L1B = RT / 32, L1 = L1A + L1B;
+  static constexpr int S2 = RT == 128 ? 3 : 4, SLOT2 = RT * 256, L2 = RT / 16 + 1;   // (a tile's loads and its bias)
+  static constexpr int Z_LD = RT + 8, Z_BYTES = 64 * Z_LD * 2, OUT_BYTES = 64 * 256;
+  static constexpr int HEAD = SHORT ? (Z_BYTES + 1023) / 1024 * 1024 : 2 * OUT_BYTES;   // Zt, then two finished tiles
+  static constexpr int RING = S1 * SLOT1 > S2 * SLOT2 ? S1 * SLOT1 : S2 * SLOT2;
+  static constexpr int BIAS_AT = HEAD + RING, BIAS_TILES = 2 * S2;
+  static constexpr int BYTES = BIAS_AT + BIAS_TILES * 256;
+  static constexpr int STORES = 4;                                                   // of a wave per step
+  static_assert(Z_BYTES <= HEAD && BYTES <= 160 * 1024, "LDS of a compute unit");
+};
+
+template <int RT, bool KC, bool SHORT>
+__device__ __forceinline__ void chain_ring(const ChainArgs& p) {
+  typedef ChainRing<RT, KC, SHORT> L;
+  typedef Panels<true> PA;
+  typedef Panels<KC> PB;
+  constexpr int TN1 = RT / 64;   // stage 1: waves 2 x 2, each 32 rows x RT / 2 columns of Zt
+  constexpr int KS = L::KS, KH = L::KH;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[L::BYTES];
+  // (what the loads write is invisible to the compiler: it must not take smem for unwritten)
+  asm volatile("" ::"v"((unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem) : "memory");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int wg = xcd_remap(blockIdx.x, p.tiles_m * p.n_slices);
+  const int tile_m = wg / p.n_slices, slice = wg % p.n_slices;
+  const int m0 = tile_m * 64;
+  const int n_tiles = (p.N + CS_BN - 1) / CS_BN;
+  const int per_slice = (n_tiles + p.n_slices - 1) / p.n_slices;
+  const int t_begin = slice * per_slice;
+  const int t_end = (t_begin + per_slice < n_tiles) ? t_begin + per_slice : n_tiles;
+  const int my_tiles = t_end - t_begin;
+  if (my_tiles <= 0) return;  // uniform over the work-group
+
+  // ---------------- stage 1: Zt = A . B1 ----------------
+  {
+    const unsigned lda = (unsigned)p.lda * 2u, ldb = (unsigned)p.ldb1 * 2u;   // bytes
+    const unsigned va = PA::load_offset(wave, lane, lda), vb = PB::load_offset(wave, lane, ldb);
+    const int lane_k = PA::load_k(wave, lane);
+    const unsigned step_b = KC ? 128u : ldb * 64u, panel_b = KC ? ldb * 64u : 128u;
+    u32x4 a_src = scalar(descriptor(p.A, (int64_t)m0 * p.lda, (int64_t)p.M * p.lda, 2));
+    u32x4 b_src = scalar(descriptor(p.B1, 0, KC ? (int64_t)p.R * p.ldb1 : (int64_t)p.K1 * p.ldb1, 2));
+    unsigned a_off = 0, b_off = 0, s_slot = L::HEAD;
+    int left = p.K1;
+    auto load_a = [&](int i) { load_to_lds(s_slot + i * 4096 + wave * 1024, lane_k < left ? va : OOB_OFFSET, a_src, a_off + (i ? lda * 32u : 0u)); };
+    auto load_b = [&](int i) {
+      load_to_lds(s_slot + 8192 + i * 4096 + wave * 1024, KC ? (lane_k < left ? vb : OOB_OFFSET) : vb, b_src,
+                  b_off + (i & 1 ? ldb * 32u : 0u) + (i >> 1) * panel_b);
+    };
+    auto next_chunk = [&]() {
+      left -= 64;
+      a_off += 128u; b_off += step_b;
+      if (left <= 0) a_src.z = b_src.z = 0;   // past the last chunk nothing is fetched
+      s_slot = s_slot + L::SLOT1 == L::HEAD + L::S1 * L::SLOT1 ? L::HEAD : s_slot + L::SLOT1;
+    };
+    bf16x8 fa[2][2], fb[2][2][TN1];
+    const unsigned a_read = PA::read_address(0, lane) + wm * 4096;
+    const unsigned b_0 = PB::read_address(0, lane);
+    const unsigned b_read = 8192 + (KC ? b_0 + wn * TN1 * 4096 : TN1 == 2 ? b_0 + wn * 8192 : b_0 ^ (wn << 6));
+    auto read_a = [&](int set, int s, unsigned slot, int ks) { fa[set][s] = PA::frag(slot + a_read, 0, ks); };
+    auto read_b = [&](int set, int s, int j, unsigned slot, int ks) { fb[set][s][j] = PB::frag(slot + b_read, j, ks); };
+#pragma unroll
+    for (int c = 0; c < L::S1; ++c) {
+#pragma unroll
+      for (int i = 0; i < L::L1A; ++i) load_a(i);
+      if (c == L::S1 - 1) break;   // (the last chunk's loads of B1 are the first phase's)
+#pragma unroll
+      for (int i = 0; i < L::L1B; ++i) load_b(i);
+      next_chunk();
+    }
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((L::S1 - 2) * L::L1 + L::L1A) : "memory");   // chunk 0
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      read_a(0, s, L::HEAD, s);
+#pragma unroll
+      for (int j = 0; j < TN1; ++j) read_b(0, s, j, L::HEAD, s);
+    }
+    f32x16 acc[TN1];
+#pragma unroll
+    for (int j = 0; j < TN1; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    unsigned c_slot = L::HEAD;
+    const int nk = (p.K1 + 63) / 64;
+    for (int kc = 0; kc < nk; ++kc) {
+      const unsigned n_slot = c_slot + L::SLOT1 == L::HEAD + L::S1 * L::SLOT1 ? L::HEAD : c_slot + L::SLOT1;
+      auto phase = [&](auto h_c) {   // (see sk_bf16_ring.h)
+        constexpr int H = decltype(h_c)::value, NM = 2 * TN1, NR = 2 * (1 + TN1), NL = H == 0 ? L::L1B : L::L1A;
+        const unsigned slot = H == 0 ? c_slot : n_slot;
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<0, NM>([&](auto tc) {
+          constexpr int t = decltype(tc)::value;
+          static_for<t * NR / NM, (t + 1) * NR / NM>([&](auto rc) {
+            constexpr int r = decltype(rc)::value, s = r / (1 + TN1), e = r % (1 + TN1);
+            if constexpr (e < TN1) read_b(1 - H, s, e, slot, 2 * (1 - H) + s);
+            else read_a(1 - H, s, slot, 2 * (1 - H) + s);
+          });
+          static_for<t * NL / NM, (t + 1) * NL / NM>([&](auto lc) {
+            if constexpr (H == 0) load_b(decltype(lc)::value);
+            else load_a(decltype(lc)::value);
+          });
+          constexpr int s = t / TN1, j = t % TN1;
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[H][s][j], fa[H][s], acc[j], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      };
+      phase(IntC<0>{});
+      next_chunk();
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((L::S1 - 2) * L::L1) : "memory");
+      phase(IntC<1>{});
+      c_slot = n_slot;
+    }
+    // rounded once to bf16; columns past R are zeros (B1 may hold anything there: its rows' neighbours)
+    bf16* const Zs = reinterpret_cast<bf16*>(smem);
+#pragma unroll
+    for (int j = 0; j < TN1; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = wn * (RT / 2) + j * 32 + q * 8 + (lane >> 5) * 4;
+        uint2 w;
+        w.x = c < p.R ? pack_bf16x2(acc[j][q * 4 + 0], acc[j][q * 4 + 1]) : 0u;
+        w.y = c < p.R ? pack_bf16x2(acc[j][q * 4 + 2], acc[j][q * 4 + 3]) : 0u;
+        *reinterpret_cast<uint2*>(Zs + (wm * 32 + (lane & 31)) * L::Z_LD + c) = w;
+      }
+  }
+  // Zt complete, stage 1's ring read by everybody and nothing under way into it
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+  // ---------------- stage 2: one [64 x 128] output tile a step ----------------
+  const unsigned ldb2 = (unsigned)p.ldb2 * 2u;
+  const unsigned v2 = PB::load_offset(wave, lane, ldb2);
+  const int lane_k2 = PA::load_k(wave, lane);
+  u32x4 b2_src{}, bias_src{};
+  auto set_tile = [&](int jt) {   // (past the run: nothing to fetch)
+    const int n0 = (t_begin + jt) * CS_BN;
+    b2_src = scalar(descriptor(p.B2, KC ? (int64_t)n0 * p.ldb2 : (int64_t)n0, jt >= my_tiles ? 0 : KC ? (int64_t)p.N * p.ldb2 : (int64_t)(p.R - 1) * p.ldb2 + p.N, 2));
+    bias_src = scalar(descriptor(p.bias, n0, p.bias != nullptr && jt < my_tiles ? p.N : 0, 2));
+  };
+  // load i of the tile into `slot`: 32 lines of panel (n panel, k panel)
+  auto load2 = [&](int i, unsigned slot) {
+    const int kp = i >> 2, np = (i >> 1) & 1, h = i & 1;
+    load_to_lds(slot + (unsigned)((np * (RT / 64) + kp) * 8192 + h * 4096) + wave * 1024, KC ? (lane_k2 + kp * 64 < p.R ? v2 : OOB_OFFSET) : v2, b2_src,
+                (h ? ldb2 * 32u : 0u) + (KC ? np * ldb2 * 64u + kp * 128u : kp * ldb2 * 64u + np * 128u));
+  };
+  auto load_bias = [&](int jt) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(L::BIAS_AT + (jt % L::BIAS_TILES) * 256), "v"(lane * 4), "s"(bias_src) : "m0");
+  };
+#pragma unroll
+  for (int t = 0; t < L::S2; ++t) {
+    set_tile(t);
+    load_bias(t);
+#pragma unroll
+    for (int i = 0; i < L::L2 - 1; ++i) load2(i, L::HEAD + t * L::SLOT2);
+  }
+  // all rows of Zt, as MFMA fragments, in every wave for the rest of the kernel
+  bf16x8 fz[2][KS];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) fz[i][ks] = read_frag_rowmajor<L::Z_LD>(reinterpret_cast<const bf16*>(smem), i * 32, ks, lane);
+  bf16x8 f2[2][KH];
+  const unsigned b2_0 = PB::read_address(0, lane);
+  const unsigned b2_read = (wave >> 1) * (RT / 64) * 8192 + (KC ? b2_0 + (wave & 1) * 4096 : b2_0 ^ ((wave & 1) << 6));
+  auto read2 = [&](int set, int s, unsigned slot, int ks) { f2[set][s] = PB::frag(slot + b2_read + (ks >> 2) * 8192, 0, ks & 3); };
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((L::S2 - 1) * L::L2) : "memory");   // tile 0; Zt is in registers
+#pragma unroll
+  for (int s = 0; s < KH; ++s) read2(0, s, L::HEAD, s);
+
+  const float scale = p.scale;
+  const GWindow out_w = make_window(p.C, (int64_t)m0 * p.ldc, (int64_t)p.M * p.ldc, 2);
+  // whole rows of the finished tile jt (none if jt is not one): wave w stores rows 16 w .. + 15
+  auto tile_out = [&](int jt) {
+    const unsigned char* const buf = smem + (jt & 1) * L::OUT_BYTES;
+    uint4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int row = wave * 16 + u * 4 + (lane >> 4);
+      v[u] = *reinterpret_cast<const uint4*>(buf + row * 256 + (((lane & 15) ^ (row & 15)) * 16));
+    }
+    const int gn = (t_begin + jt) * CS_BN + (lane & 15) * 8;
+    const unsigned at = jt >= 0 && gn < p.N ? ((unsigned)(wave * 16 + (lane >> 4)) * (unsigned)p.ldc + (unsigned)gn) * 2u : OOB_OFFSET;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) window_store16(out_w, at + (unsigned)(u * 8) * (unsigned)p.ldc, v[u]);
+  };
+  unsigned c_slot = L::HEAD;
+  for (int jt = 0; jt < my_tiles; ++jt) {
+    const unsigned n_slot = c_slot + L::SLOT2 == L::HEAD + L::S2 * L::SLOT2 ? L::HEAD : c_slot + L::SLOT2;
+    f32x16 acc[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    set_tile(jt + L::S2);
+    auto phase = [&](auto h_c) {
+      constexpr int H = decltype(h_c)::value;
+      const unsigned slot = H == 0 ? c_slot : n_slot;
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<0, KH>([&](auto sc) {
+        constexpr int s = decltype(sc)::value;
+        read2(1 - H, s, slot, KH * (1 - H) + s);
+        if constexpr (H == 1) {   // this tile's slot is free
+          if constexpr (s == 0) load_bias(jt + L::S2);
+          static_for<s*(L::L2 - 1) / KH, (s + 1) * (L::L2 - 1) / KH>([&](auto lc) { load2(decltype(lc)::value, c_slot); });
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[H][s], fz[i][KH * H + s], acc[i], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    phase(IntC<0>{});
+    // This tile is in registers, the tile before it in LDS, the next tile has landed: younger than its loads are those of S2 - 2
+    // tiles and, once it was not among the first S2, the stores of S2 - 1 steps.
+    if (jt + 1 >= L::S2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((L::S2 - 2) * L::L2 + (L::S2 - 1) * L::STORES) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((L::S2 - 2) * L::L2) : "memory");
+    phase(IntC<1>{});
+    if constexpr (!SHORT) tile_out(jt - 1);
+    // ---- this wave's 32 columns of the tile (see chain_small) ----
+    const unsigned char* const bias = smem + L::BIAS_AT + (jt % L::BIAS_TILES) * 256 + wave * 64;
+    unsigned char* const out = smem + (jt & 1) * L::OUT_BYTES;
+    uint2 bv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bv[q] = *reinterpret_cast<const uint2*>(bias + (q * 8 + (lane >> 5) * 4) * 2);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = i * 32 + (lane & 31);
+#pragma unroll
+      for (int pr = 0; pr < 2; ++pr) {
+        uint2 w[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int q = 2 * pr + h;
+          const float b0 = bf16_bits_to_float(bv[q].x & 0xffffu), b1 = bf16_bits_to_float(bv[q].x >> 16);
+          const float b2 = bf16_bits_to_float(bv[q].y & 0xffffu), b3 = bf16_bits_to_float(bv[q].y >> 16);
+          w[h].x = pack_bf16x2(acc[i][q * 4 + 0] * scale + b0, acc[i][q * 4 + 1] * scale + b1);
+          w[h].y = pack_bf16x2(acc[i][q * 4 + 2] * scale + b2, acc[i][q * 4 + 3] * scale + b3);
+        }
+        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 s0 = __builtin_amdgcn_permlane32_swap(w[0].x, w[1].x, false, false);
+        const u32x2 s1 = __builtin_amdgcn_permlane32_swap(w[0].y, w[1].y, false, false);
+        const int piece = wave * 4 + pr * 2 + (lane >> 5);
+        const uint4 v = make_uint4(s0.x, s1.x, s0.y, s1.y);
+        if constexpr (SHORT) {
+          const int gn = (t_begin + jt) * CS_BN + piece * 8;
+          window_store16(out_w, gn < p.N ? ((unsigned)row * (unsigned)p.ldc + (unsigned)gn) * 2u : OOB_OFFSET, v);
+        } else {
+          *reinterpret_cast<uint4*>(out + row * 256 + ((piece ^ (row & 15)) * 16)) = v;
+        }
+      }
+    }
+    c_slot = n_slot;
+  }
+  // the last tile leaves; no load may land in LDS that is someone else's
+  if constexpr (!SHORT) {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    tile_out(my_tiles - 1);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
-template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC>
+
+// RING: both stages on rings of loads (chain_ring), for fused launches of 64-row tiles.
+template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC, bool RING = false>
+__global__ __launch_bounds__(256, chain_outs(MB, RT) == 1 ? 2 : 1) void chain_small_kernel(const ChainArgs p) {
+  if constexpr (RING) chain_ring<RT, B2_KC, false>(p);
+  else chain_small<MB, RT, B2_KC, FUSED, B1_KC, false>(p);
+}
+template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC, bool RING = false>
 __global__ __launch_bounds__(256) void chain_short_kernel(const ChainArgs p) {
-  chain_small<MB, RT, B2_KC, FUSED, B1_KC, true>(p);
+  if constexpr (RING) chain_ring<RT, B2_KC, true>(p);
+  else chain_small<MB, RT, B2_KC, FUSED, B1_KC, true>(p);
 }
 
 bool chain_supported(int R) { return R >= 16 && R <= 512; }
@@ -720,16 +993,32 @@ static hipError_t launch_small_mb(const ChainArgs& a, hipStream_t s) {
   // A lone token tile has next to nothing to store beside the weights it reads ([1 x 528] -> 131072, R = 128,
   // runs of 4, 13.5 : 12.4).
   const int run = ((a.N + CS_BN - 1) / CS_BN + a.n_slices - 1) / a.n_slices;
-  if (run <= (MB == 64 ? 3 : 2) || a.tiles_m == 1) {
-    static const std::string brief =
-        kernel_label("chain_short_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC)});
-    return launch_kernel(brief.c_str(), chain_work(a, FUSED), chain_short_kernel<MB, RT, B2_KC, FUSED, B1_KC>, dim3((unsigned)grid),
-                         dim3(256), s, a);
+  const bool brief = run <= (MB == 64 ? 3 : 2) || a.tiles_m == 1;
+  // Fused launches of 64-row tiles run on rings but for the long runs of a narrow sketch in more than a round: there
+  // the rings and the finished tiles would leave room for one work-group on a CU instead of two ([12128 x 1728] -> 3872,
+  // R = 16, 46.2 us on rings, 35.6 without; [11483 x 624] -> 3328, R = 32, 29.7, 23.9).
+  const Work work = chain_work(a, FUSED);
+  if constexpr (FUSED && MB == 64) {
+    if (brief || RT > 64 || grid <= NUM_CUS) {
+      static const std::string names[2] = {kernel_label("chain_small_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC), lbl(true)}),
+                                           kernel_label("chain_short_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC), lbl(true)})};
+      return brief ? launch_kernel(names[1].c_str(), work, chain_short_kernel<MB, RT, B2_KC, FUSED, B1_KC, true>, dim3((unsigned)grid), dim3(256), s, a)
+                   : launch_kernel(names[0].c_str(), work, chain_small_kernel<MB, RT, B2_KC, FUSED, B1_KC, true>, dim3((unsigned)grid), dim3(256), s, a);
+    }
   }
-  static const std::string name =
-      kernel_label("chain_small_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC)});
-  return launch_kernel(name.c_str(), chain_work(a, FUSED), chain_small_kernel<MB, RT, B2_KC, FUSED, B1_KC>, dim3((unsigned)grid),
-                       dim3(256), s, a);
+  if constexpr (!(FUSED && MB == 64)) {   // (fused, 64 rows: brief runs are the rings')
+    if (brief) {
+      static const std::string name =
+          kernel_label("chain_short_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC)});
+      return launch_kernel(name.c_str(), work, chain_short_kernel<MB, RT, B2_KC, FUSED, B1_KC>, dim3((unsigned)grid), dim3(256), s, a);
+    }
+  }
+  if constexpr (!(FUSED && MB == 64 && RT > 64)) {
+    static const std::string name =
+        kernel_label("chain_small_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC)});
+    return launch_kernel(name.c_str(), work, chain_small_kernel<MB, RT, B2_KC, FUSED, B1_KC>, dim3((unsigned)grid), dim3(256), s, a);
+  }
+  return hipErrorInvalidValue;
 }
 
 template <int RT, bool B2_KC, bool FUSED, bool B1_KC>
@@ -760,6 +1049,7 @@ hipError_t launch_chain_bf16(bool b_kc, bool fused, ChainArgs a, hipStream_t s) 
     return hipErrorInvalidValue;
   if (a.bm == 0) a.bm = CH_BM;
   if (a.bm != CH_BM && !(a.bm == 128 && a.R <= 128)) return hipErrorInvalidValue;
+  if (fused && a.tail.n + a.tail.n2 > 0) return hipErrorInvalidValue;   // (no plan asks a fused launch to carry one)
   a.tiles_m = (a.M + a.bm - 1) / a.bm;
   if (tracing()) {
     if (fused) {
