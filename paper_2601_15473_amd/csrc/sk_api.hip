@@ -556,7 +556,15 @@ Plan pick_plan(const Shape& s, sk_op op, bool workspace) {
     if (s.R > 64 || s.T <= 32 || k1 <= 1792 || k1 * chain_shape(s.T, n2, s.R, false).slices <= 6144) return PLAN_TWO_GEMM;
   }
   if (chain_ok && s.R <= 128) {
-    return k1 * chain_shape(s.T, n2, s.R, false).slices <= 6144 ? PLAN_FUSED : PLAN_SPLIT_EXPAND;
+    // ... and, the walk of a work-group on rings being the shorter one, a contraction of up to 1536 in one round of them at
+    // any number of slices past the few tokens above (fused : split, us: 4053 tokens, 1280 -> 2144, R = 48 13.1 : 17.3; 3813,
+    // 1344 <- 2912, R = 128 18.5 : 25.0; 1064, 1344 -> 5168, R = 128 13.5 : 17.0; 417, 1408 <- 832, R = 64 8.9 : 9.2; 300,
+    // 1792 -> 4096, R = 32 10.1 : 9.0; from 2500 on split is ahead nearly always, 1693, 3520 <- 496 15.8 : 9.6).  A long walk in more than a round is not fused either
+    // (10442 tokens, 2928 <- 5136, R = 64 75 : 48; 14101, 3872 <- 4752, R = 16 71 : 52).
+    const ChainShape c = chain_shape(s.T, n2, s.R, false);
+    const bool one_round = (s.T + c.bm - 1) / c.bm * c.slices <= NUM_CUS;
+    if (k1 * c.slices <= 6144 ? one_round || k1 <= 1536 : one_round && k1 <= 1536 && s.T > 256) return PLAN_FUSED;
+    return PLAN_SPLIT_EXPAND;
   }
   return PLAN_TWO_GEMM;
 }

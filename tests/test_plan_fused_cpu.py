@@ -1,0 +1,19 @@
+"""Where a narrow sketch's two contractions are fused (host trace, no GPU): on either side of each line of the rule."""
+import pytest
+
+from paper_2601_15473_amd import libsk as sk
+from test_plan_choice_cpu import _kernels
+
+
+@pytest.mark.parametrize("call,shape,fused", [
+    # (tokens, in, out, R): up to 1536 long in one round of work-groups, at any number of slices
+    ("fwd", (257, 1536, 4096, 32), True), ("fwd", (257, 1552, 4096, 32), False), ("bwd_input", (1064, 5168, 1344, 128), True),
+    ("fwd", (4096, 1536, 2048, 64), True), ("fwd", (4096, 1552, 2048, 64), False), ("fwd", (4096, 1536, 4096, 64), True),
+    # length times slices up to 6144: in one round, or up to 1536 long
+    ("fwd", (16384, 3072, 3072, 64), True), ("fwd", (16448, 3072, 3072, 64), False), ("fwd", (16448, 1536, 3072, 64), True),
+    ("bwd_input", (10442, 5136, 2928, 64), False), ("bwd_input", (16384, 6144, 768, 32), True), ("bwd_input", (16384, 768, 6144, 32), True),
+    ("bwd_input", (16384, 768, 6160, 32), False),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_fused_or_split(call, shape, fused):
+    names = _kernels(call, *shape)
+    assert (len(names) == 1) == fused and names[-1] in ("chain_short", "chain_small"), names
