@@ -1189,9 +1189,9 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
   // benchmark configurations (bf16; the dual kernel is built for a few tile pairs only);
   // everything else runs the two gradients one after the other.
   const WeightPlan w = plan_weight(s);
-  // (not when Z^T is recomputed in split form: that is four launches of its own)
-  const bool bf16_auto = s.dtype == SK_BF16 && g_plan.load(std::memory_order_relaxed) == PLAN_AUTO &&
-                         !w.own_colsum && w.z_splits == 1;
+  const bool bf16_any_z = s.dtype == SK_BF16 && g_plan.load(std::memory_order_relaxed) == PLAN_AUTO && !w.own_colsum;
+  // (Z^T recomputed in ranges over a long input: a schedule of its own, for narrow sketches)
+  const bool bf16_auto = bf16_any_z && w.z_splits == 1;
   const Plan in_plan = pick_plan(s, SK_OP_BWD_INPUT, true);
   int z_tile = bf16_auto ? choose_tile(s.R, tokens, in, 1) : -1;
   const GemmKind du_kind = GEMM_NN_F32_COLSUM;
@@ -1216,19 +1216,29 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
   red.splits = w.splits; red.splits2 = w.colsum_splits;
 
   // --- narrow sketch: split-K slabs of G beside Z^T | Z^T.dY | expand dX, carrying the sums ---
+  // (Z^T in ranges: their slabs, and one more launch that sums them, four launches instead of six: 4096 tokens, 8192 -> 8192, R = 16
+  // 68.1 : 62.5 us, 1024 41.5 : 30.8; 2048, 4096 -> 4096, R = 64 39.2 : 33.3; 3000, 6000 -> 7008, R = 96 78.8 : 65.7)
   const SketchPlan q = plan_sketch(s, out);
-  if (bf16_auto && chain_supported(s.R) && s.R <= 128 && q.splits > 1 && w.splits > 1 &&
-      dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT, z_tile)) {
+  const bool z_ranges = bf16_any_z && w.z_splits > 1;
+  if (bf16_any_z && chain_supported(s.R) && s.R <= 128 && q.splits > 1 && (z_ranges || w.splits > 1) &&
+      (z_ranges ? dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT_F32, w.z_tile) : dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT, z_tile))) {
     g_hip_error.clear();
     GemmArgs g = dense_args(dY, out, U_cat, out, ws_in, s.R, tokens, s.R, out, 1.0f, nullptr);
     g.splits = q.splits; g.k_per_split = q.k_per_split;
-    hipError_t e = launch_dual_gemm_bf16(GEMM_NT_F32, q.tile, g, GEMM_TT, z_tile, z, hs);
+    float* const zpart = reinterpret_cast<float*>(ws_w + w.zpart_at());
+    if (z_ranges) { z.C = zpart; z.splits = w.z_splits; z.k_per_split = w.z_k_per_split; }
+    hipError_t e = z_ranges ? launch_dual_gemm_bf16(GEMM_NT_F32, q.tile, g, GEMM_TT_F32, w.z_tile, z, hs)
+                            : launch_dual_gemm_bf16(GEMM_NT_F32, q.tile, g, GEMM_TT, z_tile, z, hs);
     if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (dY.U^T beside x.S)");
+    if (z_ranges) {
+      e = launch_reduce_to_bf16(zpart, Z, (int64_t)s.R * w.ldz, w.z_splits, hs);
+      if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (sum of x.S)");
+    }
     ChainArgs c{};
     c.A = dY; c.B1 = U_cat; c.B2 = S_cat; c.bias = nullptr; c.C = dX;
     c.lda = out; c.ldb1 = out; c.ldb2 = s.R; c.ldc = in;
     c.M = (int)tokens; c.K1 = (int)out; c.R = s.R; c.N = (int)in; c.scale = scale;
-    { const ChainShape cs = chain_shape(tokens, in, s.R, false); c.n_slices = cs.slices; c.bm = cs.bm; }
+    { const ChainShape cs = chain_shape(tokens, in, s.R, z_ranges); c.n_slices = cs.slices; c.bm = cs.bm; }
     c.Z = ws_in; c.z_splits = q.splits; c.z_slab = (int64_t)tokens * s.R;
     // Z^T.dY, then the expansion of dX carrying the sum of the token splits
     e = launch_gemm_bf16(du_kind, w.tile, du, hs);

@@ -431,6 +431,9 @@ const DualPair kDualPairs[] = {
     {GEMM_NN_F32_COLSUM, TILE_128x128, GEMM_NT, TILE_128x128},
     {GEMM_NT, TILE_64x64, GEMM_TT, TILE_64x64},                // R = 256..384 at BERT-base width
     {GEMM_NN_F32_COLSUM, TILE_128x64, GEMM_NT, TILE_128x64},
+    {GEMM_NT_F32, TILE_64x64, GEMM_TT_F32, TILE_64x128},       // narrow sketch of a long input: Z^T in ranges as well
+    {GEMM_NT_F32, TILE_64x128, GEMM_TT_F32, TILE_128x128},
+    {GEMM_NT_F32, TILE_64x128, GEMM_TT_F32, TILE_128x64},
 };
 int dual_pair_index(GemmKind ka, int ta, GemmKind kb, int tb) {
   for (int i = 0; i < (int)(sizeof(kDualPairs) / sizeof(kDualPairs[0])); ++i)
@@ -481,6 +484,9 @@ hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKi
   typedef GemmTile<128, 128, true, false, float, true> NNFC_128x128;
   typedef GemmTile<64, 64, true, true, bf16, false> NT_64x64;
   typedef GemmTile<128, 64, true, true, bf16, false> NT_128x64;
+  typedef GemmTile<64, 128, false, true, float, false> TTF_64x128;
+  typedef GemmTile<128, 128, false, true, float, false> TTF_128x128;
+  typedef GemmTile<128, 64, false, true, float, false> TTF_128x64;
   // 64 x 64 tiles in one round, two work-groups to a CU: on the ring, as a product by itself (backward pass of 568 tokens,
   // 1216 -> 352, R = 48, 22.1 -> 17.8 us; 1024, 1024 -> 1024, R = 64, 21.0 -> 18.5; 1500, 768 -> 768, R = 192, 28.8 -> 25.5; on a
   // ring of their own the 128 x 64 tiles of the other pairs are level with the staged ones)
@@ -499,6 +505,9 @@ hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKi
     case 4: return launch_kernel(name, work, dual_gemm_kernel<NNFC_128x128, NT_128x128>, grid, block, s, a, b, (int)ga);
     case 5: return launch_kernel(name, work, dual_gemm_kernel<NT_64x64, TT_64x64>, grid, block, s, a, b, (int)ga);
     case 6: return launch_kernel(name, work, dual_gemm_kernel<NNFC_128x64, NT_128x64>, grid, block, s, a, b, (int)ga);
+    case 7: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x64, TTF_64x128>, grid, block, s, a, b, (int)ga);
+    case 8: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x128, TTF_128x128>, grid, block, s, a, b, (int)ga);
+    case 9: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x128, TTF_128x64>, grid, block, s, a, b, (int)ga);
     default: return hipErrorInvalidValue;
   }
 }
