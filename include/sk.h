@@ -64,7 +64,8 @@ typedef enum {
   SK_OP_BWD_WEIGHT = 2,
   SK_OP_BWD_WEIGHT_FIRST = 3, /* sized so that it serves any column range (asked with a smaller l or k: any
                                  range of that many columns) */
-  SK_OP_BWD = 4               /* sk_linear_bwd: both gradients in one call */
+  SK_OP_BWD = 4,              /* sk_linear_bwd: both gradients in one call */
+  SK_OP_BWD_TWO_SIDED = 5     /* sk_linear_bwd_two_sided */
 } sk_op;
 
 /*
@@ -183,6 +184,17 @@ sk_status sk_linear_bwd_weight_first(const void* x, const void* U_cat, const voi
                                      int64_t tokens, int64_t in, int64_t out, int32_t l, int32_t k,
                                      int64_t col_begin, int64_t col_count, sk_dtype dtype,
                                      void* workspace, size_t workspace_bytes, void* stream);
+
+/*
+ * The two-sided layer's whole backward pass: what sk_linear_bwd and sk_linear_bwd_weight_first with
+ * col_begin = col_count = R / 2 compute (same formulas and rounding points; the order of the fp32 partial sums of the
+ * dY . U_cat^T behind dA may differ), with those columns of dY . U_cat^T formed once where the schedule allows it.
+ *   R = l*k a multiple of 32 (else SK_ERR_UNSUPPORTED); dA [in, R / 2] fp32, dense (output).
+ * Workspace: sk_linear_workspace_bytes(SK_OP_BWD_TWO_SIDED, ...).
+ */
+sk_status sk_linear_bwd_two_sided(const void* x, const void* dY, const void* S_cat, const void* U_cat, void* dX, float* dU_cat, float* dbias,
+                                  float* dA, int64_t tokens, int64_t in, int64_t out, int32_t l, int32_t k, sk_dtype dtype,
+                                  void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * to[i][j] = bf16(from[i][j]) for j < n[i], i < count (1 to 3 arrays, 16-byte aligned), in one launch: the

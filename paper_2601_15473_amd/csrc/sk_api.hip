@@ -691,6 +691,8 @@ size_t workspace_for(sk_op op, const Shape& s) {
       const NarrowPlan n = plan_narrow(s);
       return n.ok && n.total() > two ? n.total() : two;
     }
+    case SK_OP_BWD_TWO_SIDED:   // both gradients' | what the first-stage gradient of half the columns takes by itself
+      return s.R % 32 == 0 ? workspace_for(SK_OP_BWD, s) + first_stage_bytes(s, s.R / 2) : 0;
     case SK_OP_BWD_WEIGHT_FIRST: {
       // the maximum over every admissible column count (narrow ranges split the tokens
       // further), so one buffer serves any range
@@ -751,6 +753,20 @@ GemmArgs dense_args(const void* A, int64_t lda, const void* B, int64_t ldb, void
 }
 
 
+// The last columns of G = dY . U_cat^T in the storage type, as a backward pass may leave them behind: `at` is null where
+// its schedule does not form them.  With them the two-sided layer's first-stage gradient is one product instead of two:
+// 4096 tokens, 768 -> 3072, R = 128, the whole backward pass 52.1 -> 39.9 us, seventeen drawn layers 1.18 times as fast.
+struct GColumns {
+  int64_t first;     // the first column asked for
+  void* room;        // [tokens, R - first] in the storage type, for a schedule that keeps G elsewhere
+  const void* at;
+  int64_t ld;
+  void take(const unsigned char* G, const Shape& s) {   // from the whole of G
+    at = G + (size_t)first * s.esize;
+    ld = s.R;
+  }
+};
+
 // Two fp32 products of the backward pass in one launch where both take the same tile, else in two.
 hipError_t gemm_pair_f32(GemmKind kind_a, int tile_a, const GemmArgs& a, GemmKind kind_b, int tile_b, const GemmArgs& b, hipStream_t st) {
   if (tile_a == tile_b) return launch_dual_gemm_f32(kind_a, a, kind_b, b, tile_a, st);
@@ -760,8 +776,9 @@ hipError_t gemm_pair_f32(GemmKind kind_a, int tile_a, const GemmArgs& a, GemmKin
 
 // sk_linear_bwd in fp32 (workspaces laid out as those of the two separate calls).
 sk_status bwd_f32(const Shape& s, const void* x, const void* dY, const void* S_cat, const void* U_cat, void* dX, float* dU_cat,
-                  float* dbias, unsigned char* ws_in, unsigned char* ws_w, hipStream_t hs) {
+                  float* dbias, unsigned char* ws_in, unsigned char* ws_w, GColumns* want, hipStream_t hs) {
   g_hip_error.clear();
+  if (want) want->take(ws_in, s);
   const float scale = 1.0f / (float)s.l;
   const WeightPlan w = plan_weight(s);
   const F32Plan gp = plan_f32_first(s.T, s.R, s.out), zp = plan_f32_first(s.T, s.R, s.in, slab_room(w.z_bytes));
@@ -801,6 +818,33 @@ sk_status bwd_f32(const Shape& s, const void* x, const void* dY, const void* S_c
     r.part2 = cpart; r.out2 = dbias; r.n2 = dbias ? s.out : 0; r.splits2 = w.splits; r.scale2 = 1.0f;
     e = launch_reduce_splits(r, hs);
     if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (sum of splits)");
+  }
+  return SK_OK;
+}
+
+// dA = (1 / l) . x^T . G for nc columns of G [tokens, nc], rows ldg apart; `part`: the slabs of split tokens.
+sk_status first_stage_gradient(const Shape& s, const void* x, const void* G, int64_t ldg, int64_t nc, float* dA, float* part, hipStream_t hs) {
+  // dA = scale * x^T . G, the token axis split in order
+  const TokenPlan t = plan_tokens(s.in, nc, s.T, s.dtype, false, 0);
+  GemmArgs a{};
+  a.A = x; a.lda = s.in;
+  a.B = G; a.ldb = ldg;
+  a.ldc = nc;
+  a.M = (int)s.in; a.N = (int)nc; a.K = (int)s.T;
+  a.splits = t.splits; a.k_per_split = t.k_per_split;
+  a.bias = nullptr; a.colsum = nullptr;
+  const float scale = 1.0f / (float)s.l;
+  if (t.splits == 1) { a.C = dA; a.scale = scale; }
+  else { a.C = part; a.scale = 1.0f; }
+  hipError_t e = s.dtype == SK_BF16 ? launch_gemm_bf16(GEMM_TN_F32_PLAIN, t.tile, a, hs)
+                       : launch_gemm_f32(GEMM_TN_F32, t.tile, a, hs);
+  if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd_weight_first (x^T.G)");
+  if (t.splits > 1) {
+    ReduceArgs r{};
+    r.part = part; r.out = dA; r.n = (int64_t)s.in * nc; r.scale = scale;
+    r.n2 = 0; r.splits = t.splits; r.splits2 = 1;
+    e = launch_reduce_splits(r, hs);
+    if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd_weight_first (sum of splits)");
   }
   return SK_OK;
 }
@@ -904,9 +948,10 @@ size_t sk_linear_workspace_bytes(sk_op op, int64_t tokens, int64_t in, int64_t o
                                  int32_t k, sk_dtype dtype) {
   Shape s;
   if (op != SK_OP_FWD && op != SK_OP_BWD_INPUT && op != SK_OP_BWD_WEIGHT &&
-      op != SK_OP_BWD_WEIGHT_FIRST && op != SK_OP_BWD)
+      op != SK_OP_BWD_WEIGHT_FIRST && op != SK_OP_BWD && op != SK_OP_BWD_TWO_SIDED)
     return (size_t)-1;
   if (check_shape(tokens, in, out, l, k, dtype, s) != SK_OK) return (size_t)-1;
+  if (op == SK_OP_BWD_TWO_SIDED && s.R % 32 != 0) return (size_t)-1;
   return workspace_for(op, s);
 }
 
@@ -1141,10 +1186,9 @@ sk_status sk_linear_bwd_weight_noalloc(const void* x, const void* S_cat, const v
                               SK_NOALLOC_SCRATCH_BYTES, stream);
 }
 
-sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const void* U_cat,
-                        void* dX, float* dU_cat, float* dbias, int64_t tokens, int64_t in,
-                        int64_t out, int32_t l, int32_t k, sk_dtype dtype, void* workspace,
-                        size_t workspace_bytes, void* stream) {
+static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, const void* U_cat, void* dX, float* dU_cat,
+                          float* dbias, int64_t tokens, int64_t in, int64_t out, int32_t l, int32_t k, sk_dtype dtype,
+                          void* workspace, size_t workspace_bytes, void* stream, GColumns* want) {
   if (!x || !dY || !S_cat || !U_cat || !dX || !dU_cat) return SK_ERR_INVALID_ARG;
   if (!aligned16(x) || !aligned16(dY) || !aligned16(S_cat) || !aligned16(U_cat) || !aligned16(dX) ||
       !aligned16(dU_cat) || !aligned16(dbias) || !aligned16(workspace))
@@ -1183,7 +1227,7 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
   // to four work-groups).  The same tiles and ranges as the separate calls, so the same results.
   // Backward pass, us, apart : shared: 60 tokens, 112 -> 176, R = 64, 18.8 : 11.0; 811, 1888 -> 1840, R = 32,
   // 34.5 : 25.9; 4096, 3072 -> 768, R = 128, 95 : 84; 1475, 1312 -> 288, R = 304, 51.7 : 45.0.
-  if (s.dtype == SK_F32) return bwd_f32(s, x, dY, S_cat, U_cat, dX, dU_cat, dbias, ws_in, ws_w, hs);
+  if (s.dtype == SK_F32) return bwd_f32(s, x, dY, S_cat, U_cat, dX, dU_cat, dbias, ws_in, ws_w, want, hs);
 
   // Shared-launch schedules exist for the shapes the automatic plans produce on the
   // benchmark configurations (bf16; the dual kernel is built for a few tile pairs only);
@@ -1240,6 +1284,10 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
     c.M = (int)tokens; c.K1 = (int)out; c.R = s.R; c.N = (int)in; c.scale = scale;
     { const ChainShape cs = chain_shape(tokens, in, s.R, z_ranges); c.n_slices = cs.slices; c.bm = cs.bm; }
     c.Z = ws_in; c.z_splits = q.splits; c.z_slab = (int64_t)tokens * s.R;
+    if (want) {
+      c.z_out = want->room; c.z_first = (int)want->first;
+      want->at = want->room; want->ld = s.R - want->first;
+    }
     // Z^T.dY, then the expansion of dX carrying the sum of the token splits
     e = launch_gemm_bf16(du_kind, w.tile, du, hs);
     if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (Z^T.dY)");
@@ -1278,6 +1326,7 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
     const GemmArgs g = dense_args(dY, out, U_cat, out, ws_in, s.R, tokens, s.R, out, 1.0f, nullptr);
     hipError_t e = launch_dual_gemm_bf16(GEMM_NT, g_tile, g, GEMM_TT, z_tile, z, hs);
     if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (dY.U^T beside x.S)");
+    if (want) want->take(ws_in, s);
     const GemmArgs dx = dense_args(ws_in, s.R, S_cat, s.R, dX, in, tokens, in, s.R, scale, nullptr);
     e = launch_dual_gemm_bf16(du_kind, w.tile, du, GEMM_NT, dx_tile, dx, hs);
     if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (Z^T.dY beside G.S^T)");
@@ -1291,8 +1340,16 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
   const sk_status a = sk_linear_bwd_input(dY, S_cat, U_cat, dX, tokens, in, out, l, k, dtype, ws_in,
                                           in_bytes, stream);
   if (a != SK_OK) return a;
+  if (want && in_plan == PLAN_TWO_GEMM) want->take(ws_in, s);
   return sk_linear_bwd_weight(x, S_cat, dY, dU_cat, dbias, tokens, in, out, l, k, dtype, ws_w, w_bytes,
                               stream);
+}
+
+sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const void* U_cat,
+                        void* dX, float* dU_cat, float* dbias, int64_t tokens, int64_t in,
+                        int64_t out, int32_t l, int32_t k, sk_dtype dtype, void* workspace,
+                        size_t workspace_bytes, void* stream) {
+  return bwd_both(x, dY, S_cat, U_cat, dX, dU_cat, dbias, tokens, in, out, l, k, dtype, workspace, workspace_bytes, stream, nullptr);
 }
 
 sk_status sk_linear_bwd_weight_first(const void* x, const void* U_cat, const void* dY, float* dA,
@@ -1324,28 +1381,27 @@ sk_status sk_linear_bwd_weight_first(const void* x, const void* U_cat, const voi
                             dense_args(dY, out, U_sub, out, G, nc, tokens, nc, out, 1.0f, nullptr), part, hs);
   if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd_weight_first (dY.U^T)");
 
-  // dA = scale * x^T . G, the token axis split in order
-  const TokenPlan t = plan_tokens(in, nc, tokens, dtype, false, 0);
-  GemmArgs a{};
-  a.A = x; a.lda = in;
-  a.B = G; a.ldb = nc;
-  a.ldc = nc;
-  a.M = (int)in; a.N = (int)nc; a.K = (int)tokens;
-  a.splits = t.splits; a.k_per_split = t.k_per_split;
-  a.bias = nullptr; a.colsum = nullptr;
-  if (t.splits == 1) { a.C = dA; a.scale = scale; }
-  else { a.C = part; a.scale = 1.0f; }
-  e = dtype == SK_BF16 ? launch_gemm_bf16(GEMM_TN_F32_PLAIN, t.tile, a, hs)
-                       : launch_gemm_f32(GEMM_TN_F32, t.tile, a, hs);
-  if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd_weight_first (x^T.G)");
-  if (t.splits > 1) {
-    ReduceArgs r{};
-    r.part = part; r.out = dA; r.n = (int64_t)in * nc; r.scale = scale;
-    r.n2 = 0; r.splits = t.splits; r.splits2 = 1;
-    e = launch_reduce_splits(r, hs);
-    if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd_weight_first (sum of splits)");
-  }
-  return SK_OK;
+  return first_stage_gradient(s, x, G, nc, nc, dA, part, hs);
+}
+
+sk_status sk_linear_bwd_two_sided(const void* x, const void* dY, const void* S_cat, const void* U_cat, void* dX, float* dU_cat, float* dbias,
+                                  float* dA, int64_t tokens, int64_t in, int64_t out, int32_t l, int32_t k, sk_dtype dtype,
+                                  void* workspace, size_t workspace_bytes, void* stream) {
+  if (!dA || !aligned16(dA) || !workspace || !aligned16(workspace)) return SK_ERR_INVALID_ARG;
+  Shape s;
+  const sk_status st = check_shape(tokens, in, out, l, k, dtype, s);
+  if (st != SK_OK) return st;
+  if (s.R % 32 != 0) return SK_ERR_UNSUPPORTED;   // (halves of a multiple of 16 columns)
+  if (workspace_bytes < workspace_for(SK_OP_BWD_TWO_SIDED, s)) return SK_ERR_WORKSPACE;
+  const int64_t half = s.R / 2;
+  unsigned char* const ws = static_cast<unsigned char*>(workspace);
+  const size_t both = workspace_for(SK_OP_BWD, s), room = align_up((size_t)s.T * half * s.esize);
+  GColumns want{half, ws + both, nullptr, 0};
+  const sk_status a = bwd_both(x, dY, S_cat, U_cat, dX, dU_cat, dbias, tokens, in, out, l, k, dtype, workspace, both, stream, &want);
+  if (a != SK_OK) return a;
+  if (want.at == nullptr)
+    return sk_linear_bwd_weight_first(x, U_cat, dY, dA, tokens, in, out, l, k, half, half, dtype, ws + both, workspace_bytes - both, stream);
+  return first_stage_gradient(s, x, want.at, want.ld, half, dA, reinterpret_cast<float*>(ws + both + room), static_cast<hipStream_t>(stream));
 }
 
 sk_status sk_round_gradients(const float* const* from, void* const* to, const int64_t* n, int32_t count, void* stream) {

@@ -548,6 +548,9 @@ __device__ __forceinline__ void chain_small(const ChainArgs& p) {
       w.x = pack_bf16x2(sum[i].x, sum[i].y);
       w.y = pack_bf16x2(sum[i].z, sum[i].w);
       *reinterpret_cast<uint2*>(Zs + r * L::Z_LD + c) = w;
+      // (asked for: the token tile's first work-group leaves its columns behind)
+      if (p.z_out != nullptr && slice == 0 && c >= p.z_first && c < p.R && m0 + r < p.M)
+        *reinterpret_cast<uint2*>(static_cast<bf16*>(p.z_out) + (int64_t)(m0 + r) * (p.R - p.z_first) + (c - p.z_first)) = w;
     }
     }  // h
   }
@@ -1050,6 +1053,7 @@ hipError_t launch_chain_bf16(bool b_kc, bool fused, ChainArgs a, hipStream_t s) 
   if (a.bm == 0) a.bm = CH_BM;
   if (a.bm != CH_BM && !(a.bm == 128 && a.R <= 128)) return hipErrorInvalidValue;
   if (fused && a.tail.n + a.tail.n2 > 0) return hipErrorInvalidValue;   // (no plan asks a fused launch to carry one)
+  if (a.z_out != nullptr && (fused || a.z_splits == 0 || a.R > 128)) return hipErrorInvalidValue;
   a.tiles_m = (a.M + a.bm - 1) / a.bm;
   if (tracing()) {
     if (fused) {
@@ -1063,6 +1067,7 @@ hipError_t launch_chain_bf16(bool b_kc, bool fused, ChainArgs a, hipStream_t s) 
     note_matrix(a.B2, b_kc ? a.N : a.R, b_kc ? a.R : a.N, a.ldb2, 2, false);
     if (a.bias != nullptr) note_matrix(a.bias, 1, a.N, a.N, 2, false);
     note_matrix(a.C, a.M, a.N, a.ldc, 2, true);
+    note_matrix(a.z_out, a.M, a.R - a.z_first, a.R - a.z_first, 2, true);
     note_reduce(a.tail);
   }
   if (b_kc) return fused ? launch_rt<true, true>(a, s) : launch_rt<true, false>(a, s);

@@ -222,6 +222,9 @@ struct ChainArgs {
   int bm;              // rows of a token tile: 64 (0 means 64), or 128 for R <= 128
   int tiles_m;         // filled in by the launcher
   float scale;
+  // The summed intermediate's columns z_first .. R - 1 rounded to bf16, dense (slabs and R <= 128 only; null: not wanted)
+  void* z_out;
+  int z_first;
   // An unrelated split reduction that this launch carries along (narrow-sketch kernels
   // only; tail.n + tail.n2 == 0 for none): its pieces are dealt over the work-groups,
   // which saves the reduction a launch of its own.

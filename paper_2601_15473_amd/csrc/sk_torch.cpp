@@ -229,17 +229,14 @@ struct LinearTwoSided : torch::autograd::Function<LinearTwoSided> {
     }
     void* const stream = stream_of(x2.device());
     const int32_t l2 = 2 * kept.l;
-    // (the second query plans every range a sketch of the given width has: `half` columns are asked for)
-    const size_t need = std::max(sk_linear_workspace_bytes(SK_OP_BWD, tokens, in, out, l2, kept.k, dt),
-                                 sk_linear_workspace_bytes(SK_OP_BWD_WEIGHT_FIRST, tokens, in, out, kept.l, kept.k, dt));
+    const size_t need = sk_linear_workspace_bytes(SK_OP_BWD_TWO_SIDED, tokens, in, out, l2, kept.k, dt);
     {
       Workspaces& w = workspaces();
       const std::lock_guard<std::mutex> lock(w.mutex);
       const Tensor& ws = w.get(x2.device(), stream, need);
-      check(sk_linear_bwd(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), dB.data_ptr<float>(),
-                          kept.bias ? db.data_ptr<float>() : nullptr, tokens, in, out, l2, kept.k, dt, ws.data_ptr(), (size_t)ws.numel(), stream));
-      check(sk_linear_bwd_weight_first(x2.data_ptr(), B.data_ptr(), dY.data_ptr(), dA.data_ptr<float>(), tokens, in, out, l2, kept.k, half, half,
-                                       dt, ws.data_ptr(), (size_t)ws.numel(), stream));
+      check(sk_linear_bwd_two_sided(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), dB.data_ptr<float>(),
+                                    kept.bias ? db.data_ptr<float>() : nullptr, dA.data_ptr<float>(), tokens, in, out, l2, kept.k, dt,
+                                    ws.data_ptr(), (size_t)ws.numel(), stream));
       if (round.count > 0) check(sk_round_gradients(round.from, round.to, round.n, round.count, stream));
     }
     return {in_shape(ctx, dX), dB_out, dA_out, db_out, Tensor(), Tensor(), Tensor(), Tensor()};

@@ -28,7 +28,7 @@ LIB_PATH = os.path.join(_HERE, "lib", "libsk.so")
 SK_OK, SK_ERR_INVALID_ARG, SK_ERR_UNSUPPORTED, SK_ERR_WORKSPACE, SK_ERR_HIP = range(5)
 SK_F32, SK_BF16 = 0, 1
 SK_NOALLOC_SCRATCH_BYTES = 32 << 20   # fixed scratch of sk_linear_bwd_weight_noalloc
-SK_OP_FWD, SK_OP_BWD_INPUT, SK_OP_BWD_WEIGHT, SK_OP_BWD_WEIGHT_FIRST, SK_OP_BWD = 0, 1, 2, 3, 4
+SK_OP_FWD, SK_OP_BWD_INPUT, SK_OP_BWD_WEIGHT, SK_OP_BWD_WEIGHT_FIRST, SK_OP_BWD, SK_OP_BWD_TWO_SIDED = range(6)
 DTYPES = {"f32": SK_F32, "bf16": SK_BF16}
 
 if not os.path.exists(LIB_PATH):
@@ -55,6 +55,8 @@ _lib.sk_linear_bwd.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp] + _tail
 _lib.sk_linear_bwd_weight_first.restype = ctypes.c_int
 _lib.sk_linear_bwd_weight_first.argtypes = [_vp, _vp, _vp, _vp, _i64, _i64, _i64, _i32, _i32, _i64, _i64,
                                             ctypes.c_int, _vp, _sz, _vp]
+_lib.sk_linear_bwd_two_sided.restype = ctypes.c_int
+_lib.sk_linear_bwd_two_sided.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp] + _tail
 _lib.sk_round_gradients.restype = ctypes.c_int
 _lib.sk_round_gradients.argtypes = [ctypes.POINTER(_vp), ctypes.POINTER(_vp), ctypes.POINTER(_i64), _i32, _vp]
 _lib.sk_linear_workspace_bytes.restype = _sz
@@ -98,7 +100,7 @@ DEBUG_EXPORTS = ("sk_set_tuning", "sk_trace_begin", "sk_trace_end", "sk_trace_ke
 
 EXPORTS = ("sk_linear_fwd", "sk_linear_bwd_input", "sk_linear_bwd_weight", "sk_linear_bwd",
            "sk_linear_bwd_weight_first", "sk_linear_bwd_weight_noalloc",
-           "sk_round_gradients", "sk_linear_workspace_bytes", "sk_status_string", "sk_last_hip_error", "sk_set_plan")
+           "sk_linear_bwd_two_sided", "sk_round_gradients", "sk_linear_workspace_bytes", "sk_status_string", "sk_last_hip_error", "sk_set_plan")
 
 
 class SkError(RuntimeError):
@@ -163,6 +165,13 @@ def sk_linear_bwd_weight_first(x, U_cat, dY, dA, tokens, d_in, d_out, l, k, col_
     return _lib.sk_linear_bwd_weight_first(_ptr(x), _ptr(U_cat), _ptr(dY), _ptr(dA),
                                            tokens, d_in, d_out, l, k, col_begin, col_count, dtype,
                                            _ptr(workspace), workspace_bytes, _stream(stream))
+
+
+def sk_linear_bwd_two_sided(x, dY, S_cat, U_cat, dX, dU_cat, dbias, dA, tokens, d_in, d_out, l, k, dtype,
+                            workspace, workspace_bytes, stream=None):
+    return _lib.sk_linear_bwd_two_sided(_ptr(x), _ptr(dY), _ptr(S_cat), _ptr(U_cat), _ptr(dX), _ptr(dU_cat),
+                                        _ptr(dbias), _ptr(dA), tokens, d_in, d_out, l, k, dtype,
+                                        _ptr(workspace), workspace_bytes, _stream(stream))
 
 
 def sk_round_gradients(sources, targets, counts, stream=None):

@@ -301,17 +301,13 @@ class SKLinearTwoSidedFunction(torch.autograd.Function):
         dev = dY.device
         with _on(dev):
             stream = _stream(dev)
-            # (the query plans every range a sketch of the given width has: `half` columns are asked for)
-            need = max(sk.sk_linear_workspace_bytes(sk.SK_OP_BWD, *ctx.args),
-                       sk.sk_linear_workspace_bytes(sk.SK_OP_BWD_WEIGHT_FIRST, tokens, d_in, d_out, l2 // 2, k, dt))
+            need = sk.sk_linear_workspace_bytes(sk.SK_OP_BWD_TWO_SIDED, *ctx.args)
             ws = _workspace(dev, stream, need)
             dX = torch.empty((tokens, d_in), dtype=dtype, device=dev)
             db = torch.empty((d_out,), dtype=torch.float32, device=dev) if ctx.has_bias else None
             dA = torch.empty((d_in, half), dtype=torch.float32, device=dev)
             dB = torch.empty((2 * half, d_out), dtype=torch.float32, device=dev)
-            sk.check(sk.sk_linear_bwd(x2, dY2, A_cat, B_cat, dX, dB, db, *ctx.args, ws, ws.numel(), stream))
-            sk.check(sk.sk_linear_bwd_weight_first(x2, B_cat, dY2, dA, tokens, d_in, d_out, l2, k,
-                                                   half, half, dt, ws, ws.numel(), stream))
+            sk.check(sk.sk_linear_bwd_two_sided(x2, dY2, A_cat, B_cat, dX, dB, db, dA, *ctx.args, ws, ws.numel(), stream))
             dB = dB[:half]   # (the rest belongs to S2^T: gradients of fixed numbers, dropped)
             if dtype != torch.float32:
                 db, dA, dB = _in_type((db, dA, dB), dtype)
