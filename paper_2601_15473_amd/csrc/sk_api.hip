@@ -563,7 +563,8 @@ Plan pick_plan(const Shape& s, sk_op op, bool workspace) {
     // (10442 tokens, 2928 <- 5136, R = 64 75 : 48; 14101, 3872 <- 4752, R = 16 71 : 52).
     const ChainShape c = chain_shape(s.T, n2, s.R, false);
     const bool one_round = (s.T + c.bm - 1) / c.bm * c.slices <= NUM_CUS;
-    if (k1 * c.slices <= 6144 ? one_round || k1 <= 1536 : one_round && k1 <= 1536 && s.T > 256) return PLAN_FUSED;
+    // (but for a caller without a workspace, whose only plan it is)
+    if (k1 * c.slices <= 6144 ? one_round || k1 <= 1536 || !workspace : one_round && k1 <= 1536 && s.T > 256) return PLAN_FUSED;
     return PLAN_SPLIT_EXPAND;
   }
   return PLAN_TWO_GEMM;

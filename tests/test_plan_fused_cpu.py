@@ -17,3 +17,18 @@ from test_plan_choice_cpu import _kernels
 def test_fused_or_split(call, shape, fused):
     names = _kernels(call, *shape)
     assert (len(names) == 1) == fused and names[-1] in ("chain_short", "chain_small"), names
+
+
+@pytest.mark.parametrize("call,shape,taken", [
+    # long walks in more than a round, which a workspace would have split, and walks too long for any
+    ("fwd", (16448, 3072, 3072, 64), True), ("bwd_input", (10442, 5136, 1152, 64), True), ("bwd_input", (16448, 768, 6144, 32), True),
+    ("bwd_input", (16448, 768, 6160, 32), False), ("fwd", (257, 1552, 4096, 32), False), ("fwd", (257, 6160, 768, 32), False),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_calls_without_a_workspace(call, shape, taken):
+    args = (*shape[:3], 1, shape[3], sk.SK_BF16)
+    P = [i << 44 for i in range(1, 6)]
+    sk.sk_trace_begin()
+    st = sk.sk_linear_fwd(*P, *args, None, 0) if call == "fwd" else sk.sk_linear_bwd_input(*P[:4], *args, None, 0)
+    names = [n for n, _ in sk.sk_trace_kernels()]
+    sk.sk_trace_end()
+    assert st == (sk.SK_OK if taken else sk.SK_ERR_WORKSPACE) and len(names) == int(taken), (st, names)
