@@ -319,12 +319,7 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const ReduceArgs p) 
     part = p.part2; out = p.out2; n = p.n2; scale = p.scale2; splits = p.splits2;
     if (i4 >= n) return;
   }
-  float4 s = *reinterpret_cast<const float4*>(part + i4);
-#pragma unroll 8
-  for (int k = 1; k < splits; ++k) {
-    const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)k * n + i4);
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-  }
+  float4 s = sum_slabs(part + i4, n, splits);
   s.x *= scale; s.y *= scale; s.z *= scale; s.w *= scale;
   *reinterpret_cast<float4*>(out + i4) = s;
 }
@@ -336,12 +331,7 @@ __global__ __launch_bounds__(256) void reduce_to_bf16_kernel(const float* __rest
                                                              int splits) {
   const int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i4 >= n) return;
-  float4 s = *reinterpret_cast<const float4*>(part + i4);
-#pragma unroll 8
-  for (int k = 1; k < splits; ++k) {
-    const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)k * n + i4);
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-  }
+  const float4 s = sum_slabs(part + i4, n, splits);
   uint2 w;
   w.x = pack_bf16x2(s.x, s.y);
   w.y = pack_bf16x2(s.z, s.w);
@@ -519,12 +509,7 @@ __global__ __launch_bounds__(256) void reduce_splits_2d_kernel(const float* __re
   const int r = blockIdx.y;
   if (c >= cols) return;
   const int64_t n = (int64_t)rows * cols, at = (int64_t)r * cols + c;
-  float4 s = *reinterpret_cast<const float4*>(part + at);
-#pragma unroll 8
-  for (int k = 1; k < splits; ++k) {
-    const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)k * n + at);
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-  }
+  const float4 s = sum_slabs(part + at, n, splits);
   *reinterpret_cast<float4*>(out + (int64_t)r * ld_out + c) =
       make_float4(s.x * scale, s.y * scale, s.z * scale, s.w * scale);
 }

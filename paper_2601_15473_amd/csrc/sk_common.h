@@ -62,6 +62,70 @@ struct ReduceArgs {
   float scale, scale2;
 };
 
+// s[u] (+)= slabs k .. k + N - 1 of piece u, in that order, behind one wait for all of them.
+template <int N, int U, bool FIRST>
+__device__ __forceinline__ void add_slabs(float4 (&s)[U], const float* const (&src)[U], int64_t n, int k) {
+  float4 v[N][U];
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[j][u] = *reinterpret_cast<const float4*>(src[u] + (int64_t)(k + j) * n);
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (FIRST && j == 0) s[u] = v[0][u];
+      else { s[u].x += v[j][u].x; s[u].y += v[j][u].y; s[u].z += v[j][u].z; s[u].w += v[j][u].w; }
+    }
+}
+
+// Sums of U pieces over `splits` slabs n elements apart, in index order.  Bound by trips to memory: a sum's launch is
+// over in a few of them, and the slabs come from other XCDs' writes.  A loop over the slabs that the compiler
+// unrolled eight times took the rest of a division by eight one trip each; here eight slabs (four, of several pieces)
+// and what is left behind them are one trip each.
+template <int U>
+__device__ __forceinline__ void sum_slabs(float4 (&s)[U], const float* const (&src)[U], int64_t n, int splits) {
+  constexpr int B = U == 1 ? 8 : 4;
+  int k = 0;
+  if (splits >= B) {
+    add_slabs<B, U, true>(s, src, n, 0);
+    for (k = B; k + B <= splits; k += B) add_slabs<B, U, false>(s, src, n, k);
+  } else {
+    switch (splits) {   // (uniform)
+      case 1: return add_slabs<1, U, true>(s, src, n, 0);
+      case 2: return add_slabs<2, U, true>(s, src, n, 0);
+      case 3: return add_slabs<3, U, true>(s, src, n, 0);
+    }
+    if constexpr (B == 8) {
+      switch (splits) {
+        case 4: return add_slabs<4, U, true>(s, src, n, 0);
+        case 5: return add_slabs<5, U, true>(s, src, n, 0);
+        case 6: return add_slabs<6, U, true>(s, src, n, 0);
+        case 7: return add_slabs<7, U, true>(s, src, n, 0);
+      }
+    }
+  }
+  switch (splits - k) {
+    case 1: return add_slabs<1, U, false>(s, src, n, k);
+    case 2: return add_slabs<2, U, false>(s, src, n, k);
+    case 3: return add_slabs<3, U, false>(s, src, n, k);
+  }
+  if constexpr (B == 8) {
+    switch (splits - k) {
+      case 4: return add_slabs<4, U, false>(s, src, n, k);
+      case 5: return add_slabs<5, U, false>(s, src, n, k);
+      case 6: return add_slabs<6, U, false>(s, src, n, k);
+      case 7: return add_slabs<7, U, false>(s, src, n, k);
+    }
+  }
+}
+__device__ __forceinline__ float4 sum_slabs(const float* src, int64_t n, int splits) {
+  float4 s[1];
+  const float* const one[1] = {src};
+  sum_slabs<1>(s, one, n, splits);
+  return s[0];
+}
+
 // One segment of a split reduction, the part that falls to work-group `block` of `nblocks`
 // (256 threads each): 16-byte pieces are dealt round-robin, U per thread and pass so that
 // their loads overlap; every piece sums its slabs in index order.  Every load is
@@ -81,16 +145,7 @@ __device__ __forceinline__ void reduce_segment_pass(const float* __restrict__ pa
       src[u] = part + (q < pieces ? q : q0) * 4;
     }
     float4 s[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) s[u] = *reinterpret_cast<const float4*>(src[u]);
-#pragma unroll 8
-    for (int k = 1; k < splits; ++k) {
-      float4 v[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4*>(src[u] + (int64_t)k * n);
-#pragma unroll
-      for (int u = 0; u < U; ++u) { s[u].x += v[u].x; s[u].y += v[u].y; s[u].z += v[u].z; s[u].w += v[u].w; }
-    }
+    sum_slabs<U>(s, src, n, splits);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t q = q0 + u * stride;
