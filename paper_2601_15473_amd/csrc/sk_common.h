@@ -82,7 +82,9 @@ __device__ __forceinline__ void add_slabs(float4 (&s)[U], const float* const (&s
 // Sums of U pieces over `splits` slabs n elements apart, in index order.  Bound by trips to memory: a sum's launch is
 // over in a few of them, and the slabs come from other XCDs' writes.  A loop over the slabs that the compiler
 // unrolled eight times took the rest of a division by eight one trip each; here eight slabs (four, of several pieces)
-// and what is left behind them are one trip each.
+// and what is left behind them are one trip each. Us, before : now: forward of 8 tokens, 4096 -> 11008, R = 2048,
+// eight slabs, 19.1 : 17.6; training step of 4096 tokens, 768 -> 3072, R = 128, five slabs beside the expansion, 45.7 : 44.1;
+// 4001, 768 -> 768, R = 384, 49.5 : 47.9.
 template <int U>
 __device__ __forceinline__ void sum_slabs(float4 (&s)[U], const float* const (&src)[U], int64_t n, int splits) {
   constexpr int B = U == 1 ? 8 : 4;
