@@ -353,24 +353,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // One work-group owns 512 columns of one run: a wave reads one whole 1 KB row segment
 // per instruction (lane = 8 columns), sixteen of them in flight, the four waves stride over the
 // rows, and their four partial sums meet in LDS and are added in wave order.
+// (As a loop unrolled sixteen times by the compiler the last rows of a run, up to fifteen a wave, were one trip each: backward pass of 8192 tokens,
+// 3072 -> 8192, R = 2048, 648 us, now 640; 9001, 4096 -> 8192 915 : 909; level where the sums ride beside a round of tiles.)
 constexpr int COLSUM_COLS = 512;
 __device__ __forceinline__ void colsum_body(const unsigned short* __restrict__ in, float* __restrict__ out,
                                             int rows, int cols, int rows_per_split, int bx, int by, float* part) {
-  constexpr int NW = 4, PLD = COLSUM_COLS + 8;
+  constexpr int NW = 4, AHEAD = 16, PLD = COLSUM_COLS + 8;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = bx * COLSUM_COLS + lane * 8;
   const int r_begin = by * rows_per_split;
   const int r_end = (r_begin + rows_per_split < rows) ? r_begin + rows_per_split : rows;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (c < cols) {
-#pragma unroll 16
-    for (int r = r_begin + wave; r < r_end; r += NW) {
-      const uint4 v = *reinterpret_cast<const uint4*>(in + (int64_t)r * cols + c);
-      const unsigned w[4] = {v.x, v.y, v.z, v.w};
+    for (int r = r_begin + wave; r < r_end; r += AHEAD * NW) {
+      uint4 v[AHEAD];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc[2 * e] += __builtin_bit_cast(float, w[e] << 16);
-        acc[2 * e + 1] += __builtin_bit_cast(float, w[e] & 0xffff0000u);
+      for (int u = 0; u < AHEAD; ++u) {   // (past the run: its last row again, not added)
+        const int at = r + u * NW < r_end ? r + u * NW : r_end - 1;
+        v[u] = *reinterpret_cast<const uint4*>(in + (int64_t)at * cols + c);
+      }
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        const bool in_run = r + u * NW < r_end;
+        const unsigned w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[2 * e] += in_run ? __builtin_bit_cast(float, w[e] << 16) : 0.f;
+          acc[2 * e + 1] += in_run ? __builtin_bit_cast(float, w[e] & 0xffff0000u) : 0.f;
+        }
       }
     }
   }

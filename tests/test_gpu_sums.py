@@ -31,3 +31,20 @@ def test_every_slab_once(sk, tuning, splits, d_out, R, dtype):  # noqa: F811
             sk.check(sk.sk_linear_bwd_weight(x, S, dY, dU, db, *shape, ws, need))
         torch.cuda.synchronize()
         assert torch.equal(dU.double(), want) and torch.equal(db.double(), dY.double().sum(0)), both
+
+
+@pytest.mark.parametrize("T", [1, 5, 63, 65, 700, 4001])
+def test_column_sums_of_their_own(sk, tuning, T):  # noqa: F811
+    """The column sums beside the 256 x 256 tile: runs of less than a batch of rows, of one and of several with a rest."""
+    tuning(sk.SK_TUNE_WTILE, 0)
+    d_in, d_out, R = 64, 1040, 256
+    g = torch.Generator(device="cuda").manual_seed(T)
+    dY = torch.randint(-8, 9, (T, d_out), generator=g, device="cuda").bfloat16()
+    x, S = torch.zeros(T, d_in, device="cuda").bfloat16(), torch.zeros(d_in, R, device="cuda").bfloat16()
+    shape = (T, d_in, d_out, 1, R, libsk.DTYPES["bf16"])
+    need = sk.sk_linear_workspace_bytes(sk.SK_OP_BWD_WEIGHT, *shape)
+    ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+    dU, db = torch.empty(R, d_out, device="cuda"), torch.empty(d_out, device="cuda")
+    sk.check(sk.sk_linear_bwd_weight(x, S, dY, dU, db, *shape, ws, need))
+    torch.cuda.synchronize()
+    assert torch.equal(db.double(), dY.double().sum(0)) and not dU.any()
