@@ -86,8 +86,13 @@ def test_outputs(T, d_in, d_out, l, k, dtype, shares):
     want = x.double().cpu().T @ (dY.double().cpu() @ U[half:].double().cpu().T) / l
     # bounds: the repository's bars, here over whole tensors: G rounded to 8 bits once, or fp32 sums
     bar = 1e-2 if dtype == "bf16" else 1e-5
-    for got in (one.dA, two.dA):
-        assert float((got.double().cpu() - want).norm() / want.norm()) < bar
+    off = [float((got.double().cpu() - want).norm() / want.norm()) for got in (one.dA, two.dA)]
+    assert max(off) < bar
+    if dtype == "bf16":
+        # The sums of G in another order, before the same single rounding: what the rounding leaves (2^-9 / sqrt(3) of it) is
+        # the error of both, and only elements whose fp32 sums lie on either side of a rounding boundary differ.  Twenty-five layers on two
+        # seeds: the error 1.000004 times the separate call's on average, at most 1.0003.
+        assert off[0] < 1.005 * off[1], off
     if shares is not None:
         sk.sk_profile_begin(32)
         sk.check(call())
