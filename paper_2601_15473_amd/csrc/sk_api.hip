@@ -559,12 +559,19 @@ Plan pick_plan(const Shape& s, sk_op op, bool workspace) {
     // ... and, the walk of a work-group on rings being the shorter one, a contraction of up to 1536 in one round of them at
     // any number of slices past the few tokens above (fused : split, us: 4053 tokens, 1280 -> 2144, R = 48 13.1 : 17.3; 3813,
     // 1344 <- 2912, R = 128 18.5 : 25.0; 1064, 1344 -> 5168, R = 128 13.5 : 17.0; 417, 1408 <- 832, R = 64 8.9 : 9.2; 300,
-    // 1792 -> 4096, R = 32 10.1 : 9.0; from 2500 on split is ahead nearly always, 1693, 3520 <- 496 15.8 : 9.6).  A long walk in more than a round is not fused either
-    // (10442 tokens, 2928 <- 5136, R = 64 75 : 48; 14101, 3872 <- 4752, R = 16 71 : 52).
+    // 1792 -> 4096, R = 32 10.1 : 9.0; from 2500 on split is ahead nearly always, 1693, 3520 <- 496 15.8 : 9.6).
     const ChainShape c = chain_shape(s.T, n2, s.R, false);
-    const bool one_round = (s.T + c.bm - 1) / c.bm * c.slices <= NUM_CUS;
-    // (but for a caller without a workspace, whose only plan it is)
-    if (k1 * c.slices <= 6144 ? one_round || k1 <= 1536 || !workspace : one_round && k1 <= 1536 && s.T > 256) return PLAN_FUSED;
+    const int64_t groups = (s.T + c.bm - 1) / c.bm * c.slices;
+    const bool one_round = groups <= NUM_CUS;
+    // Past a round a longer walk is fused where no slice repeats it and no round is nearly empty: above R = 64 at any number
+    // of work-groups, up to R = 64 from one and a half rounds on (such work-groups share a CU, so a few past a round make it
+    // last twice as long).  470 layers of 8192 to 70000 tokens, contractions of 1552 to 6144, time fused over split, median (least to most):
+    // 64-row tiles R > 64 0.94 (0.82-1.02), R <= 64 up to 1.5 rounds 1.06 (0.91-1.20); 128-row tiles R > 64 0.87 (0.70-1.00), R <= 64
+    // up to 1.5 rounds 1.04 (0.93-1.20), past it 0.88 (0.80-1.02); two and more slices, 64 rows 1.12 (0.95-1.57), 128 rows 1.02 (0.92-1.29).
+    // Input gradient of 65536 tokens, 768 -> 3072, R = 128 125 : 147 us; of 10442, 5136 -> 2928, R = 64 (two slices) 75 : 48.
+    const bool long_walk = c.slices == 1 && (s.R > 64 || groups * 2 > 3 * NUM_CUS);
+    // (a caller without a workspace has no other plan)
+    if (k1 * c.slices <= 6144 ? one_round || k1 <= 1536 || long_walk || !workspace : one_round && k1 <= 1536 && s.T > 256) return PLAN_FUSED;
     return PLAN_SPLIT_EXPAND;
   }
   return PLAN_TWO_GEMM;

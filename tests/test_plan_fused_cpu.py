@@ -13,6 +13,13 @@ from test_plan_choice_cpu import _kernels
     ("fwd", (16384, 3072, 3072, 64), True), ("fwd", (16448, 3072, 3072, 64), False), ("fwd", (16448, 1536, 3072, 64), True),
     ("bwd_input", (10442, 5136, 2928, 64), False), ("bwd_input", (16384, 6144, 768, 32), True), ("bwd_input", (16384, 768, 6144, 32), True),
     ("bwd_input", (16384, 768, 6160, 32), False),
+    # a longer walk past a round: above R = 64, or from one and a half rounds on, where no slice repeats it; 64-row tiles ...
+    ("fwd", (16448, 3072, 3072, 80), True), ("fwd", (24576, 3072, 3072, 64), False), ("fwd", (24577, 3072, 3072, 64), True),
+    ("bwd_input", (20000, 768, 3072, 128), True), ("fwd", (16448, 3072, 3088, 128), False), ("bwd_input", (24747, 4576, 2864, 96), False),
+    # ... and 128-row ones
+    ("bwd_input", (65536, 768, 3072, 128), True), ("fwd", (262144, 3072, 768, 64), True), ("fwd", (32832, 3072, 768, 96), True),
+    ("fwd", (49152, 1552, 768, 64), False), ("fwd", (49153, 1552, 768, 64), True), ("fwd", (65536, 2048, 3088, 128), False),
+    ("fwd", (65536, 6144, 768, 128), True), ("fwd", (65536, 6160, 768, 128), False),
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_fused_or_split(call, shape, fused):
     names = _kernels(call, *shape)
