@@ -997,26 +997,26 @@ static hipError_t launch_small_mb(const ChainArgs& a, hipStream_t s) {
   // runs of 4, 13.5 : 12.4).
   const int run = ((a.N + CS_BN - 1) / CS_BN + a.n_slices - 1) / a.n_slices;
   const bool brief = run <= (MB == 64 ? 3 : 2) || a.tiles_m == 1;
-  // Fused launches of 64-row tiles run on rings but for the long runs of a narrow sketch in more than a round: there
-  // the rings and the finished tiles would leave room for one work-group on a CU instead of two ([12128 x 1728] -> 3872,
-  // R = 16, 46.2 us on rings, 35.6 without; [11483 x 624] -> 3328, R = 32, 29.7, 23.9).
+  // Fused launches of 64-row tiles run on rings but for those of a narrow sketch in more than a round: there the rings and the
+  // finished tiles would leave room for one work-group on a CU (of short runs, two) instead of two and more, us, on rings : without:
+  // [12128 x 1728] -> 3872, R = 16, 46.2 : 35.6; [11483 x 624] -> 3328, R = 32, 29.7 : 23.9; short runs, [17339 x 512] -> 176, R = 32,
+  // 11.5 : 10.6; [22078 x 112] -> 192, R = 32, 9.2 : 8.6.
+  const bool ring = RT > 64 || grid <= NUM_CUS;
   const Work work = chain_work(a, FUSED);
   if constexpr (FUSED && MB == 64) {
-    if (brief || RT > 64 || grid <= NUM_CUS) {
+    if (ring) {
       static const std::string names[2] = {kernel_label("chain_small_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC), lbl(true)}),
                                            kernel_label("chain_short_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC), lbl(true)})};
       return brief ? launch_kernel(names[1].c_str(), work, chain_short_kernel<MB, RT, B2_KC, FUSED, B1_KC, true>, dim3((unsigned)grid), dim3(256), s, a)
                    : launch_kernel(names[0].c_str(), work, chain_small_kernel<MB, RT, B2_KC, FUSED, B1_KC, true>, dim3((unsigned)grid), dim3(256), s, a);
     }
   }
-  if constexpr (!(FUSED && MB == 64)) {   // (fused, 64 rows: brief runs are the rings')
+  if constexpr (!(FUSED && MB == 64 && RT > 64)) {
     if (brief) {
       static const std::string name =
           kernel_label("chain_short_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC)});
       return launch_kernel(name.c_str(), work, chain_short_kernel<MB, RT, B2_KC, FUSED, B1_KC>, dim3((unsigned)grid), dim3(256), s, a);
     }
-  }
-  if constexpr (!(FUSED && MB == 64 && RT > 64)) {
     static const std::string name =
         kernel_label("chain_small_kernel", {lbl(MB), lbl(RT), lbl(B2_KC), lbl(FUSED), lbl(B1_KC)});
     return launch_kernel(name.c_str(), work, chain_small_kernel<MB, RT, B2_KC, FUSED, B1_KC>, dim3((unsigned)grid), dim3(256), s, a);

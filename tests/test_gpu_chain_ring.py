@@ -35,6 +35,21 @@ def test_long_runs_of_a_narrow_sketch(sk, tuning, tokens, ring):  # noqa: F811
     assert name.startswith("chain_small_kernel<64, 64,") and name.endswith("true>") == ring, name
 
 
+@pytest.mark.parametrize("tokens,R,ring", [(64 * 256, 32, True), (64 * 256 + 1, 32, False), (64 * 256 + 1, 80, True)])
+def test_short_runs_past_a_round(sk, tuning, tokens, R, ring):  # noqa: F811
+    """Three output tiles, the last one ragged: a narrow sketch leaves the rings with the first work-group past a round."""
+    # bound of check_all: the repository's bf16 bar (the intermediate and the result rounded to 8 bits once each)
+    w = W.Workload("chain_short_round", tokens, 208, 272, 1, R, "bf16", seed=4)
+    check_all(sk, w, 1)
+    sk.sk_set_plan(1)
+    try:
+        for call in ("fwd", "bwd_input"):
+            name, = _kernels_of(sk, DeviceLayer(W.generate(w), sk), (call,))
+            assert name.startswith("chain_short_kernel<64, ") and (name.count(",") == 5) == ring, name
+    finally:
+        sk.sk_set_plan(0)
+
+
 @pytest.mark.parametrize("R", [16, 48, 80])
 def test_infinities_stay_in_their_rows(sk, tuning, R):  # noqa: F811
     """As in the plan of two GEMMs: sketch columns the kernel pads with meet no infinity of x."""
