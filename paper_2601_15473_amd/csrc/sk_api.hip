@@ -1270,9 +1270,12 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
   // --- narrow sketch: split-K slabs of G beside Z^T | Z^T.dY | expand dX, carrying the sums ---
   // (Z^T in ranges: their slabs, and one more launch that sums them, four launches instead of six: 4096 tokens, 8192 -> 8192, R = 16
   // 68.1 : 62.5 us, 1024 41.5 : 30.8; 2048, 4096 -> 4096, R = 64 39.2 : 33.3; 3000, 6000 -> 7008, R = 96 78.8 : 65.7)
+  // Not where dX by itself is one fused launch that nearly fills the chip while the slabs of G are large: from 9600 tokens on, R > 64
+  // (13476 tokens, 2400 -> 336, R = 112 75.4 us here, one after the other 63.2; 15303, 5600 -> 416, R = 128 158.8 : 128.8; 30 layers of
+  // 9934 to 15489 tokens 0.98 to 1.23 times the time, below that 0.84 to 1.11, and 0.97 at the median).
   const SketchPlan q = plan_sketch(s, out);
-  const bool z_ranges = bf16_any_z && w.z_splits > 1;
-  if (bf16_any_z && chain_supported(s.R) && s.R <= 128 && q.splits > 1 && (z_ranges || w.splits > 1) &&
+  const bool z_ranges = bf16_any_z && w.z_splits > 1 && !(in_plan == PLAN_FUSED && s.R > 64 && tokens > 9600);
+  if (bf16_any_z && chain_supported(s.R) && s.R <= 128 && q.splits > 1 && (z_ranges || (w.z_splits == 1 && w.splits > 1)) &&
       (z_ranges ? dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT_F32, w.z_tile) : dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT, z_tile))) {
     g_hip_error.clear();
     GemmArgs g = dense_args(dY, out, U_cat, out, ws_in, s.R, tokens, s.R, out, 1.0f, nullptr);

@@ -44,6 +44,11 @@ RANGES = ["few_rows", "reduce_to_bf16", "few_rows"]
     ("fwd", (2048, 768, 768, 128), ["chain_short"]), ("fwd", (4096, 768, 3072, 128), ["chain_small"]),
     ("fwd", (16384, 384, 384, 128), ["chain_short"]), ("fwd", (16384, 384, 512, 128), ["chain_small"]),
     ("fwd", (40000, 384, 256, 32), ["chain_short"]), ("fwd", (40000, 384, 384, 32), ["chain_small"]),
+    # narrow ones over a long input: x . S in ranges beside dY . U^T, unless dX is one fused launch of many tokens
+    ("bwd", (9600, 2400, 336, 112), ["dual_gemm", "reduce_to_bf16", "kernel", "chain_small"]),
+    ("bwd", (9601, 2400, 336, 112), ["chain_small", "kernel", "reduce_to_bf16", "kernel", "reduce_splits"]),
+    ("bwd", (9601, 4992, 336, 64), ["dual_gemm", "reduce_to_bf16", "kernel", "chain_small"]),
+    ("bwd", (9601, 2400, 6160, 112), ["dual_gemm", "reduce_to_bf16", "kernel", "chain_small"]),
     # wide sketches: the first two contractions beside each other, or alone on 256 x 256 tiles
     ("bwd", (12288, 768, 768, 768), ["dual_gemm", "dual_gemm", "reduce_splits"]),
     ("bwd", (33222, 208, 48, 544), ["dual_gemm", "dual_gemm", "reduce_splits"]),
