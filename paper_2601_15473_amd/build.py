@@ -73,7 +73,8 @@ def build(verbose: bool = True) -> str:
     objs = [os.path.join(bdir, s.replace(".hip", ".o")) for s in SOURCES]
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         list(ex.map(_compile, SOURCES, objs))
-    r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", OUT],
+    # (a name of its own: what links to it finds the file beside itself, not the path it was built at)
+    r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-soname,libsk.so", *objs, "-o", OUT],
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)

@@ -9,8 +9,12 @@
 // forward-mode gradients, arguments that are to be refused -- and the Python functions go on from there.
 #include <Python.h>
 
+#include <dlfcn.h>
+#include <stdlib.h>
+
 #include <list>
 #include <mutex>
+#include <string>
 
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
@@ -341,9 +345,24 @@ PyMethodDef methods[] = {
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_sktorch", "libsk under autograd, in native code", -1, methods, nullptr, nullptr, nullptr, nullptr};
 
+// The folder of the file that `address` was loaded from, without links.
+std::string folder_of(const void* address) {
+  Dl_info info;
+  char* const path = dladdr(address, &info) != 0 && info.dli_fname != nullptr ? realpath(info.dli_fname, nullptr) : nullptr;
+  const std::string s = path != nullptr ? path : "";
+  free(path);
+  return s.substr(0, s.rfind('/') + 1);
+}
+
 }  // namespace
 
 PyMODINIT_FUNC PyInit__sktorch() {
+  // (the loader takes a libsk.so that the process has already, say of another copy of this package)
+  const std::string here = folder_of(&module), sk = folder_of(reinterpret_cast<const void*>(&sk_linear_fwd));
+  if (here != sk) {
+    PyErr_Format(PyExc_ImportError, "%s_sktorch.so is bound to %slibsk.so, not to the one beside it", here.c_str(), sk.c_str());
+    return nullptr;
+  }
   PyObject* const nn = PyImport_ImportModule("torch.nn");
   if (nn == nullptr) return nullptr;
   g_parameter = reinterpret_cast<PyTypeObject*>(PyObject_GetAttrString(nn, "Parameter"));   // (kept for good)
