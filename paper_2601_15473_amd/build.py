@@ -51,7 +51,7 @@ def build_torch(verbose: bool = True) -> str:
     root = os.path.dirname(torch.__file__)
     include = os.path.join(root, "include")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas",
-           "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1", f'-DSK_TORCH_VERSION="{torch.__version__}"', f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
            "-isystem", include, "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
            "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
            os.path.join(CSRC, "sk_torch.cpp"), OUT, "-L" + os.path.join(root, "lib"),
@@ -80,7 +80,12 @@ def build(verbose: bool = True) -> str:
         raise RuntimeError("link failed:\n" + r.stderr)
     if verbose:
         print(f"built {OUT}")
-    build_torch(verbose)
+    try:
+        import torch  # noqa: F401
+    except ImportError:   # (libsk.so serves callers without PyTorch)
+        print(f"no PyTorch here: {OUT_TORCH} not built")
+    else:
+        build_torch(verbose)
     return OUT
 
 

@@ -363,6 +363,19 @@ PyMODINIT_FUNC PyInit__sktorch() {
     PyErr_Format(PyExc_ImportError, "%s_sktorch.so is bound to %slibsk.so, not to the one beside it", here.c_str(), sk.c_str());
     return nullptr;
   }
+  // (torch's C++ layouts change from one version to the next, also where every symbol is still there)
+  const std::string version = SK_TORCH_VERSION;
+  PyObject* const torch = PyImport_ImportModule("torch");
+  PyObject* const got = torch != nullptr ? PyObject_GetAttrString(torch, "__version__") : nullptr;
+  Py_XDECREF(torch);
+  if (got == nullptr) return nullptr;
+  const char* const now = PyUnicode_AsUTF8(got);
+  if (now == nullptr || now != version) {
+    if (now != nullptr) PyErr_Format(PyExc_ImportError, "_sktorch.so was built for PyTorch %s, this is %s", version.c_str(), now);
+    Py_DECREF(got);
+    return nullptr;
+  }
+  Py_DECREF(got);
   PyObject* const nn = PyImport_ImportModule("torch.nn");
   if (nn == nullptr) return nullptr;
   g_parameter = reinterpret_cast<PyTypeObject*>(PyObject_GetAttrString(nn, "Parameter"));   // (kept for good)

@@ -18,6 +18,7 @@ from __future__ import annotations
 import collections
 import contextlib
 import math
+import warnings
 
 import torch
 
@@ -25,9 +26,10 @@ from . import libsk as sk
 
 try:
     from .lib import _sktorch as _native
-except ImportError as e:
-    raise ImportError("the PyTorch layers' native functions are missing or do not load: build them with "
-                      f"`python -m paper_2601_15473_amd.build` ({e})") from e
+except ImportError as e:   # not built, or for another PyTorch: the functions below serve every call
+    warnings.warn("the PyTorch layers go without their native functions, at up to twice the host time a call; build them with "
+                  f"`python -m paper_2601_15473_amd.build` ({e})", RuntimeWarning)
+    _native = None
 
 _DTYPES = {torch.float32: sk.SK_F32, torch.bfloat16: sk.SK_BF16}
 _workspaces: "collections.OrderedDict" = collections.OrderedDict()
@@ -55,7 +57,8 @@ def _workspace(device: torch.device, stream: int, nbytes: int) -> torch.Tensor:
 def release_workspaces() -> None:
     """Give the layers' scratch buffers back to the allocator (they are re-created on demand)."""
     _workspaces.clear()
-    _native.release_workspaces()
+    if _native is not None:
+        _native.release_workspaces()
 
 
 def _check(x: torch.Tensor, name: str, dtype: torch.dtype):
@@ -170,7 +173,7 @@ class SKLinearFunction(torch.autograd.Function):
 def sklinear(x, S_cat, U_cat, bias, num_terms: int, low_rank: int):
     """Functional form; see SKLinearFunction.  The native function computes the same for plain tensors
     outside of compilation, tracing and torch's modes and transforms, and takes nothing else."""
-    if not torch.compiler.is_compiling():
+    if _native is not None and not torch.compiler.is_compiling():
         y = _native.linear(x, S_cat, U_cat, bias, num_terms, low_rank)
         if y is not None:
             return y
@@ -367,7 +370,7 @@ class SKLinearTwoSided(torch.nn.Module):
     def forward(self, x: torch.Tensor) -> torch.Tensor:
         stage = self._stage_matrices()
         args = (x, *(_held(self, n) for n in ("S1_cat", "U1_cat", "U2_cat", "S2T_cat", "bias")))
-        if not torch.compiler.is_compiling():
+        if _native is not None and not torch.compiler.is_compiling():
             y = _native.linear_two_sided(*args, *stage, self.num_terms, self.low_rank)
             if y is not None:
                 return y

@@ -4,6 +4,8 @@ import shutil
 import subprocess
 import sys
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PACKAGE = "paper_2601_15473_amd"
 
@@ -47,3 +49,41 @@ except ImportError as e:
     print(e)
 """)
     assert "libsk.so" in got and ROOT in got, got
+
+
+@pytest.mark.parametrize("torch_is", ["this one", "another"])
+def test_layers_without_their_native_functions(tmp_path, torch_is):
+    """Missing, or built for another PyTorch: a warning, and the Python functions serve every call (here: their refusal of CPU tensors)."""
+    where = _copy(tmp_path)
+    if torch_is == "this one":
+        os.remove(os.path.join(where, PACKAGE, "lib", "_sktorch.so"))
+    got = _run(where, f"""
+import warnings, torch
+if {torch_is == "another"}:
+    torch.__version__ = torch.torch_version.TorchVersion("2.9.1")
+with warnings.catch_warnings(record=True) as said:
+    warnings.simplefilter("always")
+    from paper_2601_15473_amd import nn
+nn.release_workspaces()
+try:
+    nn.sklinear(torch.zeros(4, 32), torch.zeros(32, 16), torch.zeros(16, 48), None, 1, 16)
+except RuntimeError as e:
+    print(nn._native, [w.category.__name__ for w in said if "native functions" in str(w.message)], "GPU only" in str(e))
+""")
+    assert got == "None ['RuntimeWarning'] True"
+
+
+def test_build_without_pytorch(tmp_path):
+    """libsk.so alone, as its callers without PyTorch need it (the compiler steps replaced: what is asked for is looked at)."""
+    got = _run(ROOT, f"""
+import sys
+sys.modules["torch"] = None
+from paper_2601_15473_amd import build as b
+done = []
+b.OUT = {str(tmp_path / "libsk.so")!r}
+b._compile = lambda src, obj: done.append(src)
+b.subprocess.run = lambda cmd, **kw: done.append(cmd[-1]) or __import__("types").SimpleNamespace(returncode=0, stderr="")
+b.build(verbose=False)
+print(len(done) == len(b.SOURCES) + 1, done[-1] == b.OUT)
+""")
+    assert got == "True True"
