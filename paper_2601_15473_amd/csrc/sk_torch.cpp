@@ -74,9 +74,22 @@ void* stream_of(const at::Device& device) {
   return static_cast<hipStream_t>(c10::hip::getCurrentHIPStreamMasqueradingAsCUDA(device.index()).stream());
 }
 
+PyObject* g_error = nullptr;   // libsk.SkError, which nn.py hands over
+
+// As libsk.check: raises SkError with its status.  (Not under the workspaces' lock: it takes the GIL and runs Python.)
 void check(sk_status s) {
   if (s == SK_OK) return;
-  TORCH_CHECK(false, sk_status_string(s), s == SK_ERR_HIP ? " -- " : "", s == SK_ERR_HIP ? sk_last_hip_error() : "");
+  pybind11::gil_scoped_acquire gil;
+  PyObject* const e = g_error != nullptr ? PyObject_CallFunction(g_error, "i", (int)s) : nullptr;
+  if (e != nullptr) {
+    PyErr_SetObject(g_error, e);
+    Py_DECREF(e);
+  } else if (!PyErr_Occurred()) {
+    PyErr_SetString(PyExc_RuntimeError, sk_status_string(s));
+  }
+  python_error error;
+  error.persist();   // (a backward pass is on another thread than its caller)
+  throw error;
 }
 
 Tensor rows(const Tensor& x, int64_t width) {
@@ -113,12 +126,14 @@ Tensor forward_pass(const Tensor& x, const Tensor& x2, const Tensor& S, const Te
   void* const stream = stream_of(x2.device());
   const size_t need = sk_linear_workspace_bytes(SK_OP_FWD, tokens, in, out, l, k, dt);
   Workspaces& w = workspaces();
+  sk_status st;
   {
     const std::lock_guard<std::mutex> lock(w.mutex);
     const Tensor& ws = w.get(x2.device(), stream, need);
-    check(sk_linear_fwd(x2.data_ptr(), S.data_ptr(), U.data_ptr(), bias.has_value() ? bias->data_ptr() : nullptr, y.data_ptr(), tokens, in,
-                        out, l, k, dt, ws.data_ptr(), (size_t)ws.numel(), stream));
+    st = sk_linear_fwd(x2.data_ptr(), S.data_ptr(), U.data_ptr(), bias.has_value() ? bias->data_ptr() : nullptr, y.data_ptr(), tokens, in,
+                       out, l, k, dt, ws.data_ptr(), (size_t)ws.numel(), stream);
   }
+  check(st);
   if (x.dim() == 2) return y;
   std::vector<int64_t> shape = x.sizes().vec();
   shape.back() = out;
@@ -182,18 +197,22 @@ struct Linear : torch::autograd::Function<Linear> {
       float* const du = need_w ? dU.data_ptr<float>() : nullptr;
       float* const dbias = db.defined() ? db.data_ptr<float>() : nullptr;
       Workspaces& w = workspaces();
-      const std::lock_guard<std::mutex> lock(w.mutex);
-      const Tensor& ws = w.get(x2.device(), stream, need);
-      void* const wp = ws.data_ptr();
-      const size_t wn = (size_t)ws.numel();
-      if (need_dx && need_w)
-        check(sk_linear_bwd(x2.data_ptr(), dY.data_ptr(), S.data_ptr(), U.data_ptr(), dX.data_ptr(), du, dbias, tokens, in, out, kept.l,
-                            kept.k, dt, wp, wn, stream));
-      else if (need_dx)
-        check(sk_linear_bwd_input(dY.data_ptr(), S.data_ptr(), U.data_ptr(), dX.data_ptr(), tokens, in, out, kept.l, kept.k, dt, wp, wn, stream));
-      else
-        check(sk_linear_bwd_weight(x2.data_ptr(), S.data_ptr(), dY.data_ptr(), du, dbias, tokens, in, out, kept.l, kept.k, dt, wp, wn, stream));
-      if (round.count > 0) check(sk_round_gradients(round.from, round.to, round.n, round.count, stream));
+      sk_status st;
+      {
+        const std::lock_guard<std::mutex> lock(w.mutex);
+        const Tensor& ws = w.get(x2.device(), stream, need);
+        void* const wp = ws.data_ptr();
+        const size_t wn = (size_t)ws.numel();
+        if (need_dx && need_w)
+          st = sk_linear_bwd(x2.data_ptr(), dY.data_ptr(), S.data_ptr(), U.data_ptr(), dX.data_ptr(), du, dbias, tokens, in, out, kept.l,
+                             kept.k, dt, wp, wn, stream);
+        else if (need_dx)
+          st = sk_linear_bwd_input(dY.data_ptr(), S.data_ptr(), U.data_ptr(), dX.data_ptr(), tokens, in, out, kept.l, kept.k, dt, wp, wn, stream);
+        else
+          st = sk_linear_bwd_weight(x2.data_ptr(), S.data_ptr(), dY.data_ptr(), du, dbias, tokens, in, out, kept.l, kept.k, dt, wp, wn, stream);
+        if (st == SK_OK && round.count > 0) st = sk_round_gradients(round.from, round.to, round.n, round.count, stream);
+      }
+      check(st);
       dU = need_du ? dU_out : Tensor();
       db = need_db ? db_out : Tensor();
     }
@@ -234,15 +253,17 @@ struct LinearTwoSided : torch::autograd::Function<LinearTwoSided> {
     void* const stream = stream_of(x2.device());
     const int32_t l2 = 2 * kept.l;
     const size_t need = sk_linear_workspace_bytes(SK_OP_BWD_TWO_SIDED, tokens, in, out, l2, kept.k, dt);
+    sk_status st;
     {
       Workspaces& w = workspaces();
       const std::lock_guard<std::mutex> lock(w.mutex);
       const Tensor& ws = w.get(x2.device(), stream, need);
-      check(sk_linear_bwd_two_sided(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), dB.data_ptr<float>(),
-                                    kept.bias ? db.data_ptr<float>() : nullptr, dA.data_ptr<float>(), tokens, in, out, l2, kept.k, dt,
-                                    ws.data_ptr(), (size_t)ws.numel(), stream));
-      if (round.count > 0) check(sk_round_gradients(round.from, round.to, round.n, round.count, stream));
+      st = sk_linear_bwd_two_sided(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), dB.data_ptr<float>(),
+                                   kept.bias ? db.data_ptr<float>() : nullptr, dA.data_ptr<float>(), tokens, in, out, l2, kept.k, dt,
+                                   ws.data_ptr(), (size_t)ws.numel(), stream);
+      if (st == SK_OK && round.count > 0) st = sk_round_gradients(round.from, round.to, round.n, round.count, stream);
     }
+    check(st);
     return {in_shape(ctx, dX), dB_out, dA_out, db_out, Tensor(), Tensor(), Tensor(), Tensor()};
   }
 };
@@ -338,9 +359,17 @@ PyObject* release_workspaces(PyObject*, PyObject*) {
   END_HANDLE_TH_ERRORS
 }
 
+PyObject* raise_as(PyObject*, PyObject* type) {
+  Py_INCREF(type);
+  Py_XDECREF(g_error);
+  g_error = type;
+  Py_RETURN_NONE;
+}
+
 PyMethodDef methods[] = {
     {"linear", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(linear)), METH_FASTCALL, "y, or None for a call it does not take"},
     {"linear_two_sided", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(linear_two_sided)), METH_FASTCALL, "y, or None for a call it does not take"},
+    {"raise_as", raise_as, METH_O, "the exception type of a refused call, made from its status"},
     {"release_workspaces", release_workspaces, METH_NOARGS, "gives the scratch buffers back to the allocator"},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_sktorch", "libsk under autograd, in native code", -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -30,6 +30,8 @@ except ImportError as e:   # not built, or for another PyTorch: the functions be
     warnings.warn("the PyTorch layers go without their native functions, at up to twice the host time a call; build them with "
                   f"`python -m paper_2601_15473_amd.build` ({e})", RuntimeWarning)
     _native = None
+else:
+    _native.raise_as(sk.SkError)
 
 _DTYPES = {torch.float32: sk.SK_F32, torch.bfloat16: sk.SK_BF16}
 _workspaces: "collections.OrderedDict" = collections.OrderedDict()

@@ -5,6 +5,7 @@ import threading
 import pytest
 import torch
 
+from paper_2601_15473_amd import libsk as sk
 from paper_2601_15473_amd import nn as sknn
 
 
@@ -112,6 +113,26 @@ def test_refusals():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("wanted", ["all", "x", "factor"])
+@pytest.mark.parametrize("two_sided", [False, True])
+def test_refused_gradients(two_sided, wanted):
+    """A gradient that is not 16-byte aligned: libsk's own error and status from the backward pass, as from the Python functions'."""
+    layer = _layer(two_sided, torch.bfloat16)
+    for p in layer.parameters():
+        p.requires_grad_(wanted != "x")
+    odd = torch.zeros(4 * 80 + 1, device="cuda").bfloat16()[1:].view(4, 80)
+    for run in (layer, lambda x: _python(layer, x)):
+        x = torch.zeros(4, 96, device="cuda").bfloat16().requires_grad_(wanted != "factor")
+        y = run(x)
+        with pytest.raises(sk.SkError, match="misaligned") as e:
+            y.backward(odd)
+        assert e.value.status == sk.SK_ERR_INVALID_ARG
+    x = torch.ones(4, 96, device="cuda").bfloat16().requires_grad_()
+    layer(x).sum().backward()     # (and the next pass is none the worse)
+    assert x.grad is not None and torch.isfinite(x.grad).all()
+
+
+@pytest.mark.gpu
 def test_threads_and_streams():
     """Each thread on a stream of its own, and all on one: results as alone."""
     layer = _layer(False, torch.bfloat16)
@@ -149,7 +170,6 @@ def test_calls_left_to_python_are_not_taken():
 @pytest.mark.gpu
 @pytest.mark.parametrize("counts", [(16,), (1, 1023), (4096, 3, 1040)])
 def test_round_gradients(counts):
-    from paper_2601_15473_amd import libsk as sk
     src = [torch.randn(n, device="cuda") for n in counts]
     src[0][0] = float("inf")
     dst = [torch.full((n + 8,), 7.0, device="cuda").bfloat16() for n in counts]
