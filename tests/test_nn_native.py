@@ -96,6 +96,104 @@ def test_hooks_transforms_and_tangents():
     assert layer(x.detach().as_subclass(Tagged)).shape == (24, 80)
 
 
+class Seen:
+    """The native functions, with what each call got from them: taken or left to Python."""
+
+    def __init__(self, native):
+        self.native, self.taken = native, []
+
+    def __getattr__(self, name):
+        f = getattr(self.native, name)
+
+        def call(*args):
+            y = f(*args)
+            self.taken.append(y is not None)
+            return y
+        return call if name.startswith("linear") else f
+
+
+def _step(layer, x, around=None):
+    x = x.clone().requires_grad_()
+    layer.zero_grad(set_to_none=True)
+    y = layer(x) if around is None else around(layer, x)
+    y.backward(torch.ones_like(y))
+    return [y.detach(), x.grad, *(p.grad for p in layer.parameters())]
+
+
+def _dispatch_mode(layer, x):
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Mode(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            ops.append(func)
+            return func(*args, **(kwargs or {}))
+    ops = []
+    with Mode():
+        y = layer(x)
+    assert ops   # (what the layer allocates, at least)
+    return y
+
+
+def _function_mode(layer, x):
+    from torch.overrides import TorchFunctionMode
+
+    class Mode(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+    with Mode():
+        return layer(x)
+
+
+def _compiled(layer, x):
+    torch._dynamo.reset()
+    return torch.compile(layer, backend="eager")(x)
+
+
+def _functional(layer, x):
+    return torch.func.functional_call(layer, dict(layer.named_parameters()), (x,))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("around,taken", [(_dispatch_mode, False), (_function_mode, False), (_compiled, None), (_functional, True)],
+                         ids=lambda f: getattr(f, "__name__", ""))
+@pytest.mark.parametrize("two_sided", [False, True])
+def test_modes_and_compilation(monkeypatch, two_sided, around, taken):
+    """The same step inside torch's modes, compiled and as a functional call; the native functions leave the modes to Python."""
+    layer = _layer(two_sided, torch.bfloat16)
+    x = torch.randn(40, 96, generator=torch.Generator().manual_seed(3)).bfloat16().cuda()
+    want = _step(layer, x)
+    seen = Seen(sknn._native)
+    monkeypatch.setattr(sknn, "_native", seen)
+    got = _step(layer, x, around)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    assert taken is None or seen.taken == [taken], seen.taken
+
+
+@pytest.mark.gpu
+def test_functional_call_with_other_weights():
+    layer, other = _layer(False, torch.bfloat16), _layer(False, torch.bfloat16)
+    with torch.no_grad():
+        other.U_cat.mul_(2.0)
+    x = torch.randn(40, 96, device="cuda").bfloat16()
+    with torch.no_grad():
+        assert torch.equal(torch.func.functional_call(layer, dict(other.named_parameters()), (x,)), other(x))
+        assert not torch.equal(layer(x), other(x))
+
+
+@pytest.mark.gpu
+def test_tracing(monkeypatch):
+    """torch.jit.trace records a Python function's call, which the trace then makes on other inputs."""
+    layer = _layer(False, torch.bfloat16)
+    x = torch.randn(40, 96, device="cuda").bfloat16()
+    other = torch.randn(40, 96, device="cuda").bfloat16()
+    seen = Seen(sknn._native)
+    monkeypatch.setattr(sknn, "_native", seen)
+    with torch.no_grad():
+        traced = torch.jit.trace(layer, x, check_trace=False)
+        assert seen.taken == [False], seen.taken
+        assert torch.equal(traced(x), layer(x)) and torch.equal(traced(other), layer(other))
+
+
 @pytest.mark.gpu
 def test_refusals():
     layer = _layer(False, torch.bfloat16)
