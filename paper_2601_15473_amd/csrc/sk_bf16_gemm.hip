@@ -477,15 +477,17 @@ hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKi
   typedef GemmTile<64, 128, false, true, float, false> TTF_64x128;
   typedef GemmTile<128, 128, false, true, float, false> TTF_128x128;
   typedef GemmTile<128, 64, false, true, float, false> TTF_128x64;
-  // 64 x 64 tiles in one round, two work-groups to a CU: on the ring, as a product by itself (backward pass of 568 tokens,
-  // 1216 -> 352, R = 48, 22.1 -> 17.8 us; 1024, 1024 -> 1024, R = 64, 21.0 -> 18.5; 1500, 768 -> 768, R = 192, 28.8 -> 25.5; on a
-  // ring of their own the 128 x 64 tiles of the other pairs are level with the staged ones)
+  // 64 x 64 tiles in one round, two work-groups to a CU: on the ring, as a product by itself.  Backward pass, us, staged : ring,
+  // narrow sketches: 2925 tokens, 1584 -> 2480, R = 64 29.6 : 26.6; 1024, 1024 -> 1024, R = 64 19.6 : 17.5; 2901, 304 -> 3824, R = 16 20.1 : 20.4;
+  // wide ones: 1600, 2464 -> 1536, R = 256 30.6 : 25.3; 1507, 3120 -> 464, R = 512 36.9 : 31.6; 4096, 768 -> 768, R = 256 (512
+  // work-groups) 24.5 : 23.5.  (On a ring of their own the 128 x 64 tiles of the other pairs are level with the staged ones.)
   typedef RingTile<64, 64, true, true, float, false> RING_NTF_64x64;
   typedef RingTile<64, 64, false, true, bf16, false> RING_TT_64x64;
   typedef RingTile<64, 64, true, true, bf16, false> RING_NT_64x64;
-  if (ga + gb <= NUM_CUS * RING_NT_64x64::PER_CU) {
+  if ((pair == 1 || pair == 5) && ga + gb <= NUM_CUS * RING_NT_64x64::PER_CU) {
+    name = "dual_gemm_kernel<ring>";
     if (pair == 1) return launch_kernel(name, work, dual_gemm_kernel<RING_NTF_64x64, RING_TT_64x64>, grid, block, s, a, b, (int)ga);
-    if (pair == 5) return launch_kernel(name, work, dual_gemm_kernel<RING_NT_64x64, RING_TT_64x64>, grid, block, s, a, b, (int)ga);
+    return launch_kernel(name, work, dual_gemm_kernel<RING_NT_64x64, RING_TT_64x64>, grid, block, s, a, b, (int)ga);
   }
   switch (pair) {
     case 0: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x128, TT_64x64>, grid, block, s, a, b, (int)ga);

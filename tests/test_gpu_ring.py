@@ -57,8 +57,28 @@ def test_either_side_of_a_round(sk, tuning, tokens):  # noqa: F811
     assert float((dev.y[:n].double() - want).abs().max() / want.std()) < 5e-2   # two roundings to 8 bits at up to six deviations
 
 
-def test_two_products_on_rings(sk):  # noqa: F811
-    for shape in ((568, 640, 352, 1, 48), (1500, 768, 768, 1, 192)):
-        T, d_in, d_out, l, k = shape
-        w = W.Workload("ring_pair", T, d_in, d_out, l, k, "bf16", seed=T)
-        check_all(sk, w, 0, single_call=True)
+@pytest.mark.parametrize("shape,ring", [
+    # wide sketches: dY . U^T beside Z^T, ragged tokens, widths and k tails, up to the 512 work-groups of a round and past it
+    ((1950, 2832, 1568, 1, 240), True), ((2086, 1072, 720, 1, 320), True), ((1507, 3120, 464, 2, 256), True), ((4097, 768, 768, 1, 256), False),
+    # narrow ones: dY . U^T in ranges beside Z^T
+    ((922, 384, 3552, 1, 48), True), ((2925, 1584, 2480, 2, 32), True), ((3585, 400, 2336, 2, 16), False),
+], ids=lambda v: "T%d_%dx%d_l%dk%d" % v if isinstance(v, tuple) else str(v))
+def test_two_products_on_rings(sk, shape, ring):  # noqa: F811
+    T, d_in, d_out, l, k = shape
+    w = W.Workload("ring_pair", T, d_in, d_out, l, k, "bf16", seed=T)
+    names = _kernels_of(sk, DeviceLayer(W.generate(w), sk), ("bwd",))
+    assert names[0] == ("dual_gemm_kernel<ring>" if ring else "dual_gemm_kernel"), names
+    check_all(sk, w, 0, single_call=True)   # bound: the repository's bf16 bar (two roundings to 8 bits)
+
+
+@pytest.mark.parametrize("tokens,d_in,d_out,R", [(4096, 768, 768, 256), (3584, 400, 2336, 32)], ids=["wide", "narrow"])
+def test_two_products_on_either_side_of_a_round(sk, tokens, d_in, d_out, R):  # noqa: F811
+    """One token more is one work-group too many for a round: dX of the tokens before it bit for bit, ring and staged."""
+    big = DeviceLayer(W.generate(W.Workload("pair_round", tokens + 1, d_in, d_out, 1, R, "bf16", seed=R)), sk)
+    small = DeviceLayer(W.generate(W.Workload("pair_round", tokens, d_in, d_out, 1, R, "bf16", seed=R)), sk)
+    for n in ("x", "dY"):
+        getattr(small, n).copy_(getattr(big, n)[:tokens])
+    for n in ("S_cat", "U_cat"):
+        getattr(small, n).copy_(getattr(big, n))
+    assert _kernels_of(sk, small, ("bwd",))[0] == "dual_gemm_kernel<ring>" and _kernels_of(sk, big, ("bwd",))[0] == "dual_gemm_kernel"
+    assert torch.equal(small.dX, big.dX[:tokens])
