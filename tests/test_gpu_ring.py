@@ -1,7 +1,7 @@
 """The GEMM tiles on a ring of chunks in LDS, which launches of one round take: contractions of fewer chunks than the
 ring has slots, ending inside a chunk, one chunk past a turn of the ring, ragged rows and columns, split
-contractions, column sums, two products in one launch -- against the fp64 oracle, and on either side of the round
-against the staged tile, bit for bit (the same sums in the same order)."""
+contractions, column sums, two products in one launch -- against the fp64 oracle, and on either side of a round
+against the staged tile, bit for bit (the same sums in the same order): both results, every tile that has a ring."""
 import pytest
 import torch
 
@@ -36,25 +36,54 @@ def test_ring_edges(sk, tuning, tile, splits, shape):  # noqa: F811
     assert len(_rings(names)) >= (1 if tile == 2 else 3), names
 
 
-@pytest.mark.parametrize("tokens", [512 * 64, 512 * 64 + 64])
-def test_either_side_of_a_round(sk, tuning, tokens):  # noqa: F811
-    """x . S and G . S^T of 64 x 64 tiles, R = in = 64: 512 tiles on the ring, 513 staged."""
-    tuning(sk.SK_TUNE_TILE, 4)
-    t = W.generate(W.Workload("ring_round", tokens, 64, 64, 1, 64, "bf16", seed=5))
-    dev = DeviceLayer(t, sk)
+def _two_gemms(sk, dev):
     sk.sk_set_plan(2)
     try:
         names = _kernels_of(sk, dev, ("fwd",))
-        sk.check(dev.fwd())
     finally:
         sk.sk_set_plan(0)
     torch.cuda.synchronize()
-    assert len(_rings(names)) == (2 if tokens == 512 * 64 else 0), names
-    n = 512 * 64
-    x, S, U, b = (torch.from_numpy(t.value[k].astype("float32")).cuda() for k in ("x", "S", "U", "b"))
-    Z = (x[:n].double() @ S.reshape(64, 64).double()).bfloat16().double()
-    want = Z @ U.reshape(64, 64).double() + b.double()
-    assert float((dev.y[:n].double() - want).abs().max() / want.std()) < 5e-2   # two roundings to 8 bits at up to six deviations
+    return names
+
+
+@pytest.mark.parametrize("tile,rows,d,R", [(4, 512 * 64, 64, 64), (1, 128 * 128, 208, 256)], ids=["64x64", "128x128"])
+def test_either_side_of_a_round(sk, tuning, tile, rows, d, R):  # noqa: F811
+    """x . S and Z . U of square tiles, the last work-group of a round and one tile of rows more: ring and staged bit for bit."""
+    tuning(sk.SK_TUNE_TILE, tile)
+    more = rows + (64 if tile == 4 else 128)
+    t = W.generate(W.Workload("ring_round", more, d, R, 1, R, "bf16", seed=5))
+    staged, ring = DeviceLayer(t, sk), DeviceLayer(W.generate(W.Workload("ring_round", rows, d, R, 1, R, "bf16", seed=5)), sk)
+    ring.x.copy_(staged.x[:rows])
+    for n in ("S_cat", "U_cat", "b"):
+        getattr(ring, n).copy_(getattr(staged, n))
+    for dev, want in ((staged, 0), (ring, 2)):
+        names = _two_gemms(sk, dev)
+        assert len(names) == 2 and len(_rings(names)) == want, names
+    assert torch.equal(ring.y, staged.y[:rows])
+    x, S, U, b = (torch.from_numpy(t.value[k].astype("float32")).cuda().double() for k in ("x", "S", "U", "b"))
+    want = (x @ S.reshape(d, R)).bfloat16().double() @ U.reshape(R, R) + b
+    assert float((staged.y.double() - want).abs().max() / want.std()) < 5e-2   # two roundings to 8 bits at up to six deviations
+
+
+@pytest.mark.parametrize("tile,R", [(1, 128), (2, 128), (4, 64)], ids=["128x128", "128x64", "64x64"])
+def test_factor_gradient_on_either_side_of_a_round(sk, tuning, tile, R):  # noqa: F811
+    """Z^T . dY with the column sums, four ragged ranges of tokens, 8192 columns (the last work-group of a round) and a tile more: the
+    columns that both have bit for bit, ring and staged."""
+    tuning(sk.SK_TUNE_WTILE, tile)
+    tuning(sk.SK_TUNE_WSPLITS, 4)
+    staged, ring = (DeviceLayer(W.generate(W.Workload("ring_round", 1100, 80, out, 1, R, "bf16", seed=6)), sk) for out in (8192 + 128, 8192))
+    ring.x.copy_(staged.x)
+    ring.S_cat.copy_(staged.S_cat)
+    ring.dY.copy_(staged.dY[:, :8192])
+    for dev, want in ((staged, False), (ring, True)):
+        names = _kernels_of(sk, dev, ("bwd_weight",))
+        assert ["float, true" in n for n in names[:2]] == [False, True] and (len(_rings(names[1:2])) == 1) == want, names
+    assert torch.equal(ring.dU, staged.dU[:, :8192]) and torch.equal(ring.db, staged.db[:8192])
+    Z = (staged.x.double() @ staged.S_cat.double()).bfloat16().double()
+    want = Z.T @ staged.dY.double()
+    # (where the library's fp32 sums of Z round the other way, at most one element in a hundred: 0.1 x 2^-8 = 4e-4)
+    assert float((staged.dU.double() - want).norm() / want.norm()) < 1e-3
+    assert float((staged.db.double() - staged.dY.double().sum(0)).norm() / staged.db.double().norm()) < 1e-5
 
 
 @pytest.mark.parametrize("shape,ring", [
