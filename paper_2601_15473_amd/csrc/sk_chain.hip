@@ -11,10 +11,13 @@
 // range.  Zt sits in LDS once and every wave lifts the whole of it into registers
 // as MFMA fragments; the waves then split each BN-wide tile of N four ways, so a B2
 // fragment is read from LDS by exactly one wave and used for all 32-row blocks.
-// Two kernels share that plan:
-//   chain_small_kernel (R <= 128, the one the automatic plans use): B2 arrives one whole
-//     [R x 128] tile at a time, double buffered across tile boundaries, and output tiles
-//     leave one step later through LDS, in whole rows;
+// Three kernels share that plan:
+//   chain_ring (R <= 128, both stages fused, 64-token tiles: what the automatic plans launch there but for narrow sketches in
+//     more than a round): every operand straight into LDS, on a ring of chunks in stage 1 and of whole tiles of B2 in stage 2;
+//   chain_small (R <= 128, every other launch of the automatic plans): B2 arrives through registers one whole [R x 128] tile at
+//     a time, double buffered across tile boundaries;
+//     in both, output tiles leave one step later through LDS, in whole rows (chain_small_kernel), in short runs
+//     straight from registers (chain_short_kernel);
 //   chain_kernel (R <= 512, forced plans only): B2 streams in 64-row chunks and the output
 //     tile is re-laid out through LDS into whole rows.
 #include "sk_bf16_lds.h"

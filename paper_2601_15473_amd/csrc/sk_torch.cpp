@@ -220,7 +220,7 @@ struct Linear : torch::autograd::Function<Linear> {
   }
 };
 
-// x, S1, U1, U2, S2^T, bias, then [S1 | U2] and [U1 ; S2^T] (nn.py keeps those two); l: terms per side
+// x, U1, U2, bias, then A = [S1 | U2] and B = [U1 ; S2^T] (nn.py keeps those two), which the passes run on; l: terms per side
 struct LinearTwoSided : torch::autograd::Function<LinearTwoSided> {
   static Tensor forward(AutogradContext* ctx, const Tensor& x, const Tensor& U1, const Tensor& U2, const std::optional<Tensor>& bias, const Tensor& A,
                         const Tensor& B, int64_t l, int64_t k) {
