@@ -137,9 +137,9 @@ sk_status sk_linear_bwd_weight_noalloc(const void* x, const void* S_cat, const v
  * bit-identical to it except on the one-pass schedule below), scheduled together.
  *   - Narrow sketches (bf16, R <= 128): kernels of the two gradients that do not depend
  *     on each other share launches -- dY . U_cat^T runs beside the recomputation of
- *     x . S_cat, and the sum of the factor gradient's token splits rides on the kernel
- *     that expands dX -- three launches instead of five, which is most of the cost at
- *     BERT-base sizes (four instead of six where x . S is recomputed in ranges).
+ *     x . S_cat, and the factor gradient beside the expansion of dX, or the sum of its
+ *     token splits on the kernel that expands dX -- two or three launches instead of five, which
+ *     is most of the cost at BERT-base sizes (four instead of six where x . S is recomputed in ranges).
  *   - Very narrow sketches (bf16, R <= 32, in <= 848, out <= 896) over up to 16384
  *     tokens: one kernel reads x and dY once, recomputes x . S_cat, and produces dX and
  *     a partial dU_cat and dbias per token tile, which a second kernel sums in tile

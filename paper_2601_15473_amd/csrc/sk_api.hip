@@ -1267,7 +1267,8 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
   red.part2 = cpart; red.out2 = dbias; red.n2 = (dbias && w.colsum_splits > 1) ? out : 0; red.scale2 = 1.0f;
   red.splits = w.splits; red.splits2 = w.colsum_splits;
 
-  // --- narrow sketch: split-K slabs of G beside Z^T | Z^T.dY | expand dX, carrying the sums ---
+  // --- narrow sketch: split-K slabs of G beside Z^T | Z^T.dY beside the expansion of dX | sums, or, where the expansion's
+  // runs are long, Z^T.dY | expand dX, carrying the sums ---
   // (Z^T in ranges: their slabs, and one more launch that sums them, four launches instead of six: 4096 tokens, 8192 -> 8192, R = 16
   // 68.1 : 62.5 us, 1024 41.5 : 30.8; 2048, 4096 -> 4096, R = 64 39.2 : 33.3; 3000, 6000 -> 7008, R = 96 78.8 : 65.7)
   // Not where dX by itself is one fused launch that nearly fills the chip while the slabs of G are large: from 9600 tokens on, R > 64
@@ -1275,7 +1276,18 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
   // 9934 to 15489 tokens 0.98 to 1.23 times the time, below that 0.84 to 1.11, and 0.97 at the median).
   const SketchPlan q = plan_sketch(s, out);
   const bool z_ranges = bf16_any_z && w.z_splits > 1 && !(in_plan == PLAN_FUSED && s.R > 64 && tokens > 9600);
-  if (bf16_any_z && chain_supported(s.R) && s.R <= 128 && q.splits > 1 && (z_ranges || (w.z_splits == 1 && w.splits > 1)) &&
+  ChainArgs c{};
+  c.A = dY; c.B1 = U_cat; c.B2 = S_cat; c.bias = nullptr; c.C = dX;
+  c.lda = out; c.ldb1 = out; c.ldb2 = s.R; c.ldc = in;
+  c.M = (int)tokens; c.K1 = (int)out; c.R = s.R; c.N = (int)in; c.scale = scale;
+  { const ChainShape cs = chain_shape(tokens, in, s.R, z_ranges); c.n_slices = cs.slices; c.bm = cs.bm; }
+  c.Z = ws_in; c.z_splits = q.splits; c.z_slab = (int64_t)tokens * s.R;
+  // Z^T.dY shares a launch with the expansion where that is over soon (launch_factor_beside_expand), also in one range
+  // of tokens: two launches, where one after the other the gradients take three or four (62 of 150 layers of 100 to 600 tokens,
+  // 64 to 4096 wide, take it, in 0.61 of the time; 570 tokens, 320 -> 1808, R = 32 19.7 : 10.3 us; x.S in ranges, 418, 3616 -> 272, R = 80
+  // 21.0 : 15.7).  Where x.S comes in ranges for a few hundred tokens the launches stay the four that the schedule's test counts.
+  const bool beside = bf16_any_z && !(z_ranges && tokens <= 320) && factor_beside_expand_supported(w.tile, du, c);
+  if (bf16_any_z && chain_supported(s.R) && s.R <= 128 && q.splits > 1 && (z_ranges || (w.z_splits == 1 && (w.splits > 1 || beside))) &&
       (z_ranges ? dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT_F32, w.z_tile) : dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT, z_tile))) {
     g_hip_error.clear();
     GemmArgs g = dense_args(dY, out, U_cat, out, ws_in, s.R, tokens, s.R, out, 1.0f, nullptr);
@@ -1289,15 +1301,15 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
       e = launch_reduce_to_bf16(zpart, Z, (int64_t)s.R * w.ldz, w.z_splits, hs);
       if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (sum of x.S)");
     }
-    ChainArgs c{};
-    c.A = dY; c.B1 = U_cat; c.B2 = S_cat; c.bias = nullptr; c.C = dX;
-    c.lda = out; c.ldb1 = out; c.ldb2 = s.R; c.ldc = in;
-    c.M = (int)tokens; c.K1 = (int)out; c.R = s.R; c.N = (int)in; c.scale = scale;
-    { const ChainShape cs = chain_shape(tokens, in, s.R, z_ranges); c.n_slices = cs.slices; c.bm = cs.bm; }
-    c.Z = ws_in; c.z_splits = q.splits; c.z_slab = (int64_t)tokens * s.R;
     if (want) {
       c.z_out = want->room; c.z_first = (int)want->first;
       want->at = want->room; want->ld = s.R - want->first;
+    }
+    if (beside) {
+      e = launch_factor_beside_expand(w.tile, du, c, hs);
+      if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (Z^T.dY beside the expansion)");
+      e = launch_reduce_splits(red, hs);
+      return e == hipSuccess ? SK_OK : hip_fail(e, "sk_linear_bwd (sum of splits)");
     }
     // Z^T.dY, then the expansion of dX carrying the sum of the token splits
     e = launch_gemm_bf16(du_kind, w.tile, du, hs);

@@ -20,7 +20,7 @@
 //     straight from registers (chain_short_kernel);
 //   chain_kernel (R <= 512, forced plans only): B2 streams in 64-row chunks and the output
 //     tile is re-laid out through LDS into whole rows.
-#include "sk_bf16_lds.h"
+#include "sk_bf16_ring.h"
 #include "sk_launch.h"
 
 namespace sk {
@@ -291,10 +291,14 @@ struct SmallLds {
   // finished output tiles, over Zt (which is in registers by then), then the B2 tiles
   static constexpr int OUTS = SHORT ? 0 : chain_outs(MB, RT);
   static constexpr int OUT_BYTES = MB * CS_BN * 2;
-  static constexpr int HEAD_BYTES = Z_BYTES > OUTS * OUT_BYTES ? Z_BYTES : OUTS * OUT_BYTES;
+  // (without either, Zt lies where the second B2 tile goes once everybody has it in registers: 64 KB in all for R = 128)
+  static constexpr bool OVER_B2 = SHORT && !FUSED;
+  static constexpr int Z_AT = OVER_B2 ? TB2::ELEMS * 2 : 0;
+  static constexpr int HEAD_BYTES = OVER_B2 ? 0 : Z_BYTES > OUTS * OUT_BYTES ? Z_BYTES : OUTS * OUT_BYTES;
   static constexpr int S2_BYTES = 2 * TB2::ELEMS * 2;
   static constexpr int S1_BYTES = FUSED ? 2 * (TA::ELEMS + TB1::ELEMS) * 2 : 0;   // (behind Zt)
-  static constexpr int BYTES = Z_BYTES + S1_BYTES > HEAD_BYTES + S2_BYTES ? Z_BYTES + S1_BYTES : HEAD_BYTES + S2_BYTES;
+  static constexpr int S1_END = Z_AT + Z_BYTES + S1_BYTES;
+  static constexpr int BYTES = S1_END > HEAD_BYTES + S2_BYTES ? S1_END : HEAD_BYTES + S2_BYTES;
 };
 
 // Scheduling of one stage-2 tile of the narrow kernel: per k step the fragment reads of
@@ -314,8 +318,9 @@ __device__ __forceinline__ void sched_stage2() {
 }
 
 // SHORT: for runs of few output tiles, which leave straight from registers as they are finished.
-template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC, bool SHORT>
-__device__ __forceinline__ void chain_small(const ChainArgs& p) {
+// LEAN: one B2 tile fetched ahead of the slabs of Zt instead of two, for a launch that shares registers (256 with the slabs, else 272).
+template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC, bool SHORT, bool LEAN = false>
+__device__ __forceinline__ void chain_small(const ChainArgs& p, const int block, unsigned char* const smem) {
   static_assert(MB == 64 || MB == 128, "token tiles are 64 or 128 rows");
   typedef SmallLds<MB, RT, B2_KC, FUSED, B1_KC, SHORT> L;
   typedef typename L::TB2 TB2;
@@ -325,13 +330,12 @@ __device__ __forceinline__ void chain_small(const ChainArgs& p) {
   // LDS reads per MFMA when B1 is read transposed, measured no faster)
   constexpr int WM1 = MB / 2, WN1 = RT / 2;
   constexpr int TM1 = WM1 / 32, TN1 = WN1 / 32;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[L::BYTES];
-  bf16* const Zs = reinterpret_cast<bf16*>(smem);
+  bf16* const Zs = reinterpret_cast<bf16*>(smem + L::Z_AT);
   bf16* const Bbuf = reinterpret_cast<bf16*>(smem + L::HEAD_BYTES);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;  // stage-1 wave grid
-  const int wg = xcd_remap(blockIdx.x, p.tiles_m * p.n_slices);
+  const int wg = xcd_remap(block, p.tiles_m * p.n_slices);
   const int tile_m = wg / p.n_slices, slice = wg % p.n_slices;
   const int m0 = tile_m * MB;
 
@@ -365,7 +369,7 @@ __device__ __forceinline__ void chain_small(const ChainArgs& p) {
   // (their 64 KB per work-group would hold up the start of stage 1 by ~0.7 us otherwise).
   if (!FUSED) {
     load_b2(rb0, 0);
-    load_b2(rb1, 1);
+    if (!LEAN) load_b2(rb1, 1);
   }
 
   // bias through a buffer window of N elements (zero elements when there is no bias:
@@ -557,6 +561,7 @@ __device__ __forceinline__ void chain_small(const ChainArgs& p) {
     }
     }  // h
   }
+  if (LEAN) load_b2(rb1, 1);   // (its registers held slabs)
   __syncthreads();  // Zt complete; stage-1 buffers (aliasing Bbuf) are free
 
   // all rows of Zt, as MFMA fragments, in every wave for the rest of the kernel
@@ -951,15 +956,37 @@ __device__ __forceinline__ void chain_ring(const ChainArgs& p) {
 }
 
 // RING: both stages on rings of loads (chain_ring), for fused launches of 64-row tiles.
+template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC, bool RING, bool SHORT>
+__device__ __forceinline__ void chain_body(const ChainArgs& p) {
+  if constexpr (RING) {
+    chain_ring<RT, B2_KC, SHORT>(p);
+  } else {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SmallLds<MB, RT, B2_KC, FUSED, B1_KC, SHORT>::BYTES];
+    chain_small<MB, RT, B2_KC, FUSED, B1_KC, SHORT>(p, blockIdx.x, smem);
+  }
+}
 template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC, bool RING = false>
 __global__ __launch_bounds__(256, chain_outs(MB, RT) == 1 ? 2 : 1) void chain_small_kernel(const ChainArgs p) {
-  if constexpr (RING) chain_ring<RT, B2_KC, false>(p);
-  else chain_small<MB, RT, B2_KC, FUSED, B1_KC, false>(p);
+  chain_body<MB, RT, B2_KC, FUSED, B1_KC, RING, false>(p);
 }
 template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC, bool RING = false>
 __global__ __launch_bounds__(256) void chain_short_kernel(const ChainArgs p) {
-  if constexpr (RING) chain_ring<RT, B2_KC, true>(p);
-  else chain_small<MB, RT, B2_KC, FUSED, B1_KC, true>(p);
+  chain_body<MB, RT, B2_KC, FUSED, B1_KC, RING, true>(p);
+}
+
+// Z^T . dY in ranges of tokens beside the expansion of dX over short runs of 64-row tiles, in one launch: the first `groups_a`
+// work-groups and the rest, two to a CU (72 KB of LDS and 240 registers at most).  Each of the two by itself is a round of work-groups that
+// wait for their first operands and for their last stores; beside each other they wait at the same time.  The sum of the
+// ranges, which the expansion carried while it came last, has a launch of its own again (2 to 3 us).  Backward pass, us, expansion
+// behind : beside: 4096 tokens, 768 -> 3072, R = 128 35.0 : 34.0; 2048, 768 -> 768, R = 128 22.9 : 21.2; 1000, 512 -> 1024, R = 48 15.0 : 12.7;
+// x . S in ranges: 418, 3616 -> 272, R = 80 21.0 : 15.7; 62 of 150 layers of 300 to 16384 tokens, 256 to 4096 wide, take it, in 0.89 of the time.
+template <int BM, int RT>
+__global__ __launch_bounds__(256, 2) void factor_beside_expand_kernel(const GemmArgs a, const ChainArgs c, const int groups_a) {
+  typedef RingTile<BM, 64, true, false, float, true> G;
+  typedef SmallLds<64, RT, true, false, true, true> L;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[G::LDS_BYTES > L::BYTES ? G::LDS_BYTES : L::BYTES];
+  if ((int)blockIdx.x < groups_a) G::run(a, blockIdx.x, smem);
+  else chain_small<64, RT, true, false, true, true, true>(c, (int)blockIdx.x - groups_a, smem);
 }
 
 bool chain_supported(int R) { return R >= 16 && R <= 512; }
@@ -987,6 +1014,11 @@ static hipError_t launch_one(const ChainArgs& a, hipStream_t s) {
                        s, a);
 }
 
+static bool brief_runs(const ChainArgs& a, int mb) {
+  const int run = ((a.N + CS_BN - 1) / CS_BN + a.n_slices - 1) / a.n_slices;
+  return run <= (mb == 64 ? 3 : 2) || a.tiles_m == 1;
+}
+
 template <int MB, int RT, bool B2_KC, bool FUSED, bool B1_KC>
 static hipError_t launch_small_mb(const ChainArgs& a, hipStream_t s) {
   const long long grid = (long long)a.tiles_m * a.n_slices;
@@ -998,8 +1030,7 @@ static hipError_t launch_small_mb(const ChainArgs& a, hipStream_t s) {
   // 2048, R = 64, runs of 4, 13.9 : 14.2; [30000 x 768] -> 768, R = 64, runs of 6, 19.3 : 20.6.
   // A lone token tile has next to nothing to store beside the weights it reads ([1 x 528] -> 131072, R = 128,
   // runs of 4, 13.5 : 12.4).
-  const int run = ((a.N + CS_BN - 1) / CS_BN + a.n_slices - 1) / a.n_slices;
-  const bool brief = run <= (MB == 64 ? 3 : 2) || a.tiles_m == 1;
+  const bool brief = brief_runs(a, MB);
   // Fused launches of 64-row tiles run on rings but for those of a narrow sketch in more than a round: there the rings and the
   // finished tiles would leave room for one work-group on a CU (of short runs, two) instead of two and more, us, on rings : without:
   // [12128 x 1728] -> 3872, R = 16, 46.2 : 35.6; [11483 x 624] -> 3328, R = 32, 29.7 : 23.9; short runs, [17339 x 512] -> 176, R = 32,
@@ -1050,6 +1081,23 @@ static hipError_t launch_rt(const ChainArgs& a, hipStream_t s) {
 
 int chain_bn(int R) { return R <= 128 ? CS_BN : 128; }
 
+static void note_chain(bool b_kc, bool fused, const ChainArgs& a) {
+  if (!tracing()) return;
+  if (fused) {
+    note_matrix(a.A, a.M, a.K1, a.lda, 2, false);
+    note_matrix(a.B1, b_kc ? a.R : a.K1, b_kc ? a.K1 : a.R, a.ldb1, 2, false);
+  } else if (a.z_splits == 0) {
+    note_matrix(a.Z, a.M, a.R, a.R, 2, false);
+  } else {   // fp32 slabs [M, R], z_slab elements apart
+    note_matrix(a.Z, 1, (int64_t)(a.z_splits - 1) * a.z_slab + (int64_t)a.M * a.R, 0, 4, false);
+  }
+  note_matrix(a.B2, b_kc ? a.N : a.R, b_kc ? a.R : a.N, a.ldb2, 2, false);
+  if (a.bias != nullptr) note_matrix(a.bias, 1, a.N, a.N, 2, false);
+  note_matrix(a.C, a.M, a.N, a.ldc, 2, true);
+  note_matrix(a.z_out, a.M, a.R - a.z_first, a.R - a.z_first, 2, true);
+  note_reduce(a.tail);
+}
+
 hipError_t launch_chain_bf16(bool b_kc, bool fused, ChainArgs a, hipStream_t s) {
   if (!chain_supported(a.R) || a.n_slices < 1 || (fused && a.R > CHAIN_FUSED_MAX_R))
     return hipErrorInvalidValue;
@@ -1058,23 +1106,42 @@ hipError_t launch_chain_bf16(bool b_kc, bool fused, ChainArgs a, hipStream_t s) 
   if (fused && a.tail.n + a.tail.n2 > 0) return hipErrorInvalidValue;   // (no plan asks a fused launch to carry one)
   if (a.z_out != nullptr && (fused || a.z_splits == 0 || a.R > 128)) return hipErrorInvalidValue;
   a.tiles_m = (a.M + a.bm - 1) / a.bm;
-  if (tracing()) {
-    if (fused) {
-      note_matrix(a.A, a.M, a.K1, a.lda, 2, false);
-      note_matrix(a.B1, b_kc ? a.R : a.K1, b_kc ? a.K1 : a.R, a.ldb1, 2, false);
-    } else if (a.z_splits == 0) {
-      note_matrix(a.Z, a.M, a.R, a.R, 2, false);
-    } else {   // fp32 slabs [M, R], z_slab elements apart
-      note_matrix(a.Z, 1, (int64_t)(a.z_splits - 1) * a.z_slab + (int64_t)a.M * a.R, 0, 4, false);
-    }
-    note_matrix(a.B2, b_kc ? a.N : a.R, b_kc ? a.R : a.N, a.ldb2, 2, false);
-    if (a.bias != nullptr) note_matrix(a.bias, 1, a.N, a.N, 2, false);
-    note_matrix(a.C, a.M, a.N, a.ldc, 2, true);
-    note_matrix(a.z_out, a.M, a.R - a.z_first, a.R - a.z_first, 2, true);
-    note_reduce(a.tail);
-  }
+  note_chain(b_kc, fused, a);
   if (b_kc) return fused ? launch_rt<true, true>(a, s) : launch_rt<true, false>(a, s);
   return fused ? launch_rt<false, true>(a, s) : launch_rt<false, false>(a, s);
+}
+
+// Up to two work-groups a CU in all: past that the two kinds queue (of six layers with 513 to 768 three were 7 % ahead, three 1 to 3 % behind).
+bool factor_beside_expand_supported(int tile, const GemmArgs& a, const ChainArgs& c) {
+  const int tiles_m = (c.M + 63) / 64;
+  int bm, bn;
+  tile_dims(tile, bm, bn);
+  if ((tile != TILE_64x64 && tile != TILE_128x64) || c.bm != 64 || c.R > 128 || (c.R > 64) != (tile == TILE_128x64) || c.z_splits > 8) return false;
+  ChainArgs t = c;
+  t.tiles_m = tiles_m;
+  const long long groups = (long long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.splits + (long long)tiles_m * c.n_slices;
+  return brief_runs(t, 64) && groups <= 2 * NUM_CUS;
+}
+
+template <int BM, int RT>
+static hipError_t launch_beside(GemmArgs a, const ChainArgs& c, hipStream_t s) {
+  a.tiles_m = (a.M + BM - 1) / BM;
+  a.tiles_n = (a.N + 63) / 64;
+  const int ga = a.tiles_m * a.tiles_n * a.splits;
+  note_gemm(a, true, false, 2, 4, true);
+  note_chain(true, false, c);
+  Work work = gemm_work(a, 2, 4, true);
+  const Work wc = chain_work(c, false);
+  work.flops += wc.flops;
+  work.bytes += wc.bytes;
+  static const std::string name = kernel_label("factor_beside_expand_kernel", {lbl(BM), lbl(RT)});
+  return launch_kernel(name.c_str(), work, factor_beside_expand_kernel<BM, RT>, dim3((unsigned)(ga + c.tiles_m * c.n_slices)), dim3(256), s, a, c, ga);
+}
+
+hipError_t launch_factor_beside_expand(int tile, GemmArgs a, ChainArgs c, hipStream_t s) {
+  if (!factor_beside_expand_supported(tile, a, c) || c.tail.n + c.tail.n2 > 0 || !within_window(128, a.lda, 64, 2)) return hipErrorInvalidValue;
+  c.tiles_m = (c.M + 63) / 64;
+  return tile == TILE_128x64 ? launch_beside<128, 128>(a, c, s) : launch_beside<64, 64>(a, c, s);
 }
 
 }  // namespace sk

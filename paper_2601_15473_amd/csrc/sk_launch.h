@@ -235,6 +235,11 @@ constexpr int CHAIN_FUSED_MAX_R = 256;
 int chain_bn(int R);   // width of the N tiles the chain kernels walk
 hipError_t launch_chain_bf16(bool b_kc, bool fused, ChainArgs a, hipStream_t s);
 
+// The factor gradient Z^T . dY of a narrow sketch (GEMM_NN_F32_COLSUM on `tile`) beside the expansion of dX from slabs of G over
+// short runs of output tiles, in one launch; ask factor_beside_expand_supported first.
+bool factor_beside_expand_supported(int tile, const GemmArgs& a, const ChainArgs& c);
+hipError_t launch_factor_beside_expand(int tile, GemmArgs a, ChainArgs c, hipStream_t s);
+
 // Backward pass of a narrow sketch (bf16, R <= 32) in one pass over x and dY: per token
 // tile (32 or 64 tokens) the kernel recomputes Z = x . S_cat, forms G = dY . U_cat^T and from it the tile of
 // dX, and leaves the tile's term of dU_cat (and of dbias) as an fp32 slab; a second kernel
