@@ -148,6 +148,9 @@ sk_status sk_linear_bwd_weight_noalloc(const void* x, const void* S_cat, const v
  *     bit-reproducible from run to run).
  *   - fp32: dY . U_cat^T shares a launch with x . S_cat, and the expansion of dX one with the
  *     factor gradient.
+ *   - Wide sketches (bf16): dY . U_cat^T runs beside the recomputation of x . S_cat and the
+ *     expansion of dX beside the factor gradient, two to four launches instead of five to seven,
+ *     unless one of the products fills the chip by itself.
  *   - Other shapes run the two gradients one after the other.
  *   x [tokens, in], dY [tokens, out], S_cat [in, R], U_cat [R, out],
  *   dX [tokens, in] (output), dU_cat [R, out] fp32 (output), dbias [out] fp32 (output) or NULL.

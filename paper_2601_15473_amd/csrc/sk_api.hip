@@ -675,6 +675,49 @@ NarrowPlan plan_narrow(const Shape& s) {
   return n;
 }
 
+// Backward pass of a wide sketch in shared launches: dY.U^T beside Z^T on one tile, each in ranges or not, the sums of those in a launch,
+// then Z^T.dY beside G.S^T.
+struct WidePlan {
+  int tile;                      // of the first two, -1: none
+  int g_splits, g_k_per_split;   // ranges of dY.U^T
+  int du_tile, dx_tile;
+};
+
+// Apart, the two gradients of a layer take five to seven launches, most of which leave CUs without a work-group or with one that waits;
+// beside each other two to four.  The ranges of Z^T and of the tokens stay those of the separate calls (dU and db come out
+// the same), those of dY.U^T are as many as its slabs have room for.  The first two have one result size, so one tile
+// serves both, the one with the least modelled time: all chunks at the rate of a CU with company (its fill: 0.62 us
+// a chunk of a 128 x 128 tile, 0.27 of a 64 x 64 one) or the longest walk by itself (0.65, 0.36), whichever is more, and slabs at 4 TB/s and
+// 2.5 us for the launch that sums them.  Backward pass, us, apart : shared: 735 tokens, 560 -> 592, R = 432 23.2 : 14.7; 2777, 3376 -> 4800,
+// R = 1360 202 : 155; 2302, 3744 -> 7200, R = 672 151 : 117; 99 of 150 layers of 512 to 16384 tokens, 512 to 4096 wide, R 144 to
+// 512, were apart, now 0.78 of the time, 24 of 50 of 2048 to 16384 tokens, R 512 to 2048, 0.86, all of 257 to 600 tokens 0.69, the rest within
+// 2 %.  Layers that shared launches before on tiles of two models of their own: 0.997 (0.87 to 1.02).
+// None where one of the first two takes the 256 x 256 tile by itself (see sk_linear_bwd).
+WidePlan plan_wide(const Shape& s, const WeightPlan& w, const FirstPlan& first) {
+  WidePlan best{-1, 1, 0, 0, 0};
+  if (tune(SK_TUNE_TILE) >= 0 || choose_tile(s.T, s.R, s.out, 1) == TILE_256x256 || choose_tile(s.R, s.T, s.in, 1) == TILE_256x256) return best;
+  best.du_tile = w.tile;
+  best.dx_tile = choose_tile(s.T, s.in, s.R, 1);
+  if (w.tile == TILE_128x128 || best.dx_tile == TILE_256x256) best.dx_tile = TILE_128x128;
+  else if (best.dx_tile == TILE_64x128) best.dx_tile = TILE_128x64;
+  if (!dual_gemm_supported(GEMM_NN_F32_COLSUM, best.du_tile, GEMM_NT, best.dx_tile)) return best;
+  double least = -1.0;
+  static const struct { int tile, side; double shared, alone; } cand[] = {{TILE_128x128, 128, 0.62, 0.65}, {TILE_64x64, 64, 0.27, 0.36}};
+  const double z_walk = (double)((s.in / w.z_splits + 63) / 64);
+  for (const auto& c : cand) {
+    const double tiles = (double)((s.T + c.side - 1) / c.side) * ((s.R + c.side - 1) / c.side);
+    for (int sp = 1; sp <= first.splits; ++sp) {
+      const int64_t kps = ((s.out + sp - 1) / sp + 63) / 64 * 64;
+      if ((s.out + kps - 1) / kps != sp) continue;
+      const double g_walk = (double)(kps / 64), all = tiles * (sp * g_walk + w.z_splits * z_walk) * c.shared / NUM_CUS;
+      const double longest = (g_walk > z_walk ? g_walk : z_walk) * c.alone;
+      const double us = (all > longest ? all : longest) + (sp > 1 ? (w.z_splits > 1 ? 0.0 : 2.5) + sp * (double)s.T * s.R * 8.0 / 4.0e6 : 0.0);
+      if (least < 0.0 || us < least) { least = us; best.tile = c.tile; best.g_splits = sp; best.g_k_per_split = (int)kps; }
+    }
+  }
+  return best;
+}
+
 size_t workspace_for(sk_op op, const Shape& s) {
   const size_t mid = align_up((size_t)s.T * s.R * s.esize);  // Z or G
   switch (op) {
@@ -1319,7 +1362,7 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
     return e == hipSuccess ? SK_OK : hip_fail(e, "sk_linear_bwd (expand + sum of splits)");
   }
 
-  // --- wide sketch (two GEMMs per gradient): dY.U^T beside Z^T | Z^T.dY beside G.S^T | sums ---
+  // --- wide sketch (two GEMMs per gradient): dY.U^T beside Z^T | sums of their ranges | Z^T.dY beside G.S^T | sums ---
   int g_tile = bf16_auto ? choose_tile(tokens, s.R, out, 1) : -1;
   // Nor do the first two share a launch on that tile: where it is faster by itself they go beside each
   // other on 128 x 128 tiles unless the two launches are modelled 3 us ahead, which sorts all of 20 shapes
@@ -1341,17 +1384,36 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
   // [16384 x 1024 -> 4096], R = 144, 103 : 112; [16384 x 4096 -> 4096], R = 512, level; the
   // best the separate launches did was 2 % ahead ([8192 x 4096 -> 8192], R = 1024, 478 : 468)
   if (dx_tile == TILE_256x256) dx_tile = TILE_128x128;
+  WidePlan pair{-1, 1, 0, 0, 0};
   const FirstPlan first = plan_first(tokens, s.R, out, true);
-  if (bf16_auto && in_plan == PLAN_TWO_GEMM && first.splits == 1 && !first.few &&
-      dual_gemm_supported(GEMM_NT, g_tile, GEMM_TT, z_tile) &&
-      dual_gemm_supported(du_kind, w.tile, GEMM_NT, dx_tile)) {
+  if (bf16_any_z && in_plan == PLAN_TWO_GEMM && !first.few) {
+    pair = plan_wide(s, w, first);
+    if (pair.tile < 0 && w.z_splits == 1 && first.splits == 1 && g_tile == z_tile && dual_gemm_supported(GEMM_NT, g_tile, GEMM_TT, z_tile) &&
+        dual_gemm_supported(du_kind, w.tile, GEMM_NT, dx_tile))
+      pair = WidePlan{g_tile, 1, 0, w.tile, dx_tile};
+  }
+  if (pair.tile >= 0) {
     g_hip_error.clear();
-    const GemmArgs g = dense_args(dY, out, U_cat, out, ws_in, s.R, tokens, s.R, out, 1.0f, nullptr);
-    hipError_t e = launch_dual_gemm_bf16(GEMM_NT, g_tile, g, GEMM_TT, z_tile, z, hs);
+    // (slabs behind G, and where a split Z has them)
+    void* const g_slabs = ws_in + align_up((size_t)tokens * s.R * s.esize);
+    float* const z_slabs = reinterpret_cast<float*>(ws_w + w.zpart_at());
+    GemmArgs g = dense_args(dY, out, U_cat, out, ws_in, s.R, tokens, s.R, out, 1.0f, nullptr);
+    RoundedSum g_sum{}, z_sum{};
+    if (pair.g_splits > 1) {
+      g.C = g_slabs; g.splits = pair.g_splits; g.k_per_split = pair.g_k_per_split;
+      g_sum = RoundedSum{static_cast<const float*>(g_slabs), ws_in, (int64_t)tokens * s.R, g.splits};
+    }
+    if (w.z_splits > 1) {
+      z.C = z_slabs; z.splits = w.z_splits; z.k_per_split = w.z_k_per_split;
+      z_sum = RoundedSum{z_slabs, Z, (int64_t)s.R * w.ldz, z.splits};
+    }
+    hipError_t e = launch_dual_gemm_bf16(g.splits > 1 ? GEMM_NT_F32 : GEMM_NT, pair.tile, g, z.splits > 1 ? GEMM_TT_F32 : GEMM_TT, pair.tile, z, hs);
     if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (dY.U^T beside x.S)");
+    e = launch_reduce_to_bf16(g_sum, z_sum, hs);
+    if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (sums of dY.U^T and x.S)");
     if (want) want->take(ws_in, s);
     const GemmArgs dx = dense_args(ws_in, s.R, S_cat, s.R, dX, in, tokens, in, s.R, scale, nullptr);
-    e = launch_dual_gemm_bf16(du_kind, w.tile, du, GEMM_NT, dx_tile, dx, hs);
+    e = launch_dual_gemm_bf16(du_kind, pair.du_tile, du, GEMM_NT, pair.dx_tile, dx, hs);
     if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (Z^T.dY beside G.S^T)");
     if (red.n + red.n2 > 0) {
       e = launch_reduce_splits(red, hs);

@@ -326,16 +326,22 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const ReduceArgs p) 
 
 // Sum of split-K slabs in index order, rounded once to bf16 (an intermediate that the
 // next GEMM reads as an operand).
-__global__ __launch_bounds__(256) void reduce_to_bf16_kernel(const float* __restrict__ part,
-                                                             bf16* __restrict__ out, int64_t n,
-                                                             int splits) {
-  const int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (i4 >= n) return;
-  const float4 s = sum_slabs(part + i4, n, splits);
+// (`second` is for two products of one launch; the sum of one alone takes 0.3 us longer with it as an argument.)
+__device__ __forceinline__ void reduce_to_bf16(const RoundedSum& p, int64_t i4) {
+  const float4 s = sum_slabs(p.part + i4, p.n, p.splits);
   uint2 w;
   w.x = pack_bf16x2(s.x, s.y);
   w.y = pack_bf16x2(s.z, s.w);
-  *reinterpret_cast<uint2*>(out + i4) = w;
+  *reinterpret_cast<uint2*>(static_cast<bf16*>(p.out) + i4) = w;
+}
+__global__ __launch_bounds__(256) void reduce_to_bf16_kernel(const RoundedSum p) {
+  const int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i4 < p.n) reduce_to_bf16(p, i4);
+}
+__global__ __launch_bounds__(256) void reduce_two_to_bf16_kernel(const RoundedSum p, const RoundedSum second) {
+  const int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i4 < p.n) reduce_to_bf16(p, i4);
+  else if (i4 - p.n < second.n) reduce_to_bf16(second, i4 - p.n);
 }
 
 // Up to three fp32 arrays rounded to bf16, one behind the other over the work-groups.  Bound by the launch:
@@ -424,6 +430,13 @@ const DualPair kDualPairs[] = {
     {GEMM_NT_F32, TILE_64x64, GEMM_TT_F32, TILE_64x128},       // narrow sketch of a long input: Z^T in ranges as well
     {GEMM_NT_F32, TILE_64x128, GEMM_TT_F32, TILE_128x128},
     {GEMM_NT_F32, TILE_64x128, GEMM_TT_F32, TILE_128x64},
+    // wide sketches again, dY.U^T, Z^T or both in ranges, and a narrow dX
+    {GEMM_NT_F32, TILE_128x128, GEMM_TT, TILE_128x128},
+    {GEMM_NT, TILE_128x128, GEMM_TT_F32, TILE_128x128},
+    {GEMM_NT_F32, TILE_128x128, GEMM_TT_F32, TILE_128x128},
+    {GEMM_NT, TILE_64x64, GEMM_TT_F32, TILE_64x64},
+    {GEMM_NT_F32, TILE_64x64, GEMM_TT_F32, TILE_64x64},
+    {GEMM_NN_F32_COLSUM, TILE_128x64, GEMM_NT, TILE_64x64},
 };
 int dual_pair_index(GemmKind ka, int ta, GemmKind kb, int tb) {
   for (int i = 0; i < (int)(sizeof(kDualPairs) / sizeof(kDualPairs[0])); ++i)
@@ -477,15 +490,21 @@ hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKi
   typedef GemmTile<64, 128, false, true, float, false> TTF_64x128;
   typedef GemmTile<128, 128, false, true, float, false> TTF_128x128;
   typedef GemmTile<128, 64, false, true, float, false> TTF_128x64;
+  typedef GemmTile<128, 128, true, true, float, false> NTF_128x128;
+  typedef GemmTile<64, 64, false, true, float, false> TTF_64x64;
   // 64 x 64 tiles in one round, two work-groups to a CU: on the ring, as a product by itself.  Backward pass, us, staged : ring,
   // narrow sketches: 2925 tokens, 1584 -> 2480, R = 64 29.6 : 26.6; 1024, 1024 -> 1024, R = 64 19.6 : 17.5; 2901, 304 -> 3824, R = 16 20.1 : 20.4;
   // wide ones: 1600, 2464 -> 1536, R = 256 30.6 : 25.3; 1507, 3120 -> 464, R = 512 36.9 : 31.6; 4096, 768 -> 768, R = 256 (512
-  // work-groups) 24.5 : 23.5.  (On a ring of their own the 128 x 64 tiles of the other pairs are level with the staged ones.)
+  // work-groups) 24.5 : 23.5.  (On rings of their own the 128 x 64 and the 128 x 128 tiles of the other pairs are level with the staged
+  // ones: 150 layers with the latter, 1.0000 of the time, 0.98 to 1.02.)
   typedef RingTile<64, 64, true, true, float, false> RING_NTF_64x64;
   typedef RingTile<64, 64, false, true, bf16, false> RING_TT_64x64;
   typedef RingTile<64, 64, true, true, bf16, false> RING_NT_64x64;
-  if ((pair == 1 || pair == 5) && ga + gb <= NUM_CUS * RING_NT_64x64::PER_CU) {
+  typedef RingTile<64, 64, false, true, float, false> RING_TTF_64x64;
+  if ((pair == 1 || pair == 5 || pair == 13 || pair == 14) && ga + gb <= NUM_CUS * RING_NT_64x64::PER_CU) {
     name = "dual_gemm_kernel<ring>";
+    if (pair == 13) return launch_kernel(name, work, dual_gemm_kernel<RING_NT_64x64, RING_TTF_64x64>, grid, block, s, a, b, (int)ga);
+    if (pair == 14) return launch_kernel(name, work, dual_gemm_kernel<RING_NTF_64x64, RING_TTF_64x64>, grid, block, s, a, b, (int)ga);
     if (pair == 1) return launch_kernel(name, work, dual_gemm_kernel<RING_NTF_64x64, RING_TT_64x64>, grid, block, s, a, b, (int)ga);
     return launch_kernel(name, work, dual_gemm_kernel<RING_NT_64x64, RING_TT_64x64>, grid, block, s, a, b, (int)ga);
   }
@@ -500,6 +519,12 @@ hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKi
     case 7: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x64, TTF_64x128>, grid, block, s, a, b, (int)ga);
     case 8: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x128, TTF_128x128>, grid, block, s, a, b, (int)ga);
     case 9: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x128, TTF_128x64>, grid, block, s, a, b, (int)ga);
+    case 10: return launch_kernel(name, work, dual_gemm_kernel<NTF_128x128, TT_128x128>, grid, block, s, a, b, (int)ga);
+    case 11: return launch_kernel(name, work, dual_gemm_kernel<NT_128x128, TTF_128x128>, grid, block, s, a, b, (int)ga);
+    case 12: return launch_kernel(name, work, dual_gemm_kernel<NTF_128x128, TTF_128x128>, grid, block, s, a, b, (int)ga);
+    case 13: return launch_kernel(name, work, dual_gemm_kernel<NT_64x64, TTF_64x64>, grid, block, s, a, b, (int)ga);
+    case 14: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x64, TTF_64x64>, grid, block, s, a, b, (int)ga);
+    case 15: return launch_kernel(name, work, dual_gemm_kernel<NNFC_128x64, NT_64x64>, grid, block, s, a, b, (int)ga);
     default: return hipErrorInvalidValue;
   }
 }
@@ -526,14 +551,19 @@ hipError_t launch_reduce_splits_2d(const float* part, float* out, int rows, int 
                        cols, ld_out, splits, scale);
 }
 
-hipError_t launch_reduce_to_bf16(const float* part, void* out, int64_t n, int splits, hipStream_t s) {
-  if (n <= 0 || (n & 3) != 0 || splits < 1) return hipErrorInvalidValue;
-  const int64_t groups = (n / 4 + 255) / 256;
-  if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
-  note_matrix(part, splits, n, n, 4, false);
-  note_matrix(out, 1, n, n, 2, true);
-  return launch_kernel("reduce_to_bf16_kernel", Work{0.0, (double)n * (4.0 * splits + 2.0)}, reduce_to_bf16_kernel, dim3((unsigned)groups), dim3(256), s,
-                       part, static_cast<bf16*>(out), n, splits);
+hipError_t launch_reduce_to_bf16(const RoundedSum& a, const RoundedSum& b, hipStream_t s) {
+  const int64_t groups = ((a.n + b.n) / 4 + 255) / 256;
+  if (groups == 0) return hipSuccess;
+  if (a.n < 0 || b.n < 0 || ((a.n | b.n) & 3) != 0 || (a.n > 0 && a.splits < 1) || (b.n > 0 && b.splits < 1) || groups > 0x7fffffffLL) return hipErrorInvalidValue;
+  Work work{0.0, 0.0};
+  for (const RoundedSum& r : {a, b}) {
+    if (r.n == 0) continue;
+    note_matrix(r.part, r.splits, r.n, r.n, 4, false);
+    note_matrix(r.out, 1, r.n, r.n, 2, true);
+    work.bytes += (double)r.n * (4.0 * r.splits + 2.0);
+  }
+  if (a.n > 0 && b.n > 0) return launch_kernel("reduce_two_to_bf16_kernel", work, reduce_two_to_bf16_kernel, dim3((unsigned)groups), dim3(256), s, a, b);
+  return launch_kernel("reduce_to_bf16_kernel", work, reduce_to_bf16_kernel, dim3((unsigned)groups), dim3(256), s, a.n > 0 ? a : b);
 }
 
 hipError_t launch_reduce_splits(const ReduceArgs& a, hipStream_t s) {

@@ -171,8 +171,17 @@ constexpr int F32_BK = 32;
 
 hipError_t launch_reduce_splits(const ReduceArgs& a, hipStream_t s);
 // out[i] = bf16(sum over s of part[s][i]), i < n (n a multiple of 4; slabs n elements apart,
-// summed in index order)
-hipError_t launch_reduce_to_bf16(const float* part, void* out, int64_t n, int splits, hipStream_t s);
+// summed in index order), of up to two products (n 0 for none)
+struct RoundedSum {
+  const float* part;
+  void* out;
+  int64_t n;
+  int splits;
+};
+hipError_t launch_reduce_to_bf16(const RoundedSum& a, const RoundedSum& b, hipStream_t s);
+inline hipError_t launch_reduce_to_bf16(const float* part, void* out, int64_t n, int splits, hipStream_t s) {
+  return launch_reduce_to_bf16(RoundedSum{part, out, n, splits}, RoundedSum{}, s);
+}
 // out[r * ld_out + c] = scale * sum over s of part[s][r * cols + c] (r < rows, c < cols, cols a multiple of 4;
 // slabs rows * cols elements apart, summed in index order): a column range of a wider matrix
 hipError_t launch_reduce_splits_2d(const float* part, float* out, int rows, int cols, int64_t ld_out,
