@@ -156,6 +156,20 @@ int choose_tile(int64_t M, int64_t N, int64_t K, int splits) {
   }
   return TILE_64x64;
 }
+// ... of an expansion in a launch of its own: also 256 x 128 on a ring, while those make one round and 128 x 128 tiles more than one.  A launch takes
+// 6.5 us + 0.0148 a k then (fitted), against the staged tiles' 9.2 + 0.0165, and fills 24 KB a chunk and 128 x 128 of the result where
+// those fill 32.  180 layers with a short input, 600 to 16384 tokens, expansions of 144 to 2048 to 512 to 8192, us, 128 x 128 or 256 x 256 : 256 x 128: 2272
+// tokens, R = 1968, 1856 out 43.1 : 36.7; 3220, 448, 1376 17.0 : 14.7; 1615, 256, 3488 13.1 : 12.5; 0.89 of the time above R = 256 (0.78 to 1.04,
+// two behind, both of 12000 tokens to 528 and 560), 0.93 below (0.90 to 0.98).  Not for the first contractions, whose operands come
+// from memory and not from the launch before: 0.84 to 1.09 of the time there, level over 40 layers.  Past a round each round costs 8 us again.
+int choose_expansion_tile(int64_t M, int64_t N, int64_t K) {
+  const int t = choose_tile(M, N, K, 1);
+  if (tune(SK_TUNE_TILE) >= 0 || K <= 128) return t;
+  const int64_t mid = (M + 255) / 256 * ((N + 127) / 128), small = small_tiles(M, N);
+  if (mid > NUM_CUS || small <= NUM_CUS) return t;
+  const double us = 6.5 + 0.0148 * (double)K;
+  return us < (t == TILE_256x256 ? big_tiles_us(M, N, (double)K, 1) : small_tiles_us(small, (double)K)) ? TILE_256x128 : t;
+}
 
 // fp32 contraction [M, N] over K: tile and split of the contraction (fp32 slabs, summed by one
 // more launch), the pair with the least modelled time.  Measured rates of one CU: a lone 64 x 64
@@ -760,7 +774,7 @@ size_t workspace_for(sk_op op, const Shape& s) {
 
 hipError_t gemm(const Shape& s, GemmKind kind, GemmArgs a, hipStream_t st) {
   if (s.dtype == SK_BF16 && few_rows_splits(a.M, a.N, a.K, false) > 0) return launch_gemm_few_rows_bf16(kind, a, st);
-  if (s.dtype == SK_BF16) return launch_gemm_bf16(kind, choose_tile(a.M, a.N, a.K, 1), a, st);
+  if (s.dtype == SK_BF16) return launch_gemm_bf16(kind, choose_expansion_tile(a.M, a.N, a.K), a, st);
   return launch_gemm_f32(kind, plan_f32(a.M, a.N, a.K, 1).tile, a, st);
 }
 

@@ -387,6 +387,19 @@ static hipError_t launch_cfg(GemmArgs a, hipStream_t s) {
   return launch_kernel(name.c_str(), work, gemm_bf16_kernel<BM, BN, A_KC, B_KC, OutT, COLSUM>, dim3((unsigned)total), dim3(256), s, a);
 }
 
+// Tiles that have a ring only.
+template <int BM, int BN, bool A_KC, bool B_KC>
+static hipError_t launch_ring(GemmArgs a, hipStream_t s) {
+  a.tiles_m = (a.M + BM - 1) / BM;
+  a.tiles_n = (a.N + BN - 1) / BN;
+  const long long total = (long long)a.tiles_m * a.tiles_n;
+  if (a.splits != 1 || total <= 0 || total > 0x7fffffffLL || (A_KC && !within_window(BM, a.lda, BK, 2)) || (B_KC && !within_window(BN, a.ldb, BK, 2)))
+    return hipErrorInvalidValue;
+  note_gemm(a, A_KC, B_KC, 2, 2, false);
+  static const std::string name = kernel_label("gemm_bf16_kernel", {lbl(BM), lbl(BN), lbl(A_KC), lbl(B_KC), "bf16", lbl(false), lbl(true)});
+  return launch_kernel(name.c_str(), gemm_work(a, 2, 2, false), gemm_bf16_kernel<BM, BN, A_KC, B_KC, bf16, false, true>, dim3((unsigned)total), dim3(256), s, a);
+}
+
 template <bool A_KC, bool B_KC, typename OutT, bool COLSUM>
 static hipError_t launch_tiles(int tile, const GemmArgs& a, hipStream_t s) {
   switch (tile) {
@@ -400,6 +413,8 @@ static hipError_t launch_tiles(int tile, const GemmArgs& a, hipStream_t s) {
 
 hipError_t launch_gemm_bf16(GemmKind kind, int tile, const GemmArgs& a, hipStream_t s) {
   if (tile == TILE_256x256) return launch_gemm256_bf16(kind, a, s);
+  if (tile == TILE_256x128 && kind == GEMM_NN) return launch_ring<256, 128, true, false>(a, s);
+  if (tile == TILE_256x128 && kind == GEMM_NT) return launch_ring<256, 128, true, true>(a, s);
   switch (kind) {
     case GEMM_NN: return launch_tiles<true, false, bf16, false>(tile, a, s);
     case GEMM_NT: return launch_tiles<true, true, bf16, false>(tile, a, s);

@@ -15,7 +15,8 @@ namespace sk {
 // [768 x 384] 10.2 -> 8.3; 128 x 128, S^T . x^T of [8192 x 1024] and R = 512 15.4 -> 12.5; Z^T . dY of
 // [8192 x 4096] in two ranges 51.3 -> 45.1; [8192 x 1024] . [1024 x 512] 16.3 -> 14.8.  What bounds it now is the fill: with
 // neither reads nor MFMAs the same loops take 80 to 95 % of the time (35 to 57 GB/s a CU, a chunk of a
-// 128 x 128 tile 0.58 us), and neither more slots nor tiles that start at different k changed that.
+// 128 x 128 tile 0.58 us), and neither more slots nor tiles that start at different k changed that.  A 256 x 128 tile, a wave's part 128 x 64,
+// fills three quarters as much for the same products, 0.83 us a chunk: for expansions of one round (choose_expansion_tile).
 template <int BM, int BN, bool A_KC, bool B_KC, typename OutT, bool COLSUM>
 struct RingTile {
   static constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;   // waves 2 x 2
@@ -104,8 +105,8 @@ RingTile<BM, BN, A_KC, B_KC, OutT, COLSUM>::run(const GemmArgs& p, const int blo
   // ---- fragments: two sets of two k steps ----
   bf16x8 fa[2][2][TM], fb[2][2][TN];
   const unsigned a_0 = PA::read_address(0, lane), b_0 = PB::read_address(0, lane);
-  const unsigned a_read = A_KC ? a_0 + wm * TM * 4096 : TM == 2 ? a_0 + wm * 8192 : a_0 ^ (wm << 6);
-  const unsigned b_read = A_BYTES + (B_KC ? b_0 + wn * TN * 4096 : TN == 2 ? b_0 + wn * 8192 : b_0 ^ (wn << 6));
+  const unsigned a_read = A_KC || TM >= 2 ? a_0 + wm * TM * 4096 : a_0 ^ (wm << 6);
+  const unsigned b_read = A_BYTES + (B_KC || TN >= 2 ? b_0 + wn * TN * 4096 : b_0 ^ (wn << 6));
   auto read_a = [&](int set, int s, int i, unsigned slot, int ks) { fa[set][s][i] = PA::frag(slot + a_read, i, ks); };
   auto read_b = [&](int set, int s, int j, unsigned slot, int ks) { fb[set][s][j] = PB::frag(slot + b_read, j, ks); };
 

@@ -100,11 +100,12 @@ enum TileCfg : int {
   TILE_128x64 = 2,
   TILE_64x128 = 3,
   TILE_64x64 = 4,
-  TILE_COUNT = 5,
+  TILE_COUNT = 5,        // (what sk_set_tuning can name)
+  TILE_256x128 = 5,      // on a ring only, GEMM_NN and GEMM_NT
 };
 
 inline void tile_dims(int tile, int& bm, int& bn) {
-  static const int dims[TILE_COUNT][2] = {{256, 256}, {128, 128}, {128, 64}, {64, 128}, {64, 64}};
+  static const int dims[][2] = {{256, 256}, {128, 128}, {128, 64}, {64, 128}, {64, 64}, {256, 128}};
   bm = dims[tile][0];
   bn = dims[tile][1];
 }
