@@ -201,6 +201,18 @@ sk_status sk_linear_bwd_two_sided(const void* x, const void* dY, const void* S_c
                                   void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * sk_linear_bwd (dA NULL) or sk_linear_bwd_two_sided, bf16, with the gradients of the factors, the bias and the first stage in the
+ * layer's own type as well: what sk_round_gradients makes of that call's, bit for bit, their last sums and the rounding in one launch.
+ *   dU_cat, dbias (or NULL), dA: fp32 room as there, contents undefined afterwards.
+ *   dU_bf16: the first dU_rows rows of dU_cat; dbias_bf16; dA_bf16 [in, R / 2] (NULL exactly if dA is): NULL for what is not wanted,
+ *   at least one of them not.
+ * Workspace: that call's.
+ */
+sk_status sk_linear_bwd_rounded(const void* x, const void* dY, const void* S_cat, const void* U_cat, void* dX, float* dU_cat, float* dbias, float* dA,
+                                void* dU_bf16, int64_t dU_rows, void* dbias_bf16, void* dA_bf16, int64_t tokens, int64_t in, int64_t out, int32_t l,
+                                int32_t k, sk_dtype dtype, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * to[i][j] = bf16(from[i][j]) for j < n[i], i < count (1 to 3 arrays, 16-byte aligned), in one launch: the
  * fp32 gradients of a bf16 layer in the layer's own type.
  */

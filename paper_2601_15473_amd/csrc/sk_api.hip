@@ -832,6 +832,17 @@ struct GColumns {
   }
 };
 
+// Where a backward pass leaves the gradients of the factors, the bias and the first stage for a launch that sums and rounds them: finished in
+// fp32 (splits 1), or in slabs where its schedule would end with a launch for their sum.
+struct Unrounded {
+  struct Part {
+    const float* at;
+    int64_t stride;
+    int splits;
+    float scale;
+  } du, db, da;
+};
+
 // Two fp32 products of the backward pass in one launch where both take the same tile, else in two.
 hipError_t gemm_pair_f32(GemmKind kind_a, int tile_a, const GemmArgs& a, GemmKind kind_b, int tile_b, const GemmArgs& b, hipStream_t st) {
   if (tile_a == tile_b) return launch_dual_gemm_f32(kind_a, a, kind_b, b, tile_a, st);
@@ -888,7 +899,8 @@ sk_status bwd_f32(const Shape& s, const void* x, const void* dY, const void* S_c
 }
 
 // dA = (1 / l) . x^T . G for nc columns of G [tokens, nc], rows ldg apart; `part`: the slabs of split tokens.
-sk_status first_stage_gradient(const Shape& s, const void* x, const void* G, int64_t ldg, int64_t nc, float* dA, float* part, hipStream_t hs) {
+sk_status first_stage_gradient(const Shape& s, const void* x, const void* G, int64_t ldg, int64_t nc, float* dA, float* part, hipStream_t hs,
+                               Unrounded* later = nullptr) {
   // dA = scale * x^T . G, the token axis split in order
   const TokenPlan t = plan_tokens(s.in, nc, s.T, s.dtype, false, 0);
   GemmArgs a{};
@@ -904,7 +916,9 @@ sk_status first_stage_gradient(const Shape& s, const void* x, const void* G, int
   hipError_t e = s.dtype == SK_BF16 ? launch_gemm_bf16(GEMM_TN_F32_PLAIN, t.tile, a, hs)
                        : launch_gemm_f32(GEMM_TN_F32, t.tile, a, hs);
   if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd_weight_first (x^T.G)");
-  if (t.splits > 1) {
+  if (t.splits > 1 && later) {
+    later->da = {part, (int64_t)s.in * nc, t.splits, scale};
+  } else if (t.splits > 1) {
     ReduceArgs r{};
     r.part = part; r.out = dA; r.n = (int64_t)s.in * nc; r.scale = scale;
     r.n2 = 0; r.splits = t.splits; r.splits2 = 1;
@@ -1253,7 +1267,7 @@ sk_status sk_linear_bwd_weight_noalloc(const void* x, const void* S_cat, const v
 
 static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, const void* U_cat, void* dX, float* dU_cat,
                           float* dbias, int64_t tokens, int64_t in, int64_t out, int32_t l, int32_t k, sk_dtype dtype,
-                          void* workspace, size_t workspace_bytes, void* stream, GColumns* want) {
+                          void* workspace, size_t workspace_bytes, void* stream, GColumns* want, Unrounded* later) {
   if (!x || !dY || !S_cat || !U_cat || !dX || !dU_cat) return SK_ERR_INVALID_ARG;
   if (!aligned16(x) || !aligned16(dY) || !aligned16(S_cat) || !aligned16(U_cat) || !aligned16(dX) ||
       !aligned16(dU_cat) || !aligned16(dbias) || !aligned16(workspace))
@@ -1323,6 +1337,13 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
   red.part = part; red.out = dU_cat; red.n = w.splits > 1 ? (int64_t)s.R * out : 0; red.scale = scale;
   red.part2 = cpart; red.out2 = dbias; red.n2 = (dbias && w.colsum_splits > 1) ? out : 0; red.scale2 = 1.0f;
   red.splits = w.splits; red.splits2 = w.colsum_splits;
+  // the sums behind everything else: in a launch of their own, or left to the one that rounds them
+  auto last_sums = [&]() -> hipError_t {
+    if (!later) return launch_reduce_splits(red, hs);
+    if (red.n > 0) later->du = {red.part, red.n, red.splits, red.scale};
+    if (red.n2 > 0) later->db = {red.part2, red.n2, red.splits2, red.scale2};
+    return hipSuccess;
+  };
 
   // --- narrow sketch: split-K slabs of G beside Z^T | Z^T.dY beside the expansion of dX | sums, or, where the expansion's
   // runs are long, Z^T.dY | expand dX, carrying the sums ---
@@ -1365,7 +1386,7 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
     if (beside) {
       e = launch_factor_beside_expand(w.tile, du, c, hs);
       if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (Z^T.dY beside the expansion)");
-      e = launch_reduce_splits(red, hs);
+      e = last_sums();
       return e == hipSuccess ? SK_OK : hip_fail(e, "sk_linear_bwd (sum of splits)");
     }
     // Z^T.dY, then the expansion of dX carrying the sum of the token splits
@@ -1429,11 +1450,8 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
     const GemmArgs dx = dense_args(ws_in, s.R, S_cat, s.R, dX, in, tokens, in, s.R, scale, nullptr);
     e = launch_dual_gemm_bf16(du_kind, pair.du_tile, du, GEMM_NT, pair.dx_tile, dx, hs);
     if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (Z^T.dY beside G.S^T)");
-    if (red.n + red.n2 > 0) {
-      e = launch_reduce_splits(red, hs);
-      if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (sum of splits)");
-    }
-    return SK_OK;
+    e = last_sums();
+    return e == hipSuccess ? SK_OK : hip_fail(e, "sk_linear_bwd (sum of splits)");
   }
 
   const sk_status a = sk_linear_bwd_input(dY, S_cat, U_cat, dX, tokens, in, out, l, k, dtype, ws_in,
@@ -1448,7 +1466,7 @@ sk_status sk_linear_bwd(const void* x, const void* dY, const void* S_cat, const 
                         void* dX, float* dU_cat, float* dbias, int64_t tokens, int64_t in,
                         int64_t out, int32_t l, int32_t k, sk_dtype dtype, void* workspace,
                         size_t workspace_bytes, void* stream) {
-  return bwd_both(x, dY, S_cat, U_cat, dX, dU_cat, dbias, tokens, in, out, l, k, dtype, workspace, workspace_bytes, stream, nullptr);
+  return bwd_both(x, dY, S_cat, U_cat, dX, dU_cat, dbias, tokens, in, out, l, k, dtype, workspace, workspace_bytes, stream, nullptr, nullptr);
 }
 
 sk_status sk_linear_bwd_weight_first(const void* x, const void* U_cat, const void* dY, float* dA,
@@ -1483,9 +1501,9 @@ sk_status sk_linear_bwd_weight_first(const void* x, const void* U_cat, const voi
   return first_stage_gradient(s, x, G, nc, nc, dA, part, hs);
 }
 
-sk_status sk_linear_bwd_two_sided(const void* x, const void* dY, const void* S_cat, const void* U_cat, void* dX, float* dU_cat, float* dbias,
-                                  float* dA, int64_t tokens, int64_t in, int64_t out, int32_t l, int32_t k, sk_dtype dtype,
-                                  void* workspace, size_t workspace_bytes, void* stream) {
+static sk_status bwd_two_sided(const void* x, const void* dY, const void* S_cat, const void* U_cat, void* dX, float* dU_cat, float* dbias, float* dA,
+                               int64_t tokens, int64_t in, int64_t out, int32_t l, int32_t k, sk_dtype dtype, void* workspace, size_t workspace_bytes,
+                               void* stream, Unrounded* later) {
   if (!dA || !aligned16(dA) || !workspace || !aligned16(workspace)) return SK_ERR_INVALID_ARG;
   Shape s;
   const sk_status st = check_shape(tokens, in, out, l, k, dtype, s);
@@ -1496,11 +1514,46 @@ sk_status sk_linear_bwd_two_sided(const void* x, const void* dY, const void* S_c
   unsigned char* const ws = static_cast<unsigned char*>(workspace);
   const size_t both = workspace_for(SK_OP_BWD, s), room = align_up((size_t)s.T * half * s.esize);
   GColumns want{half, ws + both, nullptr, 0};
-  const sk_status a = bwd_both(x, dY, S_cat, U_cat, dX, dU_cat, dbias, tokens, in, out, l, k, dtype, workspace, both, stream, &want);
+  const sk_status a = bwd_both(x, dY, S_cat, U_cat, dX, dU_cat, dbias, tokens, in, out, l, k, dtype, workspace, both, stream, &want, later);
   if (a != SK_OK) return a;
   if (want.at == nullptr)
     return sk_linear_bwd_weight_first(x, U_cat, dY, dA, tokens, in, out, l, k, half, half, dtype, ws + both, workspace_bytes - both, stream);
-  return first_stage_gradient(s, x, want.at, want.ld, half, dA, reinterpret_cast<float*>(ws + both + room), static_cast<hipStream_t>(stream));
+  return first_stage_gradient(s, x, want.at, want.ld, half, dA, reinterpret_cast<float*>(ws + both + room), static_cast<hipStream_t>(stream), later);
+}
+
+sk_status sk_linear_bwd_two_sided(const void* x, const void* dY, const void* S_cat, const void* U_cat, void* dX, float* dU_cat, float* dbias,
+                                  float* dA, int64_t tokens, int64_t in, int64_t out, int32_t l, int32_t k, sk_dtype dtype,
+                                  void* workspace, size_t workspace_bytes, void* stream) {
+  return bwd_two_sided(x, dY, S_cat, U_cat, dX, dU_cat, dbias, dA, tokens, in, out, l, k, dtype, workspace, workspace_bytes, stream, nullptr);
+}
+
+sk_status sk_linear_bwd_rounded(const void* x, const void* dY, const void* S_cat, const void* U_cat, void* dX, float* dU_cat, float* dbias, float* dA,
+                                void* dU_bf16, int64_t dU_rows, void* dbias_bf16, void* dA_bf16, int64_t tokens, int64_t in, int64_t out, int32_t l,
+                                int32_t k, sk_dtype dtype, void* workspace, size_t workspace_bytes, void* stream) {
+  if ((!dU_bf16 && !dbias_bf16 && !dA_bf16) || !aligned16(dU_bf16) || !aligned16(dbias_bf16) || !aligned16(dA_bf16)) return SK_ERR_INVALID_ARG;
+  if ((dbias_bf16 && !dbias) || (dA_bf16 != nullptr) != (dA != nullptr)) return SK_ERR_INVALID_ARG;
+  Shape s;
+  const sk_status st = check_shape(tokens, in, out, l, k, dtype, s);
+  if (st != SK_OK) return st;
+  if (dtype != SK_BF16) return SK_ERR_UNSUPPORTED;
+  if (dU_bf16 && (dU_rows < 1 || dU_rows > s.R)) return SK_ERR_INVALID_ARG;
+  Unrounded u{{dU_cat, 0, 1, 1.0f}, {dbias, 0, 1, 1.0f}, {dA, 0, 1, 1.0f}};
+  const sk_status a = dA ? bwd_two_sided(x, dY, S_cat, U_cat, dX, dU_cat, dbias, dA, tokens, in, out, l, k, dtype, workspace, workspace_bytes, stream, &u)
+                         : bwd_both(x, dY, S_cat, U_cat, dX, dU_cat, dbias, tokens, in, out, l, k, dtype, workspace, workspace_bytes, stream, nullptr, &u);
+  if (a != SK_OK) return a;
+  RoundArgs r{};
+  int count = 0;
+  auto add = [&](const Unrounded::Part& part, void* to, int64_t n) {
+    if (!to) return;
+    r.from[count] = part.at; r.to[count] = static_cast<unsigned short*>(to); r.n[count] = n;
+    r.stride[count] = part.splits > 1 ? part.stride : n; r.splits[count] = part.splits; r.scale[count] = part.scale;
+    ++count;
+  };
+  add(u.du, dU_bf16, dU_rows * out);
+  add(u.db, dbias_bf16, out);
+  add(u.da, dA_bf16, in * (s.R / 2));
+  const hipError_t e = launch_round_gradients(r, static_cast<hipStream_t>(stream));
+  return e == hipSuccess ? SK_OK : hip_fail(e, "sk_linear_bwd_rounded (sums and rounding)");
 }
 
 sk_status sk_round_gradients(const float* const* from, void* const* to, const int64_t* n, int32_t count, void* stream) {
@@ -1508,7 +1561,8 @@ sk_status sk_round_gradients(const float* const* from, void* const* to, const in
   RoundArgs a{};
   for (int i = 0; i < count; ++i) {
     if (!from[i] || !to[i] || !aligned16(from[i]) || !aligned16(to[i]) || n[i] < 1) return SK_ERR_INVALID_ARG;
-    a.from[i] = from[i]; a.to[i] = static_cast<unsigned short*>(to[i]); a.n[i] = n[i];
+    a.from[i] = from[i]; a.to[i] = static_cast<unsigned short*>(to[i]); a.n[i] = a.stride[i] = n[i];
+    a.splits[i] = 1; a.scale[i] = 1.0f;
   }
   g_hip_error.clear();
   const hipError_t e = launch_round_gradients(a, static_cast<hipStream_t>(stream));

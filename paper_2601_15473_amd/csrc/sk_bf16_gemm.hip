@@ -344,8 +344,9 @@ __global__ __launch_bounds__(256) void reduce_two_to_bf16_kernel(const RoundedSu
   else if (i4 - p.n < second.n) reduce_to_bf16(second, i4 - p.n);
 }
 
-// Up to three fp32 arrays rounded to bf16, one behind the other over the work-groups.  Bound by the launch:
-// 246 k numbers (a two-sided BERT-base layer's gradients) 2.7 us, through torch's fused copy 13.6.
+// Up to three fp32 arrays, whole or in slabs, rounded to bf16, one behind the other over the work-groups.  Bound by the launch:
+// 246 k numbers (a two-sided BERT-base layer's gradients) 2.7 us, through torch's fused copy 13.6.  The sums of their ranges here instead of
+// ahead of it are two launches less of that layer's six backward.
 __global__ __launch_bounds__(256) void round_gradients_kernel(const RoundArgs p) {
   int64_t i4 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
 #pragma unroll
@@ -354,10 +355,11 @@ __global__ __launch_bounds__(256) void round_gradients_kernel(const RoundArgs p)
       const float* const from = p.from[s] + i4;
       unsigned short* const to = p.to[s] + i4;
       if (i4 + 4 <= p.n[s]) {
-        const float4 v = *reinterpret_cast<const float4*>(from);
+        float4 v = sum_slabs(from, p.stride[s], p.splits[s]);
+        v.x *= p.scale[s]; v.y *= p.scale[s]; v.z *= p.scale[s]; v.w *= p.scale[s];
         *reinterpret_cast<uint2*>(to) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
       } else {
-        for (int e = 0; i4 + e < p.n[s]; ++e) to[e] = (unsigned short)pack_bf16x2(from[e], 0.f);
+        for (int e = 0; i4 + e < p.n[s]; ++e) to[e] = (unsigned short)pack_bf16x2(from[e] * p.scale[s], 0.f);
       }
       return;
     }
@@ -590,15 +592,19 @@ hipError_t launch_reduce_splits(const ReduceArgs& a, hipStream_t s) {
 
 hipError_t launch_round_gradients(const RoundArgs& a, hipStream_t s) {
   int64_t pieces = 0;
+  Work work{0.0, 0.0};
   for (int i = 0; i < RoundArgs::MAX; ++i) {
+    if (a.n[i] == 0) continue;
+    if (a.n[i] < 0 || a.splits[i] < 1 || (a.splits[i] > 1 && (a.n[i] & 3) != 0)) return hipErrorInvalidValue;
     pieces += (a.n[i] + 3) / 4;
-    note_matrix(a.from[i], 1, a.n[i], a.n[i], 4, false);
+    note_matrix(a.from[i], a.splits[i], a.n[i], a.stride[i], 4, false);
     note_matrix(a.to[i], 1, a.n[i], a.n[i], 2, true);
+    work.bytes += (double)a.n[i] * (4.0 * a.splits[i] + 2.0);
   }
   const int64_t groups = (pieces + 255) / 256;
   if (groups <= 0) return hipSuccess;
   if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
-  return launch_kernel("round_gradients_kernel", Work{0.0, 24.0 * pieces}, round_gradients_kernel, dim3((unsigned)groups), dim3(256), s, a);
+  return launch_kernel("round_gradients_kernel", work, round_gradients_kernel, dim3((unsigned)groups), dim3(256), s, a);
 }
 
 }  // namespace sk

@@ -187,12 +187,15 @@ inline hipError_t launch_reduce_to_bf16(const float* part, void* out, int64_t n,
 // slabs rows * cols elements apart, summed in index order): a column range of a wider matrix
 hipError_t launch_reduce_splits_2d(const float* part, float* out, int rows, int cols, int64_t ld_out,
                                    int splits, float scale, hipStream_t s);
-// to[i][j] = bf16(from[i][j]), j < n[i], of up to three arrays (n 0 for none)
+// to[i][j] = bf16(scale[i] * sum over k < splits[i] of from[i][k * stride[i] + j]), j < n[i], of up to three arrays (n 0 for none; slabs
+// summed in index order; with more than one of them n a multiple of 4)
 struct RoundArgs {
   static constexpr int MAX = 3;
   const float* from[MAX];
   unsigned short* to[MAX];
-  int64_t n[MAX];
+  int64_t n[MAX], stride[MAX];
+  int splits[MAX];
+  float scale[MAX];
 };
 hipError_t launch_round_gradients(const RoundArgs& a, hipStream_t s);
 // Two GEMMs that do not depend on each other in one launch (see dual_gemm_kernel); built

@@ -203,14 +203,18 @@ struct Linear : torch::autograd::Function<Linear> {
         const Tensor& ws = w.get(x2.device(), stream, need);
         void* const wp = ws.data_ptr();
         const size_t wn = (size_t)ws.numel();
-        if (need_dx && need_w)
+        if (need_dx && need_w && round.count > 0)
+          st = sk_linear_bwd_rounded(x2.data_ptr(), dY.data_ptr(), S.data_ptr(), U.data_ptr(), dX.data_ptr(), du, dbias, nullptr,
+                                     need_du ? dU_out.data_ptr() : nullptr, U.size(0), need_db ? db_out.data_ptr() : nullptr, nullptr, tokens, in, out, kept.l,
+                                     kept.k, dt, wp, wn, stream);
+        else if (need_dx && need_w)
           st = sk_linear_bwd(x2.data_ptr(), dY.data_ptr(), S.data_ptr(), U.data_ptr(), dX.data_ptr(), du, dbias, tokens, in, out, kept.l,
                              kept.k, dt, wp, wn, stream);
         else if (need_dx)
           st = sk_linear_bwd_input(dY.data_ptr(), S.data_ptr(), U.data_ptr(), dX.data_ptr(), tokens, in, out, kept.l, kept.k, dt, wp, wn, stream);
         else
           st = sk_linear_bwd_weight(x2.data_ptr(), S.data_ptr(), dY.data_ptr(), du, dbias, tokens, in, out, kept.l, kept.k, dt, wp, wn, stream);
-        if (st == SK_OK && round.count > 0) st = sk_round_gradients(round.from, round.to, round.n, round.count, stream);
+        if (st == SK_OK && round.count > 0 && !need_dx) st = sk_round_gradients(round.from, round.to, round.n, round.count, stream);
       }
       check(st);
       dU = need_du ? dU_out : Tensor();
@@ -243,12 +247,11 @@ struct LinearTwoSided : torch::autograd::Function<LinearTwoSided> {
     Tensor dX = at::empty({tokens, in}, x2.options()), dA = at::empty({in, half}, f32), dB = at::empty({2 * half, out}, f32), db;
     if (kept.bias) db = at::empty({out}, f32);
     const Tensor dB_used = dB.narrow(0, 0, half);   // (the rest belongs to S2^T: gradients of fixed numbers)
-    Rounding round;
     Tensor dA_out = dA, dB_out = dB_used, db_out = db;
-    if (dt != SK_F32) {
-      if (kept.bias) db_out = round.add(db, A.options());
-      dA_out = round.add(dA, A.options());
-      dB_out = round.add(dB_used, A.options());
+    if (dt != SK_F32) {   // each a tensor of its own
+      if (kept.bias) db_out = at::empty(db.sizes(), A.options());
+      dA_out = at::empty(dA.sizes(), A.options());
+      dB_out = at::empty(dB_used.sizes(), A.options());
     }
     void* const stream = stream_of(x2.device());
     const int32_t l2 = 2 * kept.l;
@@ -258,10 +261,15 @@ struct LinearTwoSided : torch::autograd::Function<LinearTwoSided> {
       Workspaces& w = workspaces();
       const std::lock_guard<std::mutex> lock(w.mutex);
       const Tensor& ws = w.get(x2.device(), stream, need);
-      st = sk_linear_bwd_two_sided(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), dB.data_ptr<float>(),
-                                   kept.bias ? db.data_ptr<float>() : nullptr, dA.data_ptr<float>(), tokens, in, out, l2, kept.k, dt,
-                                   ws.data_ptr(), (size_t)ws.numel(), stream);
-      if (st == SK_OK && round.count > 0) st = sk_round_gradients(round.from, round.to, round.n, round.count, stream);
+      if (dt != SK_F32)
+        st = sk_linear_bwd_rounded(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), dB.data_ptr<float>(),
+                                   kept.bias ? db.data_ptr<float>() : nullptr, dA.data_ptr<float>(), dB_out.data_ptr(), half,
+                                   kept.bias ? db_out.data_ptr() : nullptr, dA_out.data_ptr(), tokens, in, out, l2, kept.k, dt, ws.data_ptr(),
+                                   (size_t)ws.numel(), stream);
+      else
+        st = sk_linear_bwd_two_sided(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), dB.data_ptr<float>(),
+                                     kept.bias ? db.data_ptr<float>() : nullptr, dA.data_ptr<float>(), tokens, in, out, l2, kept.k, dt,
+                                     ws.data_ptr(), (size_t)ws.numel(), stream);
     }
     check(st);
     return {in_shape(ctx, dX), dB_out, dA_out, db_out, Tensor(), Tensor(), Tensor(), Tensor()};

@@ -57,6 +57,8 @@ _lib.sk_linear_bwd_weight_first.argtypes = [_vp, _vp, _vp, _vp, _i64, _i64, _i64
                                             ctypes.c_int, _vp, _sz, _vp]
 _lib.sk_linear_bwd_two_sided.restype = ctypes.c_int
 _lib.sk_linear_bwd_two_sided.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp] + _tail
+_lib.sk_linear_bwd_rounded.restype = ctypes.c_int
+_lib.sk_linear_bwd_rounded.argtypes = [_vp] * 9 + [_i64, _vp, _vp] + _tail
 _lib.sk_round_gradients.restype = ctypes.c_int
 _lib.sk_round_gradients.argtypes = [ctypes.POINTER(_vp), ctypes.POINTER(_vp), ctypes.POINTER(_i64), _i32, _vp]
 _lib.sk_linear_workspace_bytes.restype = _sz
@@ -100,7 +102,7 @@ DEBUG_EXPORTS = ("sk_set_tuning", "sk_trace_begin", "sk_trace_end", "sk_trace_ke
 
 EXPORTS = ("sk_linear_fwd", "sk_linear_bwd_input", "sk_linear_bwd_weight", "sk_linear_bwd",
            "sk_linear_bwd_weight_first", "sk_linear_bwd_weight_noalloc",
-           "sk_linear_bwd_two_sided", "sk_round_gradients", "sk_linear_workspace_bytes", "sk_status_string", "sk_last_hip_error", "sk_set_plan")
+           "sk_linear_bwd_two_sided", "sk_linear_bwd_rounded", "sk_round_gradients", "sk_linear_workspace_bytes", "sk_status_string", "sk_last_hip_error", "sk_set_plan")
 
 
 class SkError(RuntimeError):
@@ -172,6 +174,13 @@ def sk_linear_bwd_two_sided(x, dY, S_cat, U_cat, dX, dU_cat, dbias, dA, tokens, 
     return _lib.sk_linear_bwd_two_sided(_ptr(x), _ptr(dY), _ptr(S_cat), _ptr(U_cat), _ptr(dX), _ptr(dU_cat),
                                         _ptr(dbias), _ptr(dA), tokens, d_in, d_out, l, k, dtype,
                                         _ptr(workspace), workspace_bytes, _stream(stream))
+
+
+def sk_linear_bwd_rounded(x, dY, S_cat, U_cat, dX, dU_cat, dbias, dA, dU_bf16, dU_rows, dbias_bf16, dA_bf16, tokens, d_in, d_out,
+                          l, k, dtype, workspace, workspace_bytes, stream=None):
+    return _lib.sk_linear_bwd_rounded(_ptr(x), _ptr(dY), _ptr(S_cat), _ptr(U_cat), _ptr(dX), _ptr(dU_cat), _ptr(dbias), _ptr(dA),
+                                      _ptr(dU_bf16), dU_rows, _ptr(dbias_bf16), _ptr(dA_bf16), tokens, d_in, d_out, l, k, dtype,
+                                      _ptr(workspace), workspace_bytes, _stream(stream))
 
 
 def sk_round_gradients(sources, targets, counts, stream=None):
