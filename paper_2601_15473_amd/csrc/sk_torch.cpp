@@ -68,6 +68,8 @@ Workspaces& workspaces() {
   return *w;
 }
 
+size_t aligned_up(size_t bytes) { return (bytes + 255) / 256 * 256; }
+
 sk_dtype dtype_of(const Tensor& t) { return t.scalar_type() == at::kFloat ? SK_F32 : SK_BF16; }
 
 void* stream_of(const at::Device& device) {
@@ -243,36 +245,37 @@ struct LinearTwoSided : torch::autograd::Function<LinearTwoSided> {
     const sk_dtype dt = dtype_of(A);
     const c10::DeviceGuard guard(x2.device());
     const Tensor dY = rows_of_gradient(grads[0], A, out);
-    const auto f32 = x2.options().dtype(at::kFloat);
-    Tensor dX = at::empty({tokens, in}, x2.options()), dA = at::empty({in, half}, f32), dB = at::empty({2 * half, out}, f32), db;
-    if (kept.bias) db = at::empty({out}, f32);
-    const Tensor dB_used = dB.narrow(0, 0, half);   // (the rest belongs to S2^T: gradients of fixed numbers)
-    Tensor dA_out = dA, dB_out = dB_used, db_out = db;
-    if (dt != SK_F32) {   // each a tensor of its own
-      if (kept.bias) db_out = at::empty(db.sizes(), A.options());
-      dA_out = at::empty(dA.sizes(), A.options());
-      dB_out = at::empty(dB_used.sizes(), A.options());
-    }
+    // (rows half .. of B's gradient belong to S2^T, fixed numbers: formed by the product, given to nobody)
+    Tensor dX = at::empty({tokens, in}, x2.options()), dA, dB, db;
     void* const stream = stream_of(x2.device());
     const int32_t l2 = 2 * kept.l;
     const size_t need = sk_linear_workspace_bytes(SK_OP_BWD_TWO_SIDED, tokens, in, out, l2, kept.k, dt);
+    Workspaces& w = workspaces();
     sk_status st;
-    {
-      Workspaces& w = workspaces();
+    if (dt != SK_F32) {   // fp32 sums behind the workspace, results each a tensor of its own
+      dB = at::empty({half, out}, A.options());
+      dA = at::empty({in, half}, A.options());
+      if (kept.bias) db = at::empty({out}, A.options());
+      const size_t at_dB = aligned_up(need), at_dA = at_dB + aligned_up((size_t)(2 * half * out) * 4), at_db = at_dA + aligned_up((size_t)(in * half) * 4);
+      const std::lock_guard<std::mutex> lock(w.mutex);
+      unsigned char* const ws = static_cast<unsigned char*>(w.get(x2.device(), stream, at_db + (size_t)out * 4).data_ptr());
+      st = sk_linear_bwd_rounded(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), reinterpret_cast<float*>(ws + at_dB),
+                                 kept.bias ? reinterpret_cast<float*>(ws + at_db) : nullptr, reinterpret_cast<float*>(ws + at_dA), dB.data_ptr(), half,
+                                 kept.bias ? db.data_ptr() : nullptr, dA.data_ptr(), tokens, in, out, l2, kept.k, dt, ws, need, stream);
+    } else {
+      const auto f32 = x2.options().dtype(at::kFloat);
+      const Tensor whole = at::empty({2 * half, out}, f32);
+      dA = at::empty({in, half}, f32);
+      dB = whole.narrow(0, 0, half);
+      if (kept.bias) db = at::empty({out}, f32);
       const std::lock_guard<std::mutex> lock(w.mutex);
       const Tensor& ws = w.get(x2.device(), stream, need);
-      if (dt != SK_F32)
-        st = sk_linear_bwd_rounded(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), dB.data_ptr<float>(),
-                                   kept.bias ? db.data_ptr<float>() : nullptr, dA.data_ptr<float>(), dB_out.data_ptr(), half,
-                                   kept.bias ? db_out.data_ptr() : nullptr, dA_out.data_ptr(), tokens, in, out, l2, kept.k, dt, ws.data_ptr(),
+      st = sk_linear_bwd_two_sided(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), whole.data_ptr<float>(),
+                                   kept.bias ? db.data_ptr<float>() : nullptr, dA.data_ptr<float>(), tokens, in, out, l2, kept.k, dt, ws.data_ptr(),
                                    (size_t)ws.numel(), stream);
-      else
-        st = sk_linear_bwd_two_sided(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), dB.data_ptr<float>(),
-                                     kept.bias ? db.data_ptr<float>() : nullptr, dA.data_ptr<float>(), tokens, in, out, l2, kept.k, dt,
-                                     ws.data_ptr(), (size_t)ws.numel(), stream);
     }
     check(st);
-    return {in_shape(ctx, dX), dB_out, dA_out, db_out, Tensor(), Tensor(), Tensor(), Tensor()};
+    return {in_shape(ctx, dX), dB, dA, db, Tensor(), Tensor(), Tensor(), Tensor()};
   }
 };
 
