@@ -1364,7 +1364,14 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
   // of tokens: two launches, where one after the other the gradients take three or four (62 of 150 layers of 100 to 600 tokens,
   // 64 to 4096 wide, take it, in 0.61 of the time; 570 tokens, 320 -> 1808, R = 32 19.7 : 10.3 us; x.S in ranges, 418, 3616 -> 272, R = 80
   // 21.0 : 15.7).  Where x.S comes in ranges for a few hundred tokens the launches stay the four that the schedule's test counts.
-  const bool beside = bf16_any_z && !(z_ranges && tokens <= 320) && factor_beside_expand_supported(w.tile, du, c);
+  bool beside = bf16_any_z && !(z_ranges && tokens <= 320) && factor_beside_expand_supported(w.tile, du, c);
+  if (!beside && z_ranges && tokens > 320 && (in <= 2 * out || tokens <= 2048)) {
+    // An expansion of two work-groups a CU with one instead, to leave room: not where dX is most of what moves (5505 tokens, 3600 -> 272, R = 48
+    // 38.6 : 41.3 us, 9664, 3024 -> 320, R = 32 48.6 : 51.8, 6520, 2432 -> 976, R = 16 37.3 : 38.0; 1198, 3248 -> 752, R = 64 21.5 : 19.8).
+    ChainArgs fewer = c;
+    fewer.n_slices = chain_shape(tokens, in, s.R, false).slices;
+    if (factor_beside_expand_supported(w.tile, du, fewer)) { beside = true; c = fewer; }
+  }
   if (bf16_any_z && chain_supported(s.R) && s.R <= 128 && q.splits > 1 && (z_ranges || (w.z_splits == 1 && (w.splits > 1 || beside))) &&
       (z_ranges ? dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT_F32, w.z_tile) : dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT, z_tile))) {
     g_hip_error.clear();

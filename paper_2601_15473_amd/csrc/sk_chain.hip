@@ -974,19 +974,21 @@ __global__ __launch_bounds__(256) void chain_short_kernel(const ChainArgs p) {
   chain_body<MB, RT, B2_KC, FUSED, B1_KC, RING, true>(p);
 }
 
-// Z^T . dY in ranges of tokens beside the expansion of dX over short runs of 64-row tiles, in one launch: the first `groups_a`
-// work-groups and the rest, two to a CU (72 KB of LDS and 240 registers at most).  Each of the two by itself is a round of work-groups that
-// wait for their first operands and for their last stores; beside each other they wait at the same time.  The sum of the
-// ranges, which the expansion carried while it came last, has a launch of its own again (2 to 3 us).  Backward pass, us, expansion
-// behind : beside: 4096 tokens, 768 -> 3072, R = 128 35.0 : 34.0; 2048, 768 -> 768, R = 128 22.9 : 21.2; 1000, 512 -> 1024, R = 48 15.0 : 12.7;
-// x . S in ranges: 418, 3616 -> 272, R = 80 21.0 : 15.7; 62 of 150 layers of 300 to 16384 tokens, 256 to 4096 wide, take it, in 0.89 of the time.
-template <int BM, int RT>
+// Z^T . dY in ranges of tokens beside the expansion of dX over runs of 64-row tiles (long ones, which leave through LDS, up to R = 64),
+// in one launch: the first `groups_a` work-groups and the rest, two to a CU (72 KB of LDS and 240 registers at most).  Each of
+// the two by itself is a round of work-groups that wait for their first operands and for their last stores, one reading
+// dY, the other writing dX; beside each other they wait at the same time.  The sum of the ranges, which the expansion carried while it came
+// last, has a launch of its own again (2 to 3 us).  Backward pass, us, expansion behind : beside: 4096 tokens, 768 -> 3072, R = 128 35.0 : 34.0;
+// 2048, 768 -> 768, R = 128 22.9 : 21.2; 1000, 512 -> 1024, R = 48 15.0 : 12.7; x . S in ranges: 418, 3616 -> 272, R = 80 21.0 : 15.7; 62 of 150 layers of
+// 300 to 16384 tokens, 256 to 4096 wide, take it with short runs, in 0.89 of the time.  Long runs: 9295, 960 -> 1504, R = 16 35.8 : 32.3; 4096, 8192 -> 8192,
+// R = 16 67.8 : 65.8; 36 of 150 such layers 0.95, 48 of 80 of 4096 to 8192 wide, R 16 to 96, 0.94.  (R = 128 with long runs would be one to a CU.)
+template <int BM, int RT, bool SHORT = true>
 __global__ __launch_bounds__(256, 2) void factor_beside_expand_kernel(const GemmArgs a, const ChainArgs c, const int groups_a) {
   typedef RingTile<BM, 64, true, false, float, true> G;
-  typedef SmallLds<64, RT, true, false, true, true> L;
+  typedef SmallLds<64, RT, true, false, true, SHORT> L;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[G::LDS_BYTES > L::BYTES ? G::LDS_BYTES : L::BYTES];
   if ((int)blockIdx.x < groups_a) G::run(a, blockIdx.x, smem);
-  else chain_small<64, RT, true, false, true, true, true>(c, (int)blockIdx.x - groups_a, smem);
+  else chain_small<64, RT, true, false, true, SHORT, true>(c, (int)blockIdx.x - groups_a, smem);
 }
 
 bool chain_supported(int R) { return R >= 16 && R <= 512; }
@@ -1120,10 +1122,10 @@ bool factor_beside_expand_supported(int tile, const GemmArgs& a, const ChainArgs
   ChainArgs t = c;
   t.tiles_m = tiles_m;
   const long long groups = (long long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * a.splits + (long long)tiles_m * c.n_slices;
-  return brief_runs(t, 64) && groups <= 2 * NUM_CUS;
+  return (brief_runs(t, 64) || c.R <= 64) && groups <= 2 * NUM_CUS;
 }
 
-template <int BM, int RT>
+template <int BM, int RT, bool SHORT = true>
 static hipError_t launch_beside(GemmArgs a, const ChainArgs& c, hipStream_t s) {
   a.tiles_m = (a.M + BM - 1) / BM;
   a.tiles_n = (a.N + 63) / 64;
@@ -1135,13 +1137,14 @@ static hipError_t launch_beside(GemmArgs a, const ChainArgs& c, hipStream_t s) {
   work.flops += wc.flops;
   work.bytes += wc.bytes;
   static const std::string name = kernel_label("factor_beside_expand_kernel", {lbl(BM), lbl(RT)});
-  return launch_kernel(name.c_str(), work, factor_beside_expand_kernel<BM, RT>, dim3((unsigned)(ga + c.tiles_m * c.n_slices)), dim3(256), s, a, c, ga);
+  return launch_kernel(name.c_str(), work, factor_beside_expand_kernel<BM, RT, SHORT>, dim3((unsigned)(ga + c.tiles_m * c.n_slices)), dim3(256), s, a, c, ga);
 }
 
 hipError_t launch_factor_beside_expand(int tile, GemmArgs a, ChainArgs c, hipStream_t s) {
   if (!factor_beside_expand_supported(tile, a, c) || c.tail.n + c.tail.n2 > 0 || !within_window(128, a.lda, 64, 2)) return hipErrorInvalidValue;
   c.tiles_m = (c.M + 63) / 64;
-  return tile == TILE_128x64 ? launch_beside<128, 128>(a, c, s) : launch_beside<64, 64>(a, c, s);
+  if (tile == TILE_128x64) return launch_beside<128, 128>(a, c, s);
+  return brief_runs(c, 64) ? launch_beside<64, 64>(a, c, s) : launch_beside<64, 64, false>(a, c, s);
 }
 
 }  // namespace sk

@@ -13,6 +13,8 @@ KERNEL = "factor_beside_expand_kernel"
 @pytest.mark.parametrize("shape,launches", [
     ((515, 400, 1040, 1, 16), 2), ((130, 64, 2064, 1, 48), 2), ((513, 80, 528, 1, 112), 3), ((1030, 272, 2320, 2, 32), 3), ((700, 1040, 1296, 1, 80), 3),
     ((2100, 784, 1040, 1, 128), 3), ((1111, 400, 2064, 1, 64), 3), ((4033, 384, 784, 1, 64), 3), ((1500, 2576, 1296, 1, 96), 4), ((900, 3600, 1040, 1, 32), 4), ((418, 3616, 272, 1, 80), 3),
+    # long runs, x . S whole and in ranges
+    ((8200, 784, 528, 1, 48), 3), ((9295, 976, 1104, 1, 16), 3), ((2100, 4112, 2064, 1, 16), 4), ((1198, 3248, 752, 1, 64), 4),
 ], ids=lambda v: "T%d_%dx%d_l%dk%d" % v if isinstance(v, tuple) else "")
 def test_against_the_oracle_and_the_separate_call(shape, launches):
     import torch
@@ -50,8 +52,10 @@ def _names(T, d_in, d_out, R):
 @pytest.mark.parametrize("shape,beside", [
     # up to two work-groups a CU
     ((16000, 128, 1024, 64), True), ((16384, 128, 1024, 64), True), ((16385, 128, 1024, 64), False),
-    # runs of up to three output tiles of 128 columns
-    ((8192, 768, 3072, 64), True), ((8192, 784, 3072, 64), False),
+    # runs of up to three output tiles of 128 columns, any up to R = 64
+    ((2048, 1536, 3072, 80), True), ((4096, 1664, 3072, 80), False), ((4096, 1664, 3072, 64), True),
+    # an expansion of one work-group a CU instead of two: dX up to twice dY, or 2048 tokens
+    ((5505, 3600, 1808, 48), True), ((5505, 3600, 272, 48), False), ((2048, 3600, 272, 48), True),
     # one range of tokens; where x . S comes in ranges from 321 on
     ((300, 320, 1808, 32), True), ((320, 3616, 272, 80), False), ((321, 3616, 272, 80), True),
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
