@@ -657,7 +657,8 @@ size_t first_stage_bytes(const Shape& s, int64_t nc) {
 // over three launches): out <= 256 0.63-0.84, out = 768 0.80-1.04, out = 1024 0.83-1.14
 // (R = 16: 0.82-1.03), out = 2048 1.06-1.31, out = 3072 1.20-1.59 -- a work-group walks all
 // of `out`, and the walk is what it cannot hide.
-// So: R <= 32, out <= 896 (1024 for R = 16), one round of work-groups, slabs of at most 32 MiB.
+// So: R <= 32, out <= 896 (1024 for R = 16), one round of work-groups, slabs of at most 32 MiB, and not where bwd_both
+// has the gradients share launches instead (`shares` there).
 struct NarrowPlan {
   bool ok;
   int tm, tiles_m;   // tokens per work-group (32 or 64), work-groups
@@ -1283,23 +1284,6 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const float scale = 1.0f / (float)l;
 
-  // --- narrow sketch, short input: one pass over x and dY | sum of the token tiles' slabs ---
-  if (const NarrowPlan n = plan_narrow(s); n.ok) {
-    g_hip_error.clear();
-    NarrowBwdArgs b{};
-    b.x = x; b.S = S_cat; b.dY = dY; b.U = U_cat; b.dX = dX;
-    b.du_slabs = reinterpret_cast<float*>(ws_in);
-    b.db_slabs = dbias ? reinterpret_cast<float*>(ws_in + n.du_bytes) : nullptr;
-    b.M = (int)tokens; b.K1 = (int)in; b.R = s.R; b.N = (int)out; b.scale = scale; b.tm = n.tm;
-    hipError_t e = launch_bwd_narrow_bf16(b, hs);
-    if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (one pass over x and dY)");
-    ReduceArgs t{};
-    t.part = b.du_slabs; t.out = dU_cat; t.n = (int64_t)s.R * out; t.splits = n.tiles_m; t.scale = scale;
-    t.part2 = b.db_slabs; t.out2 = dbias; t.n2 = dbias ? out : 0; t.splits2 = n.tiles_m; t.scale2 = 1.0f;
-    e = launch_reduce_tiles(t, hs);
-    return e == hipSuccess ? SK_OK : hip_fail(e, "sk_linear_bwd (sum of the token tiles)");
-  }
-
   // --- fp32: dY.U^T beside x.S | sums of their slabs | Z^T.dY beside G.S^T | sums of the token splits ---
   // A partner by itself leaves the chip idle ([4096 x 768] . U^T, R = 128, is 128 work-groups of 24
   // chunks: 17 us) or is over in a launch's own time (64 tokens, 256 -> 256, R = 16: six launches of one
@@ -1372,6 +1356,29 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
     fewer.n_slices = chain_shape(tokens, in, s.R, false).slices;
     if (factor_beside_expand_supported(w.tile, du, fewer)) { beside = true; c = fewer; }
   }
+  // --- narrow sketch, short input: one pass over x and dY | sum of the token tiles' slabs ---
+  // Not, by itself, where the two gradients share launches (below) up to 4095 tokens.  One pass : shared, backward call, us: 255 tokens,
+  // 304 -> 752, R = 16 14.0 : 8.4; 1024, 768 -> 768, R = 32 15.7 : 13.3; 2411, 768 -> 992, R = 16 18.7 : 15.9.  Of 200 layers (200 to 16384 tokens, 64 to
+  // 1024 outputs) 115 can share: 0.60 to 0.97 of the time up to 4095 tokens (mean 0.81), beyond (90 other layers included)
+  // 0.83 to 1.13; none of the other 85 (outputs up to 240) is faster without this pass (1.08 to 1.41).
+  const bool shares = beside && !z_ranges && tokens < 4096 && tune(SK_TUNE_NARROW_BWD) < 0 && q.splits > 1 &&
+                      dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT, z_tile);
+  if (const NarrowPlan n = plan_narrow(s); n.ok && !shares) {
+    g_hip_error.clear();
+    NarrowBwdArgs b{};
+    b.x = x; b.S = S_cat; b.dY = dY; b.U = U_cat; b.dX = dX;
+    b.du_slabs = reinterpret_cast<float*>(ws_in);
+    b.db_slabs = dbias ? reinterpret_cast<float*>(ws_in + n.du_bytes) : nullptr;
+    b.M = (int)tokens; b.K1 = (int)in; b.R = s.R; b.N = (int)out; b.scale = scale; b.tm = n.tm;
+    hipError_t e = launch_bwd_narrow_bf16(b, hs);
+    if (e != hipSuccess) return hip_fail(e, "sk_linear_bwd (one pass over x and dY)");
+    ReduceArgs t{};
+    t.part = b.du_slabs; t.out = dU_cat; t.n = (int64_t)s.R * out; t.splits = n.tiles_m; t.scale = scale;
+    t.part2 = b.db_slabs; t.out2 = dbias; t.n2 = dbias ? out : 0; t.splits2 = n.tiles_m; t.scale2 = 1.0f;
+    e = launch_reduce_tiles(t, hs);
+    return e == hipSuccess ? SK_OK : hip_fail(e, "sk_linear_bwd (sum of the token tiles)");
+  }
+
   if (bf16_any_z && chain_supported(s.R) && s.R <= 128 && q.splits > 1 && (z_ranges || (w.z_splits == 1 && (w.splits > 1 || beside))) &&
       (z_ranges ? dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT_F32, w.z_tile) : dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT, z_tile))) {
     g_hip_error.clear();

@@ -13,6 +13,8 @@ KERNEL = "factor_beside_expand_kernel"
 @pytest.mark.parametrize("shape,launches", [
     ((515, 400, 1040, 1, 16), 2), ((130, 64, 2064, 1, 48), 2), ((513, 80, 528, 1, 112), 3), ((1030, 272, 2320, 2, 32), 3), ((700, 1040, 1296, 1, 80), 3),
     ((2100, 784, 1040, 1, 128), 3), ((1111, 400, 2064, 1, 64), 3), ((4033, 384, 784, 1, 64), 3), ((1500, 2576, 1296, 1, 96), 4), ((900, 3600, 1040, 1, 32), 4), ((418, 3616, 272, 1, 80), 3),
+    # instead of one pass over x and dY
+    ((255, 304, 752, 1, 16), 2), ((2411, 768, 992, 1, 16), 3), ((4095, 848, 880, 2, 16), 3),
     # long runs, x . S whole and in ranges
     ((8200, 784, 528, 1, 48), 3), ((9295, 976, 1104, 1, 16), 3), ((2100, 4112, 2064, 1, 16), 4), ((1198, 3248, 752, 1, 64), 4),
 ], ids=lambda v: "T%d_%dx%d_l%dk%d" % v if isinstance(v, tuple) else "")
@@ -58,6 +60,9 @@ def _names(T, d_in, d_out, R):
     ((5505, 3600, 1808, 48), True), ((5505, 3600, 272, 48), False), ((2048, 3600, 272, 48), True),
     # one range of tokens; where x . S comes in ranges from 321 on
     ((300, 320, 1808, 32), True), ((320, 3616, 272, 80), False), ((321, 3616, 272, 80), True),
+    # instead of one pass over x and dY up to 4095 tokens, where there is a launch to share
+    ((4095, 768, 768, 32), True), ((4096, 768, 768, 32), False), ((4095, 768, 768, 16), True), ((4096, 768, 768, 16), False), ((4095, 768, 368, 16), True),
+    ((2000, 768, 240, 32), False),
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_which_layers_take_it(shape, beside):
     names = _names(*shape)
