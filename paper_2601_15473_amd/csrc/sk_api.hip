@@ -156,6 +156,16 @@ int choose_tile(int64_t M, int64_t N, int64_t K, int splits) {
   }
   return TILE_64x64;
 }
+// ... of a bf16 result in a launch of its own: where 128 x 128 tiles leave CUs without a work-group and 128 x 64 or 64 x 128 ones make more
+// than a round, still 128 x 128.  Those run on the ring then, a chunk in 0.5 us on 50 to 100 % of the CUs; the smaller ones run on the staged loop, one or two to a CU,
+// and fill 48 KB for the 32 of the larger.  Calls, us, 128 x 64 : 128 x 128: forward, 4001 tokens, 768 -> 768, R = 384 17.0 : 15.7; expansions of
+// 144 to 1008, 30 of 600 to 12000 tokens 0.83 to 0.95 of the call; first contractions of 256 to 4600, 30 layers of 2400 to 16384 tokens, R 192 to 1008,
+// forward 0.76 to 0.96 (2689 tokens, 3664 -> 320, R = 976 54.8 : 41.5), input gradient 0.85 to 1.00, factor gradient 0.82 to 1.00.  Where 64 x 64 is chosen (128 x 64 does
+// not make a round) it stays: 1.03 to 1.11.
+int lone_tile(int t, int64_t M, int64_t N, int64_t K) {
+  return (t == TILE_128x64 || t == TILE_64x128) && K > 128 && small_tiles(M, N) <= NUM_CUS ? TILE_128x128 : t;
+}
+
 // ... of an expansion in a launch of its own: also 256 x 128 on a ring, while those make one round and 128 x 128 tiles more than one.  A launch takes
 // 6.5 us + 0.0148 a k then (fitted), against the staged tiles' 9.2 + 0.0165, and fills 24 KB a chunk and 128 x 128 of the result where
 // those fill 32.  180 layers with a short input, 600 to 16384 tokens, expansions of 144 to 2048 to 512 to 8192, us, 128 x 128 or 256 x 256 : 256 x 128: 2272
@@ -163,8 +173,9 @@ int choose_tile(int64_t M, int64_t N, int64_t K, int splits) {
 // two behind, both of 12000 tokens to 528 and 560), 0.93 below (0.90 to 0.98).  Not for the first contractions, whose operands come
 // from memory and not from the launch before: 0.84 to 1.09 of the time there, level over 40 layers.  Past a round each round costs 8 us again.
 int choose_expansion_tile(int64_t M, int64_t N, int64_t K) {
-  const int t = choose_tile(M, N, K, 1);
+  int t = choose_tile(M, N, K, 1);
   if (tune(SK_TUNE_TILE) >= 0 || K <= 128) return t;
+  t = lone_tile(t, M, N, K);
   const int64_t mid = (M + 255) / 256 * ((N + 127) / 128), small = small_tiles(M, N);
   if (mid > NUM_CUS || small <= NUM_CUS) return t;
   const double us = 6.5 + 0.0148 * (double)K;
@@ -301,6 +312,7 @@ FirstPlan plan_first(int64_t M, int64_t N, int64_t K, bool rows) {
     }
   }
   if (f.splits > 1) f.slab_bytes = align_up((size_t)f.splits * M * N * 4);
+  else f.tile = lone_tile(f.tile, M, N, K);
   return f;
 }
 
