@@ -156,14 +156,23 @@ int choose_tile(int64_t M, int64_t N, int64_t K, int splits) {
   }
   return TILE_64x64;
 }
-// ... of a bf16 result in a launch of its own: where 128 x 128 tiles leave CUs without a work-group and 128 x 64 or 64 x 128 ones make more
-// than a round, still 128 x 128.  Those run on the ring then, a chunk in 0.5 us on 50 to 100 % of the CUs; the smaller ones run on the staged loop, one or two to a CU,
+// ... of a bf16 result in a launch of its own: where 128 x 64 or 64 x 128 tiles make more than a round and 128 x 128 ones no more than
+// one, those.  They run on the ring then, a chunk in 0.5 us on 50 to 100 % of the CUs; the smaller ones run on the staged loop, one or two to a CU,
 // and fill 48 KB for the 32 of the larger.  Calls, us, 128 x 64 : 128 x 128: forward, 4001 tokens, 768 -> 768, R = 384 17.0 : 15.7; expansions of
 // 144 to 1008, 30 of 600 to 12000 tokens 0.83 to 0.95 of the call; first contractions of 256 to 4600, 30 layers of 2400 to 16384 tokens, R 192 to 1008,
 // forward 0.76 to 0.96 (2689 tokens, 3664 -> 320, R = 976 54.8 : 41.5), input gradient 0.85 to 1.00, factor gradient 0.82 to 1.00.  Where 64 x 64 is chosen (128 x 64 does
 // not make a round) it stays: 1.03 to 1.11.
-int lone_tile(int t, int64_t M, int64_t N, int64_t K) {
-  return (t == TILE_128x64 || t == TILE_64x128) && K > 128 && small_tiles(M, N) <= NUM_CUS ? TILE_128x128 : t;
+// Exactly one round of the smaller ones has every CU fetching, of the larger ones (at most) half of them, which is behind where the operands come from memory
+// or the walk is short: 120 such layers, times the smaller tiles' call: x . S and expansions forward 0.97 to 1.08 over 160 to 1536, 0.88 to 0.97 over 2048 and more (three of 18 at
+// 1.01 to 1.03); input gradient 0.98 to 1.10 (4075 tokens, 512 -> 256, R = 1200 20.9 : 23.0), level from 2048 on; S^T . x^T 0.85 to 0.95 where x is in the
+// Infinity Cache from the call before, 1.03 to 1.11 where it is not (4079 tokens, 2560 -> 1536, R = 480 43.4 : 48.2), as in training.  So those stay, but for
+// forward ones over 2048 and more.  (A result at most 64 wide never makes more of the smaller ones than of 128 x 128, half of each padding.)
+int lone_tile(GemmKind kind, int t, int64_t M, int64_t N, int64_t K) {
+  if ((t != TILE_128x64 && t != TILE_64x128) || K <= 128 || small_tiles(M, N) > NUM_CUS) return t;
+  int bm, bn;
+  tile_dims(t, bm, bn);
+  const int64_t groups = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+  return groups > NUM_CUS || (kind == GEMM_NN && K >= 2048) ? TILE_128x128 : t;
 }
 
 // ... of an expansion in a launch of its own: also 256 x 128 on a ring, while those make one round and 128 x 128 tiles more than one.  A launch takes
@@ -172,10 +181,10 @@ int lone_tile(int t, int64_t M, int64_t N, int64_t K) {
 // tokens, R = 1968, 1856 out 43.1 : 36.7; 3220, 448, 1376 17.0 : 14.7; 1615, 256, 3488 13.1 : 12.5; 0.89 of the time above R = 256 (0.78 to 1.04,
 // two behind, both of 12000 tokens to 528 and 560), 0.93 below (0.90 to 0.98).  Not for the first contractions, whose operands come
 // from memory and not from the launch before: 0.84 to 1.09 of the time there, level over 40 layers.  Past a round each round costs 8 us again.
-int choose_expansion_tile(int64_t M, int64_t N, int64_t K) {
+int choose_expansion_tile(GemmKind kind, int64_t M, int64_t N, int64_t K) {
   int t = choose_tile(M, N, K, 1);
   if (tune(SK_TUNE_TILE) >= 0 || K <= 128) return t;
-  t = lone_tile(t, M, N, K);
+  t = lone_tile(kind, t, M, N, K);
   const int64_t mid = (M + 255) / 256 * ((N + 127) / 128), small = small_tiles(M, N);
   if (mid > NUM_CUS || small <= NUM_CUS) return t;
   const double us = 6.5 + 0.0148 * (double)K;
@@ -268,9 +277,9 @@ int few_rows_splits(int64_t M, int64_t N, int64_t K, bool first) {
   return splits;
 }
 
-FirstPlan plan_first(int64_t M, int64_t N, int64_t K, bool rows) {
+FirstPlan plan_first(GemmKind kind, int64_t M, int64_t N, int64_t K) {
   FirstPlan f{};
-  if (const int sp = rows ? few_rows_splits(M, N, K, true) : 0; sp > 0) {
+  if (const int sp = kind != GEMM_TT ? few_rows_splits(M, N, K, true) : 0; sp > 0) {
     f.few = true;
     f.splits = sp;
     f.k_per_split = (int)(((K + sp - 1) / sp + 63) / 64 * 64);
@@ -312,7 +321,7 @@ FirstPlan plan_first(int64_t M, int64_t N, int64_t K, bool rows) {
     }
   }
   if (f.splits > 1) f.slab_bytes = align_up((size_t)f.splits * M * N * 4);
-  else f.tile = lone_tile(f.tile, M, N, K);
+  else f.tile = lone_tile(kind, f.tile, M, N, K);
   return f;
 }
 
@@ -448,7 +457,7 @@ WeightPlan plan_weight(const Shape& s) {
     // Z^T [R, T] recomputed as a general GEMM over `in` (plan_first: split over a long
     // `in` when its tiles are few -- the paper's 8192-wide layers at R = 16: 64 tiles of
     // 64 x 64 walking 128 chunks each took 51 us, four ranges and the sum take 17)
-    const FirstPlan f = plan_first(s.R, s.T, s.in, false);
+    const FirstPlan f = plan_first(GEMM_TT, s.R, s.T, s.in);
     w.z_tile = f.tile;
     w.z_splits = f.splits;
     w.z_k_per_split = f.k_per_split;
@@ -648,7 +657,7 @@ size_t first_stage_bytes(const Shape& s, int64_t nc) {
   // region of the dA slabs
   size_t g_slabs;
   if (s.dtype == SK_BF16) {
-    g_slabs = plan_first(s.T, nc, s.out, true).slab_bytes;
+    g_slabs = plan_first(GEMM_NT, s.T, nc, s.out).slab_bytes;
   } else {
     g_slabs = plan_f32_first(s.T, nc, s.out).slab_bytes;
   }
@@ -753,7 +762,7 @@ size_t workspace_for(sk_op op, const Shape& s) {
       // the maximum over the plans, so one buffer serves whichever is selected
       size_t need = mid;
       if (s.dtype == SK_BF16)   // two GEMMs with the first one split: slabs behind the intermediate
-        need += plan_first(s.T, s.R, op == SK_OP_FWD ? s.in : s.out, true).slab_bytes;
+        need += plan_first(op == SK_OP_FWD ? GEMM_NN : GEMM_NT, s.T, s.R, op == SK_OP_FWD ? s.in : s.out).slab_bytes;
       else
         need += plan_f32_first(s.T, s.R, op == SK_OP_FWD ? s.in : s.out).slab_bytes;
       if (s.dtype == SK_BF16 && chain_supported(s.R)) {
@@ -787,7 +796,7 @@ size_t workspace_for(sk_op op, const Shape& s) {
 
 hipError_t gemm(const Shape& s, GemmKind kind, GemmArgs a, hipStream_t st) {
   if (s.dtype == SK_BF16 && few_rows_splits(a.M, a.N, a.K, false) > 0) return launch_gemm_few_rows_bf16(kind, a, st);
-  if (s.dtype == SK_BF16) return launch_gemm_bf16(kind, choose_expansion_tile(a.M, a.N, a.K), a, st);
+  if (s.dtype == SK_BF16) return launch_gemm_bf16(kind, choose_expansion_tile(kind, a.M, a.N, a.K), a, st);
   return launch_gemm_f32(kind, plan_f32(a.M, a.N, a.K, 1).tile, a, st);
 }
 
@@ -808,7 +817,7 @@ hipError_t first_gemm(const Shape& s, GemmKind kind, GemmKind kind_slabs, GemmAr
     r.splits = a.splits; r.splits2 = 1; r.scale2 = 1.0f;
     return launch_reduce_splits(r, st);
   }
-  const FirstPlan f = plan_first(a.M, a.N, a.K, true);
+  const FirstPlan f = plan_first(kind, a.M, a.N, a.K);
   if (f.splits == 1) return f.few ? launch_gemm_few_rows_bf16(kind, a, st) : launch_gemm_bf16(kind, f.tile, a, st);
   void* out = a.C;
   a.C = slabs; a.splits = f.splits; a.k_per_split = f.k_per_split;
@@ -1446,7 +1455,7 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
   // best the separate launches did was 2 % ahead ([8192 x 4096 -> 8192], R = 1024, 478 : 468)
   if (dx_tile == TILE_256x256) dx_tile = TILE_128x128;
   WidePlan pair{-1, 1, 0, 0, 0};
-  const FirstPlan first = plan_first(tokens, s.R, out, true);
+  const FirstPlan first = plan_first(GEMM_NT, tokens, s.R, out);
   if (bf16_any_z && in_plan == PLAN_TWO_GEMM && !first.few) {
     pair = plan_wide(s, w, first);
     if (pair.tile < 0 && w.z_splits == 1 && first.splits == 1 && g_tile == z_tile && dual_gemm_supported(GEMM_NT, g_tile, GEMM_TT, z_tile) &&
