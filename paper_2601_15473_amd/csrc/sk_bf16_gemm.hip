@@ -432,45 +432,66 @@ hipError_t launch_gemm_bf16(GemmKind kind, int tile, const GemmArgs& a, hipStrea
 }
 
 namespace {
-// The pairs of (kind, tile) the dual kernel is built for: the ones the backward pass's
-// plans produce on the benchmark shapes.  `first` should be the longer-running GEMM: its
+typedef GemmTile<64, 64, true, true, bf16, false> NT_64x64;
+typedef GemmTile<128, 64, true, true, bf16, false> NT_128x64;
+typedef GemmTile<128, 128, true, true, bf16, false> NT_128x128;
+typedef GemmTile<64, 64, true, true, float, false> NTF_64x64;
+typedef GemmTile<64, 128, true, true, float, false> NTF_64x128;
+typedef GemmTile<128, 128, true, true, float, false> NTF_128x128;
+typedef GemmTile<64, 64, false, true, bf16, false> TT_64x64;
+typedef GemmTile<128, 128, false, true, bf16, false> TT_128x128;
+typedef GemmTile<64, 64, false, true, float, false> TTF_64x64;
+typedef GemmTile<64, 128, false, true, float, false> TTF_64x128;
+typedef GemmTile<128, 64, false, true, float, false> TTF_128x64;
+typedef GemmTile<128, 128, false, true, float, false> TTF_128x128;
+typedef GemmTile<128, 64, true, false, float, true> NNFC_128x64;
+typedef GemmTile<128, 128, true, false, float, true> NNFC_128x128;
+typedef RingTile<64, 64, true, true, bf16, false> RING_NT_64x64;
+typedef RingTile<64, 64, true, true, float, false> RING_NTF_64x64;
+typedef RingTile<64, 64, false, true, bf16, false> RING_TT_64x64;
+typedef RingTile<64, 64, false, true, float, false> RING_TTF_64x64;
+
+// The pairs of (kind, tile) the dual kernel is built for, the ones the backward pass's plans produce, with the kernel
+// of each and, for those on 64 x 64 tiles, the one on rings.  The first should be the longer-running GEMM: its
 // work-groups are dispatched first and the other's fill in beside them.
-struct DualPair { GemmKind ka; int ta; GemmKind kb; int tb; };
+typedef void (*DualKernel)(GemmArgs, GemmArgs, int);
+struct DualPair { GemmKind ka; int ta; GemmKind kb; int tb; DualKernel staged, ring; };
 const DualPair kDualPairs[] = {
-    {GEMM_NT_F32, TILE_64x128, GEMM_TT, TILE_64x64},           // narrow sketch, R in 65..128
-    {GEMM_NT_F32, TILE_64x64, GEMM_TT, TILE_64x64},            // narrow sketch, R <= 64
-    {GEMM_NT, TILE_128x128, GEMM_TT, TILE_128x128},            // wide sketch: dY.U^T beside Z^T
-    {GEMM_NN_F32_COLSUM, TILE_128x64, GEMM_NT, TILE_128x128},  // wide sketch: Z^T.dY beside G.S^T
-    {GEMM_NN_F32_COLSUM, TILE_128x128, GEMM_NT, TILE_128x128},
-    {GEMM_NT, TILE_64x64, GEMM_TT, TILE_64x64},                // R = 256..384 at BERT-base width
-    {GEMM_NN_F32_COLSUM, TILE_128x64, GEMM_NT, TILE_128x64},
-    {GEMM_NT_F32, TILE_64x64, GEMM_TT_F32, TILE_64x128},       // narrow sketch of a long input: Z^T in ranges as well
-    {GEMM_NT_F32, TILE_64x128, GEMM_TT_F32, TILE_128x128},
-    {GEMM_NT_F32, TILE_64x128, GEMM_TT_F32, TILE_128x64},
-    // wide sketches again, dY.U^T, Z^T or both in ranges, and a narrow dX
-    {GEMM_NT_F32, TILE_128x128, GEMM_TT, TILE_128x128},
-    {GEMM_NT, TILE_128x128, GEMM_TT_F32, TILE_128x128},
-    {GEMM_NT_F32, TILE_128x128, GEMM_TT_F32, TILE_128x128},
-    {GEMM_NT, TILE_64x64, GEMM_TT_F32, TILE_64x64},
-    {GEMM_NT_F32, TILE_64x64, GEMM_TT_F32, TILE_64x64},
-    {GEMM_NN_F32_COLSUM, TILE_128x64, GEMM_NT, TILE_64x64},
+    // narrow sketch: R in 65..128, R <= 64; of a long input, Z^T in ranges as well
+    {GEMM_NT_F32, TILE_64x128, GEMM_TT, TILE_64x64, dual_gemm_kernel<NTF_64x128, TT_64x64>, nullptr},
+    {GEMM_NT_F32, TILE_64x64, GEMM_TT, TILE_64x64, dual_gemm_kernel<NTF_64x64, TT_64x64>, dual_gemm_kernel<RING_NTF_64x64, RING_TT_64x64>},
+    {GEMM_NT_F32, TILE_64x64, GEMM_TT_F32, TILE_64x128, dual_gemm_kernel<NTF_64x64, TTF_64x128>, nullptr},
+    {GEMM_NT_F32, TILE_64x128, GEMM_TT_F32, TILE_128x128, dual_gemm_kernel<NTF_64x128, TTF_128x128>, nullptr},
+    {GEMM_NT_F32, TILE_64x128, GEMM_TT_F32, TILE_128x64, dual_gemm_kernel<NTF_64x128, TTF_128x64>, nullptr},
+    // wide sketch, dY.U^T beside Z^T: both whole, the one, the other or both in ranges
+    {GEMM_NT, TILE_128x128, GEMM_TT, TILE_128x128, dual_gemm_kernel<NT_128x128, TT_128x128>, nullptr},
+    {GEMM_NT_F32, TILE_128x128, GEMM_TT, TILE_128x128, dual_gemm_kernel<NTF_128x128, TT_128x128>, nullptr},
+    {GEMM_NT, TILE_128x128, GEMM_TT_F32, TILE_128x128, dual_gemm_kernel<NT_128x128, TTF_128x128>, nullptr},
+    {GEMM_NT_F32, TILE_128x128, GEMM_TT_F32, TILE_128x128, dual_gemm_kernel<NTF_128x128, TTF_128x128>, nullptr},
+    {GEMM_NT, TILE_64x64, GEMM_TT, TILE_64x64, dual_gemm_kernel<NT_64x64, TT_64x64>, dual_gemm_kernel<RING_NT_64x64, RING_TT_64x64>},
+    {GEMM_NT, TILE_64x64, GEMM_TT_F32, TILE_64x64, dual_gemm_kernel<NT_64x64, TTF_64x64>, dual_gemm_kernel<RING_NT_64x64, RING_TTF_64x64>},
+    {GEMM_NT_F32, TILE_64x64, GEMM_TT_F32, TILE_64x64, dual_gemm_kernel<NTF_64x64, TTF_64x64>, dual_gemm_kernel<RING_NTF_64x64, RING_TTF_64x64>},
+    // wide sketch, Z^T.dY beside G.S^T
+    {GEMM_NN_F32_COLSUM, TILE_128x64, GEMM_NT, TILE_128x128, dual_gemm_kernel<NNFC_128x64, NT_128x128>, nullptr},
+    {GEMM_NN_F32_COLSUM, TILE_128x128, GEMM_NT, TILE_128x128, dual_gemm_kernel<NNFC_128x128, NT_128x128>, nullptr},
+    {GEMM_NN_F32_COLSUM, TILE_128x64, GEMM_NT, TILE_128x64, dual_gemm_kernel<NNFC_128x64, NT_128x64>, nullptr},
+    {GEMM_NN_F32_COLSUM, TILE_128x64, GEMM_NT, TILE_64x64, dual_gemm_kernel<NNFC_128x64, NT_64x64>, nullptr},
 };
-int dual_pair_index(GemmKind ka, int ta, GemmKind kb, int tb) {
-  for (int i = 0; i < (int)(sizeof(kDualPairs) / sizeof(kDualPairs[0])); ++i)
-    if (kDualPairs[i].ka == ka && kDualPairs[i].ta == ta && kDualPairs[i].kb == kb && kDualPairs[i].tb == tb)
-      return i;
-  return -1;
+const DualPair* dual_pair(GemmKind ka, int ta, GemmKind kb, int tb) {
+  for (const DualPair& p : kDualPairs)
+    if (p.ka == ka && p.ta == ta && p.kb == kb && p.tb == tb) return &p;
+  return nullptr;
 }
 }  // namespace
 
 bool dual_gemm_supported(GemmKind kind_a, int tile_a, GemmKind kind_b, int tile_b) {
-  return dual_pair_index(kind_a, tile_a, kind_b, tile_b) >= 0;
+  return dual_pair(kind_a, tile_a, kind_b, tile_b) != nullptr;
 }
 
 hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKind kind_b, int tile_b,
                                  GemmArgs b, hipStream_t s) {
-  const int pair = dual_pair_index(kind_a, tile_a, kind_b, tile_b);
-  if (pair < 0) return hipErrorInvalidValue;
+  const DualPair* const pair = dual_pair(kind_a, tile_a, kind_b, tile_b);
+  if (pair == nullptr) return hipErrorInvalidValue;
   int bm, bn;
   tile_dims(tile_a, bm, bn);
   a.tiles_m = (a.M + bm - 1) / bm;
@@ -494,56 +515,13 @@ hipError_t launch_dual_gemm_bf16(GemmKind kind_a, int tile_a, GemmArgs a, GemmKi
     work.flops += wb.flops;
     work.bytes += wb.bytes;
   }
-  const char* name = "dual_gemm_kernel";
-  typedef GemmTile<64, 128, true, true, float, false> NTF_64x128;
-  typedef GemmTile<64, 64, true, true, float, false> NTF_64x64;
-  typedef GemmTile<64, 64, false, true, bf16, false> TT_64x64;
-  typedef GemmTile<128, 128, true, true, bf16, false> NT_128x128;
-  typedef GemmTile<128, 128, false, true, bf16, false> TT_128x128;
-  typedef GemmTile<128, 64, true, false, float, true> NNFC_128x64;
-  typedef GemmTile<128, 128, true, false, float, true> NNFC_128x128;
-  typedef GemmTile<64, 64, true, true, bf16, false> NT_64x64;
-  typedef GemmTile<128, 64, true, true, bf16, false> NT_128x64;
-  typedef GemmTile<64, 128, false, true, float, false> TTF_64x128;
-  typedef GemmTile<128, 128, false, true, float, false> TTF_128x128;
-  typedef GemmTile<128, 64, false, true, float, false> TTF_128x64;
-  typedef GemmTile<128, 128, true, true, float, false> NTF_128x128;
-  typedef GemmTile<64, 64, false, true, float, false> TTF_64x64;
   // 64 x 64 tiles in one round, two work-groups to a CU: on the ring, as a product by itself.  Backward pass, us, staged : ring,
   // narrow sketches: 2925 tokens, 1584 -> 2480, R = 64 29.6 : 26.6; 1024, 1024 -> 1024, R = 64 19.6 : 17.5; 2901, 304 -> 3824, R = 16 20.1 : 20.4;
   // wide ones: 1600, 2464 -> 1536, R = 256 30.6 : 25.3; 1507, 3120 -> 464, R = 512 36.9 : 31.6; 4096, 768 -> 768, R = 256 (512
   // work-groups) 24.5 : 23.5.  (On rings of their own the 128 x 64 and the 128 x 128 tiles of the other pairs are level with the staged
   // ones: 150 layers with the latter, 1.0000 of the time, 0.98 to 1.02.)
-  typedef RingTile<64, 64, true, true, float, false> RING_NTF_64x64;
-  typedef RingTile<64, 64, false, true, bf16, false> RING_TT_64x64;
-  typedef RingTile<64, 64, true, true, bf16, false> RING_NT_64x64;
-  typedef RingTile<64, 64, false, true, float, false> RING_TTF_64x64;
-  if ((pair == 1 || pair == 5 || pair == 13 || pair == 14) && ga + gb <= NUM_CUS * RING_NT_64x64::PER_CU) {
-    name = "dual_gemm_kernel<ring>";
-    if (pair == 13) return launch_kernel(name, work, dual_gemm_kernel<RING_NT_64x64, RING_TTF_64x64>, grid, block, s, a, b, (int)ga);
-    if (pair == 14) return launch_kernel(name, work, dual_gemm_kernel<RING_NTF_64x64, RING_TTF_64x64>, grid, block, s, a, b, (int)ga);
-    if (pair == 1) return launch_kernel(name, work, dual_gemm_kernel<RING_NTF_64x64, RING_TT_64x64>, grid, block, s, a, b, (int)ga);
-    return launch_kernel(name, work, dual_gemm_kernel<RING_NT_64x64, RING_TT_64x64>, grid, block, s, a, b, (int)ga);
-  }
-  switch (pair) {
-    case 0: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x128, TT_64x64>, grid, block, s, a, b, (int)ga);
-    case 1: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x64, TT_64x64>, grid, block, s, a, b, (int)ga);
-    case 2: return launch_kernel(name, work, dual_gemm_kernel<NT_128x128, TT_128x128>, grid, block, s, a, b, (int)ga);
-    case 3: return launch_kernel(name, work, dual_gemm_kernel<NNFC_128x64, NT_128x128>, grid, block, s, a, b, (int)ga);
-    case 4: return launch_kernel(name, work, dual_gemm_kernel<NNFC_128x128, NT_128x128>, grid, block, s, a, b, (int)ga);
-    case 5: return launch_kernel(name, work, dual_gemm_kernel<NT_64x64, TT_64x64>, grid, block, s, a, b, (int)ga);
-    case 6: return launch_kernel(name, work, dual_gemm_kernel<NNFC_128x64, NT_128x64>, grid, block, s, a, b, (int)ga);
-    case 7: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x64, TTF_64x128>, grid, block, s, a, b, (int)ga);
-    case 8: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x128, TTF_128x128>, grid, block, s, a, b, (int)ga);
-    case 9: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x128, TTF_128x64>, grid, block, s, a, b, (int)ga);
-    case 10: return launch_kernel(name, work, dual_gemm_kernel<NTF_128x128, TT_128x128>, grid, block, s, a, b, (int)ga);
-    case 11: return launch_kernel(name, work, dual_gemm_kernel<NT_128x128, TTF_128x128>, grid, block, s, a, b, (int)ga);
-    case 12: return launch_kernel(name, work, dual_gemm_kernel<NTF_128x128, TTF_128x128>, grid, block, s, a, b, (int)ga);
-    case 13: return launch_kernel(name, work, dual_gemm_kernel<NT_64x64, TTF_64x64>, grid, block, s, a, b, (int)ga);
-    case 14: return launch_kernel(name, work, dual_gemm_kernel<NTF_64x64, TTF_64x64>, grid, block, s, a, b, (int)ga);
-    case 15: return launch_kernel(name, work, dual_gemm_kernel<NNFC_128x64, NT_64x64>, grid, block, s, a, b, (int)ga);
-    default: return hipErrorInvalidValue;
-  }
+  const bool ring = pair->ring != nullptr && ga + gb <= NUM_CUS * RING_NT_64x64::PER_CU;
+  return launch_kernel(ring ? "dual_gemm_kernel<ring>" : "dual_gemm_kernel", work, ring ? pair->ring : pair->staged, grid, block, s, a, b, (int)ga);
 }
 
 __global__ __launch_bounds__(256) void reduce_splits_2d_kernel(const float* __restrict__ part,

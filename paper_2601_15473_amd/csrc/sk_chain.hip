@@ -1136,7 +1136,7 @@ static hipError_t launch_beside(GemmArgs a, const ChainArgs& c, hipStream_t s) {
   const Work wc = chain_work(c, false);
   work.flops += wc.flops;
   work.bytes += wc.bytes;
-  static const std::string name = kernel_label("factor_beside_expand_kernel", {lbl(BM), lbl(RT)});
+  static const std::string name = kernel_label("factor_beside_expand_kernel", {lbl(BM), lbl(RT), lbl(SHORT)});
   return launch_kernel(name.c_str(), work, factor_beside_expand_kernel<BM, RT, SHORT>, dim3((unsigned)(ga + c.tiles_m * c.n_slices)), dim3(256), s, a, c, ga);
 }
 

@@ -249,7 +249,7 @@ int chain_bn(int R);   // width of the N tiles the chain kernels walk
 hipError_t launch_chain_bf16(bool b_kc, bool fused, ChainArgs a, hipStream_t s);
 
 // The factor gradient Z^T . dY of a narrow sketch (GEMM_NN_F32_COLSUM on `tile`) beside the expansion of dX from slabs of G over
-// short runs of output tiles, in one launch; ask factor_beside_expand_supported first.
+// short runs of output tiles, up to R = 64 over runs of any length, in one launch; ask factor_beside_expand_supported first.
 bool factor_beside_expand_supported(int tile, const GemmArgs& a, const ChainArgs& c);
 hipError_t launch_factor_beside_expand(int tile, GemmArgs a, ChainArgs c, hipStream_t s);
 

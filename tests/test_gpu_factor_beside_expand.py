@@ -10,15 +10,17 @@ KERNEL = "factor_beside_expand_kernel"
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,launches", [
+@pytest.mark.parametrize("runs,shape,launches", [(runs, *c) for runs, cases in (("short", [
     ((515, 400, 1040, 1, 16), 2), ((130, 64, 2064, 1, 48), 2), ((513, 80, 528, 1, 112), 3), ((1030, 272, 2320, 2, 32), 3), ((700, 1040, 1296, 1, 80), 3),
     ((2100, 784, 1040, 1, 128), 3), ((1111, 400, 2064, 1, 64), 3), ((4033, 384, 784, 1, 64), 3), ((1500, 2576, 1296, 1, 96), 4), ((900, 3600, 1040, 1, 32), 4), ((418, 3616, 272, 1, 80), 3),
     # instead of one pass over x and dY
     ((255, 304, 752, 1, 16), 2), ((2411, 768, 992, 1, 16), 3), ((4095, 848, 880, 2, 16), 3),
-    # long runs, x . S whole and in ranges
-    ((8200, 784, 528, 1, 48), 3), ((9295, 976, 1104, 1, 16), 3), ((2100, 4112, 2064, 1, 16), 4), ((1198, 3248, 752, 1, 64), 4),
-], ids=lambda v: "T%d_%dx%d_l%dk%d" % v if isinstance(v, tuple) else "")
-def test_against_the_oracle_and_the_separate_call(shape, launches):
+    # an expansion of fewer work-groups, to leave room
+    ((1198, 3248, 752, 1, 64), 4),
+]), ("long", [   # x . S whole and in ranges
+    ((8200, 784, 528, 1, 48), 3), ((9295, 976, 1104, 1, 16), 3), ((2100, 4112, 2064, 1, 16), 4),
+])) for c in cases], ids=lambda v: "T%d_%dx%d_l%dk%d" % v if isinstance(v, tuple) else v if isinstance(v, str) else "")
+def test_against_the_oracle_and_the_separate_call(runs, shape, launches):
     import torch
     from test_gpu_parity import DeviceLayer, _kernels_of, check_all
     T, d_in, d_out, l, k = shape
@@ -27,6 +29,7 @@ def test_against_the_oracle_and_the_separate_call(shape, launches):
     t = W.generate(w)
     names = _kernels_of(libsk, DeviceLayer(t, libsk), ("bwd",))
     assert len(names) == launches and any(n.startswith(KERNEL) for n in names[-2:]), names
+    assert [n.endswith("true>") for n in names if n.startswith(KERNEL)] == [runs == "short"], names   # (results straight from registers, or through LDS)
     one, again, sep = DeviceLayer(t, libsk), DeviceLayer(t, libsk), DeviceLayer(t, libsk)
     again.ws.fill_(255)
     libsk.check(one.bwd())
