@@ -723,11 +723,18 @@ struct WidePlan {
 // beside each other two to four.  The ranges of Z^T and of the tokens stay those of the separate calls (dU and db come out
 // the same), those of dY.U^T are as many as its slabs have room for.  The first two have one result size, so one tile
 // serves both, the one with the least modelled time: all chunks at the rate of a CU with company (its fill: 0.62 us
-// a chunk of a 128 x 128 tile, 0.27 of a 64 x 64 one) or the longest walk by itself (0.65, 0.36), whichever is more, and slabs at 4 TB/s and
-// 2.5 us for the launch that sums them.  Backward pass, us, apart : shared: 735 tokens, 560 -> 592, R = 432 23.2 : 14.7; 2777, 3376 -> 4800,
+// a chunk of a 128 x 128 tile, 0.27 of a 64 x 64 one) or the longest walk of a CU (0.65, 0.36 by itself, of more than a round half way between
+// an even share of them and the whole number that the fullest CU has), whichever is more, and slabs at 4 TB/s and 2.5 us for the launch
+// that sums them.  64 x 64 tiles past two work-groups a CU run on the staged loop, which long walks of dY.U^T keep waiting: 0.33.
+// (Fitted to the first launch and its sums of 250 layers over every tile and range: 1.017 of the best choice's time at the mean, one in eight more than 5 %
+// behind; without the fullest CU and the staged rate 1.031 and one in five, up to 1.5.)  Backward pass, us, those two out : in: 7024 tokens,
+// 256 -> 6000, R = 192 104 : 86; 1383, 96 -> 7408, R = 992 105 : 86; 2142, 1360 -> 2992, R = 576 58.7 : 50.7; 110 of 1200 layers took another pair, in 0.95
+// of the time (0.82 to 1.04).
+// Backward pass, us, apart : shared: 735 tokens, 560 -> 592, R = 432 23.2 : 14.7; 2777, 3376 -> 4800,
 // R = 1360 202 : 155; 2302, 3744 -> 7200, R = 672 151 : 117; 99 of 150 layers of 512 to 16384 tokens, 512 to 4096 wide, R 144 to
 // 512, were apart, now 0.78 of the time, 24 of 50 of 2048 to 16384 tokens, R 512 to 2048, 0.86, all of 257 to 600 tokens 0.69, the rest within
-// 2 %.  Layers that shared launches before on tiles of two models of their own: 0.997 (0.87 to 1.02).
+// 2 %.  Layers that shared launches before on tiles of two models of their own: 0.997 (0.87 to 1.02).  390 more layers of up to 400
+// inputs and 2000 to 8192 outputs, where there is little to share: 0.86, eight of them 2 to 6 % behind.
 // None where one of the first two takes the 256 x 256 tile by itself (see sk_linear_bwd).
 WidePlan plan_wide(const Shape& s, const WeightPlan& w, const FirstPlan& first) {
   WidePlan best{-1, 1, 0, 0, 0};
@@ -738,17 +745,23 @@ WidePlan plan_wide(const Shape& s, const WeightPlan& w, const FirstPlan& first) 
   else if (best.dx_tile == TILE_64x128) best.dx_tile = TILE_128x64;
   if (!dual_gemm_supported(GEMM_NN_F32_COLSUM, best.du_tile, GEMM_NT, best.dx_tile)) return best;
   double least = -1.0;
-  static const struct { int tile, side; double shared, alone; } cand[] = {{TILE_128x128, 128, 0.62, 0.65}, {TILE_64x64, 64, 0.27, 0.36}};
   const double z_walk = (double)((s.in / w.z_splits + 63) / 64);
-  for (const auto& c : cand) {
-    const double tiles = (double)((s.T + c.side - 1) / c.side) * ((s.R + c.side - 1) / c.side);
+  for (const int tile : {TILE_128x128, TILE_64x64}) {
+    const int side = tile == TILE_128x128 ? 128 : 64;
+    const int64_t tiles = ((s.T + side - 1) / side) * ((s.R + side - 1) / side);
     for (int sp = 1; sp <= first.splits; ++sp) {
       const int64_t kps = ((s.out + sp - 1) / sp + 63) / 64 * 64;
       if ((s.out + kps - 1) / kps != sp) continue;
-      const double g_walk = (double)(kps / 64), all = tiles * (sp * g_walk + w.z_splits * z_walk) * c.shared / NUM_CUS;
-      const double longest = (g_walk > z_walk ? g_walk : z_walk) * c.alone;
+      const bool staged = tiles * (sp + w.z_splits) > 2 * NUM_CUS && w.z_splits == 1 && s.out >= 1024;
+      const double shared = tile == TILE_128x128 ? 0.62 : staged ? 0.33 : 0.27, alone = tile == TILE_128x128 ? 0.65 : 0.36;
+      auto walks = [&](int64_t groups, double chunks) {
+        const double deep = 0.5 * ((double)groups / NUM_CUS + (double)((groups + NUM_CUS - 1) / NUM_CUS));
+        return chunks * (groups > NUM_CUS && deep * shared > alone ? deep * shared : alone);
+      };
+      const double g_walk = (double)(kps / 64), all = tiles * (sp * g_walk + w.z_splits * z_walk) * shared / NUM_CUS;
+      const double g_us = walks(tiles * sp, g_walk), z_us = walks(tiles * w.z_splits, z_walk), longest = g_us > z_us ? g_us : z_us;
       const double us = (all > longest ? all : longest) + (sp > 1 ? (w.z_splits > 1 ? 0.0 : 2.5) + sp * (double)s.T * s.R * 8.0 / 4.0e6 : 0.0);
-      if (least < 0.0 || us < least) { least = us; best.tile = c.tile; best.g_splits = sp; best.g_k_per_split = (int)kps; }
+      if (least < 0.0 || us < least) { least = us; best.tile = tile; best.g_splits = sp; best.g_k_per_split = (int)kps; }
     }
   }
   return best;
