@@ -735,12 +735,14 @@ struct WidePlan {
 // 512, were apart, now 0.78 of the time, 24 of 50 of 2048 to 16384 tokens, R 512 to 2048, 0.86, all of 257 to 600 tokens 0.69, the rest within
 // 2 %.  Layers that shared launches before on tiles of two models of their own: 0.997 (0.87 to 1.02).  390 more layers of up to 400
 // inputs and 2000 to 8192 outputs, where there is little to share: 0.86, eight of them 2 to 6 % behind.
-// None where one of the first two takes the 256 x 256 tile by itself (see sk_linear_bwd).
+// None where one of the first two takes the 256 x 256 tile by itself (see sk_linear_bwd), or where dX does and is modelled more than 24 us ahead on it:
+// 12520 tokens, 7296 -> 144, R = 352 223 : 234; 14077, 8080 -> 1216, R = 320 302 : 317; ten such layers 0.99 to 1.05, from 15 to 24 us 0.80 to 1.04 (mean 0.95).
 WidePlan plan_wide(const Shape& s, const WeightPlan& w, const FirstPlan& first) {
   WidePlan best{-1, 1, 0, 0, 0};
   if (tune(SK_TUNE_TILE) >= 0 || choose_tile(s.T, s.R, s.out, 1) == TILE_256x256 || choose_tile(s.R, s.T, s.in, 1) == TILE_256x256) return best;
   best.du_tile = w.tile;
   best.dx_tile = choose_tile(s.T, s.in, s.R, 1);
+  if (best.dx_tile == TILE_256x256 && small_tiles_us(small_tiles(s.T, s.in), (double)s.R) - big_tiles_us(s.T, s.in, (double)s.R, 1) > 24.0) return best;
   if (w.tile == TILE_128x128 || best.dx_tile == TILE_256x256) best.dx_tile = TILE_128x128;
   else if (best.dx_tile == TILE_64x128) best.dx_tile = TILE_128x64;
   if (!dual_gemm_supported(GEMM_NN_F32_COLSUM, best.du_tile, GEMM_NT, best.dx_tile)) return best;

@@ -52,6 +52,9 @@ RANGES = ["few_rows", "reduce_to_bf16", "few_rows"]
     # wide sketches: the first two contractions beside each other, or alone on 256 x 256 tiles
     ("bwd", (12288, 768, 768, 768), ["dual_gemm", "dual_gemm", "reduce_splits"]),
     ("bwd", (33222, 208, 48, 544), ["dual_gemm", "dual_gemm", "reduce_splits"]),
+    # ... dX on 128 x 128 tiles beside Z^T.dY, or alone on 256 x 256 ones where those are far ahead
+    ("bwd", (9153, 7792, 576, 416), ["dual_gemm", "reduce_to_bf16", "dual_gemm", "reduce_splits"]),
+    ("bwd", (12520, 7296, 144, 352), ["kernel", "crew", "kernel", "reduce_to_bf16", "kernel", "reduce_splits"]),
     ("bwd", (12288, 4096, 1024, 1024), ["crew", "crew", "crew", "kernel", "reduce_splits"]),
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else v if isinstance(v, str) else "")
 def test_kernels_on_either_side(call, shape, want):
