@@ -68,8 +68,6 @@ Workspaces& workspaces() {
   return *w;
 }
 
-size_t aligned_up(size_t bytes) { return (bytes + 255) / 256 * 256; }
-
 sk_dtype dtype_of(const Tensor& t) { return t.scalar_type() == at::kFloat ? SK_F32 : SK_BF16; }
 
 void* stream_of(const at::Device& device) {
@@ -252,18 +250,20 @@ struct LinearTwoSided : torch::autograd::Function<LinearTwoSided> {
     const size_t need = sk_linear_workspace_bytes(SK_OP_BWD_TWO_SIDED, tokens, in, out, l2, kept.k, dt);
     Workspaces& w = workspaces();
     sk_status st;
-    if (dt != SK_F32) {   // fp32 sums behind the workspace, results each a tensor of its own
+    const auto f32 = x2.options().dtype(at::kFloat);
+    if (dt != SK_F32) {   // results each a tensor of its own; their fp32 sums in one that goes back to the allocator with the pass
       dB = at::empty({half, out}, A.options());
       dA = at::empty({in, half}, A.options());
       if (kept.bias) db = at::empty({out}, A.options());
-      const size_t at_dB = aligned_up(need), at_dA = at_dB + aligned_up((size_t)(2 * half * out) * 4), at_db = at_dA + aligned_up((size_t)(in * half) * 4);
+      const Tensor sums = at::empty({2 * half * out + in * half + out}, f32);
+      float* const sum_dB = sums.data_ptr<float>();
+      float* const sum_dA = sum_dB + 2 * half * out;
       const std::lock_guard<std::mutex> lock(w.mutex);
-      unsigned char* const ws = static_cast<unsigned char*>(w.get(x2.device(), stream, at_db + (size_t)out * 4).data_ptr());
-      st = sk_linear_bwd_rounded(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), reinterpret_cast<float*>(ws + at_dB),
-                                 kept.bias ? reinterpret_cast<float*>(ws + at_db) : nullptr, reinterpret_cast<float*>(ws + at_dA), dB.data_ptr(), half,
-                                 kept.bias ? db.data_ptr() : nullptr, dA.data_ptr(), tokens, in, out, l2, kept.k, dt, ws, need, stream);
+      const Tensor& ws = w.get(x2.device(), stream, need);
+      st = sk_linear_bwd_rounded(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), sum_dB, kept.bias ? sum_dA + in * half : nullptr, sum_dA,
+                                 dB.data_ptr(), half, kept.bias ? db.data_ptr() : nullptr, dA.data_ptr(), tokens, in, out, l2, kept.k, dt, ws.data_ptr(),
+                                 (size_t)ws.numel(), stream);
     } else {
-      const auto f32 = x2.options().dtype(at::kFloat);
       const Tensor whole = at::empty({2 * half, out}, f32);
       dA = at::empty({in, half}, f32);
       dB = whole.narrow(0, 0, half);

@@ -256,6 +256,23 @@ def test_threads_and_streams():
     assert torch.equal(layer(xs[0]), want[0])
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("two_sided", [False, True])
+def test_a_pass_keeps_its_workspace_and_nothing_else(two_sided):
+    layer = (sknn.SKLinearTwoSided if two_sided else sknn.SKLinear)(256, 768, 2, 64, dtype=torch.bfloat16, seed=7)
+    x, dY = torch.randn(500, 256, device="cuda").bfloat16().requires_grad_(), torch.randn(500, 768, device="cuda").bfloat16()
+    sknn.release_workspaces()     # (other tests' streams)
+    op, l = (sk.SK_OP_BWD_TWO_SIDED, 4) if two_sided else (sk.SK_OP_BWD, 2)
+    most = max(sk.sk_linear_workspace_bytes(o, 500, 256, 768, l, 64, sk.SK_BF16) for o in (sk.SK_OP_FWD, op))
+    for _ in range(2):
+        torch.autograd.grad(layer(x), (x, *layer.parameters()), dY)
+        torch.cuda.synchronize()
+    held = torch.cuda.memory_allocated()
+    sknn.release_workspaces()
+    held -= torch.cuda.memory_allocated()
+    assert 0 < held <= most + 512, (held, most)   # (the allocator's rounding)
+
+
 def test_calls_left_to_python_are_not_taken():
     t = torch.zeros(4, 32)
     assert sknn._native.linear(t, t, t, None, 1, 16) is None                  # not on a GPU
