@@ -141,8 +141,8 @@ sk_status sk_linear_bwd_weight_noalloc(const void* x, const void* S_cat, const v
  *     token splits on the kernel that expands dX -- two or three launches instead of five, which
  *     is most of the cost at BERT-base sizes (four instead of six where x . S is recomputed in ranges).
  *   - Very narrow sketches (bf16, R <= 32, in <= 848, out <= 896) over up to 16384
- *     tokens, from 4096 on or where the factor gradient shares no launch with the
- *     expansion: one kernel reads x and dY once, recomputes x . S_cat, and produces dX and
+ *     tokens, where the factor gradient shares no launch with the expansion, and from 4096
+ *     tokens on also where it could unless out > in: one kernel reads x and dY once, recomputes x . S_cat, and produces dX and
  *     a partial dU_cat and dbias per token tile, which a second kernel sums in tile
  *     order -- two launches, dY read once.  dU_cat and dbias then differ from the
  *     separate call's in the order of their fp32 partial sums (they remain
@@ -151,7 +151,8 @@ sk_status sk_linear_bwd_weight_noalloc(const void* x, const void* S_cat, const v
  *     factor gradient.
  *   - Wide sketches (bf16): dY . U_cat^T runs beside the recomputation of x . S_cat and the
  *     expansion of dX beside the factor gradient, two to four launches instead of five to seven,
- *     unless one of the products fills the chip by itself.
+ *     unless one of the products fills the chip by itself (or dX is far ahead on tiles of its own),
+ *     or dY . U_cat^T is the few-rows kernel's (up to 256 tokens and not many columns).
  *   - Other shapes run the two gradients one after the other.
  *   x [tokens, in], dY [tokens, out], S_cat [in, R], U_cat [R, out],
  *   dX [tokens, in] (output), dU_cat [R, out] fp32 (output), dbias [out] fp32 (output) or NULL.

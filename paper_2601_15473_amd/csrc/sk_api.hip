@@ -1382,10 +1382,11 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
   c.Z = ws_in; c.z_splits = q.splits; c.z_slab = (int64_t)tokens * s.R;
   // Z^T.dY shares a launch with the expansion where that is over soon (launch_factor_beside_expand), also in one range
   // of tokens: two launches, where one after the other the gradients take three or four (62 of 150 layers of 100 to 600 tokens,
-  // 64 to 4096 wide, take it, in 0.61 of the time; 570 tokens, 320 -> 1808, R = 32 19.7 : 10.3 us; x.S in ranges, 418, 3616 -> 272, R = 80
-  // 21.0 : 15.7).  Where x.S comes in ranges for a few hundred tokens the launches stay the four that the schedule's test counts.
-  bool beside = bf16_any_z && !(z_ranges && tokens <= 320) && factor_beside_expand_supported(w.tile, du, c);
-  if (!beside && z_ranges && tokens > 320 && (in <= 2 * out || tokens <= 2048)) {
+  // 64 to 4096 wide, take it, in 0.61 of the time; 570 tokens, 320 -> 1808, R = 32 19.7 : 10.3 us; 164 of 250 layers of 1 to 99 tokens, 0.72 (0.57 to 0.98),
+  // 60, 512 -> 1696, R = 48 17.0 : 9.8 against the few-rows kernel; x.S in ranges, 418, 3616 -> 272, R = 80 21.0 : 15.7, 80 layers of 9 to 320
+  // tokens 0.80 to 0.84, 34, 3696 -> 1248, R = 112 20.1 : 16.2).
+  bool beside = bf16_any_z && factor_beside_expand_supported(w.tile, du, c);
+  if (!beside && z_ranges && (in <= 2 * out || tokens <= 2048)) {
     // An expansion of two work-groups a CU with one instead, to leave room: not where dX is most of what moves (5505 tokens, 3600 -> 272, R = 48
     // 38.6 : 41.3 us, 9664, 3024 -> 320, R = 32 48.6 : 51.8, 6520, 2432 -> 976, R = 16 37.3 : 38.0; 1198, 3248 -> 752, R = 64 21.5 : 19.8).
     ChainArgs fewer = c;
@@ -1393,11 +1394,12 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
     if (factor_beside_expand_supported(w.tile, du, fewer)) { beside = true; c = fewer; }
   }
   // --- narrow sketch, short input: one pass over x and dY | sum of the token tiles' slabs ---
-  // Not, by itself, where the two gradients share launches (below) up to 4095 tokens.  One pass : shared, backward call, us: 255 tokens,
+  // Not, by itself, where the two gradients share launches (below), up to 4095 tokens or with more outputs than inputs.  One pass : shared, backward call, us: 255 tokens,
   // 304 -> 752, R = 16 14.0 : 8.4; 1024, 768 -> 768, R = 32 15.7 : 13.3; 2411, 768 -> 992, R = 16 18.7 : 15.9.  Of 200 layers (200 to 16384 tokens, 64 to
-  // 1024 outputs) 115 can share: 0.60 to 0.97 of the time up to 4095 tokens (mean 0.81), beyond (90 other layers included)
-  // 0.83 to 1.13; none of the other 85 (outputs up to 240) is faster without this pass (1.08 to 1.41).
-  const bool shares = beside && !z_ranges && tokens < 4096 && tune(SK_TUNE_NARROW_BWD) < 0 && q.splits > 1 &&
+  // 1024 outputs) 115 can share: 0.60 to 0.97 of the time up to 4095 tokens (mean 0.81);
+  // of 160 layers of 4096 to 16384, 126 with more outputs than inputs, all of which a work-group of the one pass walks, 0.80 to 1.01 (mean 0.92, one at 1.05), the other 34 0.91
+  // to 1.09 (mean 1.01); none of the other 85 (outputs up to 240) is faster without this pass (1.08 to 1.41).
+  const bool shares = beside && !z_ranges && (tokens < 4096 || in < out) && tune(SK_TUNE_NARROW_BWD) < 0 && q.splits > 1 &&
                       dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT, z_tile);
   if (const NarrowPlan n = plan_narrow(s); n.ok && !shares) {
     g_hip_error.clear();

@@ -19,7 +19,8 @@ def test_split_recomputation_beside_the_other_product(sk, shape):  # noqa: F811
     check_all(sk, w, 0, single_call=True)
     t = W.generate(w)
     names = _kernels_of(sk, DeviceLayer(t, sk), ("bwd",))
-    assert [n.split("<")[0] for n in names[:2]] == ["dual_gemm_kernel", "reduce_to_bf16_kernel"] and len(names) == 4, names
+    # (300 tokens are one range: no sums behind the factor gradient beside the expansion)
+    assert [n.split("<")[0] for n in names[:2]] == ["dual_gemm_kernel", "reduce_to_bf16_kernel"] and len(names) == (3 if T == 300 else 4), names
     one, sep = DeviceLayer(t, sk), DeviceLayer(t, sk)
     sk.check(one.bwd())
     sk.check(sep.bwd_weight())
