@@ -141,8 +141,8 @@ sk_status sk_linear_bwd_weight_noalloc(const void* x, const void* S_cat, const v
  *     token splits on the kernel that expands dX -- two or three launches instead of five, which
  *     is most of the cost at BERT-base sizes (four instead of six where x . S is recomputed in ranges).
  *   - Very narrow sketches (bf16, R <= 32, in <= 848, out <= 896) over up to 16384
- *     tokens, where the factor gradient shares no launch with the expansion, and from 4096
- *     tokens on also where it could unless out > in: one kernel reads x and dY once, recomputes x . S_cat, and produces dX and
+ *     tokens, from 4096 on or where the factor gradient shares no launch with the
+ *     expansion: one kernel reads x and dY once, recomputes x . S_cat, and produces dX and
  *     a partial dU_cat and dbias per token tile, which a second kernel sums in tile
  *     order -- two launches, dY read once.  dU_cat and dbias then differ from the
  *     separate call's in the order of their fp32 partial sums (they remain

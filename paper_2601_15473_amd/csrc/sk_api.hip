@@ -1394,12 +1394,13 @@ static sk_status bwd_both(const void* x, const void* dY, const void* S_cat, cons
     if (factor_beside_expand_supported(w.tile, du, fewer)) { beside = true; c = fewer; }
   }
   // --- narrow sketch, short input: one pass over x and dY | sum of the token tiles' slabs ---
-  // Not, by itself, where the two gradients share launches (below), up to 4095 tokens or with more outputs than inputs.  One pass : shared, backward call, us: 255 tokens,
+  // Not, by itself, where the two gradients share launches (below) up to 4095 tokens.  One pass : shared, backward call, us: 255 tokens,
   // 304 -> 752, R = 16 14.0 : 8.4; 1024, 768 -> 768, R = 32 15.7 : 13.3; 2411, 768 -> 992, R = 16 18.7 : 15.9.  Of 200 layers (200 to 16384 tokens, 64 to
-  // 1024 outputs) 115 can share: 0.60 to 0.97 of the time up to 4095 tokens (mean 0.81);
-  // of 160 layers of 4096 to 16384, 126 with more outputs than inputs, all of which a work-group of the one pass walks, 0.80 to 1.01 (mean 0.92, one at 1.05), the other 34 0.91
-  // to 1.09 (mean 1.01); none of the other 85 (outputs up to 240) is faster without this pass (1.08 to 1.41).
-  const bool shares = beside && !z_ranges && (tokens < 4096 || in < out) && tune(SK_TUNE_NARROW_BWD) < 0 && q.splits > 1 &&
+  // 1024 outputs) 115 can share: 0.60 to 0.97 of the time up to 4095 tokens (mean 0.81).
+  // Beyond, the ranges of tokens are much longer than the one pass's 32 or 64 and db's sums further from 64 bits: 1.15 times its 4.7e-8 from 4096 to 8191, 1.26 times its 6.1e-8 up to
+  // 16384 (1.00 to 1.05 below; dU and dX 1.00 everywhere; 90 layers), so the one pass stays there, though of 160 layers that can share 126 with more outputs than inputs would take 0.80 to
+  // 1.01 of the time (mean 0.92, one at 1.05), 34 others 0.91 to 1.09 (mean 1.01); none of the other 85 (outputs up to 240) is faster without this pass (1.08 to 1.41).
+  const bool shares = beside && !z_ranges && tokens < 4096 && tune(SK_TUNE_NARROW_BWD) < 0 && q.splits > 1 &&
                       dual_gemm_supported(GEMM_NT_F32, q.tile, GEMM_TT, z_tile);
   if (const NarrowPlan n = plan_narrow(s); n.ok && !shares) {
     g_hip_error.clear();
