@@ -42,6 +42,9 @@ using torch::autograd::variable_list;
 // Calls queue their kernels under the lock: two threads that share a stream share its buffer.
 struct Workspaces {
   static constexpr size_t MAX_STREAMS = 8;
+  // Most that a pass keeps here beside its workspace: an allocation a pass is 1 us of host, 1 to 2 % of a small two-sided layer's step, and the sums
+  // of a large one (4096 -> 11008, 2048 columns: 107 MB) would stay on every stream.
+  static constexpr size_t MAX_SUMS = 4 << 20;
   struct Entry {
     c10::DeviceIndex device;
     void* stream;
@@ -251,18 +254,20 @@ struct LinearTwoSided : torch::autograd::Function<LinearTwoSided> {
     Workspaces& w = workspaces();
     sk_status st;
     const auto f32 = x2.options().dtype(at::kFloat);
-    if (dt != SK_F32) {   // results each a tensor of its own; their fp32 sums in one that goes back to the allocator with the pass
+    if (dt != SK_F32) {   // results each a tensor of its own; their fp32 sums behind the workspace while they are small, else in one that goes back with the pass
       dB = at::empty({half, out}, A.options());
       dA = at::empty({in, half}, A.options());
       if (kept.bias) db = at::empty({out}, A.options());
-      const Tensor sums = at::empty({2 * half * out + in * half + out}, f32);
-      float* const sum_dB = sums.data_ptr<float>();
-      float* const sum_dA = sum_dB + 2 * half * out;
+      const int64_t sums = 2 * half * out + in * half + out;
+      const bool behind = (size_t)sums * 4 <= Workspaces::MAX_SUMS;
+      const Tensor own = behind ? Tensor() : at::empty({sums}, f32);
+      const size_t at_sums = (need + 255) / 256 * 256;
       const std::lock_guard<std::mutex> lock(w.mutex);
-      const Tensor& ws = w.get(x2.device(), stream, need);
+      unsigned char* const ws = static_cast<unsigned char*>(w.get(x2.device(), stream, behind ? at_sums + (size_t)sums * 4 : need).data_ptr());
+      float* const sum_dB = behind ? reinterpret_cast<float*>(ws + at_sums) : own.data_ptr<float>();
+      float* const sum_dA = sum_dB + 2 * half * out;
       st = sk_linear_bwd_rounded(x2.data_ptr(), dY.data_ptr(), A.data_ptr(), B.data_ptr(), dX.data_ptr(), sum_dB, kept.bias ? sum_dA + in * half : nullptr, sum_dA,
-                                 dB.data_ptr(), half, kept.bias ? db.data_ptr() : nullptr, dA.data_ptr(), tokens, in, out, l2, kept.k, dt, ws.data_ptr(),
-                                 (size_t)ws.numel(), stream);
+                                 dB.data_ptr(), half, kept.bias ? db.data_ptr() : nullptr, dA.data_ptr(), tokens, in, out, l2, kept.k, dt, ws, need, stream);
     } else {
       const Tensor whole = at::empty({2 * half, out}, f32);
       dA = at::empty({in, half}, f32);

@@ -257,16 +257,19 @@ def test_threads_and_streams():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("two_sided", [False, True])
-def test_a_pass_keeps_its_workspace_and_nothing_else(two_sided):
-    layer = (sknn.SKLinearTwoSided if two_sided else sknn.SKLinear)(256, 768, 2, 64, dtype=torch.bfloat16, seed=7)
-    x, dY = torch.randn(500, 256, device="cuda").bfloat16().requires_grad_(), torch.randn(500, 768, device="cuda").bfloat16()
+@pytest.mark.parametrize("two_sided,d_in,d_out,k,beside", [
+    # (fp32 sums of up to 4 MiB stay behind the workspace of a two-sided layer: 128 x (2 x 768 + 256) + 768 numbers, and 128 x (2 x 4096 + 1024) + 4096)
+    (False, 256, 768, 64, 0), (True, 256, 768, 64, 920_576 + 256), (True, 1024, 4096, 64, 0),
+])
+def test_what_a_pass_keeps(two_sided, d_in, d_out, k, beside):
+    layer = (sknn.SKLinearTwoSided if two_sided else sknn.SKLinear)(d_in, d_out, 2, k, dtype=torch.bfloat16, seed=7)
+    x, dY = torch.randn(500, d_in, device="cuda").bfloat16().requires_grad_(), torch.randn(500, d_out, device="cuda").bfloat16()
     sknn.release_workspaces()     # (other tests' streams)
     op, l = (sk.SK_OP_BWD_TWO_SIDED, 4) if two_sided else (sk.SK_OP_BWD, 2)
-    most = max(sk.sk_linear_workspace_bytes(o, 500, 256, 768, l, 64, sk.SK_BF16) for o in (sk.SK_OP_FWD, op))
+    most = max(sk.sk_linear_workspace_bytes(o, 500, d_in, d_out, l, k, sk.SK_BF16) for o in (sk.SK_OP_FWD, op)) + beside
     for _ in range(2):
         torch.autograd.grad(layer(x), (x, *layer.parameters()), dY)
-        torch.cuda.synchronize()
+    torch.cuda.synchronize()
     held = torch.cuda.memory_allocated()
     sknn.release_workspaces()
     held -= torch.cuda.memory_allocated()
